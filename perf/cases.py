@@ -1,0 +1,259 @@
+"""The work this library is used for, as cases that can be timed and compared.
+
+A case is one pass through the public entry points, as a program that compresses one layer's
+cache and then generates from it would make it:
+
+  compress    score -> select -> evict_merge of one layer's prompt (the whole prefill path)
+  reuse_lse   the same where the attention kernel hands over its row log-sum-exp, with the
+              key x value redundancy and the score-weighted merge, expanded for the layer's attention
+  rebudget    select -> evict_merge -> expand on scores that are already at hand (another
+              budget or merge ratio for the same prompt)
+  generate    evict_merge into a live cache, decode_init and a run of generated tokens
+  statistics  sparsity and redundancy rate of every head
+
+`prepare` makes the inputs on the GPU from the seed alone.  Attention mass in real prompts is
+heavy-tailed (a few tokens take most of it) and keys and values are redundant (groups of similar
+vectors): keys carry an exponentially distributed component along a direction their queries share,
+which makes the accumulated scores a power law, and belong to groups whose members' cosines lie
+on both sides of the merge threshold.
+"""
+import math
+
+import torch
+
+from paper_2412_08521_amd import binding as B
+
+# (batch, q heads, kv heads, head_dim, positions, window, budget), pooling width 7, merge ratio 0.5 and
+# tau 0.6 unless stated: the five synthetic workloads of this repository, and sizes between them
+
+
+def _case(name, kind, batch, q_heads, kv_heads, head_dim, seq_len, window, budget, merge_ratio=0.5, tau=0.6,
+          pool_kernel=7, f32=False, kept=True, steps=0, attn=False):
+    return dict(name=name, kind=kind, batch=batch, q_heads=q_heads, kv_heads=kv_heads, head_dim=head_dim,
+                seq_len=seq_len, window=window, budget=budget, merge_ratio=merge_ratio, tau=tau,
+                pool_kernel=pool_kernel, f32=f32, kept=kept, steps=steps, attn=attn)
+
+
+def listed():
+    return [
+        # a short prompt: launches and latency are all there is; nothing kept between calls (every
+        # call allocates its own workspace and outputs, the binding's default)
+        _case("compress_1k", "compress", 1, 4, 4, 64, 1024, 32, 64, kept=False),
+        # an ordinary prompt of a model without grouped queries
+        _case("compress_4k", "compress", 1, 32, 32, 128, 4096, 32, 256),
+        # several ragged sequences: odd length, heads that do not divide over the chip's dies, the
+        # smaller head size, another pooling width, nothing kept
+        _case("compress_ragged", "compress", 3, 6, 2, 64, 5003, 33, 301, merge_ratio=0.8, tau=0.7, pool_kernel=5,
+              kept=False),
+        # long prompts with grouped queries
+        _case("compress_16k", "compress", 1, 32, 8, 128, 16384, 32, 256),
+        _case("compress_32k", "compress", 4, 32, 8, 128, 32768, 64, 128),
+        # the longest context of the workloads, at a 1.6 % budget
+        _case("compress_128k", "compress", 1, 32, 8, 128, 131072, 64, 2048),
+        # the float32 mode, used to check a bf16 result
+        _case("compress_f32", "compress", 1, 8, 2, 128, 3000, 32, 200, f32=True),
+        # serving with an attention kernel that returns its log-sum-exp
+        _case("reuse_lse_8k", "reuse_lse", 1, 32, 8, 128, 8000, 64, 512, merge_ratio=1.0),
+        # another budget for a long prompt whose scores are kept
+        _case("rebudget_128k", "rebudget", 1, 32, 8, 128, 131072, 64, 4096, merge_ratio=1.0),
+        # generation from a small and from a large cache
+        _case("generate_b128", "generate", 4, 32, 8, 128, 4096, 64, 128, steps=32),
+        _case("generate_b2048", "generate", 1, 32, 8, 128, 16384, 64, 2048, steps=32, attn=True),
+        # the per-head statistics that the budget of a model is chosen by
+        _case("statistics_16k", "statistics", 1, 32, 8, 128, 16384, 32, 256),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return min(hi, int(round(math.exp(rng.uniform(math.log(lo), math.log(hi))))))
+
+
+def draw(rng):
+    kind = rng.choice(["compress", "compress", "compress", "reuse_lse", "rebudget", "generate", "generate", "statistics"])
+    while True:
+        head_dim = rng.choice([64, 128, 128])
+        kv_heads = rng.choice([1, 2, 3, 4, 8, 8, 16, 32])
+        group = rng.choice([1, 2, 4, 8] if kind == "generate" else [1, 2, 3, 4, 4, 7, 8])
+        batch = rng.choice([1, 1, 1, 2, 3, 4])
+        f32 = rng.random() < 0.15
+        most = {"compress": 131072, "reuse_lse": 65536, "rebudget": 262144, "generate": 32768, "statistics": 32768}[kind]
+        seq_len = _log_int(rng, 600, 6000 if f32 else most)
+        if rng.random() < 0.4:
+            seq_len = max(512, seq_len // 64 * 64)
+        window = rng.choice([16, 32, 32, 33, 64, 64, 100])
+        budget = min(seq_len // 2, window + _log_int(rng, 32, 4096))
+        c = _case("", kind, batch, kv_heads * group, kv_heads, head_dim, seq_len, window, budget,
+                  merge_ratio=rng.choice([0.25, 0.5, 0.5, 1.0, 2.0]), tau=rng.choice([0.5, 0.6, 0.6, 0.7]),
+                  pool_kernel=rng.choice([1, 3, 5, 7, 7, 7]), f32=f32, kept=rng.random() < 0.6,
+                  steps=rng.randint(8, 40) if kind == "generate" else 0, attn=rng.random() < 0.3)
+        del c["name"]
+        # no more work than the largest listed case: matrix products (f32 ones run at a
+        # sixteenth of the rate) and memory
+        rows = batch * kv_heads * (group + 2) * seq_len * head_dim * (4 if f32 else 2)
+        if work(c)["flops"] * (16 if f32 else 1) <= 1.0e14 and rows <= 1.5e9:
+            return c
+
+
+def _params(c, **over):
+    return B.EmsParams(c["batch"], c["q_heads"], c["kv_heads"], c["head_dim"], c["seq_len"], c["window"], c["budget"],
+                       merge_ratio=c["merge_ratio"], tau=c["tau"], pool_kernel=c["pool_kernel"],
+                       dtype=B.EMS_F32 if c["f32"] else B.EMS_BF16, **over)
+
+
+def _layer(c, gen, want_q):
+    """One layer's q, k, v."""
+    b, hkv, n, d = c["batch"], c["kv_heads"], c["seq_len"], c["head_dim"]
+    dt = torch.float32 if c["f32"] else torch.bfloat16
+    g = c["q_heads"] // hkv
+    randn = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+    n_groups = max(4, (c["budget"] - c["window"]) // 2)
+    u = randn(b, hkv, 1, d)
+    u /= u.norm(dim=-1, keepdim=True)
+    k = torch.empty((b, hkv, n, d), dtype=dt, device="cuda")
+    v = torch.empty_like(k)
+    q = torch.empty((b, c["q_heads"], n, d), dtype=dt, device="cuda") if want_q else None
+    for i in range(b):
+        for h in range(hkv):
+            who = torch.randint(0, n_groups, (n,), device="cuda", generator=gen)
+            share = 0.4 + 0.55 * torch.rand((n, 1), device="cuda", generator=gen)
+            for x in (k, v):
+                x[i, h] = share.sqrt() * randn(n_groups, d)[who] + (1 - share).sqrt() * randn(n, d)
+            heavy = torch.empty((n, 1), device="cuda").exponential_(1.0, generator=gen)
+            k[i, h] += (0.25 * math.sqrt(d) * heavy * u[i, h]).to(dt)
+            if want_q:
+                for j in range(h * g, (h + 1) * g):
+                    q[i, j] = randn(n, d) + 4.0 * u[i, h]
+    return q, k, v
+
+
+def _ws(nbytes):
+    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device="cuda")
+
+
+def _expand_out(p, n_imp, n_tbm):
+    shape = (p.batch, p.kv_heads, n_imp + n_tbm + p.window)
+    k = torch.empty(shape + (p.head_dim,), dtype=p.torch_dtype, device="cuda")
+    return k, torch.empty_like(k), torch.empty(shape, dtype=torch.int32, device="cuda")
+
+
+def prepare(case, seed):
+    c = case
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    p = _params(c)
+    kind = c["kind"]
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    s = {"kind": kind, "p": p}
+    s["q"], s["k"], s["v"] = _layer(c, gen, want_q=kind != "statistics")
+    # workspaces and output buffers that a serving loop keeps; None: the calls make their own
+    s["ws"] = [_ws(x) for x in B.ems_workspace_bytes(p)] if c["kept"] else [None] * 3
+    heads = (p.batch, p.kv_heads)
+    s["scores"] = s["index"] = s["merged"] = s["expanded"] = None
+    if c["kept"]:
+        s["scores"] = tuple(torch.empty(heads + (p.seq_len,), device="cuda") for _ in range(2))
+        s["index"] = tuple(torch.empty(heads + (n,), dtype=torch.int32, device="cuda") for n in (n_imp, n_tbm))
+        s["merged"] = B.alloc_evict_merge_outputs(p, "cuda")
+        s["expanded"] = _expand_out(p, n_imp, n_tbm)
+    if kind == "reuse_lse":
+        s["lse"] = B.ems_attention_lse(p, s["q"], s["k"])
+    elif kind in ("rebudget", "generate"):
+        s["scores"] = B.ems_global_local_score(p, s["q"], s["k"])
+        s["q"] = None
+    elif kind == "statistics":
+        # power-law scores as the prefill leaves them, a sixteenth of the mass in the last window's row sums
+        pareto = lambda: torch.empty(heads + (p.seq_len,), device="cuda").exponential_(1.0, generator=gen).exp()  # noqa: E731
+        s["scores"] = (pareto(), pareto() / 16)
+    if kind == "generate":
+        s["index"] = B.ems_select(p, *s["scores"])
+        s["merged"] = B.alloc_evict_merge_outputs(p, "cuda")
+        s["ws"][2] = _ws(B.ems_workspace_bytes(p)[2])
+        s["state"] = B.DecodeState(p, s["merged"]["k_out"], s["merged"]["v_out"])
+        s["step_ws"] = _ws(B.ems_decode_workspace_bytes(p))
+        s["attn"] = c["attn"]
+        s["step_out"] = None
+        if c["kept"]:
+            s["step_out"] = dict(decision=torch.empty(heads + (2,), dtype=torch.int32, device="cuda"),
+                                 sim=torch.empty(heads, device="cuda"),
+                                 attn=torch.empty((p.batch, p.q_heads, s["state"].n_tokens + 1), device="cuda")
+                                 if c["attn"] else None)
+        s["tokens"] = [tuple(torch.randn((p.batch, h, p.head_dim), device="cuda", generator=gen).to(p.torch_dtype)
+                             for h in (p.q_heads, p.kv_heads, p.kv_heads)) for _ in range(c["steps"])]
+    torch.cuda.synchronize()
+    return s
+
+
+def run(state):
+    s = state
+    p, kind, k, v = s["p"], s["kind"], s["k"], s["v"]
+    ws_score, ws_select, ws_merge = s["ws"]
+    if kind == "compress":
+        scores = B.ems_global_local_score(p, s["q"], k, ws=ws_score, out=s["scores"])
+        index = B.ems_select(p, *scores, ws=ws_select, out=s["index"])
+        merged = B.ems_evict_merge(p, k, v, *index, ws=ws_merge, out=s["merged"])
+        return scores, index, merged
+    if kind == "reuse_lse":
+        scores = B.ems_global_local_score_from_lse(p, s["q"], k, s["lse"], ws=ws_score, out=s["scores"])
+        imp, tbm, pooled = B.ems_select(p, *scores, want_pooled=True, ws=ws_select, out=s["index"])
+        merged = B.ems_evict_merge_variant(p, B.EMS_SIM_KEY_VALUE, k, v, pooled, imp, tbm, ws=ws_merge, out=s["merged"])
+        return scores, (imp, tbm, pooled), merged, B.ems_expand(p, merged, tbm, out=s["expanded"])
+    if kind == "rebudget":
+        index = B.ems_select(p, *s["scores"], ws=ws_select, out=s["index"])
+        merged = B.ems_evict_merge(p, k, v, *index, ws=ws_merge, out=s["merged"])
+        return index, merged, B.ems_expand(p, merged, index[1], out=s["expanded"])
+    if kind == "generate":
+        imp, tbm = s["index"]
+        merged = B.ems_evict_merge(p, k, v, imp, tbm, ws=ws_merge, out=s["merged"])
+        st = B.ems_decode_init(p, merged, tbm, *s["scores"], state=s["state"])
+        for t, (q_new, k_new, v_new) in enumerate(s["tokens"]):
+            last = B.ems_decode_step(p, st, t, q_new, k_new, v_new, want_attn=s["attn"], ws=s["step_ws"], out=s["step_out"])
+        return [getattr(st, name) for name in B.STATE_FIELDS], last
+    return B.ems_sparsity_rate(p, 0.9, *s["scores"]), B.ems_redundancy_rate(p, k, v)
+
+
+def work(case):
+    """Inputs read once, outputs written once.  The score forms every causal logit twice (the
+    weights need their row's log-sum-exp, and the matrix of weights is larger than the memory traffic
+    of forming it again), once when the log-sum-exp comes with the call."""
+    c = case
+    e = 4 if c["f32"] else 2
+    units, n, d, w, nb = c["batch"] * c["kv_heads"], c["seq_len"], c["head_dim"], c["window"], c["budget"]
+    g = c["q_heads"] // c["kv_heads"]
+    n_imp = nb - w
+    n_tbm = min(int(c["merge_ratio"] * nb), n - nb)
+    n_exp = n_imp + n_tbm + w
+    row = d * e
+    logits = 2.0 * d * (n * (n + 1) / 2) * g                                    # one causal product of a unit
+    score = (g + 1) * n * row + 8 * n
+    select = 8 * n + 4 * (n_imp + n_tbm)
+    merge = 2 * row * (nb + n_tbm) + 2 * row * (nb + 1) + 4 * (2 * (n_imp + n_tbm) + nb + 2 * n_tbm + n_imp + n_tbm)
+    sim = 2.0 * d * n_imp * n_tbm
+    expand = 2 * row * (nb + n_exp) + 4 * (3 * n_exp)
+    kind = c["kind"]
+    if kind == "compress":
+        return {"bytes": units * (score + select + merge), "flops": units * (2 * logits + sim)}
+    if kind == "reuse_lse":
+        return {"bytes": units * (score + 4 * g * n + select + 4 * n + merge + 4 * n_exp + expand), "flops": units * (logits + 2 * sim)}
+    if kind == "rebudget":
+        return {"bytes": units * (select + merge + expand), "flops": units * sim}
+    if kind == "generate":
+        # a step reads the cache's keys for the attention row and the centres' keys again for the
+        # cosines, and reads or writes every table element's scalars
+        step = row * (nb + n_imp) + (g + 2) * row + 40 * n_exp + 4 * (nb + 2 * n_imp)
+        if c["attn"]:
+            step += 4 * g * (n_exp + 1)
+        init = 4 * (3 * n_exp + 2 * nb) + 24 * n_exp + w * row
+        flops = 2.0 * d * g * (nb + 1) + 4.0 * d * n_imp
+        return {"bytes": units * (merge + init + c["steps"] * step), "flops": units * (sim + c["steps"] * flops)}
+    return {"bytes": units * (8 * n + 2 * n * row + 4 * n), "flops": units * 2 * 2.0 * d * (n * (n + 1) / 2)}
+
+
+def tolerance(case):
+    """Measured: the bf16 mode against the float32 mode on the same inputs (other matrix instructions,
+    other order of the sums) leaves the scores within 3e-6 and the similarities within 2e-7 of each
+    other, and the bf16 rows within 5e-6 while every decision falls alike; expanded keys, once more
+    rounded, 1.8e-3.  A token whose two best centres agree to the last bits may go to the
+    other one, and two centres that tie may leave a generation's cache in the other order: that
+    moves a row or two among all the rows (rel), by as much as the row itself (max), and a few of the
+    whole values (differ)."""
+    if case["kind"] == "statistics" or case["f32"]:
+        return {"rel": 2e-5, "max": 0.9, "differ": 5e-3}
+    return {"rel": 7e-3, "max": 0.9, "differ": 5e-3}

@@ -246,6 +246,138 @@ def work(case):
     return {"bytes": units * (8 * n + 2 * n * row + 4 * n), "flops": units * 2 * 2.0 * d * (n * (n + 1) / 2)}
 
 
+# ---- the same in 64 bits, in plain torch: one (batch, kv-head) at a time, rows in blocks
+
+def _scores64(q, k, window, scale):
+    """Column sums of one kv-head's attention weights over all rows and over the last `window` rows."""
+    n = k.shape[0]
+    glo = torch.zeros(n, dtype=torch.float64, device=k.device)
+    loc = torch.zeros_like(glo)
+    step = max(64, min(n, (1 << 27) // n))                                     # a gigabyte of weights at a time
+    for r0 in range(0, n, step):
+        r1 = min(n, r0 + step)
+        later = torch.ones(r1 - r0, r1 - r0, dtype=torch.bool, device=k.device).triu(1)
+        for qh in q:
+            a = qh[r0:r1].double() @ k[:r1].double().T * scale
+            a[:, r0:r1].masked_fill_(later, -math.inf)
+            a = torch.softmax(a, dim=-1)
+            glo[:r1] += a.sum(0)
+            if r1 > n - window:
+                loc[:r1] += a[max(0, n - window - r0):].sum(0)
+    return glo, loc
+
+
+def _combined64(glo, loc):
+    return torch.maximum(glo * (loc.mean() / glo.mean()), loc)
+
+
+def _select64(c, glo, loc, n_imp, n_tbm):
+    width = c["pool_kernel"]
+    pooled = torch.nn.functional.avg_pool1d(_combined64(glo, loc)[None], width, 1, width // 2)[0]
+    order = torch.argsort(pooled[:c["seq_len"] - c["window"]], descending=True, stable=True)
+    return order[:n_imp].sort().values, order[n_imp:n_imp + n_tbm].sort().values, pooled
+
+
+def _unit64(x):
+    norm = x.norm(dim=-1, keepdim=True)
+    return torch.where(norm > 0, x / norm, 0.0), norm[:, 0]
+
+
+def _merge64(c, k, v, imp, tbm, weight=None):
+    """One kv-head's compact cache; with a weight per token, the score-weighted merge by key x value redundancy."""
+    k, v = k.double(), v.double()
+    nb, n, n_imp = c["budget"], c["seq_len"], len(imp)
+    (uc, cn), (ut, tn) = _unit64(k[imp]), _unit64(k[tbm])
+    sim = ut @ uc.T
+    if weight is not None:
+        sim = sim * (_unit64(v[tbm])[0] @ _unit64(v[imp])[0].T)
+    best, dest = sim.max(dim=1)
+    dest = torch.where(best > float(torch.tensor(c["tau"], dtype=torch.float32)), dest, n_imp)
+    w = torch.ones_like(k[:, 0]) if weight is None else weight.double().clamp(min=0)
+    member = torch.zeros(n_imp + 1, dtype=torch.long, device=k.device).index_add_(0, dest, torch.ones_like(dest))
+    total = torch.zeros(n_imp + 1, dtype=torch.float64, device=k.device).index_add_(0, dest, w[tbm])
+    total[:n_imp] += w[imp]
+    mean = []
+    for centre, rest in ((uc, ut), (v[imp], v[tbm])):
+        m = torch.zeros(n_imp + 1, k.shape[1], dtype=torch.float64, device=k.device).index_add_(0, dest, rest * w[tbm, None])
+        m[:n_imp] += centre * w[imp, None]
+        mean.append(torch.where(total[:, None] > 0, m / total[:, None], 0.0))
+    alone = ((member[:n_imp] == 0) | (total[:n_imp] <= 0))[:, None]
+    out = [torch.cat([torch.where(alone, x[imp], m[:n_imp] * s), x[n - c["window"]:], m[n_imp:]])
+           for x, m, s in ((k, mean[0], cn[:, None]), (v, mean[1], 1.0))]
+    return {"k_out": out[0], "v_out": out[1], "kept_pos": None, "tbm_dest": None, "tbm_sim": best,
+            "k_norm": torch.cat([cn, tn]), "slot_count": None}, dest
+
+
+def _expand64(c, merged, dest):
+    n_imp, nb, norm = len(merged["k_norm"]) - len(dest), c["budget"], merged["k_norm"]
+    live = dest < n_imp
+    at = torch.where(live, dest, 0)
+    ratio = torch.where(live & (norm[at] > 0), norm[n_imp:] / norm[at], 0.0)
+    k, v = merged["k_out"], merged["v_out"]
+    return (torch.cat([k[:n_imp], k[at] * ratio[:, None], k[n_imp:nb]]),
+            torch.cat([v[:n_imp], v[at] * live[:, None], v[n_imp:nb]]), None)
+
+
+def _statistics64(c, glo, loc, k, v):
+    n, tau, zeta = c["seq_len"], float(torch.tensor(c["tau"], dtype=torch.float32)), float(torch.tensor(0.9, dtype=torch.float32))
+    s = _combined64(glo.double(), loc.double()).sort(descending=True).values
+    n_k = int((s.cumsum(0) < zeta * s.sum()).sum()) + 1
+    uk, uv = _unit64(k.double())[0], _unit64(v.double())[0]
+    best = torch.full((n,), -math.inf, dtype=torch.float64, device=k.device)
+    for r0 in range(0, n, 2048):
+        r1 = min(n, r0 + 2048)
+        r = (uk[r0:r1] @ uk[:r1].T) * (uv[r0:r1] @ uv[:r1].T)
+        r[:, r0:r1].masked_fill_(torch.ones(r1 - r0, r1 - r0, dtype=torch.bool, device=k.device).triu(), -math.inf)
+        best[r0:r1] = r.max(dim=1).values
+    return 1 - n_k / n, (best >= tau).sum() / n, best
+
+
+def _stacked(c, heads):
+    """Per-head results (tensors, dicts, tuples, None) -> the same with [batch, kv_heads, ...] tensors."""
+    x = heads[0]
+    if x is None:
+        return None
+    if isinstance(x, dict):
+        return {name: _stacked(c, [h[name] for h in heads]) for name in x}
+    if isinstance(x, tuple):
+        return tuple(_stacked(c, list(h)) for h in zip(*heads))
+    t = torch.stack([torch.as_tensor(h, dtype=torch.float64, device="cuda") for h in heads])
+    return t.view((c["batch"], c["kv_heads"]) + tuple(t.shape[1:]))
+
+
+def exact(case, seed):
+    """None in the place of indices and counts.  A generation has none: its cache keeps rows rounded to
+    16 bits at every step, and what later steps decide depends on the rounded ones."""
+    c = case
+    if c["kind"] == "generate":
+        return None
+    s = prepare(c, seed)
+    g = c["q_heads"] // c["kv_heads"]
+    n_imp, n_tbm = c["budget"] - c["window"], min(int(c["merge_ratio"] * c["budget"]), c["seq_len"] - c["budget"])
+    heads = []
+    for u in range(c["batch"] * c["kv_heads"]):
+        b, h = divmod(u, c["kv_heads"])
+        k, v = s["k"][b, h], s["v"][b, h]
+        if c["kind"] in ("rebudget", "statistics"):
+            glo, loc = (x[b, h].double() for x in s["scores"])
+        else:
+            glo, loc = _scores64(s["q"][b, h * g:(h + 1) * g], k, c["window"], c["head_dim"] ** -0.5)
+        if c["kind"] == "statistics":
+            rate, red, best = _statistics64(c, glo, loc, k, v)
+            heads.append(((rate, None), (red, best)))
+            continue
+        imp, tbm, pooled = _select64(c, glo, loc, n_imp, n_tbm)
+        merged, dest = _merge64(c, k, v, imp, tbm, pooled if c["kind"] == "reuse_lse" else None)
+        if c["kind"] == "compress":
+            heads.append(((glo, loc), (None, None), merged))
+        elif c["kind"] == "reuse_lse":
+            heads.append(((glo, loc), (None, None, pooled), merged, _expand64(c, merged, dest)))
+        else:
+            heads.append(((None, None), merged, _expand64(c, merged, dest)))
+    return _stacked(c, heads)
+
+
 def tolerance(case):
     """Measured: the bf16 mode against the float32 mode on the same inputs (other matrix instructions,
     other order of the sums) leaves the scores within 3e-6 and the similarities within 2e-7 of each
@@ -253,7 +385,10 @@ def tolerance(case):
     rounded, 1.8e-3.  A token whose two best centres agree to the last bits may go to the
     other one, and two centres that tie may leave a generation's cache in the other order: that
     moves a row or two among all the rows (rel), by as much as the row itself (max), and a few of the
-    whole values (differ)."""
-    if case["kind"] == "statistics" or case["f32"]:
+    whole values (differ).  The rates of the statistics are counts of tokens whose best value reaches a
+    threshold: where one of them is a rounding away from it, a head's rate is 1 / N off."""
+    if case["kind"] == "statistics":
+        return {"rel": 2e-4, "max": 0.9, "differ": 5e-3}
+    if case["f32"]:
         return {"rel": 2e-5, "max": 0.9, "differ": 5e-3}
     return {"rel": 7e-3, "max": 0.9, "differ": 5e-3}

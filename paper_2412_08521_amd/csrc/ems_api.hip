@@ -77,7 +77,8 @@ void partition_sizes(const ems_params* p, int* n_imp, int* n_tbm)
 }
 
 struct ScorePlan {
-    int n_chunks, chunk_rows, loc_chunk0, n_pad, p1_splits;
+    int n_chunks, chunk_rows, loc_chunk0, n_pad;
+    ems::ScoreDeal deal;
     size_t off_lse2, off_part_glo, off_part_loc, off_part_m, off_part_l, off_queue, total;
 };
 
@@ -108,21 +109,19 @@ ScorePlan plan_score(const ems_params* p)
     s.off_lse2 = off; off += align_up(sizeof(float) * (size_t)p->batch * p->q_heads * s.n_pad);
     s.off_part_glo = off;
     s.off_part_loc = off;
-    if (s.n_chunks > 1) {
+    s.deal = ems::score_deal(p->batch, p->q_heads, p->kv_heads, N, p->head_dim, p->dtype == EMS_F32);
+    if (s.deal.p2_waves) {
+        off += align_up(sizeof(float) * s.deal.p2_floats);
+        s.off_part_loc = off;
+        off += align_up(sizeof(float) * s.deal.p2_floats);
+    } else if (s.n_chunks > 1) {
         off += align_up(sizeof(float) * (size_t)bkv * s.n_chunks * N);
         s.off_part_loc = off;
         off += align_up(sizeof(float) * (size_t)bkv * (s.n_chunks - s.loc_chunk0) * N);
     }
-    // Pass 1: a row tile's key range is cut into splits while there are too few row tiles to
-    // balance the causal triangle over the chip (short sequences); partial (max, sum) pairs
-    // are then combined by a small kernel.
-    const int rpb = kpb;                                              // query rows per pass-1 wave
-    const long long row_tiles = (long long)p->batch * p->q_heads * ((N + rpb - 1) / rpb);
-    s.p1_splits = 1;
-    while (s.p1_splits < 8 && row_tiles * s.p1_splits < 2048 && (N + rpb - 1) / rpb >= 2 * s.p1_splits) s.p1_splits *= 2;
     s.off_part_m = off; s.off_part_l = off;
-    if (s.p1_splits > 1) {
-        const size_t one = align_up(sizeof(float) * (size_t)s.p1_splits * p->batch * p->q_heads * s.n_pad);
+    if (s.deal.p1_waves) {
+        const size_t one = align_up(sizeof(float) * s.deal.p1_floats);
         off += one; s.off_part_l = off; off += one;
     }
     s.off_queue = off; off += kAlign;                                   // work-queue cursors of the second pass
@@ -231,7 +230,8 @@ static void fill_score_args(ems::ScoreArgs& a, const ems_params* p, const ScoreP
     a.part_m = w ? reinterpret_cast<float*>(w + plan.off_part_m) : nullptr;
     a.part_l = w ? reinterpret_cast<float*>(w + plan.off_part_l) : nullptr;
     a.queue = w ? reinterpret_cast<int*>(w + plan.off_queue) : nullptr;
-    a.p1_splits = plan.p1_splits;
+    a.p1_waves = plan.deal.p1_waves; a.p1_len = plan.deal.p1_len;
+    a.p2_waves = plan.deal.p2_waves; a.p2_len = plan.deal.p2_len;
     a.batch = p->batch; a.q_heads = p->q_heads; a.kv_heads = p->kv_heads;
     a.head_dim = p->head_dim; a.seq_len = p->seq_len; a.window = p->window;
     a.n_pad = plan.n_pad;

@@ -14,8 +14,8 @@ struct ScoreArgs {
     float* lse_opt;     // [B*Hq, N] natural log, nullable
     float* lse2;        // [B*Hq, n_pad] base-2 log-sum-exp of c*S, +inf past N (workspace)
     const float* lse_in_nat;  // caller's natural-log row log-sum-exp for pass 2, or null
-    float* part_glo;    // [B*Hkv, n_chunks, N] (workspace, n_chunks > 1 only)
-    float* part_loc;    // [B*Hkv, n_chunks - loc_chunk0, N]
+    float* part_glo;    // [B*Hkv, n_chunks, N] (workspace, n_chunks > 1 only), or of an even deal
+    float* part_loc;    // [B*Hkv, n_chunks - loc_chunk0, N]    [B*Hkv, p2_waves + key tiles, keys per tile] each
     int batch, q_heads, kv_heads, head_dim, seq_len, window;
     int n_pad;          // seq_len rounded up to a multiple of 64
     int n_chunks;       // row chunks of pass 2
@@ -23,18 +23,18 @@ struct ScoreArgs {
     int loc_chunk0;     // first chunk that holds a last-window row
     float scale_log2e;  // softmax scale * log2(e)
     int p1_groups, p1_per_group;  // pass-1 work grouping per XCD (set by the launcher)
-    int p1_splits;      // pass 1: key-range splits per row tile (1 = none)
-    float* part_m;      // [p1_splits, B*Hq, n_pad] partial running maxima (workspace, p1_splits > 1)
-    float* part_l;      // [p1_splits, B*Hq, n_pad] partial sums relative to them
+    // Even deals (score_deal): waves per head and stages per wave; 0 waves = the pass uses work queues.
+    int p1_waves, p1_len, p2_waves, p2_len;
+    float* part_m;      // [B*Hq, p1_waves + row tiles, rows per tile] partial running maxima (workspace)
+    float* part_l;      // partial sums relative to them
     // Work queues (set by the launchers): a wave takes its work items from the queue of its XCD; once
     // that is empty, the first pass goes on with another XCD's queue, the second pass with a pool that
     // every XCD draws from.
     int* queue;         // [2][kXcds + 1] cursors: second pass, first pass (workspace; cleared before a pass)
     int p1_local;       // first pass: items per XCD queue
-    int p1_dynamic;     // first pass: 1 = waves stay and draw (and steal), 0 = one item per block
     int queue_clear;    // the cursors are known to be clear (the pass follows the first pass's launch)
     int q_dynamic;      // 1: waves stay and take items from the cursors; 0: one item per block, by block index
-    int q_share;        // (batch * kv_heads) / 8 heads per XCD queue; 0 = everything is in the pool
+    int q_share;        // (batch * kv_heads) / 8 heads per XCD queue; 0 = no queues
     int p2_split;       // row chunks below this index are in the pool
     int p2_local, p2_pool;   // items per XCD queue, items in the pool
 };
@@ -151,6 +151,10 @@ struct StatsArgs {
 };
 
 int score_keys_per_block(int dtype_is_f32);
+// How the score passes of a launch are dealt: waves per head and stages per wave of each pass (0 waves:
+// the pass is long enough for its work queues), and the floats of one partial-result array.
+struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len; size_t p1_floats, p2_floats; };
+ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32);
 int select_chunks(int seq_len);     // blocks per head of the long-sequence select
 int select_coarse_bins();
 hipError_t launch_sparsity(const StatsArgs& a, hipStream_t st);

@@ -14,6 +14,7 @@
 #include "ems_common.h"
 #include "ems_kernels.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace ems {
@@ -93,6 +94,10 @@ __device__ __forceinline__ int opaque_lane(int v)
     return v;
 }
 
+// Tells the compiler that a tuple without a value yet begins its life here (an accumulator set in only
+// some branches would otherwise keep its registers through the loops around it).
+__device__ __forceinline__ void defined_here(f32x16_t& v) { asm volatile("" : "=v"(v)); }
+
 // LDS byte address of a __shared__ object.
 __device__ __forceinline__ unsigned lds_address(const void* p)
 {
@@ -152,16 +157,8 @@ static long long xcd_grid(long long n_groups, long long per_group)    // 8 x (it
 // Second pass: from the queue of its XCD (items that stream the same operand stay on one L2)
 // and, once that is empty, from a pool of the lightest items that every XCD draws from.  Returns
 // the item's index in its queue (pool = true: in the pool), or -1 when both are empty.
-__device__ __forceinline__ int take_work_item(int* cursors, int n_local, int n_pool, bool dynamic, bool& pool)
+__device__ __forceinline__ int take_work_item(int* cursors, int n_local, int n_pool, bool& pool)
 {
-    if (!dynamic) {
-        // short launches: one item per block, fixed by the block index (block b is the (b / 8)-th
-        // of its XCD: first the XCD's queue, then every eighth item of the pool)
-        const int x = blockIdx.x % kXcds, i = blockIdx.x / kXcds;
-        pool = i >= n_local;
-        const int k = pool ? (i - n_local) * kXcds + x : i;
-        return pool && k >= n_pool ? -1 : k;
-    }
     int k = -1, from_pool = 0;
     if (threadIdx.x == 0) {
         if (n_local > 0) {
@@ -211,6 +208,84 @@ __host__ __device__ inline long long p2_items_upto(int I, int r, int n_key_tiles
     return r * whole * (whole + 1) / 2 + (n - whole) * n_key_tiles;
 }
 
+// ---- the even deal.  Launches too short for work queues (a few items per wave, so whole items are
+// left over at the end) are cut by stages instead: a head's work is laid out as one line of stages,
+// unit (row tile or key tile) after unit, and every wave takes an equal stretch of it, going from one
+// unit into the next in its middle.  A stretch leaves its part of a unit's result in slot (wave + unit)
+// of the head -- along the line each new part raises one of the two by one, so the slots are distinct --
+// and a small kernel adds a unit's parts in order.  A wave's stretch follows from its place in the head
+// and the stretch length alone.  Units start at whole trips of the 16-bit interior loops (kTrip),
+// so that cuts at multiples of a trip leave no odd stages for the masked loops.  Every unit is preceded
+// by `lead` stages that do not exist: what a wave pays for beginning a unit beside its stages (the
+// stationary operand's load, 8 us when all waves load at once, and the masked stages, 2.0 us where an
+// interior stage takes 1.5: head size 128, measured in the kernels).
+constexpr int kStreamRows = 32;            // rows per stage (one MFMA row tile)
+constexpr int kTrip = 4;
+
+// First pass: unit u = 32 * kSub query rows, its stages = 32 keys each up to the diagonal's end.
+template <int kSub>
+struct DealPass1 {
+    static constexpr int kAlign = kSub % kTrip == 0 ? kTrip : 1;
+    static constexpr int kLead = kSub % kTrip == 0 ? 8 : 2;
+    int n_stages, n_units;
+    __host__ __device__ explicit DealPass1(int N) : n_stages((N + kStreamRows - 1) / kStreamRows), n_units((n_stages + kSub - 1) / kSub) {}
+    __host__ __device__ int start(int u) const { return kSub * (u * (u + 1) / 2) + kLead * u; }
+    __host__ __device__ int first(int u) const { return start(u) + kLead; }      // its first real stage
+    __host__ __device__ int end(int u) const               // (only the last unit may be short)
+    {
+        const int n = kSub * (u + 1) < n_stages ? kSub * (u + 1) : n_stages;
+        return first(u) + (n + kAlign - 1) / kAlign * kAlign;
+    }
+    __host__ __device__ int total() const { return end(n_units - 1); }
+    __device__ int unit_at(int pos) const                  // the unit that holds stage `pos` of the line
+    {
+        int lo = 0, hi = n_units;                          // start(lo) <= pos < start(hi)
+        while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (start(mid) <= pos) lo = mid; else hi = mid; }
+        return lo;
+    }
+};
+
+// Second pass: unit u = 32 * kSub keys, its stages = 32 query rows each (of every q-head of the group)
+// from the diagonal on.
+template <int kSub>
+struct DealPass2 {
+    int n_units, rows_all, lead;                           // rows_all: stages of unit 0, padding included
+    __host__ __device__ DealPass2(int N, int group)
+    {
+        const int n_stages = (N + kStreamRows - 1) / kStreamRows;
+        n_units = (n_stages + kSub - 1) / kSub;
+        const int a = align(group);
+        rows_all = (n_stages + a - 1) / a * a;
+        // (the operand's load is paid once for the q-heads of the group, the masked stages by each)
+        lead = kSub % kTrip ? (group == 1 ? 2 : 1) : ((2 * group + 5 + group / 2) / group + a - 1) / a * a;
+    }
+    // a stretch that starts and ends at these multiples holds whole trips (of stages x q-heads)
+    static __host__ __device__ int align(int group) { return kSub % kTrip ? 1 : group % 4 == 0 ? 1 : group % 2 == 0 ? 2 : kTrip; }
+    __host__ __device__ int start(int u) const { return u * (rows_all + lead) - kSub * (u * (u - 1) / 2); }
+    __host__ __device__ int first(int u) const { return start(u) + lead; }
+    __host__ __device__ int end(int u) const { return start(u + 1); }
+    __host__ __device__ int total() const { return start(n_units); }
+    __device__ int unit_at(int pos) const
+    {
+        int lo = 0, hi = n_units;
+        while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (start(mid) <= pos) lo = mid; else hi = mid; }
+        return lo;
+    }
+};
+
+// A value that is the same in every lane, into a scalar register.
+__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// Wave of an even deal -> its place: the waves of a head are neighbours on one XCD (and share its L2).
+struct DealPlace { int head, wave; };
+__device__ __forceinline__ DealPlace deal_place(int heads, int waves)
+{
+    const int n = heads * waves, per_xcd = (n + kXcds - 1) / kXcds;
+    const int i = blockIdx.x / kXcds, w = (int)(blockIdx.x % kXcds) * per_xcd + i;
+    if (i >= per_xcd || w >= n) return {-1, 0};
+    return {scalar(w / waves), scalar(w % waves)};
+}
+
 // sum of the 16 accumulator-derived values with four independent partial sums
 __device__ __forceinline__ float sum16(const float (&p)[16])
 {
@@ -223,6 +298,31 @@ __device__ __forceinline__ float sum16(const float (&p)[16])
 __device__ __forceinline__ f32x16_t zero_acc()
 {
     return f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+}
+
+__device__ __forceinline__ float max16(const f32x16_t& acc)
+{
+    float t0 = fmaxf(fmaxf(acc[0], acc[1]), acc[2]);
+    float t1 = fmaxf(fmaxf(acc[3], acc[4]), acc[5]);
+    float t2 = fmaxf(fmaxf(acc[6], acc[7]), acc[8]);
+    float t3 = fmaxf(fmaxf(acc[9], acc[10]), acc[11]);
+    float t4 = fmaxf(fmaxf(acc[12], acc[13]), acc[14]);
+    t0 = fmaxf(fmaxf(t0, t1), t2);
+    t3 = fmaxf(fmaxf(t3, t4), acc[15]);
+    return fmaxf(t0, t3);
+}
+
+// The largest exponent of a tile among its keys up to row `last_row` (31: all).
+template <typename T, int D>
+__device__ __forceinline__ float pass1_tile_max(const frag_t (&ak)[Tile<T, D>::kFrags], const frag_t (&bq)[Tile<T, D>::kFrags],
+                                                float c, int last_row, int half)
+{
+    f32x16_t acc = zero_acc();
+#pragma unroll
+    for (int f = 0; f < Tile<T, D>::kFrags; ++f) mma<T>(acc, ak[f], bq[f]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = acc_row(r, half) > last_row ? -INFINITY : acc[r];
+    return max16(acc) * c;
 }
 
 // One 32-key x 32-query tile of the online softmax.  kMasked tiles may cross the diagonal.
@@ -240,14 +340,7 @@ __device__ __forceinline__ void pass1_tile(const frag_t (&ak)[Tile<T, D>::kFrags
         for (int r = 0; r < 16; ++r)
             if (key0 + acc_row(r, half) > qi) acc[r] = -INFINITY;
     }
-    float t0 = fmaxf(fmaxf(acc[0], acc[1]), acc[2]);
-    float t1 = fmaxf(fmaxf(acc[3], acc[4]), acc[5]);
-    float t2 = fmaxf(fmaxf(acc[6], acc[7]), acc[8]);
-    float t3 = fmaxf(fmaxf(acc[9], acc[10]), acc[11]);
-    float t4 = fmaxf(fmaxf(acc[12], acc[13]), acc[14]);
-    t0 = fmaxf(fmaxf(t0, t1), t2);
-    t3 = fmaxf(fmaxf(t3, t4), acc[15]);
-    const float tmax = fmaxf(t0, t3);
+    const float tmax = max16(acc);
     const float m_new = fmaxf(m_run, tmax * c);
     const float m_use = (kMasked && m_new == -INFINITY) ? 0.f : m_new;
     float p[16];
@@ -257,21 +350,27 @@ __device__ __forceinline__ void pass1_tile(const frag_t (&ak)[Tile<T, D>::kFrags
     m_run = m_new;
 }
 
-// Combines the partial (max, sum) pairs of pass 1's key-range splits into the row
-// log-sum-exp, in split order.
+// Combines the partial (max, sum) pairs that the waves of an even deal left for a row tile into the
+// row log-sum-exp, in stage order.
+template <int kSub>
 __global__ __launch_bounds__(256) void lse_combine_kernel(ScoreArgs a)
 {
+    constexpr int kRows = 32 * kSub;
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    const size_t bh = blockIdx.y, BH = (size_t)a.batch * a.q_heads;
+    const size_t bh = blockIdx.y;
     if (i >= a.n_pad) return;
     float v = INFINITY;                                           // rows past the end: weight zero in pass 2
     if (i < a.seq_len) {
+        const DealPass1<kSub> deal(a.seq_len);
+        const int u = i / kRows;
+        const int first = deal.first(u) / a.p1_len, last = (deal.end(u) - 1) / a.p1_len;
+        const size_t at = (bh * (a.p1_waves + deal.n_units) + u) * kRows + i % kRows;     // + wave * kRows
         float M = -INFINITY;
-        for (int s = 0; s < a.p1_splits; ++s) M = fmaxf(M, a.part_m[((size_t)s * BH + bh) * a.n_pad + i]);
+        for (int w = first; w <= last; ++w) M = fmaxf(M, a.part_m[at + (size_t)w * kRows]);
         float L = 0.f;
-        for (int s = 0; s < a.p1_splits; ++s) {
-            const float m = a.part_m[((size_t)s * BH + bh) * a.n_pad + i];
-            if (m > -INFINITY) L += a.part_l[((size_t)s * BH + bh) * a.n_pad + i] * exp2_fast(m - M);
+        for (int w = first; w <= last; ++w) {
+            const float m = a.part_m[at + (size_t)w * kRows];
+            if (m > -INFINITY) L += a.part_l[at + (size_t)w * kRows] * exp2_fast(m - M);
         }
         v = M + log2_fast(L);
         if (a.lse_opt) a.lse_opt[bh * a.seq_len + i] = v * 0.693147180559945309f;
@@ -294,6 +393,30 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(ScoreArgs a, int keys
         g += a.part_glo[((size_t)bkv * a.n_chunks + I) * N + j];
         if (I >= a.loc_chunk0)
             l += a.part_loc[((size_t)bkv * (a.n_chunks - a.loc_chunk0) + (I - a.loc_chunk0)) * N + j];
+    }
+    a.s_glo[(size_t)bkv * N + j] = g;
+    a.s_loc[(size_t)bkv * N + j] = l;
+}
+
+// The same for an even deal: the waves that had a share of a key tile's rows, in row order.
+template <int kSub>
+__global__ __launch_bounds__(256) void score_reduce_deal_kernel(ScoreArgs a)
+{
+    constexpr int kKeys = 32 * kSub;
+    const int N = a.seq_len, bkv = blockIdx.y;
+    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= N) return;
+    const DealPass2<kSub> deal(N, a.q_heads / a.kv_heads);
+    const int u = j / kKeys, u0 = deal.first(u), u1 = deal.end(u);
+    const int first = u0 / a.p2_len, last = (u1 - 1) / a.p2_len;
+    const size_t at = ((size_t)bkv * (a.p2_waves + deal.n_units) + u) * kKeys + j % kKeys;   // + wave * kKeys
+    float g = 0.f, l = 0.f;
+    for (int w = first; w <= last; ++w) {
+        const int r_begin = u * kKeys + (max(w * a.p2_len, u0) - u0) * kStreamRows;
+        const int r_end = u * kKeys + (min((w + 1) * a.p2_len, u1) - u0) * kStreamRows;
+        if (r_begin >= N) break;                          // padding
+        g += a.part_glo[at + (size_t)w * kKeys];
+        if (r_end > N - a.window) l += a.part_loc[at + (size_t)w * kKeys];
     }
     a.s_glo[(size_t)bkv * N + j] = g;
     a.s_loc[(size_t)bkv * N + j] = l;
@@ -334,7 +457,6 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 // registers in the 16-bit types) and LDS stages in the wave's ring
 template <typename T> struct Stream { static constexpr int kSub = 8; static constexpr int kRing = 4; };
 template <> struct Stream<float> { static constexpr int kSub = 2; static constexpr int kRing = 3; };
-constexpr int kStreamRows = 32;            // query rows per stage (one MFMA row tile)
 template <int v> using ic = std::integral_constant<int, v>;
 
 // The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
@@ -407,7 +529,7 @@ __device__ __forceinline__ void stream_edge_tile(const frag_t (&aq)[Tile<T, D>::
     }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_stream_kernel(ScoreArgs a)
 {
     constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
@@ -444,11 +566,29 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int BKV = a.batch * a.kv_heads;
     // Long launches: a wave stays and takes item after item until the queues are empty -- the exit
     // every wave reaches (the cursors only grow); between two items nothing of the wave is in flight.
-    // Short launches: one item per block.
+    // Shorter ones: the wave's stretch of an even deal, one part of a key tile after the other.
     // When the heads do not divide over the XCDs there are no queues: the groups (I, head) are
     // dealt to the XCDs in turn and every block has one item, fixed by its index.
-    for (bool first = true; first || a.q_dynamic; first = false) {
-    int I, J, bkv;
+    const DealPass2<kSub> deal(N, G);
+    DealPlace place{-1, 0};
+    int pos = 0, pos_end = 0;
+    if constexpr (kDeal) {
+        place = deal_place(BKV, a.p2_waves);
+        if (place.head < 0) return;
+        pos = place.wave * a.p2_len;
+        pos_end = scalar(min(pos + a.p2_len, deal.total()));
+    }
+    for (bool first = true; first || kDeal || a.q_dynamic; first = false) {
+    int I = 0, J, bkv, r_begin, r_end;
+    if constexpr (kDeal) {
+        if (pos >= pos_end) break;
+        J = scalar(deal.unit_at(pos));
+        bkv = place.head;
+        const int u0 = deal.first(J), to = min(pos_end, deal.end(J));
+        r_begin = scalar(J * kKeys + (max(pos, u0) - u0) * kStreamRows);
+        r_end = scalar(min(J * kKeys + (to - u0) * kStreamRows, N));
+        pos = scalar(to);
+    } else {
     if (a.q_share == 0) {
         int bid = xcd_work_item(BKV * n_chunks, n_key_tiles, blockIdx.x % kXcds, blockIdx.x / kXcds);
         if (bid < 0) break;
@@ -457,7 +597,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         I = n_chunks - 1 - bid / BKV;
     } else {
         bool pool;
-        const int k = take_work_item(a.queue, a.p2_local, a.p2_pool, a.q_dynamic != 0, pool);
+        const int k = take_work_item(a.queue, a.p2_local, a.p2_pool, pool);
         if (k < 0) break;
         const int r_tiles = R / kKeys;
         const int top = pool ? a.p2_split - 1 : n_chunks - 1;
@@ -474,10 +614,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         J = rem % cnt;
         bkv = pool ? rem / cnt : (int)(blockIdx.x % kXcds) + kXcds * (rem / cnt);
     }
+    r_begin = max(I * R, J * kKeys);                        // both multiples of 32
+    r_end = min((I + 1) * R, N);
+    }
+    if (r_begin >= r_end) continue;                         // pair above the diagonal (the queues hold none), or padding
     const int key_base = J * kKeys;
-    const int r_begin = max(I * R, key_base);               // both multiples of 32
-    const int r_end = min((I + 1) * R, N);
-    if (r_begin >= r_end) continue;                         // pair above the diagonal (the queues hold none)
     // [r_begin, e_end) touches the diagonal, [e_end, i_end) is interior, [i_end, r_end) holds
     // window rows (each range may be empty; all bounds but r_end are multiples of 32)
     const int win0 = N - W;
@@ -492,7 +633,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const T* Q0 = reinterpret_cast<const T*>(a.q) + ((size_t)(b * a.q_heads + kvh * G) * N) * D;
     const float* L0 = a.lse2 + (size_t)(b * a.q_heads + kvh * G) * a.n_pad;
 
-    const int lane = threadIdx.x;
+    const int lane = opaque_lane(threadIdx.x);              // (what follows from it is formed for every item, not kept from one to the next)
     const int col = lane & 31, half = lane >> 5;
 
     frag_t bk[kSub][kFrags];
@@ -584,40 +725,106 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         }
     };
 
-    float part[kSub][kEps], loc[kSub];
+    float part[kSub][kEps];
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        loc[s] = 0.f;
+    for (int s = 0; s < kSub; ++s)
 #pragma unroll
         for (int e = 0; e < kEps; ++e) part[s][e] = 0.f;
-    }
 
     wait_vmem_all_visible();
 
-    // ---- edge rows: [r_begin, e_end) and [i_end, r_end) of every q-head of the group
+    // the vector ALU's share of one MFMA slot: kEps accumulator elements turned into weights and
+    // added to the column sums, written operation by operation so that no instruction follows
+    // the one it depends on (the scheduler keeps this order where it does not interleave itself)
+    auto weigh = [&](float (&sum)[kEps], const f32x16_t& s_acc, const f32x16_t& l, int f) __attribute__((always_inline)) {
+        float x[kEps];
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) x[e] = __builtin_fmaf(s_acc[f * kEps + e], c, -l[f * kEps + e]);
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) x[e] = exp2_fast(x[e]);
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) sum[e] += x[e];
+    };
+
+    // ---- edge rows: [r_begin, e_end) and [i_end, r_end) of every q-head of the group.  A stage has
+    // n_tiles key subtiles at or below the diagonal, the last of them masked when the stage is on
+    // it; the chain of the next tile runs under the weights of the present one.
+    float loc[kSub];
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) loc[s] = 0.f;
     {
         const int lead = (e_end - r_begin) / kStreamRows;
         const int per_head = lead + (r_end - i_end + kStreamRows - 1) / kStreamRows;
         const int n_stages = per_head * G;
-        auto row_of = [&](int t) __attribute__((always_inline)) {
-            const int u = t % per_head;
+        auto row_of = [&](int u) __attribute__((always_inline)) {
             return u < lead ? r_begin + u * kStreamRows : i_end + (u - lead) * kStreamRows;
         };
-        for (int t = 0; t < kRing - 1 && t < n_stages; ++t) issue(t / per_head, row_of(t), t % kRing, std::false_type{});
+        int g_next = 0, u_next = 0, u_now = 0;              // next stage to fetch (q-head, place in the head); place of the present one
+        auto issue_edge = [&](int slot) __attribute__((always_inline)) {
+            issue(g_next, row_of(u_next), slot, std::false_type{});
+            if (++u_next == per_head) { u_next = 0; ++g_next; }
+        };
+        for (int t = 0; t < kRing - 1 && t < n_stages; ++t) issue_edge(t);
         for (int t = 0; t < n_stages; ++t) {
-            if (t + kRing - 1 < n_stages)
-                issue((t + kRing - 1) / per_head, row_of(t + kRing - 1), (t + kRing - 1) % kRing, std::false_type{});
+            if (t + kRing - 1 < n_stages) issue_edge((t + kRing - 1) % kRing);
             wait_landed(t, min(n_stages - 1, t + kRing - 1));
             frag_t aq[kFrags];
             f32x16_t lse_v;
             fetch_rows(t % kRing, aq, lse_v);
-            const int row0 = row_of(t);
+            const int row0 = row_of(u_now);
+            if (++u_now == per_head) u_now = 0;
+            const int below = (row0 - key_base) / kStreamRows + 1;   // key subtiles at or below the diagonal
+            if (row0 < win0 && row0 + 31 >= win0) {
+                // the window begins inside the stage: rows are told apart element by element
 #pragma unroll
-            for (int ks = 0; ks < kSub; ++ks) {
-                const int ks0 = key_base + ks * 32;
-                if (row0 + 31 >= ks0)                        // wave-uniform: not entirely above the diagonal
-                    stream_edge_tile<T, D>(aq, bk[ks], lse_v, c, part[ks][0], loc[ks], row0, ks0 + col, half, win0);
-                __builtin_amdgcn_sched_barrier(0);           // one tile's temporaries at a time
+                for (int ks = 0; ks < kSub; ++ks) {
+                    const int ks0 = key_base + ks * 32;
+                    if (ks < below)                          // wave-uniform
+                        stream_edge_tile<T, D>(aq, bk[ks], lse_v, c, part[ks][0], loc[ks], row0, ks0 + col, half, win0);
+                    __builtin_amdgcn_sched_barrier(0);       // one tile's temporaries at a time
+                }
+            } else {
+                const int n_tiles = min(below, kSub);
+                const int first_row = below <= kSub ? col : 0;       // the last tile's rows before it are above the diagonal
+                const bool window = row0 >= win0;
+                f32x16_t acc[2];
+                defined_here(acc[1]);
+                mma_first<T>(acc[0], aq[0], bk[0][0]);
+#pragma unroll
+                for (int f = 1; f < kFrags; ++f) mma<T>(acc[0], aq[f], bk[0][f]);
+#pragma unroll
+                for (int ks = 0; ks < kSub; ++ks) {
+                    float sum[kEps];
+#pragma unroll
+                    for (int e = 0; e < kEps; ++e) sum[e] = 0.f;
+                    const bool last = ks + 1 >= n_tiles;     // wave-uniform
+                    if (ks + 1 < kSub && !last) {
+                        const int kn = ks + 1 < kSub ? ks + 1 : ks;
+#pragma unroll
+                        for (int f = 0; f < kFrags; ++f) {
+                            if (f == 0) mma_first<T>(acc[kn & 1], aq[0], bk[kn][0]);
+                            else mma<T>(acc[kn & 1], aq[f], bk[kn][f]);
+                            weigh(sum, acc[ks & 1], lse_v, f);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    } else {
+                        float x[16];
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) x[r] = exp2_fast(__builtin_fmaf(acc[ks & 1][r], c, -lse_v[r]));
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sum[r % kEps] += acc_row(r, half) < first_row ? 0.f : x[r];
+                    }
+#pragma unroll
+                    for (int e = 0; e < kEps; ++e) part[ks][e] += sum[e];
+                    if (window) {                            // wave-uniform
+                        float t16 = sum[0];
+#pragma unroll
+                        for (int e = 1; e < kEps; ++e) t16 += sum[e];
+                        loc[ks] += t16;
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (last) break;
+                }
             }
             // the slot is re-filled by the DMA issued at the top of the next iteration: the
             // fragments above are in registers by then (their uses wait for them)
@@ -688,18 +895,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         // previous pair (for p = 0 the last pair of the previous stage, whose rows' log-sum-exp is
         // in the other register set).  An accumulator is first read two MFMAs and a dozen vector
         // instructions after the chain that wrote it has ended.
-        // the vector ALU's share of one MFMA slot: kEps accumulator elements turned into weights and
-        // added to the column sums, written operation by operation so that no instruction follows
-        // the one it depends on (the scheduler keeps this order where it does not interleave itself)
-        auto weigh = [&](float (&sum)[kEps], const f32x16_t& s_acc, const f32x16_t& l, int f) __attribute__((always_inline)) {
-            float x[kEps];
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) x[e] = __builtin_fmaf(s_acc[f * kEps + e], c, -l[f * kEps + e]);
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) x[e] = exp2_fast(x[e]);
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) sum[e] += x[e];
-        };
         auto stage = [&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;         // stage t of the trip, t = u (mod kUnroll)
             constexpr int set = u & 1;
@@ -763,22 +958,31 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         wait_vmem<0>();                                     // no DMA may outlive the wave's LDS
     }
 
+    // where the keys' sums go: key kj to out_glo[kj]
     const int loc_chunk0 = a.loc_chunk0;
-    float* out_glo = a.n_chunks == 1 ? a.s_glo + (size_t)bkv * N
-                                     : a.part_glo + ((size_t)bkv * n_chunks + I) * N;
+    float* out_glo;
     float* out_loc = nullptr;
-    if (a.n_chunks == 1) out_loc = a.s_loc + (size_t)bkv * N;
-    else if (I >= loc_chunk0)
-        out_loc = a.part_loc + ((size_t)bkv * (n_chunks - loc_chunk0) + (I - loc_chunk0)) * N;
+    if constexpr (kDeal) {
+        const ptrdiff_t at = ((ptrdiff_t)bkv * (a.p2_waves + deal.n_units) + place.wave + J) * kKeys - key_base;
+        out_glo = a.part_glo + at;
+        if (r_end > win0) out_loc = a.part_loc + at;
+    } else {
+        out_glo = a.n_chunks == 1 ? a.s_glo + (size_t)bkv * N
+                                  : a.part_glo + ((size_t)bkv * n_chunks + I) * N;
+        if (a.n_chunks == 1) out_loc = a.s_loc + (size_t)bkv * N;
+        else if (I >= loc_chunk0)
+            out_loc = a.part_loc + ((size_t)bkv * (n_chunks - loc_chunk0) + (I - loc_chunk0)) * N;
+    }
+    const int out_lane = opaque_lane(lane);                 // (likewise not kept across the loops above)
 #pragma unroll
     for (int s = 0; s < kSub; ++s) {
         float g = part[s][0];
 #pragma unroll
         for (int e = 1; e < kEps; ++e) g += part[s][e];
-        const float gsum = g + __shfl_xor(g, 32);           // the half-waves hold disjoint rows of the same keys
-        const float lsum = loc[s] + __shfl_xor(loc[s], 32);
-        const int kj = key_base + s * 32 + col;
-        if (half == 0 && kj < N) {
+        const float gsum = g + __shfl(g, out_lane ^ 32);    // the half-waves hold disjoint rows of the same keys
+        const float lsum = loc[s] + __shfl(loc[s], out_lane ^ 32);
+        const int kj = key_base + s * 32 + out_lane;
+        if (out_lane < 32 && kj < N) {
             out_glo[kj] = gsum;
             if (out_loc) out_loc[kj] = lsum;
         }
@@ -803,7 +1007,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 //                    i.e. no later exponent exceeds m by ~100: if a sum does leave the range,
 //                    the wave redoes its interior stages with the online form.
 // ------------------------------------------------------------------------------------
-template <typename T, int D>
+template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_stream_kernel(ScoreArgs a)
 {
     constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
@@ -827,21 +1031,41 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int N = a.seq_len;
     const int n_row_tiles = (N + kRows - 1) / kRows;
     const int G = a.q_heads / a.kv_heads;
-    // A wave stays and takes item after item until every queue is empty: the exit every wave
-    // reaches (the cursors only grow); between two items nothing of the wave is in flight.
-    // (Short launches: one item per block, by block index.)
-    for (bool first = true; first || a.p1_dynamic; first = false) {
-    int from_xcd = blockIdx.x % kXcds;
-    const int k_item = a.p1_dynamic ? take_or_steal(a.queue + (kXcds + 1), a.p1_local, from_xcd) : (int)(blockIdx.x / kXcds);
-    if (k_item < 0) break;
-    int bid = xcd_work_item(a.p1_groups, a.p1_per_group, from_xcd, k_item);
-    if (bid < 0) continue;                                  // padding
-    const int S = a.p1_splits, sp = bid % S; bid /= S;           // this wave's share of the key range
-    const int g = bid % G; bid /= G;
-    const int BKV = a.batch * a.kv_heads;
-    int rt, bkv;                                  // bkv = b * kv_heads + kv
-    if (a.p1_groups == BKV) { rt = n_row_tiles - 1 - (bid % n_row_tiles); bkv = bid / n_row_tiles; }
-    else { bkv = bid % BKV; rt = n_row_tiles - 1 - (bid / BKV); }   // heaviest row tiles first
+    // Long launches: a wave stays and takes item after item until every queue is empty -- the exit
+    // every wave reaches (the cursors only grow); between two items nothing of the wave is in flight.
+    // Shorter ones: the wave's stretch of an even deal, one part of a row tile after the other.
+    const DealPass1<kSub> deal(N);
+    DealPlace place{-1, 0};
+    int pos = 0, pos_end = 0;
+    if constexpr (kDeal) {
+        place = deal_place(a.batch * a.q_heads, a.p1_waves);
+        if (place.head < 0) return;
+        pos = place.wave * a.p1_len;
+        pos_end = scalar(min(pos + a.p1_len, deal.total()));
+    }
+    for (;;) {
+    int rt, bkv, g, t0 = 0, t1;                             // bkv = b * kv_heads + kv; key stages [t0, t1)
+    if constexpr (kDeal) {
+        if (pos >= pos_end) break;
+        rt = scalar(deal.unit_at(pos));
+        g = scalar(place.head % G); bkv = scalar(place.head / G);
+        const int u0 = deal.first(rt), to = min(pos_end, deal.end(rt));
+        t0 = scalar(max(pos, u0) - u0); t1 = scalar(to - u0);
+        pos = scalar(to);
+        if (t0 >= t1) continue;                             // before the unit's first stage
+    } else {
+        int from_xcd;
+        const int k_item = take_or_steal(a.queue + (kXcds + 1), a.p1_local, from_xcd);
+        if (k_item < 0) break;
+        int bid = xcd_work_item(a.p1_groups, a.p1_per_group, from_xcd, k_item);
+        if (bid < 0) continue;                              // padding
+        g = bid % G; bid /= G;
+        const int BKV = a.batch * a.kv_heads;
+        if (a.p1_groups == BKV) { rt = n_row_tiles - 1 - (bid % n_row_tiles); bkv = bid / n_row_tiles; }
+        else { bkv = bid % BKV; rt = n_row_tiles - 1 - (bid / BKV); }   // heaviest row tiles first
+        t1 = kSub * (rt + 1);
+    }
+    t1 = min(t1, (min(N, (rt + 1) * kRows) + kStreamRows - 1) / kStreamRows);   // the stages the row tile can see
     const int b = bkv / a.kv_heads, kvh = bkv % a.kv_heads;
     const int h = kvh * G + g;
 
@@ -923,29 +1147,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         for (int f = 0; f < kFrags; ++f) k_out[f] = *reinterpret_cast<const frag_t*>(ks + frag_off[f]);
     };
 
-    // this wave's key stages: [t0, t1) of the stages a row tile can see; the stages from t_diag on
-    // touch the diagonal
-    const int last_key = min(N, q_base + kRows);                // exclusive
-    const int n_all = (last_key + kStreamRows - 1) / kStreamRows;
-    const int t0 = (int)((long long)n_all * sp / S), t1 = (int)((long long)n_all * (sp + 1) / S);
+    // of this part's key stages [t0, t1), those from t_diag on touch the diagonal
     const int t_diag = max(t0, q_base / kStreamRows);
     const int n_edge = max(t1 - t_diag, 0);
-    // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form --
-    // one when there is no diagonal stage to take the reference from, more until the pipelined
-    // rest is whole trips of the loop
+    // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form, so
+    // that the pipelined rest is whole trips of the loop
     const int n_int_all = max(min(t1, t_diag) - t0, 0);
-    int n_lead = n_edge == 0 && n_int_all > 0 ? 1 : 0;
-    n_lead = __builtin_amdgcn_readfirstlane(n_lead + (n_int_all - n_lead) % kUnroll);   // (wave-uniform; kept in a scalar register)
+    const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
     const int n_int = n_int_all - n_lead;                        // a multiple of kUnroll, >= 0
 
     float m_run[kSub], l_run[kSub];
 #pragma unroll
     for (int s = 0; s < kSub; ++s) { m_run[s] = -INFINITY; l_run[s] = 0.f; }
 
-    // Online form over a list of stages: `n_a` stages from `first_a`, then `n_b` from `first_b`.
-    auto online_phase = [&](int first_a, int n_a, int first_b, int n_b) __attribute__((always_inline)) {
-        const int n_stages = n_a + n_b;
-        auto stage_of = [&](int u) __attribute__((always_inline)) { return u < n_a ? first_a + u : first_b + (u - n_a); };
+    // Textbook online softmax over the stages [first, end), one tile at a time.
+    auto online_phase = [&](int first, int end) __attribute__((always_inline)) {
+        const int n_stages = end - first;
+        auto stage_of = [&](int u) __attribute__((always_inline)) { return first + u; };
         for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(stage_of(u), u % kRing, std::false_type{});
         for (int u = 0; u < n_stages; ++u) {
             if (u + kRing - 1 < n_stages) issue(stage_of(u + kRing - 1), (u + kRing - 1) % kRing, std::false_type{});
@@ -964,28 +1182,91 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         wait_vmem<0>();
     };
 
-    wait_vmem_all_visible();
-    online_phase(t0, n_lead, t_diag, n_edge);
-
-    if (n_int > 0) {
-        // A lane that has seen no key yet (its half of the diagonal tile lay above the diagonal)
-        // borrows the reference of the other half of the wave, which holds the same queries.
-        float m_fix[kSub], l_save[kSub];
+    // Reference exponents: the largest logit of the first stage the part takes (masked where that
+    // stage is on the diagonal), the same for both half-waves; -inf where a query sees nothing of it.
+    const int d0 = q_base / kStreamRows;                        // subtile s is on the diagonal in stage d0 + s
+    auto reference = [&](const frag_t (&ak)[kFrags], int t) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < kSub; ++s) {
-            const float m_o = __shfl_xor(m_run[s], 32);
-            m_fix[s] = m_run[s] == -INFINITY ? (m_o == -INFINITY ? 0.f : m_o) : m_run[s];
-            l_save[s] = l_run[s];
+            if (s >= t - d0) {                                  // wave-uniform
+                const float m = pass1_tile_max<T, D>(ak, bq[s], c, s == t - d0 ? col : 31, half);
+                m_run[s] = fmaxf(m, __shfl_xor(m, 32));
+            }
+            __builtin_amdgcn_sched_barrier(0);                  // one tile's temporaries at a time
         }
+    };
+    // the vector ALU's share of one MFMA slot, operation by operation (no instruction follows
+    // the one it depends on)
+    auto weigh = [&](float (&sum)[kEps], const f32x16_t& s_acc, float m, int f) __attribute__((always_inline)) {
+        float x[kEps];
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) x[e] = __builtin_fmaf(s_acc[f * kEps + e], c, -m);
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) x[e] = exp2_fast(x[e]);
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) sum[e] += x[e];
+    };
+    float lsum[kSub][kEps];
+#pragma unroll
+    for (int s = 0; s < kSub; ++s)
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) lsum[s][e] = 0.f;
+
+    wait_vmem_all_visible();
+
+    // ---- edge stages: the n_lead interior ones, then those on the diagonal.  Subtiles go from the
+    // last one down to the one on the diagonal, which is masked; the chain of the next tile runs
+    // under the weights of the present one.
+    {
+        const int n_stages = n_lead + n_edge;
+        auto stage_of = [&](int u) __attribute__((always_inline)) { return u < n_lead ? t0 + u : t_diag + (u - n_lead); };
+        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(stage_of(u), u % kRing, std::false_type{});
+        for (int u = 0; u < n_stages; ++u) {
+            if (u + kRing - 1 < n_stages) issue(stage_of(u + kRing - 1), (u + kRing - 1) % kRing, std::false_type{});
+            wait_landed(u, min(n_stages - 1, u + kRing - 1));
+            frag_t ak[kFrags];
+            fetch_keys(u % kRing, ak);
+            const int t = stage_of(u);
+            if (u == 0) reference(ak, t);
+            const int s_last = max(t - d0, 0);                   // the lowest subtile that sees the stage
+            const int last_row = t >= d0 ? col : 31;             // its keys after this row are above the diagonal
+            f32x16_t acc[2];
+            defined_here(acc[kSub & 1]);
+            mma_first<T>(acc[(kSub - 1) & 1], ak[0], bq[kSub - 1][0]);
+#pragma unroll
+            for (int f = 1; f < kFrags; ++f) mma<T>(acc[(kSub - 1) & 1], ak[f], bq[kSub - 1][f]);
+#pragma unroll
+            for (int s = kSub - 1; s >= 0; --s) {
+                const bool last = s <= s_last;                   // wave-uniform
+                if (s > 0 && !last) {
+                    const int sn = s > 0 ? s - 1 : 0;
+#pragma unroll
+                    for (int f = 0; f < kFrags; ++f) {
+                        if (f == 0) mma_first<T>(acc[sn & 1], ak[0], bq[sn][0]);
+                        else mma<T>(acc[sn & 1], ak[f], bq[sn][f]);
+                        weigh(lsum[s], acc[s & 1], m_run[s], f);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                } else {
+                    float x[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) x[r] = exp2_fast(__builtin_fmaf(acc[s & 1][r], c, -m_run[s]));
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) lsum[s][r % kEps] += acc_row(r, half) > last_row ? 0.f : x[r];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (last) break;
+            }
+        }
+        wait_vmem<0>();
+    }
+
+    // ---- interior stages
+    if (n_int > 0) {
         const int ti0 = t0 + n_lead;                             // interior stages [ti0, ti0 + n_int)
 
         frag_t ak[2][kFrags];
         f32x16_t acc[4];
-        float lsum[kSub][kEps];
-#pragma unroll
-        for (int s = 0; s < kSub; ++s)
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) lsum[s][e] = 0.f;
 
         // issue cursor: where four DMA instructions go under one M0, a running source address
         // that advances by a stage until the last stage is issued and then stays
@@ -1012,6 +1293,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         if constexpr (kRing > 3) issue_next(ic<2>{});
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_keys(0, ak[0]);
+        if (n_edge + n_lead == 0) reference(ak[0], ti0);         // wave-uniform; the pipeline sums the stage like every other
         // the pipeline starts on a pair that weighs nothing: exponents of -inf
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[2][r] = acc[3][r] = -INFINITY;
@@ -1019,17 +1301,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         // One stage = kPairs rounds; in round p the chains of query subtiles 2p and 2p+1 alternate
         // and after each MFMA the vector ALU weighs kEps elements of the matching tile of the
         // previous pair (same structure as the second pass; the exponent's offset is the lane's m).
-        // the vector ALU's share of one MFMA slot, operation by operation (no instruction follows
-        // the one it depends on)
-        auto weigh = [&](float (&sum)[kEps], const f32x16_t& s_acc, float m, int f) __attribute__((always_inline)) {
-            float x[kEps];
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) x[e] = __builtin_fmaf(s_acc[f * kEps + e], c, -m);
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) x[e] = exp2_fast(x[e]);
-#pragma unroll
-            for (int e = 0; e < kEps; ++e) sum[e] += x[e];
-        };
         auto stage = [&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;         // the stage's place in the trip
             constexpr int set = u & 1;
@@ -1047,11 +1318,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                 for (int f = 0; f < kFrags; ++f) {
                     if (f == 0) mma_first<T>(accA, ak[set][0], bq[2 * p][0]);
                     else mma<T>(accA, ak[set][f], bq[2 * p][f]);
-                    weigh(lsum[psa], prevA, m_fix[psa], f);
+                    weigh(lsum[psa], prevA, m_run[psa], f);
                     __builtin_amdgcn_sched_barrier(0);
                     if (f == 0) mma_first<T>(accB, ak[set][0], bq[2 * p + 1][0]);
                     else mma<T>(accB, ak[set][f], bq[2 * p + 1][f]);
-                    weigh(lsum[psa + 1], prevB, m_fix[psa + 1], f);
+                    weigh(lsum[psa + 1], prevB, m_run[psa + 1], f);
                     if (kPairs > 1 && p == 1 && f == 0) {   // the other register set is free; early, so that the LDS latency hides
                         wait_vmem<(kRing - 2) * kLoads>();
                         fetch_keys((u + 1) % kRing, ak[1 - set]);
@@ -1080,36 +1351,28 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             constexpr int rp = ((kPairs % 2 ? 1 + kPairs - 1 : kPairs - 1)) & 1;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                lsum[kSub - 2][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp][r], c, -m_fix[kSub - 2]));
-                lsum[kSub - 1][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp + 1][r], c, -m_fix[kSub - 1]));
+                lsum[kSub - 2][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp][r], c, -m_run[kSub - 2]));
+                lsum[kSub - 1][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp + 1][r], c, -m_run[kSub - 1]));
             }
         }
         wait_vmem<0>();
 
-        // fold the interior sums into the running pair; a sum outside the float range (or NaN)
-        // sends the whole wave back through its interior stages in the online form
-        bool bad = false;
+    }
+
+    // the sums are relative to the references; one outside the float range (or NaN) sends the whole
+    // wave back through all of the part's stages in the online form
+    bool bad = false;
 #pragma unroll
-        for (int s = 0; s < kSub; ++s) {
-            float t = lsum[s][0];
+    for (int s = 0; s < kSub; ++s) {
+        l_run[s] = lsum[s][0];
 #pragma unroll
-            for (int e = 1; e < kEps; ++e) t += lsum[s][e];
-            // l_run is relative to m_run (or empty); rebase it to m_fix
-            const float l_old = m_run[s] == -INFINITY ? 0.f : l_run[s];
-            l_run[s] = l_old + t;
-            m_run[s] = m_fix[s];
-            bad |= !(l_run[s] < INFINITY);
-        }
-        if (__any(bad)) {
+        for (int e = 1; e < kEps; ++e) l_run[s] += lsum[s][e];
+        bad |= !(l_run[s] < INFINITY);
+    }
+    if (__any(bad)) {
 #pragma unroll
-            for (int s = 0; s < kSub; ++s) {
-                // back to the state after the first online phase (a lane that had seen a key has a
-                // sum of at least one; an empty sum means the lane had no reference of its own)
-                l_run[s] = l_save[s];
-                m_run[s] = l_save[s] == 0.f ? -INFINITY : m_fix[s];
-            }
-            online_phase(ti0, n_int, 0, 0);
-        }
+        for (int s = 0; s < kSub; ++s) { m_run[s] = -INFINITY; l_run[s] = 0.f; }
+        online_phase(t0, t1);
     }
 
     const size_t bh = (size_t)(b * a.q_heads + h);
@@ -1123,12 +1386,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         const float Mu = (M == -INFINITY) ? 0.f : M;
         const float L = l_run[s] * exp2_fast(m_run[s] - Mu) + l_o * exp2_fast(m_o - Mu);
         const int qi = q_base + s * 32 + col;
-        if (S > 1) {
-            // partial (reference, sum) of this key range; combined by lse_combine_kernel
-            if (half == 0 && qi < a.n_pad) {
-                a.part_m[((size_t)sp * a.batch * a.q_heads + bh) * a.n_pad + qi] = M;
-                a.part_l[((size_t)sp * a.batch * a.q_heads + bh) * a.n_pad + qi] = L;
-            }
+        if constexpr (kDeal) {
+            // this part's (reference, sum); combined by lse_combine_kernel.  A sum far above its
+            // reference gives its exponent to the reference: against another part's larger reference
+            // 2^(M - other) could otherwise leave the float range while L still makes up for it.
+            const size_t at = (bh * (a.p1_waves + deal.n_units) + place.wave + rt) * kRows + s * 32 + col;
+            const int e = L > 0x1p40f ? __builtin_amdgcn_frexp_expf(L) : 0;
+            if (half == 0) { a.part_m[at] = M + (float)e; a.part_l[at] = __builtin_amdgcn_ldexpf(L, -e); }
             continue;
         }
         const float v = Mu + log2_fast(L);
@@ -1141,42 +1405,101 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
 int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<float>::kSub : Stream<bf16_t>::kSub); }
 
+// Stretch length and waves per head of an even deal of `heads` lines of `total` stages over the
+// `resident` waves the chip holds (one per SIMD, fewer where the rings fill the LDS first).  More than one round of waves is worth it only where the heads
+// divide the waves badly; a part costs about two and a half stages beside its stages (stationary
+// operand, ring start).
+static void deal_over_waves(int resident, long long heads, long long total, int align, int shortest, int* len, int* waves)
+{
+    double best = 0.;
+    for (int rounds = 1; rounds <= 4; ++rounds) {
+        const long long per_head = std::max(1ll, (long long)resident * rounds / heads);
+        long long l = std::max((long long)shortest, (total + per_head - 1) / per_head);
+        l = (l + align - 1) / align * align;
+        const long long w = (total + l - 1) / l;
+        const double cost = (double)((heads * w + resident - 1) / resident) * ((double)l + 2.5);
+        if (rounds == 1 || cost < best) { best = cost; *len = (int)l; *waves = (int)w; }
+    }
+}
+
+// Which launches are dealt evenly (bf16, head size 128, times of the pass in us, even deal against whole
+// items; both with the masked stages in the pipeline):
+//   first pass    1 x 32 heads:  8192: 247 / 358 (queues), 249 (key-range splits, now gone);  16384: 907 / 922;
+//                 24000: 1917 / 1996;  32768 (4096 row tiles): 3530 / 3545;  4 x 32768: 14164 / 13903
+//   second pass   32 over 8 heads:  8192: 251 / 319;  16384: 921 / 969;  2 x 16384: 1844 / 1874;
+//                 4 x 16384: 3933 / 3659;  4 x 32768: 16.8 / 14.1 ms (waves that stream different rows
+//                 share no lines of their L2: the more rows there are, the more that costs)
+//                 fewer heads than XCDs, 6 over 2:  16384: 200 / 249;  32768: 690 / 774;  4 over 1, 131072:
+//                 7.19 / 7.47 ms (the alternative is one block per item, without queues)
+constexpr int kDealUnits = 4 * 1024;       // first pass: below four row tiles per resident wave
+constexpr double kDealStages = 1200.;      // second pass: up to so many stages per resident wave
+
+template <int kSub>
+static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len, int resident)
+{
+    ScoreDeal d{};
+    const long long BHQ = (long long)batch * q_heads, BKV = (long long)batch * kv_heads;
+    const int G = q_heads / kv_heads, rows = 32 * kSub;
+    const DealPass1<kSub> d1(seq_len);
+    if (BHQ * d1.n_units < kDealUnits) {
+        deal_over_waves(resident, BHQ, d1.total(), DealPass1<kSub>::kAlign, 4, &d.p1_len, &d.p1_waves);
+        d.p1_floats = (size_t)BHQ * (d.p1_waves + d1.n_units) * rows;
+    }
+    const DealPass2<kSub> d2(seq_len, G);
+    const double stages = 0.5 * (double)BKV * G * d2.rows_all * d2.n_units / 1024.;
+    const bool fits = (d2.rows_all + 8.) * d2.n_units < 1073741824.;      // a line's stages are counted in 32 bits
+    if (fits && (stages <= kDealStages || BKV < kXcds)) {
+        deal_over_waves(resident, BKV, d2.total(), DealPass2<kSub>::align(G), 1, &d.p2_len, &d.p2_waves);
+        d.p2_floats = (size_t)BKV * (d.p2_waves + d2.n_units) * rows;
+    }
+    return d;
+}
+
+ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32)
+{
+    // (three 16 KB stages of 512-byte rows: three waves in a compute unit's LDS instead of four)
+    return f32 ? score_deal_t<Stream<float>::kSub>(batch, q_heads, kv_heads, seq_len, head_dim == 128 ? 768 : 1024)
+               : score_deal_t<Stream<bf16_t>::kSub>(batch, q_heads, kv_heads, seq_len, 1024);
+}
+
+static long long deal_grid(long long heads, long long waves) { return kXcds * ((heads * waves + kXcds - 1) / kXcds); }
+
 template <typename T, int D>
 static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)
 {
-    constexpr int kRows = 32 * Stream<T>::kSub;
+    constexpr int kSub = Stream<T>::kSub, kRows = 32 * kSub;
     const int BKV = a.batch * a.kv_heads, G = a.q_heads / a.kv_heads;
     const int n_row_tiles = (a.seq_len + kRows - 1) / kRows;
+    ScoreArgs a1 = a;
+    if (a.p1_waves) {
+        const long long grid = deal_grid((long long)a.batch * a.q_heads, a.p1_waves);
+        if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+        a.queue_clear = 0;
+        hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, true>), dim3((unsigned)grid), dim3(kWave), 0, st, a1);
+        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+        hipLaunchKernelGGL(lse_combine_kernel<kSub>, dim3((a.n_pad + 255) / 256, a.batch * a.q_heads), dim3(256), 0, st, a1);
+        return hipGetLastError();
+    }
     // work items of one (b, kv-head) stream the same K: one group per XCD when there are enough
     // heads to keep all XCDs busy, else groups of the G q-heads of one row tile
-    ScoreArgs a1 = a;
-    const int S = a.p1_splits < 1 ? 1 : a.p1_splits;
-    a1.p1_splits = S;
-    if (BKV >= kXcds) { a1.p1_groups = BKV; a1.p1_per_group = n_row_tiles * G * S; }
-    else { a1.p1_groups = BKV * n_row_tiles; a1.p1_per_group = G * S; }
-    // one queue per XCD; resident waves, one per SIMD (128 per XCD) at most.  The reset (long
-    // launches only: short ones do not use the cursors) clears the second pass's cursors as well.
+    if (BKV >= kXcds) { a1.p1_groups = BKV; a1.p1_per_group = n_row_tiles * G; }
+    else { a1.p1_groups = BKV * n_row_tiles; a1.p1_per_group = G; }
+    // one queue per XCD; resident waves, one per SIMD (128 per XCD).  The reset clears the second
+    // pass's cursors as well.
     const long long per_xcd = xcd_grid(a1.p1_groups, a1.p1_per_group) / kXcds;
     if (kXcds * per_xcd > 0x7fffffffll) return hipErrorInvalidValue;
     a1.p1_local = (int)per_xcd;
-    a1.p1_dynamic = per_xcd >= 4 * 128;                     // at least four rounds per resident wave
-    const unsigned grid1 = (unsigned)(kXcds * (a1.p1_dynamic ? 128 : per_xcd));
-    a.queue_clear = a1.p1_dynamic;                          // tells a second pass that follows whether it still has to clear its cursors
-    if (a1.p1_dynamic) {
-        hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
-        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    }
-    hipLaunchKernelGGL((score_pass1_stream_kernel<T, D>), dim3(grid1), dim3(kWave), 0, st, a1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || S == 1) return e;
-    hipLaunchKernelGGL(lse_combine_kernel, dim3((a.n_pad + 255) / 256, a.batch * a.q_heads), dim3(256), 0, st, a1);
+    a.queue_clear = 1;                                      // tells a second pass that follows that its cursors are clear
+    hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
+    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, false>), dim3(kXcds * 128), dim3(kWave), 0, st, a1);
     return hipGetLastError();
 }
 
 template <typename T, int D>
 static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
 {
-    constexpr int kKeys = 32 * Stream<T>::kSub;
+    constexpr int kSub = Stream<T>::kSub, kKeys = 32 * kSub;
     const int BKV = a.batch * a.kv_heads;
     const int n_key_tiles = (a.seq_len + kKeys - 1) / kKeys;
     if (a.lse_in_nat) {
@@ -1184,24 +1507,32 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
         hipLaunchKernelGGL(lse_to_base2_kernel, g, dim3(256), 0, st, a);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
+    const dim3 reduce_grid((a.seq_len + 255) / 256, BKV);
+    if (a.p2_waves) {
+        const long long grid = deal_grid(BKV, a.p2_waves);
+        if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((score_pass2_stream_kernel<T, D, true>), dim3((unsigned)grid), dim3(kWave), 0, st, a);
+        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+        hipLaunchKernelGGL(score_reduce_deal_kernel<kSub>, reduce_grid, dim3(256), 0, st, a);
+        return hipGetLastError();
+    }
     // Queues: an XCD queue per share of the heads when they divide over the XCDs (else no queues:
-    // groups dealt to the XCDs in turn, one block per pair).  With at least four rounds of items per resident wave (one wave per SIMD:
-    // 128 per XCD) the waves stay and draw from the cursors, and the lightest row chunks -- about
-    // 4.5 % of the items, which covers the spread between XCDs; more costs more in lost L2 sharing
-    // than it balances -- go to the pool; shorter launches get one block per item.
+    // groups dealt to the XCDs in turn, one block per pair).  The resident waves (one per SIMD:
+    // 128 per XCD) draw from the cursors, and the lightest row chunks -- about 4.5 % of the items,
+    // which covers the spread between XCDs; more costs more in lost L2 sharing than it balances --
+    // go to the pool.
     ScoreArgs a2 = a;
     const int r_tiles = a.chunk_rows / kKeys, top = a.n_chunks - 1;
     const long long all = p2_items_upto(top, r_tiles, n_key_tiles);
     a2.q_share = BKV % kXcds == 0 ? BKV / kXcds : 0;
-    a2.q_dynamic = a2.q_share && (long long)BKV * all >= 4ll * 128 * kXcds;
+    a2.q_dynamic = a2.q_share != 0;
     a2.p2_split = 0;
     if (a2.q_dynamic)
         while (a2.p2_split < top && p2_items_upto(a2.p2_split, r_tiles, n_key_tiles) <= all * 45 / 1000) ++a2.p2_split;
     const long long low = p2_items_upto(a2.p2_split - 1, r_tiles, n_key_tiles);
     const long long n_local = a2.q_share * (all - low), n_pool = (long long)BKV * low;
-    const long long per_xcd = n_local + (n_pool + kXcds - 1) / kXcds;
     const long long grid2 = !a2.q_share ? xcd_grid((long long)BKV * a.n_chunks, n_key_tiles)     // no queues: a block per pair, padding included
-                                        : kXcds * (a2.q_dynamic ? 128 : per_xcd);
+                                        : kXcds * 128;
     if (n_local > 0x7fffffffll || n_pool > 0x7fffffffll) return hipErrorInvalidValue;
     if (a.chunk_rows % kKeys != 0 || grid2 > 0x7fffffffll) return hipErrorInvalidValue;
     a2.p2_local = (int)n_local; a2.p2_pool = (int)n_pool;
@@ -1209,12 +1540,11 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
         hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
-    hipLaunchKernelGGL((score_pass2_stream_kernel<T, D>), dim3((unsigned)grid2), dim3(kWave), 0, st, a2);
+    hipLaunchKernelGGL((score_pass2_stream_kernel<T, D, false>), dim3((unsigned)grid2), dim3(kWave), 0, st, a2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.n_chunks > 1) {
-        dim3 g((a.seq_len + 255) / 256, BKV);
-        hipLaunchKernelGGL(score_reduce_kernel, g, dim3(256), 0, st, a, kKeys);
+        hipLaunchKernelGGL(score_reduce_kernel, reduce_grid, dim3(256), 0, st, a, kKeys);
         e = hipGetLastError();
     }
     return e;

@@ -72,6 +72,46 @@ def test_score_every_remainder_of_interior_stages(group, mode):
             np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape", [
+    (1, 1030, 1030, 64, 70, 5),      # more heads than resident waves: one stretch per head
+    (1, 40, 40, 64, 1111, 100),      # stretches that end inside the diagonal stages and inside the window
+    (2, 16, 2, 128, 1537, 600),      # eight q-heads per kv-head; the window spans several stretches and key tiles
+    (5, 5, 5, 64, 257, 64),          # second unit of one row; most stretches shorter than their lead
+    (1, 96, 32, 64, 3000, 33),       # three q-heads per kv-head, several units per stretch
+])
+def test_score_even_deal(shape, mode):
+    """Launches that are cut by stages: every part of every unit is counted once, whatever a stretch's
+    ends fall on.  Tolerance: the stated bars."""
+    b, hq, hkv, d, n, w = shape
+    _log("even deal", shape, "mode", mode)
+    inp = ems_inputs.small(b, hq, hkv, d, n, seed=n + w)
+    p = B.EmsParams(b, hq, hkv, d, n, w, dtype=mode)
+    s_glo, s_loc, lse = B.ems_global_local_score(p, dev_tensor(inp.q, mode), dev_tensor(inp.k, mode), want_lse=True)
+    o_glo, o_loc, o_lse = ems_ref.score(ref_params(p), inp.f32("q"), inp.f32("k"), want_lse=True)
+    assert_rel(s_glo.cpu().numpy(), o_glo, RTOL[mode], "s_glo")
+    assert_rel(s_loc.cpu().numpy(), o_loc, RTOL[mode], "s_loc")
+    np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
+
+
+@pytest.mark.parametrize("mode", MODES)
+def test_score_first_stage_far_below_the_others(mode):
+    """The first stage of a part gives the reference exponent; here later logits exceed it by far more than
+    the float range, so the sums overflow and the parts are redone with a running maximum.  A weight is
+    2^x with |x| up to 4 * 64 * 1.44 = 370 formed in float32: relative error a few times 370 * 2^-23 * ln 2 = 3e-5."""
+    b, hq, hkv, d, n, w = 1, 4, 2, 64, 1500, 40
+    inp = ems_inputs.small(b, hq, hkv, d, n, seed=21)
+    kf = inp.f32("k").copy()
+    kf[:, :, 700:] *= 64.0                                   # exact in bf16
+    q, k = dev_tensor(inp.q, mode), torch.from_numpy(kf).cuda().to(torch.float32 if mode == B.EMS_F32 else torch.bfloat16)
+    p = B.EmsParams(b, hq, hkv, d, n, w, dtype=mode)
+    s_glo, s_loc, lse = B.ems_global_local_score(p, q, k, want_lse=True)
+    o_glo, o_loc, o_lse = ems_ref.score(ref_params(p), inp.f32("q"), kf, want_lse=True)
+    assert_rel(s_glo.cpu().numpy(), o_glo, max(RTOL[mode], 4e-4), "s_glo")
+    assert_rel(s_loc.cpu().numpy(), o_loc, max(RTOL[mode], 4e-4), "s_loc")
+    np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=2e-6, atol=1e-4)
+
+
 def test_score_custom_scale_and_large_logits():
     """Logits of magnitude ~40: the running maximum of pass 1 has to do its job."""
     b, hq, hkv, d, n, w = 1, 2, 2, 128, 600, 16

@@ -14,7 +14,7 @@ CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libems_hip.so")
 SOURCES = ["ems_api.hip", "score.hip", "select.hip", "merge.hip", "decode.hip", "stats.hip"]
-HEADERS = ["ems_common.h", "ems_kernels.h", "ems_rows.h", os.path.join("..", "..", "include", "ems.h")]
+HEADERS = ["ems_common.h", "ems_kernels.h", "ems_rows.h", "ems_stream.h", os.path.join("..", "..", "include", "ems.h")]
 # the benchmark's ceiling measurements: a library of their own, outside the product's interface
 PROBE_DIR = os.path.join(_HERE, "bench_probe")
 PROBE_LIB = os.path.join(_HERE, "libems_probe.so")
@@ -26,13 +26,14 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Wall", "-Wno-unused-function",
          # the LDS-DMA inline assembly names M0 as clobbered, which clang flags as reserved
          "-Wno-inline-asm"] + os.environ.get("EMS_EXTRA_HIPCC_FLAGS", "").split()
-# The score kernels read every accumulator element with the vector ALU: matrix results go to
+# These kernels read every accumulator element with the vector ALU: matrix results go to
 # ordinary vector registers, never to the accumulation file (which the ALU cannot read).
-FILE_FLAGS = {"score.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Rpass-analysis=kernel-resource-usage"]}
+_STREAM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Rpass-analysis=kernel-resource-usage"]
+FILE_FLAGS = {"score.hip": _STREAM, "stats.hip": _STREAM}
 # Kernels that count their own vector-memory operations (s_waitcnt vmcnt(n) by hand around the
 # LDS DMA): a register spill would add scratch loads/stores the count does not know about, so
 # such a build is rejected instead of being allowed to run with a silent race.
-NO_SCRATCH = {"score.hip": ("score_pass1", "score_pass2")}
+NO_SCRATCH = {"score.hip": ("score_pass1", "score_pass2"), "stats.hip": ("redundancy_stream",)}
 
 
 def _check_no_scratch(src: str, remarks: str) -> None:

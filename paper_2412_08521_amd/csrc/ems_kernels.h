@@ -147,6 +147,7 @@ struct StatsArgs {
     float* r_out;           // [bkv]
     float* best;            // [bkv, seq_len]
     int bkv, head_dim, seq_len;
+    int red_waves, red_len; // 16-bit redundancy: waves per head, stages per wave (set by the launcher; else 0)
     float zeta, tau;
 };
 

@@ -13,131 +13,15 @@
 // the stationary operand), with a private LDS ring for the streamed operand.
 #include "ems_common.h"
 #include "ems_kernels.h"
-
-#include <algorithm>
-#include <type_traits>
+#include "ems_stream.h"
 
 namespace ems {
-
-// ---- staging of the streamed operand: global memory -> LDS without passing through
-// registers (global_load_lds_dwordx4), a ring of stages deep.
-//
-// One instruction moves 64 lanes x 16 bytes into 1 KiB of consecutive LDS; which 16 bytes of
-// global memory a lane fetches is free, so rows are stored unpadded with their 16-byte
-// chunks XOR-swizzled by the row number: the 16 lanes that read one chunk column of 16
-// consecutive rows then hit 16 different bank groups.  Rows past the end of the matrix
-// re-read the last row: callers never let such rows contribute (they are masked by
-// causality or carry an infinite log-sum-exp).
-template <typename T, int D>
-__device__ __forceinline__ int swz_key(int row)
-{
-    return Tile<T, D>::kChunksPerRow >= 16 ? (row & 15) : ((row >> 1) & 7);
-}
-
-// One DMA instruction: every lane moves `kBytes` (16 or 4) from base + off (off per lane,
-// base wave-uniform) to LDS byte address lds_addr + lane * kBytes (lds_addr wave-uniform;
-// the hardware takes it from M0).  Written as inline assembly on purpose: the compiler would
-// otherwise make every later LDS read wait for all DMA in flight, which defeats prefetching
-// more than one stage ahead.  Completion is tracked by hand with wait_vmem().
-template <int kBytes>
-__device__ __forceinline__ void dma_to_lds(const void* base, unsigned off, unsigned lds_addr)
-{
-    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_addr);
-    if (kBytes == 16)
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(m0v) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(m0v) : "memory", "m0");
-}
-
-// Four 16-byte DMA instructions under one M0 value: the instruction's immediate offset
-// (0, 1024, 2048, 3072) is added to the global address and to the LDS address alike, so
-// instruction i moves 1 KiB from base + off_i + 1024 i to LDS lds_addr + 1024 i.  The
-// per-lane offsets are passed without the 1024 i term; those of a stage's second (third, ..)
-// group of four hold the group's 4 KiB instead, so that all groups share one base.
-__device__ __forceinline__ void dma_to_lds_x4(const void* base, unsigned off0, unsigned off1, unsigned off2,
-                                              unsigned off3, unsigned lds_addr)
-{
-    const unsigned m0v = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile("s_mov_b32 m0, %5\n\t"
-                 "global_load_lds_dwordx4 %0, %4\n\t"
-                 "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
-                 "global_load_lds_dwordx4 %3, %4 offset:3072"
-                 ::"v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base), "s"(m0v) : "memory", "m0");
-}
-
-// The same two with the LDS address given as a wave-uniform base plus a compile-time offset: one
-// scalar instruction sets M0.
-template <int kLdsOff>
-__device__ __forceinline__ void dma_to_lds_x4_at(const void* base, unsigned off0, unsigned off1, unsigned off2,
-                                                 unsigned off3, unsigned lds_base)
-{
-    asm volatile("s_add_u32 m0, %5, %6\n\t"
-                 "global_load_lds_dwordx4 %0, %4\n\t"
-                 "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
-                 "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
-                 "global_load_lds_dwordx4 %3, %4 offset:3072"
-                 ::"v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base), "s"(lds_base), "n"(kLdsOff) : "memory", "m0", "scc");
-}
-template <int kLdsOff>
-__device__ __forceinline__ void dma_dword_to_lds_at(const void* base, unsigned off, unsigned lds_base)
-{
-    asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dword %0, %1" ::"v"(off), "s"(base), "s"(lds_base), "n"(kLdsOff)
-                 : "memory", "m0", "scc");
-}
-
-// The value itself, made opaque to the optimiser (stops loop-invariant code motion of what is
-// computed from it).
-__device__ __forceinline__ int opaque_lane(int v)
-{
-    asm volatile("" : "+v"(v));
-    return v;
-}
-
-// Tells the compiler that a tuple without a value yet begins its life here (an accumulator set in only
-// some branches would otherwise keep its registers through the loops around it).
-__device__ __forceinline__ void defined_here(f32x16_t& v) { asm volatile("" : "=v"(v)); }
-
-// LDS byte address of a __shared__ object.
-__device__ __forceinline__ unsigned lds_address(const void* p)
-{
-    return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
-// Wait until at most kOutstanding of this wave's vector-memory operations are in flight
-// (they complete in order), leaving the other counters alone.  The counts the kernels pass
-// assume that between the DMA of a stage and its wait the wave issues NO other vector-memory
-// instruction -- in particular no scratch (spill) load or store: the build rejects a score
-// kernel whose compiled form uses scratch memory.
-template <int kOutstanding>
-__device__ __forceinline__ void wait_vmem()
-{
-    static_assert(kOutstanding >= 0 && kOutstanding < 64, "vmcnt is a 6-bit counter");
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kOutstanding) : "memory");
-}
-
-// The same wait for "nothing in flight", in the form the compiler can see: used once after
-// the stationary operand's ordinary loads, so that the compiler does not re-insert a full
-// wait for them in front of their first use inside the main loop.
-__device__ __forceinline__ void wait_vmem_all_visible()
-{
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), expcnt and lgkmcnt left alone
-}
-
-// One wait for every LDS read in flight, in the form the compiler can see.  Placed well after a
-// batch of fragment reads, it replaces the separate wait the compiler would otherwise put in
-// front of each fragment's first use (a dozen scalar instructions per stage).
-__device__ __forceinline__ void wait_lds_all_visible()
-{
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0), vmcnt and expcnt left alone
-}
 
 // The hardware deals workgroups to the 8 XCDs (each with its own L2) round-robin in launch
 // order: block b runs on XCD b % 8.  First pass: work is cut into groups of `per_group`
 // consecutive work items that stream the same operand; group g belongs to XCD g % 8 so that the
 // group shares one L2.  Returns the linear index of the k-th work item of XCD `xcd`, or -1 for
 // padding.
-constexpr int kXcds = 8;
 __device__ __forceinline__ int xcd_work_item(int n_groups, int per_group, int xcd, int k)
 {
     const int group = (k / per_group) * kXcds + xcd;
@@ -208,43 +92,6 @@ __host__ __device__ inline long long p2_items_upto(int I, int r, int n_key_tiles
     return r * whole * (whole + 1) / 2 + (n - whole) * n_key_tiles;
 }
 
-// ---- the even deal.  Launches too short for work queues (a few items per wave, so whole items are
-// left over at the end) are cut by stages instead: a head's work is laid out as one line of stages,
-// unit (row tile or key tile) after unit, and every wave takes an equal stretch of it, going from one
-// unit into the next in its middle.  A stretch leaves its part of a unit's result in slot (wave + unit)
-// of the head -- along the line each new part raises one of the two by one, so the slots are distinct --
-// and a small kernel adds a unit's parts in order.  A wave's stretch follows from its place in the head
-// and the stretch length alone.  Units start at whole trips of the 16-bit interior loops (kTrip),
-// so that cuts at multiples of a trip leave no odd stages for the masked loops.  Every unit is preceded
-// by `lead` stages that do not exist: what a wave pays for beginning a unit beside its stages (the
-// stationary operand's load, 8 us when all waves load at once, and the masked stages, 2.0 us where an
-// interior stage takes 1.5: head size 128, measured in the kernels).
-constexpr int kStreamRows = 32;            // rows per stage (one MFMA row tile)
-constexpr int kTrip = 4;
-
-// First pass: unit u = 32 * kSub query rows, its stages = 32 keys each up to the diagonal's end.
-template <int kSub>
-struct DealPass1 {
-    static constexpr int kAlign = kSub % kTrip == 0 ? kTrip : 1;
-    static constexpr int kLead = kSub % kTrip == 0 ? 8 : 2;
-    int n_stages, n_units;
-    __host__ __device__ explicit DealPass1(int N) : n_stages((N + kStreamRows - 1) / kStreamRows), n_units((n_stages + kSub - 1) / kSub) {}
-    __host__ __device__ int start(int u) const { return kSub * (u * (u + 1) / 2) + kLead * u; }
-    __host__ __device__ int first(int u) const { return start(u) + kLead; }      // its first real stage
-    __host__ __device__ int end(int u) const               // (only the last unit may be short)
-    {
-        const int n = kSub * (u + 1) < n_stages ? kSub * (u + 1) : n_stages;
-        return first(u) + (n + kAlign - 1) / kAlign * kAlign;
-    }
-    __host__ __device__ int total() const { return end(n_units - 1); }
-    __device__ int unit_at(int pos) const                  // the unit that holds stage `pos` of the line
-    {
-        int lo = 0, hi = n_units;                          // start(lo) <= pos < start(hi)
-        while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (start(mid) <= pos) lo = mid; else hi = mid; }
-        return lo;
-    }
-};
-
 // Second pass: unit u = 32 * kSub keys, its stages = 32 query rows each (of every q-head of the group)
 // from the diagonal on.
 template <int kSub>
@@ -273,19 +120,6 @@ struct DealPass2 {
     }
 };
 
-// A value that is the same in every lane, into a scalar register.
-__device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Wave of an even deal -> its place: the waves of a head are neighbours on one XCD (and share its L2).
-struct DealPlace { int head, wave; };
-__device__ __forceinline__ DealPlace deal_place(int heads, int waves)
-{
-    const int n = heads * waves, per_xcd = (n + kXcds - 1) / kXcds;
-    const int i = blockIdx.x / kXcds, w = (int)(blockIdx.x % kXcds) * per_xcd + i;
-    if (i >= per_xcd || w >= n) return {-1, 0};
-    return {scalar(w / waves), scalar(w % waves)};
-}
-
 // sum of the 16 accumulator-derived values with four independent partial sums
 __device__ __forceinline__ float sum16(const float (&p)[16])
 {
@@ -293,11 +127,6 @@ __device__ __forceinline__ float sum16(const float (&p)[16])
 #pragma unroll
     for (int r = 4; r < 16; r += 4) { s0 += p[r]; s1 += p[r + 1]; s2 += p[r + 2]; s3 += p[r + 3]; }
     return (s0 + s1) + (s2 + s3);
-}
-
-__device__ __forceinline__ f32x16_t zero_acc()
-{
-    return f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 }
 
 __device__ __forceinline__ float max16(const f32x16_t& acc)
@@ -457,7 +286,6 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 // registers in the 16-bit types) and LDS stages in the wave's ring
 template <typename T> struct Stream { static constexpr int kSub = 8; static constexpr int kRing = 4; };
 template <> struct Stream<float> { static constexpr int kSub = 2; static constexpr int kRing = 3; };
-template <int v> using ic = std::integral_constant<int, v>;
 
 // The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
 // the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
@@ -485,22 +313,6 @@ __device__ __forceinline__ void advance_cursor(int& h_left, int& t_left, const c
     q += aq;
     l += al;
 }
-
-// The same for one source without heads (the first pass's keys).
-template <int kStep>
-__device__ __forceinline__ void advance_cursor(int& t_left, const char*& k)
-{
-    long long ak;
-    asm volatile(
-        "s_cmp_gt_i32 %[t], 1\n\t"
-        "s_cselect_b64 %[ak], %[ks], 0\n\t"
-        "s_sub_u32 %[t], %[t], 1"
-        : [t] "+s"(t_left), [ak] "=&s"(ak)
-        : [ks] "i"(kStep)
-        : "scc");
-    k += ak;
-}
-
 
 // One 32-row x 32-key tile of the edge loop: weights added into the lane's column sums; the
 // tile may cross the diagonal and may hold last-window rows.
@@ -1405,23 +1217,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
 int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<float>::kSub : Stream<bf16_t>::kSub); }
 
-// Stretch length and waves per head of an even deal of `heads` lines of `total` stages over the
-// `resident` waves the chip holds (one per SIMD, fewer where the rings fill the LDS first).  More than one round of waves is worth it only where the heads
-// divide the waves badly; a part costs about two and a half stages beside its stages (stationary
-// operand, ring start).
-static void deal_over_waves(int resident, long long heads, long long total, int align, int shortest, int* len, int* waves)
-{
-    double best = 0.;
-    for (int rounds = 1; rounds <= 4; ++rounds) {
-        const long long per_head = std::max(1ll, (long long)resident * rounds / heads);
-        long long l = std::max((long long)shortest, (total + per_head - 1) / per_head);
-        l = (l + align - 1) / align * align;
-        const long long w = (total + l - 1) / l;
-        const double cost = (double)((heads * w + resident - 1) / resident) * ((double)l + 2.5);
-        if (rounds == 1 || cost < best) { best = cost; *len = (int)l; *waves = (int)w; }
-    }
-}
-
 // Which launches are dealt evenly (bf16, head size 128, times of the pass in us, even deal against whole
 // items; both with the masked stages in the pipeline):
 //   first pass    1 x 32 heads:  8192: 247 / 358 (queues), 249 (key-range splits, now gone);  16384: 907 / 922;
@@ -1461,8 +1256,6 @@ ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head
     return f32 ? score_deal_t<Stream<float>::kSub>(batch, q_heads, kv_heads, seq_len, head_dim == 128 ? 768 : 1024)
                : score_deal_t<Stream<bf16_t>::kSub>(batch, q_heads, kv_heads, seq_len, 1024);
 }
-
-static long long deal_grid(long long heads, long long waves) { return kXcds * ((heads * waves + kXcds - 1) / kXcds); }
 
 template <typename T, int D>
 static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)

@@ -92,3 +92,40 @@ def test_redundancy_rate_matches_oracle(shape, mode):
     assert 0.02 < o_rate.mean() < 0.5
     # the rate is exactly the count of the kernel's own best values
     np.testing.assert_array_equal(got, (best >= np.float32(tau)).sum(-1))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bh_n", [(1, 1), (3, 2), (2, 33), (1, 127), (5, 128), (2, 129), (1, 257), (1100, 70), (40, 1025), (1, 4100)])
+@pytest.mark.parametrize("scale", ["plain", "extreme"])
+def test_redundancy_edges(bh_n, d, scale):
+    """Token tiles of 128 with one row more or less, more heads than resident waves, stretches that end inside
+    the diagonal's stages; rows of norm zero and rows scaled by 2^30 to 2^45 either way (cosines do not
+    change, the products of two rows' norms leave the range the short form is made for).  Tolerance: a cosine
+    is a float32 sum of 128 products, 128 * 2^-24 = 8e-6 at most, two of them multiplied."""
+    bh, n = bh_n
+    _log("redundancy edges", bh_n, d, scale)
+    inp = ems_inputs.small(1, bh, bh, d, n, seed=n + d)
+    kf, vf = inp.f32("k").copy(), inp.f32("v").copy()
+    for t in range(5, n, 7):
+        kf[:, :, t] = kf[:, :, t // 2]
+        vf[:, :, t] = vf[:, :, t // 2] + 0.5 * vf[:, :, t]
+    kf[:, :, 3::50] = 0.0
+    if scale == "extreme":
+        kf[:, :, 1::5] *= 2.0 ** 30
+        vf[:, :, 1::5] *= 2.0 ** 45
+        vf[:, :, 2::9] *= 2.0 ** -40
+    kb, vb = ems_inputs.f32_to_bf16_bits(kf), ems_inputs.f32_to_bf16_bits(vf)
+    p = B.EmsParams(1, bh, bh, d, n, 1, tau=0.6)
+    rate, best = B.ems_redundancy_rate(p, dev_tensor(kb, B.EMS_BF16), dev_tensor(vb, B.EMS_BF16))
+    best = best.cpu().numpy()
+    if bh <= 40:
+        _, o_best = ems_ref.redundancy(RefParams(1, bh, bh, d, n, 1, tau=0.6), ems_inputs.bf16_bits_to_f32(kb), ems_inputs.bf16_bits_to_f32(vb))
+    else:                                              # heads are independent: the first and the last of many
+        pick = [0, bh - 1]
+        o = RefParams(1, 2, 2, d, n, 1, tau=0.6)
+        _, o_best = ems_ref.redundancy(o, ems_inputs.bf16_bits_to_f32(kb)[:, pick], ems_inputs.bf16_bits_to_f32(vb)[:, pick])
+        got = np.rint(rate.cpu().numpy() * n)
+        np.testing.assert_array_equal(got, (best >= np.float32(0.6)).sum(-1))
+        best = best[:, pick]
+    assert (best[..., 0] == -np.inf).all()
+    np.testing.assert_allclose(best[..., 1:], o_best[..., 1:], rtol=0, atol=2e-5)

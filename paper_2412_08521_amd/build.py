@@ -29,7 +29,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # These kernels read every accumulator element with the vector ALU: matrix results go to
 # ordinary vector registers, never to the accumulation file (which the ALU cannot read).
 _STREAM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Rpass-analysis=kernel-resource-usage"]
-FILE_FLAGS = {"score.hip": _STREAM, "stats.hip": _STREAM}
+FILE_FLAGS = {"score.hip": _STREAM, "stats.hip": _STREAM, "merge.hip": _STREAM[:2]}
 # Kernels that count their own vector-memory operations (s_waitcnt vmcnt(n) by hand around the
 # LDS DMA): a register spill would add scratch loads/stores the count does not know about, so
 # such a build is rejected instead of being allowed to run with a silent race.

@@ -77,6 +77,11 @@ struct MergeArgs {
     int slice_rows, n_slices;
     float* part_best;     // [B*Hkv, n_slices, n_tbm] best similarity within the slice
     int32_t* part_arg;    // [B*Hkv, n_slices, n_tbm] its centre
+    // set by the launcher: output rows per wave; merge blocks per head, of which the first share the zero
+    // class; where their sums go and how many floats a head has there
+    int rows_per_wave, merge_blocks, zero_blocks;
+    float* zero_part;
+    size_t zero_stride;
 };
 
 struct ExpandArgs {

@@ -6,25 +6,6 @@
 
 namespace ems {
 
-// sum of squares of the 16-byte fragment's elements, in f32
-template <typename T> __device__ __forceinline__ float frag_sumsq(const frag_t& f);
-template <> __device__ __forceinline__ float frag_sumsq<bf16_t>(const frag_t& f)
-{
-    const bf16x8_t v = __builtin_bit_cast(bf16x8_t, f);
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { const float x = (float)v[i]; s = __builtin_fmaf(x, x, s); }
-    return s;
-}
-template <> __device__ __forceinline__ float frag_sumsq<float>(const frag_t& f)
-{
-    const f32x4_t v = __builtin_bit_cast(f32x4_t, f);
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) s = __builtin_fmaf(v[i], v[i], s);
-    return s;
-}
-
 // dot product of the 8 bf16 elements of two 16-byte row pieces, f32 accumulation
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float dot8_bf16(const frag_t& x, const frag_t& y)
@@ -38,7 +19,26 @@ __device__ __forceinline__ float dot8_bf16(const frag_t& x, const frag_t& y)
     return acc;
 }
 
+// sum of squares of the 16-byte fragment's elements, in f32
+template <typename T> __device__ __forceinline__ float frag_sumsq(const frag_t& f);
+template <> __device__ __forceinline__ float frag_sumsq<bf16_t>(const frag_t& f) { return dot8_bf16(f, f); }
+template <> __device__ __forceinline__ float frag_sumsq<float>(const frag_t& f)
+{
+    const f32x4_t v = __builtin_bit_cast(f32x4_t, f);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = __builtin_fmaf(v[i], v[i], s);
+    return s;
+}
+
 __device__ __forceinline__ float inv_norm(float sumsq) { return sumsq > 0.f ? 1.0f / sqrtf(sumsq) : 0.f; }
+
+// the same by the hardware's reciprocal square root (1 ulp), which is not made for the smallest values
+__device__ __forceinline__ float inv_norm_fast(float sumsq)
+{
+    if (sumsq >= 0x1p-100f) return __builtin_amdgcn_rsqf(sumsq);
+    return inv_norm(sumsq);
+}
 
 template <typename T> struct Pack;
 template <> struct Pack<bf16_t> {

@@ -15,6 +15,8 @@
 #include "ems_kernels.h"
 #include "ems_rows.h"
 
+#include <algorithm>
+
 namespace ems {
 
 constexpr int kMrgWaves = 4;
@@ -23,10 +25,27 @@ constexpr int kDestDepth = 4;        // centre stages whose rows a block has in 
 constexpr int kDestMaxSlices = 16;   // centre slices per head at most
 constexpr int kMergeWaves = 8;       // output rows per merge block
 constexpr int kMergeBlock = kMergeWaves * kWave;
-constexpr int kMergePiece = 4096;    // TBM tokens whose destinations a merge block holds in LDS
+constexpr int kMergeStretch = 512;   // TBM tokens that a wave of a merge block sifts at a time
+constexpr int kMergeMaxRows = 8;     // output rows per wave of a merge block at most
+constexpr int kMergeFew = 4;         // members up to which a slot is one lane group's work
+constexpr int kZeroTokens = 512;     // TBM tokens per block of a shared zero class
 
 template <typename T> struct DestCfg { static constexpr int kStageRows = 64; };
 template <> struct DestCfg<float> { static constexpr int kStageRows = 32; };
+
+// Blocks are dealt to the 8 XCDs in turn by their index; each XCD takes consecutive (head, block of the
+// head) pairs, so that the rows of a head are gathered into one L2 by every kernel of the stage (4032
+// centres, 4096 tokens, 8 heads: a head's keys are 2 MB of the 4 MB, all heads' 16 MB).
+constexpr int kMrgXcds = 8;
+struct HeadBlock { int head, block; };
+__device__ __forceinline__ HeadBlock head_block(int heads, int per_head)
+{
+    const int n = heads * per_head, per_xcd = (n + kMrgXcds - 1) / kMrgXcds;
+    const int i = blockIdx.x / kMrgXcds, w = (int)(blockIdx.x % kMrgXcds) * per_xcd + i;
+    if (i >= per_xcd || w >= n) return {-1, 0};
+    return {w / per_head, w % per_head};
+}
+static long long head_grid(long long heads, long long per_head) { return kMrgXcds * ((heads * per_head + kMrgXcds - 1) / kMrgXcds); }
 
 __device__ __forceinline__ int clamp_pos(int p, int n) { return min(max(p, 0), n - 1); }
 
@@ -34,11 +53,14 @@ __device__ __forceinline__ int clamp_pos(int p, int n) { return min(max(p, 0), n
 // Destination of every TBM token (Eq. 5, then the threshold).  The redundancy is the key
 // cosine, the value cosine or their product (Sec. 4.1; similarity ablation of App. B):
 // kSim = 0 / 1 / 2, i.e. one or two sources, each with its own MFMA contraction.
-// Block = (128 TBM tokens, one (b, kv-head)); each wave keeps 32 TBM rows in registers as
-// the MFMA B operand (tokens -> lanes) and the centre rows stream through LDS as the A
-// operand (centres -> accumulator registers), so the running arg-max is a per-lane pair.
+// Block = (128 * kTok TBM tokens, one slice of the centres, one (b, kv-head)); each wave keeps
+// 32 * kTok TBM rows in registers as the MFMA B operand (tokens -> lanes) and the centre rows stream
+// through LDS as the A operand (centres -> accumulator registers), so the running arg-max is a
+// per-lane pair.  A centre row is gathered once per token tile: with many tokens larger tiles pay
+// (4032 centres, 4096 tokens, 8 heads: 88 us with one tile of 32 per wave, 77 with two; four leave one
+// wave per SIMD: 108).
 // ------------------------------------------------------------------------------------
-template <typename T, int D, int kSim>
+template <typename T, int D, int kSim, int kTok>
 __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
 {
     constexpr int kStageRows = DestCfg<T>::kStageRows;
@@ -52,7 +74,10 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
     __shared__ __attribute__((aligned(16))) float lds_rn[kSrc][kStageRows];
 
     const int N = a.seq_len, n_imp = a.n_imp, n_tbm = a.n_tbm;
-    const int bkv = blockIdx.z, slice = blockIdx.y;
+    const int tiles = (n_tbm + kMrgWaves * 32 * kTok - 1) / (kMrgWaves * 32 * kTok);
+    const HeadBlock hb = head_block(a.bkv, tiles * a.n_slices);
+    if (hb.head < 0) return;                                // block-uniform
+    const int bkv = hb.head, slice = hb.block / tiles, tile = hb.block % tiles;
     const int c_begin = slice * a.slice_rows, c_end = min(n_imp, c_begin + a.slice_rows);   // this block's centres
     const T* K = reinterpret_cast<const T*>(a.k) + ((size_t)bkv * N) * D;
     const T* V = reinterpret_cast<const T*>(a.v) + ((size_t)bkv * N) * D;
@@ -65,41 +90,14 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int col = lane & 31, half = lane >> 5;
-    const int ti = blockIdx.x * (kMrgWaves * 32) + wave * 32 + col;   // this lane's TBM token
-    const bool t_ok = ti < n_tbm;
-    const int t_pos = t_ok ? clamp_pos(tbm[ti], N) : 0;
-
-    frag_t bt[kSrc][kFrags];
-    float t_rn[kSrc];
-    float k_sumsq = 0.f;
-#pragma unroll
-    for (int s = 0; s < kSrc; ++s) {
-        float ss = 0.f;
-#pragma unroll
-        for (int f = 0; f < kFrags; ++f) {
-            bt[s][f] = load_frag_or_zero(src[s], (size_t)t_pos * Tile<T, D>::kRowBytes + f * 32 + half * 16, t_ok);
-            ss += frag_sumsq<T>(bt[s][f]);
-        }
-        ss += __shfl_xor(ss, 32);
-        t_rn[s] = inv_norm(ss);
-        if (kSim != 1 && s == 0) k_sumsq = ss;
-    }
-    if constexpr (kSim == 1) {                                      // the key norm is an output in every mode
-#pragma unroll
-        for (int f = 0; f < kFrags; ++f)
-            k_sumsq += frag_sumsq<T>(load_frag_or_zero(K, (size_t)t_pos * Tile<T, D>::kRowBytes + f * 32 + half * 16, t_ok));
-        k_sumsq += __shfl_xor(k_sumsq, 32);
-    }
-
-    float best = -INFINITY;
-    int arg = 0;
+    const int ti0 = (tile * kMrgWaves + wave) * (32 * kTok) + col;   // this lane's first TBM token (of kTok, 32 apart)
 
     // A round is kDestDepth stages of kStageRows centres.  All of a round's centre positions,
     // then all of its rows, are requested before the first stage is used: two global round
-    // trips per round, however many stages it has.
-    for (int r0 = c_begin; r0 < c_end; r0 += kDestDepth * kStageRows) {
-        int pos_pf[kDestDepth][kPerThread];
-        frag_t pf[kDestDepth][kSrc][kPerThread];
+    // trips per round, however many stages it has; the first round's share theirs with the tokens'.
+    int pos_pf[kDestDepth][kPerThread];
+    frag_t pf[kDestDepth][kSrc][kPerThread];
+    auto request_positions = [&](int r0) __attribute__((always_inline)) {
 #pragma unroll
         for (int st = 0; st < kDestDepth; ++st)
 #pragma unroll
@@ -107,6 +105,8 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                 const int ci = r0 + st * kStageRows + (threadIdx.x + i * kMrgBlock) / kCpr;
                 pos_pf[st][i] = ci < c_end ? clamp_pos(imp[ci], N) : -1;
             }
+    };
+    auto request_rows = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int st = 0; st < kDestDepth; ++st)
 #pragma unroll
@@ -116,6 +116,54 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                 for (int s = 0; s < kSrc; ++s)
                     pf[st][s][i] = load_frag_or_zero(src[s], ((size_t)max(pos_pf[st][i], 0) * kCpr + cc) * 16, pos_pf[st][i] >= 0);
             }
+    };
+
+    frag_t bt[kTok][kSrc][kFrags], kt[kSim == 1 ? kTok : 1][kFrags];
+    float t_rn[kTok][kSrc], k_sumsq[kTok];
+    int t_pos[kTok];
+#pragma unroll
+    for (int tk = 0; tk < kTok; ++tk) t_pos[tk] = ti0 + 32 * tk < n_tbm ? clamp_pos(tbm[ti0 + 32 * tk], N) : 0;
+    request_positions(c_begin);
+#pragma unroll
+    for (int tk = 0; tk < kTok; ++tk) {                              // (a lane past the list's end: any row, its result is not kept)
+#pragma unroll
+        for (int s = 0; s < kSrc; ++s)
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f)
+                bt[tk][s][f] = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(src[s]) + (size_t)t_pos[tk] * Tile<T, D>::kRowBytes + f * 32 + half * 16);
+        if constexpr (kSim == 1) {                                  // the key norm is an output in every mode
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f)
+                kt[tk][f] = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(K) + (size_t)t_pos[tk] * Tile<T, D>::kRowBytes + f * 32 + half * 16);
+        }
+    }
+    request_rows();
+#pragma unroll
+    for (int tk = 0; tk < kTok; ++tk) {
+#pragma unroll
+        for (int s = 0; s < kSrc; ++s) {
+            float ss = 0.f;
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) ss += frag_sumsq<T>(bt[tk][s][f]);
+            ss += __shfl_xor(ss, 32);
+            t_rn[tk][s] = inv_norm(ss);
+            if (s == 0) k_sumsq[tk] = ss;
+        }
+        if constexpr (kSim == 1) {
+            float ss = 0.f;
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) ss += frag_sumsq<T>(kt[tk][f]);
+            k_sumsq[tk] = ss + __shfl_xor(ss, 32);
+        }
+    }
+
+    float best[kTok];
+    int arg[kTok];
+#pragma unroll
+    for (int tk = 0; tk < kTok; ++tk) { best[tk] = -INFINITY; arg[tk] = 0; }
+
+    for (int r0 = c_begin; r0 < c_end; r0 += kDestDepth * kStageRows) {
+        if (r0 != c_begin) { request_positions(r0); request_rows(); }
 #pragma unroll
         for (int st = 0; st < kDestDepth; ++st) {
             const int c0 = r0 + st * kStageRows;
@@ -130,7 +178,7 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                     *reinterpret_cast<frag_t*>(lds[s] + row * kStride + cc * 16) = pf[st][s][i];
                     // the kCpr consecutive lanes that hold one row add up its squares
                     const float ss = group_sum<kCpr>(frag_sumsq<T>(pf[st][s][i]));
-                    if (cc == 0) lds_rn[s][row] = inv_norm(ss);
+                    if (cc == 0) lds_rn[s][row] = c0 + row < c_end ? inv_norm_fast(ss) : __builtin_nanf("");
                 }
             }
             __syncthreads();
@@ -138,54 +186,76 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
             for (int rs = 0; rs < kStageRows / 32; ++rs) {
                 const int cbase = c0 + rs * 32;
                 if (cbase >= c_end) continue;                  // block-uniform
-                f32x16_t acc[kSrc];
+                f32x16_t acc[kTok][kSrc];
 #pragma unroll
                 for (int s = 0; s < kSrc; ++s) {
-                    acc[s] = f32x16_t{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int f = 0; f < kFrags; ++f) {
                         const frag_t ac = *reinterpret_cast<const frag_t*>(lds[s] + (rs * 32 + col) * kStride + f * 32 + half * 16);
-                        mma<T>(acc[s], ac, bt[s][f]);
+#pragma unroll
+                        for (int tk = 0; tk < kTok; ++tk) {
+                            if (f == 0) mma_first<T>(acc[tk][s], ac, bt[tk][s][f]);
+                            else mma<T>(acc[tk][s], ac, bt[tk][s][f]);
+                        }
                     }
                 }
+                // Four operations per element: the token's own norm is applied to the maximum only, the
+                // winner is noted by its register (a constant) and the tile by one select per tile.
+                float before[kTok];
+                int reg[kTok];
+#pragma unroll
+                for (int tk = 0; tk < kTok; ++tk) { before[tk] = best[tk]; reg[tk] = 0; }
 #pragma unroll
                 for (int q4 = 0; q4 < 4; ++q4) {
-                    f32x4_t rn[kSrc];
+                    f32x4_t rn[kSrc];                          // NaN past the slice's end: never the larger one
 #pragma unroll
                     for (int s = 0; s < kSrc; ++s)
                         rn[s] = *reinterpret_cast<const f32x4_t*>(lds_rn[s] + rs * 32 + 8 * q4 + 4 * half);
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int ci = cbase + 8 * q4 + 4 * half + e;
-                        float sim = (acc[0][4 * q4 + e] * rn[0][e]) * t_rn[0];
-                        if constexpr (kSrc == 2) sim *= (acc[1][4 * q4 + e] * rn[1][e]) * t_rn[1];
-                        if (ci < c_end && sim > best) { best = sim; arg = ci; }
-                    }
+                    for (int tk = 0; tk < kTok; ++tk)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float sim = acc[tk][0][4 * q4 + e] * rn[0][e];
+                            if constexpr (kSrc == 2) sim = (sim * t_rn[tk][0]) * ((acc[tk][1][4 * q4 + e] * rn[1][e]) * t_rn[tk][1]);
+                            reg[tk] = sim > best[tk] ? 4 * q4 + e : reg[tk];
+                            best[tk] = fmaxf(best[tk], sim);   // (NaN counts as the smaller one)
+                        }
                 }
+#pragma unroll
+                for (int tk = 0; tk < kTok; ++tk)
+                    if (best[tk] > before[tk]) arg[tk] = cbase + acc_row(reg[tk], half);
             }
         }
     }
-    // the other half-wave looked at the other centres of every tile
-    const float best_o = __shfl_xor(best, 32);
-    const int arg_o = __shfl_xor(arg, 32);
-    if (best_o > best || (best_o == best && arg_o < arg)) { best = best_o; arg = arg_o; }
-    if (half == 0 && t_ok) {
-        if (a.n_slices == 1) {
-            a.tbm_sim[(size_t)bkv * n_tbm + ti] = best;
-            a.tbm_dest[(size_t)bkv * n_tbm + ti] = best > a.tau ? arg : a.budget;
-        } else {
-            a.part_best[((size_t)bkv * a.n_slices + slice) * n_tbm + ti] = best;
-            a.part_arg[((size_t)bkv * a.n_slices + slice) * n_tbm + ti] = arg;
+#pragma unroll
+    for (int tk = 0; tk < kTok; ++tk) {
+        if constexpr (kSrc == 1)
+            if (best[tk] > -INFINITY) best[tk] *= t_rn[tk][0];
+        // the other half-wave looked at the other centres of every tile
+        const float best_o = __shfl_xor(best[tk], 32);
+        const int arg_o = __shfl_xor(arg[tk], 32);
+        if (best_o > best[tk] || (best_o == best[tk] && arg_o < arg[tk])) { best[tk] = best_o; arg[tk] = arg_o; }
+        const int ti = ti0 + 32 * tk;
+        if (half == 0 && ti < n_tbm) {
+            if (a.n_slices == 1) {
+                a.tbm_sim[(size_t)bkv * n_tbm + ti] = best[tk];
+                a.tbm_dest[(size_t)bkv * n_tbm + ti] = best[tk] > a.tau ? arg[tk] : a.budget;
+            } else {
+                a.part_best[((size_t)bkv * a.n_slices + slice) * n_tbm + ti] = best[tk];
+                a.part_arg[((size_t)bkv * a.n_slices + slice) * n_tbm + ti] = arg[tk];
+            }
+            if (slice == 0) a.k_norm[(size_t)bkv * (n_imp + n_tbm) + n_imp + ti] = sqrtf(k_sumsq[tk]);
         }
-        if (slice == 0) a.k_norm[(size_t)bkv * (n_imp + n_tbm) + n_imp + ti] = sqrtf(k_sumsq);
     }
 }
 
 // The best slice of every TBM token (lowest slice, hence lowest centre, on ties), then the
-// threshold.  One thread per token.
+// threshold.  One thread per token.  Also clears the count of the zero class, on which the merge's
+// blocks count their arrivals.
 __global__ __launch_bounds__(kMrgBlock) void dest_combine_kernel(MergeArgs a)
 {
     const int bkv = blockIdx.y, ti = blockIdx.x * kMrgBlock + threadIdx.x;
+    if (ti == 0) a.slot_count[(size_t)bkv * (a.n_imp + 1) + a.n_imp] = 0;
     if (ti >= a.n_tbm) return;
     const float* pb = a.part_best + (size_t)bkv * a.n_slices * a.n_tbm + ti;
     const int32_t* pa = a.part_arg + (size_t)bkv * a.n_slices * a.n_tbm + ti;
@@ -254,14 +324,6 @@ struct RowAcc {
         wsum += w;
         return sqrtf(ss);
     }
-    __device__ __forceinline__ float add(const T* K, const T* V, int pos, int piece)
-    {
-        return accumulate(load_piece(K, pos, piece), load_piece(V, pos, piece));
-    }
-    __device__ __forceinline__ float add_weighted(const T* K, const T* V, int pos, int piece, float w)
-    {
-        return accumulate_weighted(load_piece(K, pos, piece), load_piece(V, pos, piece), w);
-    }
     // adds the groups together: afterwards every group holds the total
     template <bool kWeighted>
     __device__ __forceinline__ void reduce_groups()
@@ -275,21 +337,18 @@ struct RowAcc {
     }
 };
 
-// Walks the staged TBM tokens (`len` of them: destination and position in LDS) in chunks
-// `first, first+step, ...` of 64, adds those whose destination is `target` to `acc` and
-// returns how many there were.
+// Adds the members of `target` among `len` listed tokens (destination and position in LDS, ascending)
+// to `acc` and returns how many there were; chunks of 64 entries.
 template <typename T, int D, bool kWeighted>
 __device__ __forceinline__ int gather_members(RowAcc<T, D>& acc, const T* K, const T* V, const float* Wt,
-                                              const int* ldest, const int* lpos, int len, int target,
-                                              int first, int step, int* wlist)
+                                              const int* ldest, const int* lpos, int len, int target, int* wlist)
 {
     constexpr int kLpr = RowAcc<T, D>::kLpr, kGroups = RowAcc<T, D>::kGroups;
     const int lane = threadIdx.x % kWave;
     const int grp = lane / kLpr, piece = lane % kLpr;
-    const int n_chunks = (len + kWave - 1) / kWave;
     int count = 0;
-    for (int ch = first; ch < n_chunks; ch += step) {
-        const int i = ch * kWave + lane;
+    for (int c0 = 0; c0 < len; c0 += kWave) {
+        const int i = c0 + lane;
         const bool match = i < len && ldest[i] == target;
         const unsigned long long mask = __ballot(match);
         if (mask == 0ull) continue;                              // wave-uniform
@@ -324,22 +383,39 @@ __device__ __forceinline__ int gather_members(RowAcc<T, D>& acc, const T* K, con
     return count;
 }
 
+// Blocks of a head: first those of the zero class (a.zero_blocks; each takes a stretch of the TBM list,
+// a wave an eighth of it), then the output rows, a.rows_per_wave per wave: class-centre slots, then the
+// local window.
+//
+// A centre block first sifts the TBM list: each wave reads an eighth of a piece of it and keeps, in
+// order, the tokens that go to one of the block's slots; a slot then looks through the few that were
+// kept.  (Walking the whole list for every slot made the kernel 107 us at 4032 slots, 4096 tokens, 8
+// heads; a single zero-class block and slots done one after the other took most of what was left.  Now
+// 48 us: about one row per 16 lanes in flight, its members' rows requested together.)  Several rows per
+// wave where that leaves enough blocks, since every block reads the list once.
+//
+// Several zero-class blocks leave their sums in a.zero_part (the slices' winners, dead by now) and
+// count their arrivals on the class's own count, which the last one to arrive overwrites with the
+// members' number after adding the blocks' sums in block order.
 template <typename T, int D, bool kWeighted>
 __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
 {
     using Acc = RowAcc<T, D>;
-    constexpr int kE = Acc::kE, kLpr = Acc::kLpr;
+    constexpr int kE = Acc::kE, kLpr = Acc::kLpr, kGroups = Acc::kGroups;
 
-    // destinations and positions of a piece of the TBM list, shared by the block's rows
-    __shared__ int ldest[kMergePiece];
-    __shared__ int lpos[kMergePiece];
+    // what was kept of a piece of the TBM list: destination and position
+    __shared__ int ldest[kMergeWaves * kMergeStretch];
+    __shared__ int lpos[kMergeWaves * kMergeStretch];
+    __shared__ int kept_n[kMergeWaves];
     __shared__ int wlist_all[kMergeWaves][kWave];
     __shared__ float zsum[kMergeWaves][2][D];
     __shared__ int zcnt[kMergeWaves];
     __shared__ float zwsum[kMergeWaves];
 
     const int N = a.seq_len, W = a.window, Nb = a.budget, n_imp = a.n_imp, n_tbm = a.n_tbm;
-    const int bkv = blockIdx.y;
+    const HeadBlock hb = head_block(a.bkv, a.merge_blocks);
+    if (hb.head < 0) return;                                // block-uniform
+    const int bkv = hb.head, blk = hb.block;
     const T* K = reinterpret_cast<const T*>(a.k) + ((size_t)bkv * N) * D;
     const T* V = reinterpret_cast<const T*>(a.v) + ((size_t)bkv * N) * D;
     T* Ko = reinterpret_cast<T*>(a.k_out) + ((size_t)bkv * (Nb + 1)) * D;
@@ -355,80 +431,58 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
     const int grp = lane / kLpr, piece = lane % kLpr;
     int* wlist = wlist_all[wave];
 
-    // what this wave produces: block 0 is the zero class (its waves split the TBM list), every
-    // other wave owns one output row: a class-centre slot, a local-window row, or nothing
-    const bool zero_class = blockIdx.x == 0;
-    const int job = zero_class ? -1 : (blockIdx.x - 1) * kMergeWaves + wave;     // wave-uniform
-    const bool centre = !zero_class && job < n_imp;
-    const bool local = !zero_class && job >= n_imp && job < n_imp + W;
-
-    if (local) {
-        // ---- local-window row: copied unchanged
-        const int pos = N - W + (job - n_imp);
-        if (grp == 0) {
-            const frag_t fk = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(K) + ((size_t)pos * kLpr + piece) * 16);
-            const frag_t fv = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(V) + ((size_t)pos * kLpr + piece) * 16);
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Ko) + ((size_t)job * kLpr + piece) * 16) = fk;
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Vo) + ((size_t)job * kLpr + piece) * 16) = fv;
-        }
-        if (lane == 0) kept[job] = pos;
-    }
-
-    // ---- class-centre slot: the centre itself is the first member
-    Acc acc; acc.clear();
-    int c_pos = 0;
-    float c_norm = 0.f;
-    frag_t raw_k = zero_frag(), raw_v = zero_frag();
-    if (centre) {
-        c_pos = clamp_pos(imp[job], N);
-        if (grp == 0) {
-            raw_k = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(K) + ((size_t)c_pos * kLpr + piece) * 16);
-            raw_v = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(V) + ((size_t)c_pos * kLpr + piece) * 16);
-            if constexpr (kWeighted) c_norm = acc.accumulate_weighted(raw_k, raw_v, fmaxf(Wt[c_pos], 0.f));
-            else c_norm = acc.accumulate(raw_k, raw_v);
-        }
-        c_norm = __shfl(c_norm, 0);
-    }
-
-    // ---- the TBM list goes through LDS a piece at a time; every wave takes its members from it
-    int joined = 0;
-    for (int p0 = 0; p0 < n_tbm; p0 += kMergePiece) {
-        const int len = min(kMergePiece, n_tbm - p0);
-        if (p0 > 0) __syncthreads();                       // the previous piece is consumed
-        for (int i = threadIdx.x; i < len; i += kMergeBlock) {
-            ldest[i] = dest[p0 + i];
-            lpos[i] = clamp_pos(tbm[p0 + i], N);
-        }
-        __syncthreads();
-        if (centre) joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, len, job, 0, 1, wlist);
-        else if (zero_class) joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, len, Nb, wave, kMergeWaves, wlist);
-    }
-
-    if (centre) {
-        const int members = 1 + joined;
-        acc.template reduce_groups<kWeighted>();
-        if (grp == 0) {
-            frag_t out_k = raw_k, out_v = raw_v;                      // nobody joined: exact copy
-            const float m = kWeighted ? acc.wsum : (float)members;    // total weight of the entry
-            if (members > 1 && m > 0.f) {
-                float ok[kE], ov[kE];
+    const bool zero_class = blk < a.zero_blocks;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    // Sifts a piece of the list from p0, up to `end`, a stretch (of at most kMergeStretch entries) per wave:
+    // the tokens whose destination is in [lo, hi), in order, one list for the block or
+    // (own) one per wave in its eighth of the arrays.  Returns the list's length.
+    auto sift = [&](int p0, int end, int lo, int hi, bool own) {
+        const int stretch = min(kMergeStretch, ((end - p0 + kMergeWaves - 1) / kMergeWaves + kWave - 1) / kWave * kWave);
+        const int i0 = p0 + wave * stretch, i1 = min(i0 + stretch, end);
+        constexpr int kAhead = 8;                            // entries in flight per lane
+        static_assert(kMergeStretch == kAhead * kWave, "the longest stretch is one round");
+        int d[kAhead], q[kAhead], n = 0;
 #pragma unroll
-                for (int i = 0; i < kE; ++i) { ok[i] = c_norm * (acc.k[i] / m); ov[i] = acc.v[i] / m; }
-                out_k = Pack<T>::pack(ok);
-                out_v = Pack<T>::pack(ov);
-            }
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Ko) + ((size_t)job * kLpr + piece) * 16) = out_k;
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Vo) + ((size_t)job * kLpr + piece) * 16) = out_v;
+        for (int u = 0; u < kAhead; ++u) {
+            const int i = i0 + u * kWave + lane;
+            d[u] = i < i1 ? dest[i] : -1;
+            q[u] = i < i1 ? tbm[i] : 0;
         }
-        if (lane == 0) {
-            kept[job] = c_pos;
-            cnt[job] = members;
-            a.k_norm[(size_t)bkv * (n_imp + n_tbm) + job] = c_norm;
+        int at0 = wave * kMergeStretch, total = 0;
+        if (!own) {                                          // block-uniform
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) n += __popcll(__ballot(d[u] >= lo && d[u] < hi));
+            __syncthreads();                                 // the previous piece is consumed
+            if (lane == 0) kept_n[wave] = n;
+            __syncthreads();
+            at0 = 0;
+            for (int w = 0; w < kMergeWaves; ++w) { at0 += w < wave ? kept_n[w] : 0; total += kept_n[w]; }
+            n = 0;
         }
-    }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const bool in = d[u] >= lo && d[u] < hi;
+            const unsigned long long mask = __ballot(in);
+            if (in) { const int at = at0 + n + __popcll(mask & below); ldest[at] = d[u]; lpos[at] = clamp_pos(q[u], N); }
+            n += __popcll(mask);
+        }
+        if (!own) __syncthreads();
+        return own ? n : total;
+    };
 
     if (zero_class) {
-        // ---- zero class: every wave has added its share in order; wave 0 adds the waves in order
+        const int per_block = (n_tbm + a.zero_blocks - 1) / a.zero_blocks;
+        const int z0 = min(blk * per_block, n_tbm), z1 = min(z0 + per_block, n_tbm);
+        Acc acc; acc.clear();
+        int joined = 0;
+        for (int p0 = z0; p0 < z1; p0 += kMergeWaves * kMergeStretch) {
+            const int n = sift(p0, z1, Nb, Nb + 1, true);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest + wave * kMergeStretch, lpos + wave * kMergeStretch, n, Nb, wlist);
+            __builtin_amdgcn_wave_barrier();
+        }
+        // every wave has added its share in order; the waves, then the blocks, are added in order
         acc.template reduce_groups<kWeighted>();
         if (grp == 0) {
 #pragma unroll
@@ -436,23 +490,177 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
         }
         if (lane == 0) { zcnt[wave] = joined; zwsum[wave] = acc.wsum; }
         __syncthreads();
-        if (wave == 0 && grp == 0) {
-            int total = 0;
-            float wtot = 0.f;
-            for (int w = 0; w < kMergeWaves; ++w) { total += zcnt[w]; wtot += zwsum[w]; }
-            const float denom = kWeighted ? wtot : (float)total;     // members, or their total weight
+        int total = 0;
+        float wtot = 0.f;
+        for (int w = 0; w < kMergeWaves; ++w) { total += zcnt[w]; wtot += zwsum[w]; }
+        const int tid = threadIdx.x;                         // thread = (key or value, element)
+        const int src = tid / D, el = tid % D;
+        float sum = 0.f;
+        if (src < 2)
+            for (int w = 0; w < kMergeWaves; ++w) sum += zsum[w][src][el];
+        if (a.zero_blocks > 1) {
+            // a record per block: sums of keys and values, members, total weight
+            constexpr int kRec = 2 * D + 2;
+            float* rec = a.zero_part + ((size_t)bkv * a.zero_stride) + (size_t)blk * kRec;
+            if (src < 2) rec[tid] = sum;
+            if (tid == 0) { rec[2 * D] = __int_as_float(total); rec[2 * D + 1] = wtot; }
+            __threadfence();
+            __syncthreads();
+            if (tid == 0) zcnt[0] = atomicAdd(&cnt[n_imp], 1);
+            __syncthreads();
+            if (zcnt[0] != a.zero_blocks - 1) return;        // block-uniform: not the last one
+            __threadfence();
+            const float* all = a.zero_part + (size_t)bkv * a.zero_stride;
+            total = 0; wtot = 0.f; sum = 0.f;
+            for (int z = 0; z < a.zero_blocks; ++z) {
+                total += __float_as_int(all[(size_t)z * kRec + 2 * D]);
+                wtot += all[(size_t)z * kRec + 2 * D + 1];
+                if (src < 2) sum += all[(size_t)z * kRec + tid];
+            }
+        }
+        const float denom = kWeighted ? wtot : (float)total;     // members, or their total weight
+        if (src < 2) {
+            const float mean = denom > 0.f ? sum / denom : 0.f;
+            (src ? Vo : Ko)[(size_t)Nb * D + el] = (T)mean;
+        }
+        if (tid == 0) cnt[n_imp] = total;
+        return;
+    }
+
+    // ---- output rows: rows_per_wave of every wave, the block's being consecutive.  (More than one
+    // per wave only where the whole list is one piece: its sifted form then serves all of them.)
+    const int rpw = a.rows_per_wave;
+    const int block0 = (blk - a.zero_blocks) * kMergeWaves * rpw, job0 = block0 + wave * rpw;
+    const int block1 = min(block0 + kMergeWaves * rpw, n_imp);
+    constexpr int kPiece = kMergeWaves * kMergeStretch;
+
+    auto local_row = [&](int job) {                          // copied unchanged by one lane group
+        const int pos = N - W + (job - n_imp);
+        const frag_t fk = Acc::load_piece(K, pos, piece), fv = Acc::load_piece(V, pos, piece);
+        *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Ko) + ((size_t)job * kLpr + piece) * 16) = fk;
+        *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Vo) + ((size_t)job * kLpr + piece) * 16) = fv;
+        if (piece == 0) kept[job] = pos;
+    };
+    // a class-centre slot's row and scalars, by one lane group
+    auto write_centre = [&](int job, const Acc& acc, const frag_t& raw_k, const frag_t& raw_v, int c_pos, float c_norm, int members) {
+        frag_t out_k = raw_k, out_v = raw_v;                          // nobody joined: exact copy
+        const float m = kWeighted ? acc.wsum : (float)members;        // total weight of the entry
+        if (members > 1 && m > 0.f) {
             float ok[kE], ov[kE];
 #pragma unroll
-            for (int i = 0; i < kE; ++i) {
-                float sk = 0.f, sv = 0.f;
-                for (int w = 0; w < kMergeWaves; ++w) { sk += zsum[w][0][piece * kE + i]; sv += zsum[w][1][piece * kE + i]; }
-                ok[i] = denom > 0.f ? sk / denom : 0.f;
-                ov[i] = denom > 0.f ? sv / denom : 0.f;
-            }
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Ko) + ((size_t)Nb * kLpr + piece) * 16) = Pack<T>::pack(ok);
-            *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Vo) + ((size_t)Nb * kLpr + piece) * 16) = Pack<T>::pack(ov);
-            if (lane == 0) cnt[n_imp] = total;
+            for (int i = 0; i < kE; ++i) { ok[i] = c_norm * (acc.k[i] / m); ov[i] = acc.v[i] / m; }
+            out_k = Pack<T>::pack(ok);
+            out_v = Pack<T>::pack(ov);
         }
+        *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Ko) + ((size_t)job * kLpr + piece) * 16) = out_k;
+        *reinterpret_cast<frag_t*>(reinterpret_cast<char*>(Vo) + ((size_t)job * kLpr + piece) * 16) = out_v;
+        if (piece == 0) {
+            kept[job] = c_pos;
+            cnt[job] = members;
+            a.k_norm[(size_t)bkv * (n_imp + n_tbm) + job] = c_norm;
+        }
+    };
+    // a slot by the whole wave: every lane group takes a share of its members
+    auto slot_by_wave = [&](int job, int len) {
+        Acc acc; acc.clear();
+        const int c_pos = clamp_pos(imp[job], N);            // the centre itself is the first member
+        float c_norm = 0.f;
+        frag_t raw_k = zero_frag(), raw_v = zero_frag();
+        if (grp == 0) {
+            raw_k = Acc::load_piece(K, c_pos, piece);
+            raw_v = Acc::load_piece(V, c_pos, piece);
+            if constexpr (kWeighted) c_norm = acc.accumulate_weighted(raw_k, raw_v, fmaxf(Wt[c_pos], 0.f));
+            else c_norm = acc.accumulate(raw_k, raw_v);
+        }
+        int joined = 0;
+        if (len >= 0) {
+            joined = gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, len, job, wlist);
+        } else {                                             // a list of several pieces: sifted by the block as it goes
+            for (int p0 = 0; p0 < n_tbm; p0 += kPiece) {
+                const int n = sift(p0, n_tbm, block0, block1, false);
+                if (job < n_imp) joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, n, job, wlist);
+            }
+        }
+        acc.template reduce_groups<kWeighted>();
+        if (grp == 0 && job < n_imp) write_centre(job, acc, raw_k, raw_v, c_pos, c_norm, 1 + joined);
+    };
+
+    if (n_tbm > kPiece) {                                    // one row per wave; every wave sifts along
+        if (block0 < n_imp) {                                // block-uniform
+            const int job = job0;
+            if (job < n_imp) slot_by_wave(job, -1);
+            else for (int p0 = 0; p0 < n_tbm; p0 += kPiece) sift(p0, n_tbm, block0, block1, false);
+        }
+        if (job0 >= n_imp && job0 < n_imp + W && grp == 0) local_row(job0);
+        return;
+    }
+    const int len = block0 < n_imp && n_tbm > 0 ? sift(0, n_tbm, block0, block1, false) : 0;
+    for (int r0 = 0; r0 < rpw; r0 += kGroups) {
+        // a row per lane group while slots have few members; else (and where a wave has one row) slot after slot
+        const int n_rows = min(kGroups, rpw - r0);
+        int mine = 0;                                        // members of this lane group's row
+        bool wide = rpw == 1;
+        if (!wide) {
+            int count[kGroups];
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) count[g] = 0;
+            for (int c0 = 0; c0 < len; c0 += kWave) {
+                const int d = c0 + lane < len ? ldest[c0 + lane] : -1;
+#pragma unroll
+                for (int g = 0; g < kGroups; ++g) {
+                    const bool match = d == job0 + r0 + g;
+                    const unsigned long long mask = __ballot(match);
+                    const int at = count[g] + __popcll(mask & below);
+                    if (match && at < kMergeFew) wlist[g * kMergeFew + at] = lpos[c0 + lane];
+                    count[g] += __popcll(mask);
+                }
+            }
+#pragma unroll
+            for (int g = 0; g < kGroups; ++g) mine = g == grp ? count[g] : mine;
+            wide = __any(grp < n_rows && mine > kMergeFew);
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        if (wide) {                                          // wave-uniform
+            for (int r = r0; r < r0 + n_rows; ++r) {
+                const int job = job0 + r;
+                if (job < n_imp) slot_by_wave(job, len);
+                else if (job < n_imp + W && grp == 0) local_row(job);
+            }
+            continue;
+        }
+        const int job = job0 + r0 + grp;
+        const bool centre = grp < n_rows && job < n_imp;
+        if (grp < n_rows && job >= n_imp && job < n_imp + W) local_row(job);
+        Acc acc; acc.clear();
+        const int c_pos = centre ? clamp_pos(imp[job], N) : 0;
+        const frag_t raw_k = load_frag_or_zero(K, ((size_t)c_pos * kLpr + piece) * 16, centre);
+        const frag_t raw_v = load_frag_or_zero(V, ((size_t)c_pos * kLpr + piece) * 16, centre);
+        const float c_w = kWeighted && centre ? fmaxf(Wt[c_pos], 0.f) : 0.f;
+        // the members, kMergeFew at most; their rows are requested before the first is added
+        if (!centre) mine = 0;
+        frag_t fk[kMergeFew], fv[kMergeFew];
+        float w[kMergeFew];
+#pragma unroll
+        for (int u = 0; u < kMergeFew; ++u) {
+            const int pos = u < mine ? wlist[grp * kMergeFew + u] : 0;
+            fk[u] = load_frag_or_zero(K, ((size_t)pos * kLpr + piece) * 16, u < mine);
+            fv[u] = load_frag_or_zero(V, ((size_t)pos * kLpr + piece) * 16, u < mine);
+            w[u] = kWeighted && u < mine ? fmaxf(Wt[pos], 0.f) : 0.f;
+        }
+        if (centre) {
+            float c_norm;
+            if constexpr (kWeighted) c_norm = acc.accumulate_weighted(raw_k, raw_v, c_w);
+            else c_norm = acc.accumulate(raw_k, raw_v);
+#pragma unroll
+            for (int u = 0; u < kMergeFew; ++u)
+                if (u < mine) {
+                    if constexpr (kWeighted) acc.accumulate_weighted(fk[u], fv[u], w[u]);
+                    else acc.accumulate(fk[u], fv[u]);
+                }
+            write_centre(job, acc, raw_k, raw_v, c_pos, c_norm, 1 + mine);
+        }
+        __builtin_amdgcn_wave_barrier();                     // the next rows' lists replace these
     }
 }
 
@@ -543,16 +751,34 @@ void dest_slicing(int n_imp, bool f32, int* slice_rows, int* n_slices)
     *n_slices = (rounds + per_slice - 1) / per_slice;
 }
 
+// Token tiles of 64 per wave read every gathered centre row less often; they take over where they still
+// make two blocks per compute unit.  Both sources of the product of
+// cosines leave registers for one, float32 rows likewise.
+template <typename T, int D, int kSim>
+static hipError_t launch_dest(const MergeArgs& a, hipStream_t st)
+{
+    constexpr int kTile = kMrgWaves * 32;
+    auto per_head = [&](int tok) { return (long long)((a.n_tbm + kTile * tok - 1) / (kTile * tok)) * a.n_slices; };
+    if constexpr (sizeof(T) == 2 && kSim != 2) {
+        if (per_head(2) * a.bkv >= 512) {
+            const long long grid = head_grid(a.bkv, per_head(2));
+            if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((dest_kernel<T, D, kSim, 2>), dim3((unsigned)grid), dim3(kMrgBlock), 0, st, a);
+            return hipGetLastError();
+        }
+    }
+    const long long grid = head_grid(a.bkv, per_head(1));
+    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((dest_kernel<T, D, kSim, 1>), dim3((unsigned)grid), dim3(kMrgBlock), 0, st, a);
+    return hipGetLastError();
+}
+
 template <typename T, int D>
-static hipError_t launch_evict_merge_t(const MergeArgs& a, hipStream_t st)
+static hipError_t launch_evict_merge_t(MergeArgs a, hipStream_t st)
 {
     hipError_t e = hipSuccess;
     if (a.n_tbm > 0) {
-        dim3 g((a.n_tbm + kMrgWaves * 32 - 1) / (kMrgWaves * 32), a.n_slices, a.bkv);
-        if (a.similarity == 0) hipLaunchKernelGGL((dest_kernel<T, D, 0>), g, dim3(kMrgBlock), 0, st, a);
-        else if (a.similarity == 1) hipLaunchKernelGGL((dest_kernel<T, D, 1>), g, dim3(kMrgBlock), 0, st, a);
-        else hipLaunchKernelGGL((dest_kernel<T, D, 2>), g, dim3(kMrgBlock), 0, st, a);
-        e = hipGetLastError();
+        e = a.similarity == 0 ? launch_dest<T, D, 0>(a, st) : a.similarity == 1 ? launch_dest<T, D, 1>(a, st) : launch_dest<T, D, 2>(a, st);
         if (e != hipSuccess) return e;
         if (a.n_slices > 1) {
             dim3 gc((a.n_tbm + kMrgBlock - 1) / kMrgBlock, a.bkv);
@@ -561,8 +787,20 @@ static hipError_t launch_evict_merge_t(const MergeArgs& a, hipStream_t st)
             if (e != hipSuccess) return e;
         }
     }
+    // Rows per wave: as many as leave two blocks per compute unit, where the TBM list is one piece.
     const int jobs = a.n_imp + a.window;
-    dim3 g(1 + (jobs + kMergeWaves - 1) / kMergeWaves, a.bkv);
+    const long long waves = (long long)jobs * a.bkv;
+    a.rows_per_wave = a.n_tbm > kMergeWaves * kMergeStretch ? 1 : (int)std::min<long long>(kMergeMaxRows, std::max<long long>(1, waves / (512 * kMergeWaves)));
+    // The zero class is shared by several blocks where the centre list was searched in slices: the
+    // winners' array then holds the blocks' sums (2 D + 2 floats per 512 tokens; a slice has one per token).
+    a.zero_blocks = a.n_slices > 1 ? std::max(1, a.n_tbm / kZeroTokens) : 1;
+    a.zero_part = a.part_best;
+    a.zero_stride = (size_t)a.n_slices * a.n_tbm;
+    const int per_block = kMergeWaves * a.rows_per_wave;
+    a.merge_blocks = a.zero_blocks + (jobs + per_block - 1) / per_block;
+    const long long grid = head_grid(a.bkv, a.merge_blocks);
+    if (grid > 0x7fffffffll) return hipErrorInvalidValue;
+    const dim3 g((unsigned)grid);
     if (a.weight) hipLaunchKernelGGL((merge_kernel<T, D, true>), g, dim3(kMergeBlock), 0, st, a);
     else hipLaunchKernelGGL((merge_kernel<T, D, false>), g, dim3(kMergeBlock), 0, st, a);
     return hipGetLastError();

@@ -170,6 +170,58 @@ SELECT_SHAPES = [
 ]
 
 
+# sizes where the select's and the merge's ways of working change: candidate lists of up to and over 4096 and
+# 16384 tokens, whole lists in ties; one and several rows per merge wave, a TBM list of more than one piece,
+# a zero class shared by several blocks, larger token tiles of the destination search
+# (bh, n, w, budget, r, d)
+MERGE_EDGES = [
+    (2, 9000, 16, 2066, 1.0, 64),        # 2050 centres in 9 slices, 2066 tokens: the zero class in four blocks
+    (8, 20000, 64, 4100, 1.0, 128),      # more than 4096 candidates; rows of a wave by lane group
+    (1, 40000, 32, 9000, 0.6, 64),       # 14400 candidates; 5400 tokens: two pieces, one row per wave
+    (1, 70000, 32, 12000, 0.5, 64),      # over 16384 candidates
+    (33, 1500, 100, 700, 1.1, 128),      # heads that do not divide over the XCDs
+    (8, 33000, 64, 2500, 2.0, 128),      # 5000 tokens, token tiles of 64
+]
+
+
+@pytest.mark.parametrize("tau", [-2.0, 0.3, 2.0])
+@pytest.mark.parametrize("shape", MERGE_EDGES)
+def test_select_and_merge_where_the_ways_change(shape, tau):
+    """Index sets against the oracle's partition of the GPU's keys, destinations and rows against the
+    oracle's: the stated bars."""
+    bh, n, w, budget, r, d = shape
+    _log("select and merge", shape, tau)
+    p = B.EmsParams(1, bh, bh, d, n, w, budget, merge_ratio=r, tau=tau)
+    glo, loc = _rand_scores(bh, n, w, seed=budget)
+    imp, tbm, pooled = B.ems_select(p, torch.from_numpy(glo).cuda(), torch.from_numpy(loc).cuda(), want_pooled=True)
+    x_imp, x_tbm = ems_ref.partition(ref_params(p), pooled.cpu().numpy().astype(np.float64))
+    assert (imp.cpu().numpy() == x_imp).all() and (tbm.cpu().numpy() == x_tbm).all()
+    if bh > 8:
+        rows = [0, 1, bh // 2, bh - 1]
+    else:
+        rows = [0, bh - 1]
+    gen = torch.Generator().manual_seed(n)
+    k, v = (torch.randn((1, bh, n, d), generator=gen).to(torch.bfloat16) for _ in range(2))
+    hot = x_imp[0, 0, 3]                                 # one centre of the first head that many tokens join
+    k[0, 0, torch.from_numpy(x_tbm[0, 0, ::3].astype(np.int64))] = k[0, 0, int(hot)].clone()
+    out = {name: t.cpu() for name, t in B.ems_evict_merge(p, k.cuda(), v.cuda(), imp, tbm).items()}
+    sub = ems_ref.RefParams(1, len(rows), len(rows), d, n, w, budget=budget, merge_ratio=r, tau=tau)
+    kf, vf = k[:, rows].float().numpy(), v[:, rows].float().numpy()
+    s_imp, s_tbm = x_imp[:, rows], x_tbm[:, rows]
+    dest = out["tbm_dest"].numpy()[:, rows]
+    if tau == 0.3:
+        o_dest, _ = ems_ref.dest(sub, kf, s_imp, s_tbm)[:2]
+        assert assert_dest_valid(dest, o_dest, kf, s_imp, s_tbm, tau, budget) <= dest.size // 100
+    else:
+        assert (dest == budget).all() if tau > 1 else (dest < s_imp.shape[-1]).all()
+    k_ref, v_ref, kept, cnt = ems_ref.merge(sub, kf, vf, s_imp, s_tbm, dest)
+    assert (out["slot_count"].numpy()[:, rows] == cnt).all() and (out["kept_pos"].numpy()[:, rows] == kept).all()
+    for got, ref in ((out["k_out"], k_ref), (out["v_out"], v_ref)):
+        got = got.float().numpy()[:, rows]
+        rms = np.sqrt((ref.astype(np.float64) ** 2).mean(-1, keepdims=True))
+        assert (np.abs(got - ref) <= 2e-2 * np.maximum(np.abs(ref), rms) + 1e-6).all()
+
+
 def _rand_scores(bh, n, w, seed):
     rng = np.random.default_rng(seed)
     glo = (rng.random((1, bh, n)) ** 4 * 5 + 1e-3).astype(np.float32)

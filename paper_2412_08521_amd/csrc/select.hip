@@ -60,13 +60,14 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sm, int& total)
 
 // One histogram update per lane (if `on`).  Scores share their leading digits, so most
 // lanes of a wave hit the same bin: the lanes that agree with the first active lane are
-// counted with one ballot and one atomic, the others fall back to their own atomic.
+// counted with one ballot and one atomic, the others fall back to their own atomic.  (Three such
+// rounds instead of one made every select kernel slower: 20.5 -> 24.3 us on 4096 tokens.)
 __device__ __forceinline__ void hist_add(int* hist, int digit, bool on)
 {
     const unsigned long long active = __ballot(on);
     if (active == 0ull) return;                                   // wave-uniform
     const int leader = __ffsll((long long)active) - 1;
-    const int d0 = __shfl(digit, leader);
+    const int d0 = __builtin_amdgcn_readlane(digit, leader);      // (the leader is the same for all lanes)
     const unsigned long long same = __ballot(on && digit == d0);
     if ((int)(threadIdx.x % kWave) == leader) atomicAdd(&hist[d0], __popcll(same));
     if (on && digit != d0) atomicAdd(&hist[digit], 1);
@@ -270,9 +271,151 @@ __global__ __launch_bounds__(kChunkBlock) void select_gather_kernel(SelectArgs a
     }
 }
 
+// Steps 3 and 4 of the header comment on keys in LDS: a block of kSelBlock threads, wave w taking the
+// ordinals [w * 64 * items, (w + 1) * 64 * items) of `count` candidates in position order (items <= 32),
+// lane l the ordinals base + i * 64.  position(ordinal) is the sequence position of a candidate.
+// kItems: `items` where it is fixed (the loops are then unrolled: 17.3 us against 20.5 rolled, 4096 tokens), else
+// 0 (rolled: 12.4 us against 15.3 for the candidates of a 16384-token prompt).
+template <int kItems, typename Position>
+__device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items, int count, const SelectArgs& a, Position position)
+{
+    constexpr int kUnroll = kItems ? kItems : 1;
+    const int items = kItems ? kItems : n_items;
+    __shared__ int hist[2][256];
+    __shared__ int suffix[2][257];
+    __shared__ int scan_sm[kSelWaves][2];
+    __shared__ int wave_tot[8];
+    __shared__ uint32_t sel_prefix[2];
+    __shared__ int sel_rem[2];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
+    const int base = wave * kWave * items + lane;
+
+    // ---- 3. radix select of two ranks (1-based, counted from the largest key)
+    if (tid < 2) {
+        sel_prefix[tid] = 0u;
+        sel_rem[tid] = tid == 0 ? a.n_imp : a.n_imp + a.n_tbm;
+    }
+    for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 512) hist[tid >> 8][tid & 255] = 0;
+        __syncthreads();
+        const uint32_t p0 = sel_prefix[0], p1 = sel_prefix[1];
+        const bool same_prefix = shift == 24 || p0 == p1;
+#pragma unroll kUnroll
+        for (int i = 0; i < items; ++i) {
+            const uint32_t key = keys[base + i * kWave];
+            const bool cand = base + i * kWave < count;
+            const int digit = (key >> shift) & 255;
+            if (shift == 24) {                             // shared leading digits
+                hist_add(hist[0], digit, cand);
+            } else {                                       // spread out: every key its own atomic
+                const uint32_t hi = key >> (shift + 8);
+                if (cand && hi == p0) atomicAdd(&hist[0][digit], 1);
+                if (!same_prefix && cand && hi == p1) atomicAdd(&hist[1][digit], 1);
+            }
+        }
+        __syncthreads();
+        if (same_prefix && tid < 256) hist[1][tid] = hist[0][tid];   // one count serves both cuts
+        __syncthreads();
+        int incl = 0;
+        if (tid < 512) {
+            incl = hist[tid >> 8][255 - (tid & 255)];
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int u = __shfl_up(incl, o);
+                if (lane >= o) incl += u;
+            }
+            if (lane == kWave - 1) wave_tot[wave] = incl;
+        }
+        __syncthreads();
+        if (tid < 512) {
+            const int t = tid >> 8;
+            for (int w = t * 4; w < wave; ++w) incl += wave_tot[w];
+            suffix[t][255 - (tid & 255)] = incl;
+            if ((tid & 255) == 0) suffix[t][256] = 0;
+        }
+        __syncthreads();
+        bool mine = false;
+        uint32_t new_prefix = 0u;
+        int new_rem = 0;
+        if (tid < 512) {
+            const int t = tid >> 8, d = tid & 255;
+            const int rem = sel_rem[t];
+            mine = suffix[t][d] >= rem && suffix[t][d + 1] < rem;
+            new_prefix = (sel_prefix[t] << 8) | (uint32_t)d;
+            new_rem = rem - suffix[t][d + 1];
+        }
+        __syncthreads();
+        if (mine) { sel_prefix[tid >> 8] = new_prefix; sel_rem[tid >> 8] = new_rem; }
+        __syncthreads();
+    }
+    const uint32_t T1 = sel_prefix[0], T2 = sel_prefix[1];
+    const int k1 = a.n_imp, k2 = a.n_imp + a.n_tbm;
+    const int G1 = k1 - sel_rem[0];               // keys greater than T1
+    const int G2 = k2 - sel_rem[1];               // keys greater than T2
+
+    // ---- 4. ordered classification: rank = #greater + #equal at lower positions; position
+    // order inside a wave is (item, lane), across waves the wave number
+    auto below_count = [&](unsigned long long m) {                 // set bits of m below this lane
+        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    };
+    auto wave_prefix = [&](int mine_, int& before) {               // exclusive scan over waves
+        __syncthreads();
+        if (lane == 0) scan_sm[wave][0] = mine_;
+        __syncthreads();
+        before = 0;
+        for (int w = 0; w < wave; ++w) before += scan_sm[w][0];
+    };
+    int eq1 = 0, eq2 = 0;
+#pragma unroll kUnroll
+    for (int i = 0; i < items; ++i) {
+        const uint32_t key = keys[base + i * kWave];
+        const bool cand = base + i * kWave < count;
+        eq1 += __popcll(__ballot(cand && key == T1));
+        eq2 += __popcll(__ballot(cand && key == T2));
+    }
+    int r1, r2;
+    wave_prefix(eq1, r1);
+    wave_prefix(eq2, r2);
+    unsigned imp_mask = 0u, tbm_mask = 0u;        // bit i: item i; items <= 32
+    int c_imp = 0, c_tbm = 0;
+#pragma unroll kUnroll
+    for (int i = 0; i < items; ++i) {
+        const uint32_t key = keys[base + i * kWave];
+        const bool cand = base + i * kWave < count;
+        // almost every (wave, item) slice lies entirely below the second cut: nothing to rank
+        if (__ballot(cand && key >= T2) == 0ull) continue;         // wave-uniform
+        const unsigned long long m1 = __ballot(cand && key == T1), m2 = __ballot(cand && key == T2);
+        int rank;
+        if (key == T1) rank = G1 + r1 + below_count(m1);
+        else if (key == T2) rank = G2 + r2 + below_count(m2);
+        else rank = key > T1 ? 0 : (key > T2 ? k1 : k2);
+        r1 += __popcll(m1); r2 += __popcll(m2);
+        const bool ii = cand && rank < k1, tt = cand && rank >= k1 && rank < k2;
+        if (ii) imp_mask |= 1u << i;
+        if (tt) tbm_mask |= 1u << i;
+        c_imp += __popcll(__ballot(ii));
+        c_tbm += __popcll(__ballot(tt));
+    }
+    int bi, bt;
+    wave_prefix(c_imp, bi);
+    wave_prefix(c_tbm, bt);
+    int32_t* imp = a.imp_idx + (size_t)blockIdx.x * a.n_imp;
+    int32_t* tbm = a.tbm_idx ? a.tbm_idx + (size_t)blockIdx.x * a.n_tbm : nullptr;
+#pragma unroll kUnroll
+    for (int i = 0; i < items; ++i) {
+        const bool ii = (imp_mask >> i) & 1u, tt = (tbm_mask >> i) & 1u;
+        if (__ballot(ii || tt) == 0ull) continue;                        // wave-uniform
+        const unsigned long long mi = __ballot(ii), mt = __ballot(tt);
+        if (ii) { const int at = bi + below_count(mi); if (at < a.n_imp) imp[at] = position(base + i * kWave); }
+        if (tt && tbm) { const int at = bt + below_count(mt); if (at < a.n_tbm) tbm[at] = position(base + i * kWave); }
+        bi += __popcll(mi); bt += __popcll(mt);
+    }
+}
+
 // Launch D: exact two-cut selection over a head's candidate list (keys already in integer order
 // form): steps 3 and 4 of the header comment.  The list is a sequence of per-chunk stretches in
 // arbitrary order; position order is chunk order, then order inside the stretch.
+constexpr int kFinishKeys = 16 * kSelBlock;      // candidates held in LDS
 constexpr int kMaxChunks = (1 << 22) / kChunk;   // the interface limits seq_len to 2^22
 __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
 {
@@ -285,6 +428,8 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
     __shared__ int ch_first[kMaxChunks + 1];     // rank (in position order) of a chunk's first candidate
     __shared__ int ch_at[kMaxChunks];            // where its stretch starts in the list
     __shared__ int scan17[kSelWaves + 1];
+    __shared__ uint32_t keys[kFinishKeys];
+    __shared__ int key_pos[kFinishKeys];
 
     const int N = a.seq_len;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
@@ -308,6 +453,40 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
         while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (ch_first[mid] <= j) lo = mid; else hi = mid; }
         return ch_at[lo] + (j - ch_first[lo]);
     };
+
+    // A list that fits (all but extreme ties) goes to LDS once, in position order: the digit passes and the
+    // three walks below would each go back to memory for it (8 heads, 8200 candidates each: 45 us, now 27).
+    int top_step = 1;
+    while (top_step * 2 < n_chunks) top_step *= 2;
+    if (M <= kFinishKeys) {                                // block-uniform
+        const int items = (M + kSelBlock - 1) / kSelBlock;
+        for (int j0 = tid; j0 < items * kSelBlock; j0 += 4 * kSelBlock) {      // four places looked up and loaded together
+            int at[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) at[u] = 0;
+            for (int step = top_step; step > 0; step >>= 1) {                  // the chunk: the last whose first rank is not above
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int mid = at[u] + step;
+                    at[u] = ((mid < n_chunks) & (ch_first[min(mid, n_chunks)] <= j0 + u * kSelBlock)) ? mid : at[u];
+                }
+            }
+            uint32_t k4[4];
+            int p4[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int j = j0 + u * kSelBlock, l = ch_at[at[u]] + (j - ch_first[at[u]]);
+                k4[u] = j < M ? ckey[l] : 0u;
+                p4[u] = j < M ? cpos[l] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (j0 + u * kSelBlock < kFinishKeys) { keys[j0 + u * kSelBlock] = k4[u]; key_pos[j0 + u * kSelBlock] = p4[u]; }
+        }
+        __syncthreads();
+        select_ranked<0>(keys, items, M, a, [&](int j) { return key_pos[j]; });
+        return;
+    }
 
     // ---- 3. radix select of two ranks (1-based, counted from the largest key)
     if (tid < 2) {
@@ -445,7 +624,7 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
 }
 
 // ------------------------------------------------------------------------------------
-// Same computation with the ranking keys held in registers.  Wave w owns the positions
+// Same computation with the ranking keys held in LDS.  Wave w owns the positions
 // [w * 64 * kItems, (w + 1) * 64 * kItems); lane l holds positions base + i * 64 + l, so
 // every load and store is coalesced and, after the keys are formed, nothing depends on
 // memory latency any more.  Used when the sequence fits (N <= 1024 * kItems).
@@ -454,18 +633,13 @@ template <int kItems>
 __global__ __launch_bounds__(kSelBlock) void select_reg_kernel(SelectArgs a)
 {
     __shared__ float red[kSelWaves][2];
-    __shared__ int hist[2][256];
-    __shared__ int suffix[2][257];
-    __shared__ int scan_sm[kSelWaves][2];
-    __shared__ int wave_tot[8];
-    __shared__ uint32_t sel_prefix[2];
-    __shared__ int sel_rem[2];
-
+    constexpr int kHalo = 31;                             // the widest window reaches 31 positions to either side
+    __shared__ uint32_t keys[kSelBlock * kItems];
+    __shared__ float comb[kHalo + kSelBlock * kItems + kHalo];   // Eq. 2 vector before pooling, zeros around it
     const int N = a.seq_len, Nc = N - a.window;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const float* glo = a.s_glo + (size_t)blockIdx.x * N;
     const float* loc = a.s_loc + (size_t)blockIdx.x * N;
-    float* comb = a.pooled + (size_t)blockIdx.x * N;      // Eq. 2 vector, before pooling
     float* s_out = a.s_gl_opt ? a.s_gl_opt + (size_t)blockIdx.x * N : nullptr;
     const int base = wave * kWave * kItems + lane;        // position of item i: base + 64 i
 
@@ -486,153 +660,35 @@ __global__ __launch_bounds__(kSelBlock) void select_reg_kernel(SelectArgs a)
     for (int w = 0; w < kSelWaves; ++w) { tot_g += red[w][0]; tot_l += red[w][1]; }
     const float align = (tot_l / (float)N) / (tot_g / (float)N);
 
-    // ---- 2. element-wise max, staged through the workspace so that the pooling window
-    // can reach into the neighbouring lanes' and waves' positions
+    // ---- 2. element-wise max, staged through LDS so that the pooling window can reach into the
+    // neighbouring lanes' and waves' positions (by way of the workspace: 2.5 us more)
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const int j = base + i * kWave;
-        if (j < N) comb[j] = fmaxf(g[i] * align, l[i]);
+        comb[kHalo + j] = j < N ? fmaxf(g[i] * align, l[i]) : 0.f;
     }
-    __syncthreads();   // the block's own global writes are visible to the whole block
+    if (tid < kHalo) { comb[tid] = 0.f; comb[kHalo + kSelBlock * kItems + tid] = 0.f; }
+    __syncthreads();
     const int half = (a.pool_kernel - 1) / 2;
     const float div = (float)a.pool_kernel;
-    uint32_t key[kItems];
+    float pool[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; ++i) pool[i] = 0.f;
+    for (int t = -half; t <= half; ++t) {                 // every element adds its neighbours from left to right
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) pool[i] += comb[kHalo + base + i * kWave + t];
+    }
 #pragma unroll
     for (int i = 0; i < kItems; ++i) {
         const int j = base + i * kWave;
-        float acc = 0.f;
-        if (half <= 3) {
-            // the usual window (width <= 7): independent, unconditional loads
-            float nb[7];
-#pragma unroll
-            for (int t = -3; t <= 3; ++t) nb[t + 3] = comb[min(max(j + t, 0), N - 1)];
-#pragma unroll
-            for (int t = -3; t <= 3; ++t)
-                acc += (t >= -half && t <= half && j + t >= 0 && j + t < N) ? nb[t + 3] : 0.f;
-        } else {
-            for (int t = -half; t <= half; ++t) {
-                const int jj = j + t;
-                if (jj >= 0 && jj < N) acc += comb[jj];
-            }
-        }
+        const float acc = pool[i];
         const float v = acc / div;
-        key[i] = order_key(v);
+        keys[j] = order_key(v);
         if (s_out && j < N) s_out[j] = v;
     }
 
-    // ---- 3. radix select of two ranks (1-based, counted from the largest key)
-    if (tid < 2) {
-        sel_prefix[tid] = 0u;
-        sel_rem[tid] = tid == 0 ? a.n_imp : a.n_imp + a.n_tbm;
-    }
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (tid < 512) hist[tid >> 8][tid & 255] = 0;
-        __syncthreads();
-        const uint32_t p0 = sel_prefix[0], p1 = sel_prefix[1];
-        const bool same_prefix = shift == 24 || p0 == p1;
-#pragma unroll
-        for (int i = 0; i < kItems; ++i) {
-            const bool cand = base + i * kWave < Nc;
-            const uint32_t hi = shift == 24 ? 0u : (key[i] >> (shift + 8));
-            const int digit = (key[i] >> shift) & 255;
-            hist_add(hist[0], digit, cand && (shift == 24 || hi == p0));
-            if (!same_prefix) hist_add(hist[1], digit, cand && hi == p1);
-        }
-        __syncthreads();
-        if (same_prefix && tid < 256) hist[1][tid] = hist[0][tid];   // one count serves both cuts
-        __syncthreads();
-        int incl = 0;
-        if (tid < 512) {
-            incl = hist[tid >> 8][255 - (tid & 255)];
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int u = __shfl_up(incl, o);
-                if (lane >= o) incl += u;
-            }
-            if (lane == kWave - 1) wave_tot[wave] = incl;
-        }
-        __syncthreads();
-        if (tid < 512) {
-            const int t = tid >> 8;
-            for (int w = t * 4; w < wave; ++w) incl += wave_tot[w];
-            suffix[t][255 - (tid & 255)] = incl;
-            if ((tid & 255) == 0) suffix[t][256] = 0;
-        }
-        __syncthreads();
-        bool mine = false;
-        uint32_t new_prefix = 0u;
-        int new_rem = 0;
-        if (tid < 512) {
-            const int t = tid >> 8, d = tid & 255;
-            const int rem = sel_rem[t];
-            mine = suffix[t][d] >= rem && suffix[t][d + 1] < rem;
-            new_prefix = (sel_prefix[t] << 8) | (uint32_t)d;
-            new_rem = rem - suffix[t][d + 1];
-        }
-        __syncthreads();
-        if (mine) { sel_prefix[tid >> 8] = new_prefix; sel_rem[tid >> 8] = new_rem; }
-        __syncthreads();
-    }
-    const uint32_t T1 = sel_prefix[0], T2 = sel_prefix[1];
-    const int k1 = a.n_imp, k2 = a.n_imp + a.n_tbm;
-    const int G1 = k1 - sel_rem[0];               // keys greater than T1
-    const int G2 = k2 - sel_rem[1];               // keys greater than T2
-
-    // ---- 4. ordered classification: rank = #greater + #equal at lower positions; position
-    // order inside a wave is (item, lane), across waves the wave number
-    auto below_count = [&](unsigned long long m) {                 // set bits of m below this lane
-        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-    };
-    auto wave_prefix = [&](int mine_, int& before) {               // exclusive scan over waves
-        __syncthreads();
-        if (lane == 0) scan_sm[wave][0] = mine_;
-        __syncthreads();
-        before = 0;
-        for (int w = 0; w < wave; ++w) before += scan_sm[w][0];
-    };
-    int eq1 = 0, eq2 = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const bool cand = base + i * kWave < Nc;
-        eq1 += __popcll(__ballot(cand && key[i] == T1));
-        eq2 += __popcll(__ballot(cand && key[i] == T2));
-    }
-    int r1, r2;
-    wave_prefix(eq1, r1);
-    wave_prefix(eq2, r2);
-    unsigned imp_mask = 0u, tbm_mask = 0u;        // bit i: item i; kItems <= 32
-    int c_imp = 0, c_tbm = 0;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const bool cand = base + i * kWave < Nc;
-        // almost every (wave, item) slice lies entirely below the second cut: nothing to rank
-        if (__ballot(cand && key[i] >= T2) == 0ull) continue;         // wave-uniform
-        const unsigned long long m1 = __ballot(cand && key[i] == T1), m2 = __ballot(cand && key[i] == T2);
-        int rank;
-        if (key[i] == T1) rank = G1 + r1 + below_count(m1);
-        else if (key[i] == T2) rank = G2 + r2 + below_count(m2);
-        else rank = key[i] > T1 ? 0 : (key[i] > T2 ? k1 : k2);
-        r1 += __popcll(m1); r2 += __popcll(m2);
-        const bool ii = cand && rank < k1, tt = cand && rank >= k1 && rank < k2;
-        if (ii) imp_mask |= 1u << i;
-        if (tt) tbm_mask |= 1u << i;
-        c_imp += __popcll(__ballot(ii));
-        c_tbm += __popcll(__ballot(tt));
-    }
-    int bi, bt;
-    wave_prefix(c_imp, bi);
-    wave_prefix(c_tbm, bt);
-    int32_t* imp = a.imp_idx + (size_t)blockIdx.x * a.n_imp;
-    int32_t* tbm = a.tbm_idx ? a.tbm_idx + (size_t)blockIdx.x * a.n_tbm : nullptr;
-#pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const bool ii = (imp_mask >> i) & 1u, tt = (tbm_mask >> i) & 1u;
-        if (__ballot(ii || tt) == 0ull) continue;                        // wave-uniform
-        const unsigned long long mi = __ballot(ii), mt = __ballot(tt);
-        if (ii) { const int at = bi + below_count(mi); if (at < a.n_imp) imp[at] = base + i * kWave; }
-        if (tt && tbm) { const int at = bt + below_count(mt); if (at < a.n_tbm) tbm[at] = base + i * kWave; }
-        bi += __popcll(mi); bt += __popcll(mt);
-    }
+    __syncthreads();
+    select_ranked<kItems>(keys, kItems, Nc, a, [](int j) { return j; });
 }
 
 template <int kItems>

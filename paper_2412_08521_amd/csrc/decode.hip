@@ -4,8 +4,8 @@
 // decode_init_kernel  builds the per-token table (position, cache row, key norm, s_Glo,
 //                     s_Loc^past, s_Loc^cur) from what the prefill compression returned.
 // decode_step_kernel  one generated token: one block per (batch, kv-head) runs the whole
-//                     step (for large caches the two sweeps over the cache rows are their own
-//                     launches over row slices, see kPart) -- attention row of the new query over the expanded run-time
+//                     step (for large caches it is four launches, three over slices of the table or
+//                     of the cache rows: decode_logits_kernel, decode_weights_kernel, kPart) -- attention row of the new query over the expanded run-time
 //                     cache (one dot product per cache ROW, shared by the tokens that share
 //                     the entry; coalesced row loads, v_dot2 partials added with DPP),
 //                     score accumulation, window ring shift, least important centre, its
@@ -176,37 +176,241 @@ __global__ __launch_bounds__(256) void decode_init_kernel(DecodeInitArgs a)
 }
 
 // ------------------------------------------------------------------------------------
-// kPart = 0: one block per (batch, kv-head) runs the whole step, kBlock = 256 (the step is a chain
-// of short dependent phases, and every instruction a wave spends on a block-wide bookkeeping
-// step is paid once per wave).
-// Large caches: one compute unit cannot pull the cache rows fast enough, so the step is four
-// launches in stream order, the two row sweeps cut into slices of a.slice_rows rows:
-//   kPart = 1  phase 1 (row dots)           grid (slices, heads), 256 threads
-//   kPart = 2  phases 2-4                    grid (1, heads), 1024 threads
-//   kPart = 3  phase 5 (centre cosines)      grid (slices, heads), 256 threads
-//   kPart = 4  phases 6-7                    grid (1, heads), 1024 threads
-// (Letting the last cosine block of a head run phases 6-7 itself saves a launch and was measured
-// slower: the next launch's latency hides behind the sweep anyway.)
-// What one part leaves for the next lives in the workspace: the staged dots and row norms, and a
-// small hand-over record per head (kHand* offsets below).
-// Dynamic LDS (floats): dot[G][budget] | rn[budget] when that fits, else the same arrays
-// live in the caller's workspace (a.lds_floats == 0).
+// One block per (batch, kv-head) runs the whole step (kPart = 0, 256 threads: the step is a chain of short
+// dependent phases, and every instruction a wave spends on a block-wide bookkeeping step is paid once
+// per wave) while the cache is small.
+//
+// Large caches: one compute unit cannot pull the cache rows fast enough, nor walk the table, so the step is
+// four launches in stream order, three of them over slices:
+//   decode_logits_kernel   slices of the token table: every token's own row against the group's queries,
+//                          logits to the workspace, the slice's maxima, sums and scalar totals to the record
+//   decode_weights_kernel  the same slices: weights, score update, the slice's least important centre
+//   kPart = 3              slices of the centre rows: the least important centre of all, phase 3 (one block),
+//                          centre cosines (phase 5)
+//   kPart = 4              one block per head, 1024 threads: phases 6-7
+// Nothing waits for another block inside a launch.  A token gathers its row although tokens share
+// entries: the row comes from the L2, and the table then needs no second look at the rows' dots.  (With row
+// slices for the dots and one block per head for softmax, update and arg-min the step was 4.9 + 13.1 +
+// 5.2 + 4.7 us at budget 2048, 3072 table elements, 8 heads: now 6.4 + 4.2 + 6.4 + 4.7.)  (Letting the last cosine block
+// of a head run phases 6-7 itself saves a launch and was measured slower: the next launch's latency hides
+// behind the sweep anyway.)
+// What one launch leaves for the next lives in the workspace: the logits, and a hand-over record per
+// head (kHand* offsets below).
+// Dynamic LDS of the one-launch step (floats): dot[G][budget] | rn[budget] when that fits, else the same
+// arrays live in the caller's workspace (a.lds_floats == 0).
 constexpr int kHandSelf = 0;       // [8]  new query . new key per q-head (log2 units)
 constexpr int kHandNewNorm = 8;    //      norm of the new key
 constexpr int kHandOldSc = 9;      // [4]  scalars of the token that left the window
 constexpr int kHandOldPos = 13;    //      its position (int)
 constexpr int kHandStar = 14;      //      the least important centre (int)
 constexpr int kHandStep = 15;      //      tokens generated before this one (int)
-constexpr int kHandPart = 16;      // [kDecodeMaxSlices][2] best cosine and its centre per slice
-constexpr int kHandOldRow = kHandPart + 2 * kDecodeMaxSlices;   // key row, then value row, of that token
+constexpr int kHandSelfTot = 16;   //      the new token's weight, all q-heads
+constexpr int kHandPart = 20;      // [kDecodeMaxSlices][2] best cosine and its centre per row slice
+constexpr int kHandStat = kHandPart + 2 * kDecodeMaxSlices;     // [18][kDecodeMaxSlices] per table slice: maxima [8], sums [8], totals of s_Glo and s_Loc
+constexpr int kHandLeast = kHandStat + 18 * kDecodeMaxSlices;   // [2][kDecodeMaxSlices] least score and its centre (int) per table slice
+constexpr int kHandOldRow = kHandLeast + 2 * kDecodeMaxSlices;  // key row, then value row, of the token that left the window
+
+// table elements a pass of a table slice covers
+constexpr int kTokTile = 128;
+
+// arg-min (kMin) or arg-max over the lanes of a wave, lowest index on ties; the same in every lane
+template <bool kMin>
+__device__ __forceinline__ void wave_arg(float& v, int& i)
+{
+    row_arg<kMin>(v, i);
+    float bv = lane_value(v, 0);
+    int bi = __builtin_amdgcn_readlane(i, 0);
+#pragma unroll
+    for (int r = 16; r < 64; r += 16) {
+        const float ov = lane_value(v, r);
+        const int oi = __builtin_amdgcn_readlane(i, r);
+        if (better<kMin>(ov, oi, bv, bi)) { bv = ov; bi = oi; }
+    }
+    v = bv; i = bi;
+}
+
+template <int D, int G>
+__global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
+{
+    using T = bf16_t;
+    constexpr int kLpr = Tile<T, D>::kChunksPerRow, kRows = 256 / kLpr;      // rows a block loads at a time
+    constexpr int kAhead = kTokTile / kRows;
+    __shared__ float sh_dot[G][kTokTile];
+    __shared__ float red[2 * G + 2][4];
+    const int E = a.n_imp + a.n_tbm, Tn = E + a.window, Nb = a.budget;
+    const int bkv = blockIdx.y, slice = blockIdx.x, tid = threadIdx.x;
+    const int grp = tid / kLpr, piece = tid % kLpr;
+    const char* Kc = reinterpret_cast<const char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
+    const float* row_norm = a.st.row_norm + (size_t)bkv * Nb;
+    const int32_t* tok_row = a.st.tok_row + (size_t)bkv * Tn;
+    const size_t tok0 = (size_t)bkv * Tn;
+    const char* qn = reinterpret_cast<const char*>(a.q_new) + (size_t)bkv * G * D * sizeof(T);
+    const char* kn = reinterpret_cast<const char*>(a.k_new) + (size_t)bkv * D * sizeof(T);
+    float* logits = a.ws + (size_t)bkv * G * Tn;
+    float* hand = a.hand + (size_t)bkv * kDecodeHandFloats;
+
+    frag_t qp[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) qp[g] = *reinterpret_cast<const frag_t*>(qn + ((size_t)g * kLpr + piece) * 16);
+
+    float m[G], l[G], tot[2] = {0.f, 0.f};                   // this thread's table elements
+#pragma unroll
+    for (int g = 0; g < G; ++g) { m[g] = -INFINITY; l[g] = 0.f; }
+    const int t_end = min((slice + 1) * a.tok_slice, Tn);
+    for (int j0 = slice * a.tok_slice; j0 < t_end; j0 += kTokTile) {
+        int rr[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) { const int j = j0 + u * kRows + grp; rr[u] = j < t_end ? tok_row[j] : -1; }
+        const int j = j0 + tid;
+        const bool mine = tid < kTokTile && j < t_end;
+        const int r = mine ? tok_row[j] : -1;
+        const float tn = mine ? a.st.tok_norm[tok0 + j] : 0.f, tg = mine ? a.st.tok_glo[tok0 + j] : 0.f;
+        const float tp = mine ? a.st.tok_past[tok0 + j] : 0.f, tc = mine ? a.st.tok_cur[tok0 + j] : 0.f;
+        frag_t fk[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) fk[u] = load_frag_or_zero(Kc, ((size_t)max(rr[u], 0) * kLpr + piece) * 16, rr[u] >= 0);
+        const float rn = r >= 0 ? row_norm[r] : 0.f;
+        if (j0 != slice * a.tok_slice) __syncthreads();      // the previous pass's dots are read
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float d = group_sum<kLpr>(dot8_bf16(fk[u], qp[g]));
+                if (piece == 0) sh_dot[g][u * kRows + grp] = d;
+            }
+        __syncthreads();
+        if (r >= 0) {
+            const float c = a.scale_log2e * (rn > 0.f ? tn / rn : 0.f);
+#pragma unroll
+            for (int g = 0; g < G; ++g) {
+                const float x = c * sh_dot[g][tid];
+                const float m_new = fmaxf(m[g], x), ref = m_new > -INFINITY ? m_new : 0.f;
+                l[g] = l[g] * exp2_fast(m[g] - ref) + exp2_fast(x - ref);
+                m[g] = m_new;
+                logits[(size_t)g * Tn + j] = x;
+            }
+            tot[0] += tg;
+            tot[1] += tp + tc;
+        }
+    }
+    // the slice's maxima, sums relative to them, and totals
+    float top[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) top[g] = m[g];
+    block_reduce<4, G, true>(top, red);
+    float sum[G + 2];
+#pragma unroll
+    for (int g = 0; g < G; ++g) sum[g] = m[g] > -INFINITY ? l[g] * exp2_fast(m[g] - top[g]) : 0.f;
+    sum[G] = tot[0]; sum[G + 1] = tot[1];
+    block_reduce<4, G + 2, false>(sum, red);
+    if (tid == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            hand[kHandStat + g * kDecodeMaxSlices + slice] = top[g];
+            hand[kHandStat + (8 + g) * kDecodeMaxSlices + slice] = sum[g];
+        }
+        hand[kHandStat + 16 * kDecodeMaxSlices + slice] = sum[G];
+        hand[kHandStat + 17 * kDecodeMaxSlices + slice] = sum[G + 1];
+    }
+    if (slice == 0 && tid < kLpr) {                          // the new token
+        const frag_t new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float d = group_sum<kLpr>(dot8_bf16(new_k, qp[g]));
+            if (piece == 0) hand[kHandSelf + g] = a.scale_log2e * d;
+        }
+        const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
+        if (piece == 0) {
+            hand[kHandNewNorm] = sqrtf(ss);
+            reinterpret_cast<int*>(hand)[kHandStep] = a.step >= 0 ? a.step : *a.st.step_count;
+        }
+    }
+}
+
+template <int G>
+__global__ __launch_bounds__(256) void decode_weights_kernel(DecodeStepArgs a)
+{
+    __shared__ float fbuf[4];
+    __shared__ int ibuf[4];
+    const int n_imp = a.n_imp, Tn = a.n_imp + a.n_tbm + a.window;
+    const int bkv = blockIdx.y, slice = blockIdx.x, tid = threadIdx.x, lane = tid % kWave;
+    const size_t tok0 = (size_t)bkv * Tn;
+    const float* logits = a.ws + (size_t)bkv * G * Tn;
+    float* hand = a.hand + (size_t)bkv * kDecodeHandFloats;
+    const int32_t* entry_tok = a.st.entry_tok + (size_t)bkv * n_imp;
+
+    // every wave combines the slices' records for itself
+    float sm[G], sl[G], m[G], inv[G], tot[2];
+    const bool on = lane < a.n_tok_slices;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        sm[g] = on ? hand[kHandStat + g * kDecodeMaxSlices + lane] : -INFINITY;
+        sl[g] = on ? hand[kHandStat + (8 + g) * kDecodeMaxSlices + lane] : 0.f;
+    }
+    tot[0] = on ? hand[kHandStat + 16 * kDecodeMaxSlices + lane] : 0.f;
+    tot[1] = on ? hand[kHandStat + 17 * kDecodeMaxSlices + lane] : 0.f;
+    float self_tot = 0.f, self_w[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const float self = hand[kHandSelf + g];
+        m[g] = fmaxf(wave_reduce<true>(sm[g]), self);
+        const float sum = wave_reduce<false>(sm[g] > -INFINITY ? sl[g] * exp2_fast(sm[g] - m[g]) : 0.f) + exp2_fast(self - m[g]);
+        inv[g] = 1.0f / sum;
+        self_w[g] = exp2_fast(self - m[g]) * inv[g];
+        self_tot += self_w[g];
+    }
+    // Eq. 2 factor on the updated scalars: this step adds one unit of weight per q-head to both totals
+    const float s_glo = wave_reduce<false>(tot[0]) + (float)G, s_loc = wave_reduce<false>(tot[1]) + (float)G;
+    const float align = s_glo > 0.f ? s_loc / s_glo : 0.f;
+
+    float bv = 0.f;
+    int bi = -1;
+    const int t_end = min((slice + 1) * a.tok_slice, Tn);
+    for (int j = slice * a.tok_slice + tid; j < t_end; j += 256) {
+        const int r = a.st.tok_row[tok0 + j];
+        float w[G];
+        if (r >= 0) {
+            const int centre_tok = r < n_imp ? entry_tok[r] : -1;
+            float add = 0.f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) { w[g] = exp2_fast(logits[(size_t)g * Tn + j] - m[g]) * inv[g]; add += w[g]; }
+            const float glo = a.st.tok_glo[tok0 + j] + add, cur = a.st.tok_cur[tok0 + j] + add;
+            const float past = a.st.tok_past[tok0 + j];
+            a.st.tok_glo[tok0 + j] = glo;
+            a.st.tok_cur[tok0 + j] = cur;
+            if (centre_tok == j) {                           // a class centre's own element
+                const float sc = fmaxf(glo * align, past + cur);
+                if (better<true>(sc, r, bv, bi)) { bv = sc; bi = r; }
+            }
+        } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g) w[g] = 0.f;
+        }
+        if (a.attn_opt) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + j] = w[g];
+        }
+    }
+    block_arg<4, true>(bv, bi, fbuf, ibuf);
+    if (tid == 0) {
+        hand[kHandLeast + slice] = bv;
+        reinterpret_cast<int*>(hand)[kHandLeast + kDecodeMaxSlices + slice] = bi;
+        if (slice == 0) {
+            hand[kHandSelfTot] = self_tot;
+            if (a.attn_opt) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + Tn] = self_w[g];
+            }
+        }
+    }
+}
 
 template <typename T, int D, int G, int kBlock, int kPart>
 __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 {
     constexpr bool kAll = kPart == 0;
-    constexpr bool kDoDots = kAll || kPart == 1, kDoSoftmax = kAll || kPart == 2;
     constexpr bool kDoCos = kAll || kPart == 3;
-    static_assert(kPart >= 0 && kPart <= 4, "parts");
+    static_assert(kAll || kPart == 3 || kPart == 4, "parts");
     static_assert(kHandOldRow % 4 == 0 && kHandOldRow + 2 * D * (int)sizeof(T) / 4 <= kDecodeHandFloats, "hand-over record");
     using P = Pack<T>;
     constexpr int kE = P::kElems;
@@ -216,7 +420,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr int kRowBytes = Tile<T, D>::kRowBytes;
     constexpr int kUnroll = 4;                               // independent loads in flight per thread
     constexpr int kPre = kBlock == 256 ? 2 : 1;              // row tiles in flight per wave
-    constexpr bool kPreload = (kAll && kBlock == 256) || kPart == 2;   // first batch of table elements fetched up front
+    constexpr bool kPreload = kAll && kBlock == 256;         // first batch of table elements fetched up front
 
     extern __shared__ float dyn_lds[];
     __shared__ float fbuf[kWaves];
@@ -235,10 +439,10 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const int tid = threadIdx.x;
     // tokens generated before this one: the caller's count, or the counter kept in the state.  The
     // counter is advanced after every block has read it: by a separate launch after the one-launch
-    // step; in the sliced step the first part copies it into every head's hand-over record,
-    // the later parts read that copy, and the last part advances it.
+    // step (by the step itself when nobody reads it); in the sliced step the first part copies it into
+    // every head's hand-over record, the later parts read that copy, and the last part advances it.
     const int step = a.step >= 0 ? a.step
-                   : (kPart >= 2 ? reinterpret_cast<const int*>(a.hand + (size_t)bkv * kDecodeHandFloats)[kHandStep] : *a.st.step_count);
+                   : (!kAll ? reinterpret_cast<const int*>(a.hand + (size_t)bkv * kDecodeHandFloats)[kHandStep] : *a.st.step_count);
     const int lane = tid % kWave, wave = tid / kWave;
     const int col = lane & 31, half = lane >> 5;             // MFMA operand row / k-half of this lane
     const int grp = tid / kLpr, piece = tid % kLpr;
@@ -254,10 +458,8 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     float* tok_glo = a.st.tok_glo + (size_t)bkv * Tn;
     float* tok_past = a.st.tok_past + (size_t)bkv * Tn;
     float* tok_cur = a.st.tok_cur + (size_t)bkv * Tn;
-    // the sweeping parts write the staged arrays to the workspace; the part that consumes them
-    // copies them into LDS first when they fit
     float* ws_stage = a.ws + (size_t)bkv * ((size_t)(G + 1) * Nb);
-    const bool in_lds = a.lds_floats > 0 && (kAll || kPart == 2);   // block-uniform
+    const bool in_lds = a.lds_floats > 0;                    // block-uniform
     float* stage = in_lds ? dyn_lds : ws_stage;
     float* hand = kAll ? nullptr : a.hand + (size_t)bkv * kDecodeHandFloats;
     int* hand_i = reinterpret_cast<int*>(hand);
@@ -291,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr int kCt = kBlock == 1024 ? 2 : 1;              // centre tokens looked up ahead per thread (phase 4)
     int ct_pre[kCt];
 #pragma unroll
-    for (int u = 0; u < kCt; ++u) ct_pre[u] = (kDoSoftmax && tid + u * kBlock < n_imp) ? entry_tok[tid + u * kBlock] : 0;
+    for (int u = 0; u < kCt; ++u) ct_pre[u] = (kAll && tid + u * kBlock < n_imp) ? entry_tok[tid + u * kBlock] : 0;
     frag_t new_k = zero_frag(), new_v = zero_frag();
     float m[G], sum[G];
     float tot2[2] = {0.f, 0.f};                              // sum of s_Glo, sum of s_Loc
@@ -313,7 +515,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             pre_tc[u] = ok ? tok_cur[j] : 0.f;
         }
     };
-    if constexpr (kDoDots) {
+    if constexpr (kAll) {
     if constexpr (kDot2) {
         frag_t qp[G];
 #pragma unroll
@@ -349,16 +551,15 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
                         for (int g = 0; g < G; ++g) {
                             sh_self[g] = a.scale_log2e * d[g];
-                            if (!kAll) hand[kHandSelf + g] = a.scale_log2e * d[g];
                         }
                     }
                 }
             }
         }
         for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
-        if (grp == 0 && (kAll || slice == 0)) {
+        if (grp == 0) {
             const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
-            if (piece == 0) { sh_newnorm = sqrtf(ss); if (!kAll) hand[kHandNewNorm] = sqrtf(ss); }
+            if (piece == 0) sh_newnorm = sqrtf(ss);
         }
     } else {
         frag_t bq[kFrags];
@@ -400,45 +601,19 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                         if (row < Nb) dot[(size_t)col * Nb + row] = acc[r16];
                         else if (row == Nb) {
                             sh_self[col] = a.scale_log2e * acc[r16];
-                            if (!kAll) hand[kHandSelf + col] = a.scale_log2e * acc[r16];
                         }
                     }
                 }
             }
         }
         for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
-        if (grp == 0 && (kAll || slice == 0)) {
-            const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
-            if (piece == 0) { sh_newnorm = sqrtf(ss); if (!kAll) hand[kHandNewNorm] = sqrtf(ss); }
-        }
-    }
-    }   // kDoDots
-    if constexpr (kPart == 1) {
-        if (slice == 0 && tid == 0) hand_i[kHandStep] = step;
-        return;
-    }
-    if constexpr (kPart == 2) {
-        // what the dots launch left: the new token's own logits and norm, the staged arrays
-        preload_table();
-        if (tid < G) sh_self[tid] = hand[kHandSelf + tid];
-        if (tid == 0) sh_newnorm = hand[kHandNewNorm];
         if (grp == 0) {
-            new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-            new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        }
-        if (in_lds) {
-            constexpr int kCopy = 8;                         // loads in flight per thread
-            for (int i0 = tid; i0 < (G + 1) * Nb; i0 += kBlock * kCopy) {
-                float t[kCopy];
-#pragma unroll
-                for (int u = 0; u < kCopy; ++u) t[u] = i0 + u * kBlock < (G + 1) * Nb ? ws_stage[i0 + u * kBlock] : 0.f;
-#pragma unroll
-                for (int u = 0; u < kCopy; ++u)
-                    if (i0 + u * kBlock < (G + 1) * Nb) dyn_lds[i0 + u * kBlock] = t[u];
-            }
+            const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
+            if (piece == 0) sh_newnorm = sqrtf(ss);
         }
     }
-    if constexpr (kDoSoftmax) {
+    }
+    if constexpr (kAll) {
     __syncthreads();
 
     // ---- phase 2: softmax over the live tokens and the new token (Eq. 1) ---------------
@@ -582,18 +757,48 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     }
     block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // its barriers also publish phase 3
     s_star = max(bi, 0);                                     // block-uniform, in [0, n_imp)
-    }   // kDoSoftmax
-    if constexpr (kPart == 2) {
-        if (grp == 0) { hand_row[piece] = old_k[piece]; hand_row[kLpr + piece] = old_v[piece]; }
-        if (tid == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) hand[kHandOldSc + i] = old_sc[i];
-            hand_i[kHandOldPos] = old_pos;
-            hand_i[kHandStar] = s_star;
-        }
-        return;
     }
-    if constexpr (kPart >= 3) s_star = hand_i[kHandStar];
+    // phase 5's first rows do not depend on the centre that is chosen
+    const int s_first = r_lo + wave * kRowsPerWave + sub;
+    frag_t row_pre[kInFlight];
+    auto load_centres = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int s = s0 + u * kRowsPerPass;
+            row_pre[u] = load_frag_or_zero(Kc, ((size_t)s * kLpr + piece) * 16, s < c_end);
+        }
+    };
+    if constexpr (kPart == 3) load_centres(s_first);
+    if constexpr (kPart == 3) {
+        // the least important centre of the table slices' (lowest on ties); the first block shifts the window
+        float v = lane < a.n_tok_slices ? hand[kHandLeast + lane] : 0.f;
+        int i = lane < a.n_tok_slices ? hand_i[kHandLeast + kDecodeMaxSlices + lane] : -1;
+        wave_arg<true>(v, i);
+        s_star = max(i, 0);
+        if (slice == 0) {
+            const int ring = step % W;
+            const int jo = E + ring, ro = n_imp + ring;
+            if (grp == 0) {
+                char* const k_at = Kc + ((size_t)ro * kLpr + piece) * 16;
+                char* const v_at = Vc + ((size_t)ro * kLpr + piece) * 16;
+                hand_row[piece] = *reinterpret_cast<const frag_t*>(k_at);
+                hand_row[kLpr + piece] = *reinterpret_cast<const frag_t*>(v_at);
+                *reinterpret_cast<frag_t*>(k_at) = *reinterpret_cast<const frag_t*>(kn + piece * 16);
+                *reinterpret_cast<frag_t*>(v_at) = *reinterpret_cast<const frag_t*>(vn + piece * 16);
+            }
+            if (tid == 0) {
+                hand_i[kHandOldPos] = tok_pos[jo];
+                hand[kHandOldSc] = tok_norm[jo]; hand[kHandOldSc + 1] = tok_glo[jo];
+                hand[kHandOldSc + 2] = tok_past[jo]; hand[kHandOldSc + 3] = tok_cur[jo];
+                const float norm = hand[kHandNewNorm], weight = hand[kHandSelfTot];
+                tok_pos[jo] = a.seq_len + step; tok_row[jo] = ro; tok_norm[jo] = norm;
+                tok_glo[jo] = weight; tok_past[jo] = 0.f; tok_cur[jo] = weight;
+                row_norm[ro] = norm;
+                hand_i[kHandStar] = s_star;
+            }
+        }
+    }
+    if constexpr (kPart == 4) s_star = hand_i[kHandStar];
     f = entry_tok[s_star];
 
     // ---- phase 5: its most similar other centre (Eq. 5, cosine of the stored keys) -----
@@ -605,14 +810,9 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     if constexpr (kDot2) {
         const frag_t sp = *reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16);
         const float rn_star = inv_norm(group_sum<kLpr>(dot8_bf16(sp, sp)));
-        const int s_first = r_lo + wave * kRowsPerWave + sub;
         for (int s0 = s_first; s0 < c_end; s0 += kRowsPerPass * kInFlight) {
-            frag_t fk[kInFlight];
-#pragma unroll
-            for (int u = 0; u < kInFlight; ++u) {
-                const int s = s0 + u * kRowsPerPass;
-                fk[u] = load_frag_or_zero(Kc, ((size_t)s * kLpr + piece) * 16, s < c_end);
-            }
+            if (kPart != 3 || s0 != s_first) load_centres(s0);
+            const frag_t (&fk)[kInFlight] = row_pre;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int s = s0 + u * kRowsPerPass;
@@ -747,14 +947,16 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     if ((step + 1) % W == 0) {
         for (int j = tid; j < Tn; j += kBlock) { tok_past[j] = tok_cur[j]; tok_cur[j] = 0.f; }
     }
-    if constexpr (kPart == 4) {
-        if (bkv == 0 && tid == 0) *a.st.step_count = step + 1;   // every block of the step reads the hand-over copy
+    // the counter: in the sliced step every block reads the hand-over copy, and a step whose number
+    // came with the call reads none
+    if (kPart == 4 || (kAll && a.step >= 0)) {
+        if (bkv == 0 && tid == 0) *a.st.step_count = step + 1;
     }
 }
 
-__global__ void decode_bump_kernel(int32_t* step_count, int step)
+__global__ void decode_bump_kernel(int32_t* step_count)
 {
-    *step_count = (step >= 0 ? step : *step_count) + 1;
+    *step_count += 1;
 }
 
 // ------------------------------------------------------------------------------------
@@ -772,54 +974,71 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
     return a.head_dim == 64 ? launch_decode_init_t<bf16_t, 64>(a, st) : launch_decode_init_t<bf16_t, 128>(a, st);
 }
 
-template <typename T, int D, int kBlock, int kPart>
+// which: 0 = the whole step, 1 = logits, 2 = weights, 3 and 4 = those parts of the step kernel
+template <typename T, int D, int G, int kWhich>
+static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
+{
+    if constexpr (kWhich == 0)
+        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 256, 0>), dim3(1, a.bkv), dim3(256), sizeof(float) * (size_t)a.lds_floats, st, a);
+    else if constexpr (kWhich == 1)
+        hipLaunchKernelGGL((decode_logits_kernel<D, G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
+    else if constexpr (kWhich == 2)
+        hipLaunchKernelGGL((decode_weights_kernel<G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
+    else if constexpr (kWhich == 3)
+        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 256, 3>), dim3(a.n_slices, a.bkv), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 1024, 4>), dim3(1, a.bkv), dim3(1024), 0, st, a);
+}
+
+template <typename T, int D, int kWhich>
 static hipError_t launch_decode_part(const DecodeStepArgs& a, hipStream_t st)
 {
-    const bool sweeps = kPart == 1 || kPart == 3;
-    const dim3 g(sweeps ? a.n_slices : 1, a.bkv), b(kBlock);
-    const size_t lds = (kPart == 0 || kPart == 2) ? sizeof(float) * (size_t)a.lds_floats : 0;
     switch (a.group) {
-        case 1: hipLaunchKernelGGL((decode_step_kernel<T, D, 1, kBlock, kPart>), g, b, lds, st, a); break;
-        case 2: hipLaunchKernelGGL((decode_step_kernel<T, D, 2, kBlock, kPart>), g, b, lds, st, a); break;
-        case 4: hipLaunchKernelGGL((decode_step_kernel<T, D, 4, kBlock, kPart>), g, b, lds, st, a); break;
-        case 8: hipLaunchKernelGGL((decode_step_kernel<T, D, 8, kBlock, kPart>), g, b, lds, st, a); break;
+        case 1: launch_decode_group<T, D, 1, kWhich>(a, st); break;
+        case 2: launch_decode_group<T, D, 2, kWhich>(a, st); break;
+        case 4: launch_decode_group<T, D, 4, kWhich>(a, st); break;
+        case 8: launch_decode_group<T, D, 8, kWhich>(a, st); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-// Whether the step runs as four launches over row slices, and how the rows are cut.  f32 rows
-// need twice the operand registers: the validation mode always takes the one-block kernel.
-bool decode_split(int budget, int n_imp, int n_tbm, int window, bool f32, int* slice_rows, int* n_slices)
+// Whether the step runs as four launches over slices, and how the centre rows and the token table are
+// cut.  f32 rows need twice the operand registers: the validation mode always takes the one-block kernel.
+bool decode_split(int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s)
 {
-    *slice_rows = 0; *n_slices = 1;
-    if (f32 || (budget <= 512 && n_imp + n_tbm + window <= 2048)) return false;
-    const int tiles = (budget + 1 + 31) / 32;                     // 32-row tiles, the new key's row included
-    int per = 4;                                                  // 128 rows per slice ...
-    while ((tiles + per - 1) / per > kDecodeMaxSlices) per *= 2;  // ... unless that makes too many slices
-    *slice_rows = per * 32;
-    *n_slices = (tiles + per - 1) / per;
+    *s = DecodeSlices{0, 1, 0, 1};
+    const int table = n_imp + n_tbm + window;
+    if (f32 || (budget <= 512 && table <= 2048)) return false;
+    auto cut = [](int n, int least, int* per, int* count) {
+        *per = least;
+        while ((n + *per - 1) / *per > kDecodeMaxSlices) *per *= 2;
+        *count = (n + *per - 1) / *per;
+    };
+    cut(n_imp, 128, &s->rows, &s->n_rows);
+    cut(table, kTokTile, &s->toks, &s->n_toks);
     return true;
 }
 
 template <typename T, int D>
 static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
 {
-    hipError_t e;
-    if (a.n_slices > 1 || a.slice_rows > 0) {
+    if (a.slice_rows > 0) {
         if constexpr (sizeof(T) == 2) {
-            e = launch_decode_part<T, D, 256, 1>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 1024, 2>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 256, 3>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 1024, 4>(a, st);
+            hipError_t e = launch_decode_part<T, D, 1>(a, st);
+            if (e == hipSuccess) e = launch_decode_part<T, D, 2>(a, st);
+            if (e == hipSuccess) e = launch_decode_part<T, D, 3>(a, st);
+            if (e == hipSuccess) e = launch_decode_part<T, D, 4>(a, st);
+            return e;                                            // the last part advances the counter
         } else {
             return hipErrorInvalidValue;
         }
-    } else {
-        e = launch_decode_part<T, D, 256, 0>(a, st);
     }
-    if (e != hipSuccess || a.slice_rows > 0) return e;           // the sliced step advances the counter itself
-    hipLaunchKernelGGL(decode_bump_kernel, dim3(1), dim3(1), 0, st, a.st.step_count, a.step);
+    const hipError_t e = launch_decode_part<T, D, 0>(a, st);
+    // A step whose number came with the call advances the counter itself: only blocks that read the
+    // counter need it to stand still until all have (2.7 us of 13.6 a step, 32 heads with a budget of 128).
+    if (e != hipSuccess || a.step >= 0) return e;
+    hipLaunchKernelGGL(decode_bump_kernel, dim3(1), dim3(1), 0, st, a.st.step_count);
     return hipGetLastError();
 }
 

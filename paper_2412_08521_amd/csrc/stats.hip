@@ -27,8 +27,23 @@ constexpr double kMassOne = 1099511627776.0;   // 2^40: fixed-point image of the
 // scores are >= 0: their bit patterns already order like the values
 __device__ __forceinline__ uint32_t score_key(float s) { return __float_as_uint(fmaxf(s, 0.f)); }
 
+constexpr int kStatLds = 32768;                // scores of a head held in LDS (128 KB)
+
+// Sum over the wave, the same in every lane.
+__device__ __forceinline__ int wave_add(int v)
+{
+    v += dpp_i<kDppXor1>(v);
+    v += dpp_i<kDppXor2>(v);
+    v += dpp_i<kDppHalfMirror>(v);
+    v += dpp_i<kDppMirror>(v);
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+}
+
+// 8 heads of 16384 tokens: 76 us with one thread walking the 256 digits of each pass and every walk over the
+// scores reading both arrays; now 40.
 __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
 {
+    __shared__ float kept[kStatLds];
     __shared__ float red[kStatWaves][2];
     __shared__ int cnt[256];
     __shared__ unsigned long long mass[256];
@@ -36,15 +51,28 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
     __shared__ uint32_t sh_prefix;
     __shared__ unsigned long long sh_mass_above;
     __shared__ int sh_count_above;
+    __shared__ unsigned long long wave_mass[4];
+    __shared__ int wave_cnt[4];
 
     const int N = a.seq_len;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const float* glo = a.s_glo + (size_t)blockIdx.x * N;
     const float* loc = a.s_loc + (size_t)blockIdx.x * N;
 
-    // Eq. 2 alignment factor, fixed-order sums
+    // Eq. 2 alignment factor, fixed-order sums; kAhead elements' loads in flight per thread
+    constexpr int kAhead = 8;
     float sg = 0.f, sl = 0.f;
-    for (int j = tid; j < N; j += kStatBlock) { sg += glo[j]; sl += loc[j]; }
+    for (int j0 = tid; j0 < N; j0 += kStatBlock * kAhead) {
+        float g[kAhead], l[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int j = j0 + u * kStatBlock;
+            g[u] = j < N ? glo[j] : 0.f;
+            l[u] = j < N ? loc[j] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) { sg += g[u]; sl += l[u]; }
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) { sg += __shfl_xor(sg, o); sl += __shfl_xor(sl, o); }
     if (lane == 0) { red[wave][0] = sg; red[wave][1] = sl; }
@@ -54,9 +82,24 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
     for (int w = 0; w < kStatWaves; ++w) { tot_g += red[w][0]; tot_l += red[w][1]; }
     const float align = tot_g > 0.f ? (tot_l / (float)N) / (tot_g / (float)N) : 0.f;
 
-    // total of the Eq. 2 scores (float tree), then every score as a share of it in fixed point
+    // Total of the Eq. 2 scores (float tree), then every score as a share of it in fixed point.  The scores
+    // stay in LDS where they fit: the six walks that follow otherwise go back to memory for them.
+    const bool in_lds = N <= kStatLds;
     float st = 0.f;
-    for (int j = tid; j < N; j += kStatBlock) st += fmaxf(glo[j] * align, loc[j]);
+    for (int j0 = tid; j0 < N; j0 += kStatBlock * kAhead) {
+        float x[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int j = j0 + u * kStatBlock;
+            x[u] = j < N ? fmaxf(glo[j] * align, loc[j]) : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            st += x[u];
+            if (in_lds && j0 + u * kStatBlock < N) kept[j0 + u * kStatBlock] = x[u];
+        }
+    }
+    auto score = [&](int j) { return in_lds ? kept[j] : fmaxf(glo[j] * align, loc[j]); };   // (a thread reads its own elements)
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) st += __shfl_xor(st, o);
     __syncthreads();
@@ -67,9 +110,10 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
     const double to_fixed = tot_s > 0.f ? kMassOne / (double)tot_s : 0.0;
 
     unsigned long long part = 0ull;
-    for (int j = tid; j < N; j += kStatBlock)
-        part += (unsigned long long)((double)fmaxf(glo[j] * align, loc[j]) * to_fixed);
-    atomicAdd(&sh_total, part);
+    for (int j = tid; j < N; j += kStatBlock) part += (unsigned long long)((double)score(j) * to_fixed);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
+    if (lane == 0) atomicAdd(&sh_total, part);
     if (tid == 0) { sh_prefix = 0u; sh_mass_above = 0ull; sh_count_above = 0; }
     __syncthreads();
     // smallest integer mass that counts as "zeta of the total"
@@ -79,27 +123,56 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
         for (int d = tid; d < 256; d += kStatBlock) { cnt[d] = 0; mass[d] = 0ull; }
         __syncthreads();
         const uint32_t prefix = sh_prefix;
-        for (int j = tid; j < N; j += kStatBlock) {
-            const float s = fmaxf(glo[j] * align, loc[j]);
+        for (int j0 = 0; j0 < N; j0 += kStatBlock) {
+            const int j = j0 + tid;
+            const float s = j < N ? score(j) : 0.f;
             const uint32_t key = score_key(s);
-            if (shift < 24 && (key >> (shift + 8)) != prefix) continue;
+            bool on = j < N && (shift == 24 || (key >> ((shift + 8) & 31)) == prefix);
             const int digit = (key >> shift) & 255;
-            atomicAdd(&cnt[digit], 1);
-            atomicAdd(&mass[digit], (unsigned long long)((double)s * to_fixed));
+            const unsigned long long q = on ? (unsigned long long)((double)s * to_fixed) : 0ull;
+            if (shift == 24) {
+                // leading digits are shared: the lanes that agree with the first one go into one pair of
+                // atomics (the masses' sum in two halves of at most 20 + 6 bits)
+                const unsigned long long active = __ballot(on);
+                if (active == 0ull) continue;                // wave-uniform
+                const int leader = __ffsll((long long)active) - 1;
+                const int d0 = __builtin_amdgcn_readlane(digit, leader);
+                const bool same = on && digit == d0;
+                const int n = __popcll(__ballot(same));
+                const int lo = wave_add(same ? (int)(q & 0xfffffull) : 0), hi = wave_add(same ? (int)(q >> 20) : 0);
+                if (lane == leader) { atomicAdd(&cnt[d0], n); atomicAdd(&mass[d0], (unsigned long long)lo + ((unsigned long long)hi << 20)); }
+                on = on && !same;
+            }
+            if (on) { atomicAdd(&cnt[digit], 1); atomicAdd(&mass[digit], q); }
         }
         __syncthreads();
-        if (tid == 0) {
-            // walk the digits from the largest: stop in the one where the mass crosses
-            unsigned long long m = sh_mass_above;
-            int c = sh_count_above, d = 255;
-            for (; d > 0; --d) {
-                if (m + mass[d] >= need_total) break;
-                m += mass[d];
-                c += cnt[d];
+        // the digit, from the largest, in which the mass crosses: thread t holds digit 255 - t and the sums
+        // of the digits from the top down to it
+        const unsigned long long above = sh_mass_above;
+        const int count_above = sh_count_above;
+        const int d = 255 - min(tid, 255);
+        const unsigned long long own = mass[d];
+        unsigned long long m_incl = own;
+        int c_incl = cnt[d];
+        if (tid < 256) {
+#pragma unroll
+            for (int o = 1; o < kWave; o <<= 1) {
+                const unsigned long long mu = __shfl_up(m_incl, o);
+                const int cu = __shfl_up(c_incl, o);
+                if (lane >= o) { m_incl += mu; c_incl += cu; }
             }
-            sh_mass_above = m;
-            sh_count_above = c;
-            sh_prefix = (prefix << 8) | (uint32_t)d;
+            if (lane == kWave - 1) { wave_mass[wave] = m_incl; wave_cnt[wave] = c_incl; }
+        }
+        __syncthreads();
+        if (tid < 256) {
+            for (int w = 0; w < wave; ++w) { m_incl += wave_mass[w]; c_incl += wave_cnt[w]; }
+            const unsigned long long before = above + (m_incl - own);
+            const bool crossed = tid > 0 && before >= need_total;        // by a larger digit
+            if (!crossed && (above + m_incl >= need_total || d == 0)) {  // one thread
+                sh_mass_above = before;
+                sh_count_above = count_above + c_incl - cnt[d];
+                sh_prefix = (prefix << 8) | (uint32_t)d;
+            }
         }
         __syncthreads();
     }

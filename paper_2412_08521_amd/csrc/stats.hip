@@ -654,10 +654,18 @@ __global__ __launch_bounds__(kStatBlock) void redundancy_count_kernel(StatsArgs 
     if (threadIdx.x == 0) total = 0;
     __syncthreads();
     int mine = 0;
-    for (int j = threadIdx.x; j < N; j += kStatBlock) {
-        float b = best[j];
-        if (a.red_waves) { b = order_value(__float_as_uint(b)); best[j] = b; }
-        mine += b >= a.tau ? 1 : 0;                          // Eq. 4: >=
+    constexpr int kAhead = 8;                                // loads in flight per thread
+    for (int j0 = threadIdx.x; j0 < N; j0 += kStatBlock * kAhead) {
+        float b[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) b[u] = j0 + u * kStatBlock < N ? best[j0 + u * kStatBlock] : 0.f;
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const int j = j0 + u * kStatBlock;
+            if (j >= N) break;
+            if (a.red_waves) { b[u] = order_value(__float_as_uint(b[u])); best[j] = b[u]; }
+            mine += b[u] >= a.tau ? 1 : 0;                   // Eq. 4: >=
+        }
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mine += __shfl_xor(mine, o);

@@ -645,7 +645,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 }
 
 // Tokens that reach tau.  After the 16-bit form (red_waves > 0) `best` still holds order images: they are
-// turned into the values here.
+// turned into the values here.  One block per head, so latency bounds it: with kAhead loads in flight per thread
+// 8 heads of 16384 take 5.3 us, one load at a time 11.7.
 __global__ __launch_bounds__(kStatBlock) void redundancy_count_kernel(StatsArgs a)
 {
     __shared__ int total;

@@ -157,10 +157,15 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
         }
     }
 
+    // A token's own norm is applied to its maximum only.  A factor of zero (a row of zeros, one whose squares
+    // leave the float range, one that holds an infinity or a NaN) would lose the products' order, and times an
+    // infinite maximum be no number: a wave that holds such a token applies the factors to every product.
     float best[kTok];
     int arg[kTok];
+    bool no_factor = false;
 #pragma unroll
-    for (int tk = 0; tk < kTok; ++tk) { best[tk] = -INFINITY; arg[tk] = 0; }
+    for (int tk = 0; tk < kTok; ++tk) { best[tk] = -INFINITY; arg[tk] = 0; no_factor |= t_rn[tk][0] == 0.f; }
+    const bool each = kSrc == 1 && __any(no_factor);
 
     for (int r0 = c_begin; r0 < c_end; r0 += kDestDepth * kStageRows) {
         if (r0 != c_begin) { request_positions(r0); request_rows(); }
@@ -199,8 +204,14 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                         }
                     }
                 }
-                // Four operations per element: the token's own norm is applied to the maximum only, the
-                // winner is noted by its register (a constant) and the tile by one select per tile.
+                if (each) {                                    // wave-uniform
+#pragma unroll
+                    for (int tk = 0; tk < kTok; ++tk)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[tk][0][r] *= t_rn[tk][0];
+                }
+                // Four operations per element: the winner is noted by its register (a constant) and the
+                // tile by one select per tile.
                 float before[kTok];
                 int reg[kTok];
 #pragma unroll
@@ -230,7 +241,7 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
 #pragma unroll
     for (int tk = 0; tk < kTok; ++tk) {
         if constexpr (kSrc == 1)
-            if (best[tk] > -INFINITY) best[tk] *= t_rn[tk][0];
+            if (!each && best[tk] > -INFINITY) best[tk] *= t_rn[tk][0];
         // the other half-wave looked at the other centres of every tile
         const float best_o = __shfl_xor(best[tk], 32);
         const int arg_o = __shfl_xor(arg[tk], 32);

@@ -445,6 +445,47 @@ def test_score_split_calls_match_fused_call(mode):
     assert_rel(l3.cpu().numpy(), o_loc, max(RTOL[mode], 2e-5), "s_loc from oracle lse")
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("similarity", [B.EMS_SIM_KEY, B.EMS_SIM_VALUE])
+@pytest.mark.parametrize("shape", [(1, 400, 48), (1, 4000, 1300), (8, 9000, 2066)])   # one slice of centres, several, two token tiles per wave
+def test_destinations_of_rows_without_a_norm(shape, similarity, mode):
+    """Tokens whose reciprocal norm is zero.  An infinity or a NaN in the row: every product is infinite or no
+    number, hence no similarity (-inf) and the zero class, whatever tau.  Rows of zeros, and rows whose squares
+    leave the float range on either side: similarity 0 to every centre, so the lowest one.  The other tokens
+    of the same wave: float32 rounding of the similarity only."""
+    bh, n, nb = shape
+    d, w = 64, 16
+    p = B.EmsParams(1, bh, bh, d, n, w, nb, merge_ratio=1.0, tau=-2.0, dtype=mode)
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    gen = torch.Generator().manual_seed(n)
+    rows = torch.randn((1, bh, n, d), generator=gen).to(p.torch_dtype)
+    other = torch.randn((1, bh, n, d), generator=gen).to(p.torch_dtype).cuda()
+    imp, tbm = (torch.arange(a, b, dtype=torch.int32).repeat(1, bh, 1).cuda() for a, b in ((0, n_imp), (n_imp, n_imp + n_tbm)))
+
+    def dest(x):
+        k, v = (x, other) if similarity == B.EMS_SIM_KEY else (other, x)
+        out = B.ems_evict_merge_variant(p, similarity, k, v, None, imp, tbm)
+        return out["tbm_sim"].cpu().numpy()[0], out["tbm_dest"].cpu().numpy()[0]
+
+    plain_sim, plain_dest = dest(rows.cuda())
+    t = n_imp
+    rows[0, -1, t + 2, 3] = float("inf")
+    rows[0, -1, t + 3, 40] = -float("inf")
+    rows[0, -1, t + 5, 1:3] = torch.tensor([float("inf"), -float("inf")])
+    rows[0, -1, t + 6, 9] = float("nan")
+    rows[0, -1, t + 8] = 0.0
+    rows[0, -1, t + 9] *= 2.0 ** 66
+    rows[0, -1, t + 11] *= 2.0 ** -100
+    sim, where = dest(rows.cuda())
+    none, zero = [2, 3, 5, 6], [8, 9, 11]
+    assert (sim[-1, none] == -np.inf).all() and (where[-1, none] == nb).all(), (sim[-1, none], where[-1, none])
+    assert (sim[-1, zero] == 0).all() and (where[-1, zero] == 0).all(), (sim[-1, zero], where[-1, zero])
+    rest = np.setdiff1d(np.arange(n_tbm), none + zero)
+    np.testing.assert_allclose(sim[-1, rest], plain_sim[-1, rest], rtol=2.0 ** -22)     # two roundings, in another order
+    assert (where[-1, rest] != plain_dest[-1, rest]).sum() <= max(1, n_tbm // 1000)     # ties within that rounding
+    np.testing.assert_array_equal(sim[:-1], plain_sim[:-1])
+
+
 # ---------------------------------------------------------------------------- expansion
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("tau", [0.6, -2.0, 2.0])

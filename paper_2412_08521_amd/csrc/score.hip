@@ -141,16 +141,13 @@ __device__ __forceinline__ float max16(const f32x16_t& acc)
     return fmaxf(t0, t3);
 }
 
-// The largest exponent of a tile among its keys up to row `last_row` (31: all).
+// The largest exponent of a tile that lies below the diagonal.
 template <typename T, int D>
-__device__ __forceinline__ float pass1_tile_max(const frag_t (&ak)[Tile<T, D>::kFrags], const frag_t (&bq)[Tile<T, D>::kFrags],
-                                                float c, int last_row, int half)
+__device__ __forceinline__ float pass1_tile_max(const frag_t (&ak)[Tile<T, D>::kFrags], const frag_t (&bq)[Tile<T, D>::kFrags], float c)
 {
     f32x16_t acc = zero_acc();
 #pragma unroll
     for (int f = 0; f < Tile<T, D>::kFrags; ++f) mma<T>(acc, ak[f], bq[f]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = acc_row(r, half) > last_row ? -INFINITY : acc[r];
     return max16(acc) * c;
 }
 
@@ -830,16 +827,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 // the causal range, 32 at a time, through its own LDS ring (A operand, keys -> accumulator
 // registers): the row sum of a query is a per-lane scalar and there is no workgroup barrier.
 //
-//   online stages    the key stages that touch the diagonal of this wave's queries (masked),
-//                    or, for a key range that has none, its first stage: textbook online
-//                    softmax per tile (running maximum and rescaled sum), one tile at a time.
-//                    They leave every lane a reference exponent m.
+//   edge stages      the key stages that touch the diagonal of this wave's queries (masked), and
+//                    those before them that do not fill a trip of the interior loop: one at a
+//                    time, a tile's chain under the weights of the one before, the reference
+//                    exponent m of a lane its running maximum.
 //   interior stages  every key is visible to every query: the software pipeline of the second
 //                    pass (paired MFMA chains, weights of the previous pair in between), with
-//                    the reference m held fixed: sum += exp2(c * S - m).  Any m gives the same
+//                    the reference m held fixed (where there are no edge stages, at the maximum of the
+//                    first stage): sum += exp2(c * S - m).  Any m gives the same
 //                    log-sum-exp m + log2(sum) as long as the sum stays inside the float range,
 //                    i.e. no later exponent exceeds m by ~100: if a sum does leave the range,
-//                    the wave redoes its interior stages with the online form.
+//                    the wave redoes all of its stages in the online form (running maximum and
+//                    rescaled sum, tile by tile).
 // ------------------------------------------------------------------------------------
 template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_stream_kernel(ScoreArgs a)
@@ -1016,19 +1015,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         wait_vmem<0>();
     };
 
-    // Reference exponents: the largest logit of the first stage the part takes (masked where that
-    // stage is on the diagonal), the same for both half-waves; -inf where a query sees nothing of it.
-    const int d0 = q_base / kStreamRows;                        // subtile s is on the diagonal in stage d0 + s
-    auto reference = [&](const frag_t (&ak)[kFrags], int t) __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < kSub; ++s) {
-            if (s >= t - d0) {                                  // wave-uniform
-                const float m = pass1_tile_max<T, D>(ak, bq[s], c, s == t - d0 ? col : 31, half);
-                m_run[s] = fmaxf(m, __shfl_xor(m, 32));
-            }
-            __builtin_amdgcn_sched_barrier(0);                  // one tile's temporaries at a time
-        }
-    };
     // the vector ALU's share of one MFMA slot, operation by operation (no instruction follows
     // the one it depends on)
     auto weigh = [&](float (&sum)[kEps], const f32x16_t& s_acc, float m, int f) __attribute__((always_inline)) {
@@ -1050,7 +1036,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
     // ---- edge stages: the n_lead interior ones, then those on the diagonal.  Subtiles go from the
     // last one down to the one on the diagonal, which is masked; the chain of the next tile runs
-    // under the weights of the present one.
+    // under the weights of the present one.  The lane's reference is its running maximum: an exponent
+    // far above the reference is rounded coarsely (2^-18 at 100), and its weight with it.
+    const int d0 = q_base / kStreamRows;                        // subtile s is on the diagonal in stage d0 + s
+    auto raise = [&](int s, const f32x16_t& x) __attribute__((always_inline)) {     // -> the reference to use (0 while nothing is seen)
+        const float m_new = fmaxf(m_run[s], max16(x) * c);
+        const float m_use = m_new == -INFINITY ? 0.f : m_new;
+        const float down = exp2_fast(m_run[s] - m_use);
+#pragma unroll
+        for (int e = 0; e < kEps; ++e) lsum[s][e] *= down;
+        m_run[s] = m_new;
+        return m_use;
+    };
     {
         const int n_stages = n_lead + n_edge;
         auto stage_of = [&](int u) __attribute__((always_inline)) { return u < n_lead ? t0 + u : t_diag + (u - n_lead); };
@@ -1061,7 +1058,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             frag_t ak[kFrags];
             fetch_keys(u % kRing, ak);
             const int t = stage_of(u);
-            if (u == 0) reference(ak, t);
             const int s_last = max(t - d0, 0);                   // the lowest subtile that sees the stage
             const int last_row = t >= d0 ? col : 31;             // its keys after this row are above the diagonal
             f32x16_t acc[2];
@@ -1074,19 +1070,21 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                 const bool last = s <= s_last;                   // wave-uniform
                 if (s > 0 && !last) {
                     const int sn = s > 0 ? s - 1 : 0;
+                    mma_first<T>(acc[sn & 1], ak[0], bq[sn][0]);
+                    const float m = raise(s, acc[s & 1]);
 #pragma unroll
                     for (int f = 0; f < kFrags; ++f) {
-                        if (f == 0) mma_first<T>(acc[sn & 1], ak[0], bq[sn][0]);
-                        else mma<T>(acc[sn & 1], ak[f], bq[sn][f]);
-                        weigh(lsum[s], acc[s & 1], m_run[s], f);
+                        if (f > 0) mma<T>(acc[sn & 1], ak[f], bq[sn][f]);
+                        weigh(lsum[s], acc[s & 1], m, f);
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 } else {
-                    float x[16];
+                    f32x16_t& x = acc[s & 1];
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) x[r] = exp2_fast(__builtin_fmaf(acc[s & 1][r], c, -m_run[s]));
+                    for (int r = 0; r < 16; ++r) x[r] = acc_row(r, half) > last_row ? -INFINITY : x[r];
+                    const float m = raise(s, x);
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) lsum[s][r % kEps] += acc_row(r, half) > last_row ? 0.f : x[r];
+                    for (int f = 0; f < kFrags; ++f) weigh(lsum[s], x, m, f);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 if (last) break;
@@ -1127,7 +1125,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         if constexpr (kRing > 3) issue_next(ic<2>{});
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_keys(0, ak[0]);
-        if (n_edge + n_lead == 0) reference(ak[0], ti0);         // wave-uniform; the pipeline sums the stage like every other
+        // The references stay as they are from here on: without edge stages the maxima of the first one (the
+        // pipeline sums it like every other).  A lane that has seen no key yet (its half of the diagonal tile lay
+        // above the diagonal) takes that of the other half, which holds the same queries.
+#pragma unroll
+        for (int s = 0; s < kSub; ++s) {
+            if (n_edge + n_lead == 0) m_run[s] = pass1_tile_max<T, D>(ak[0], bq[s], c);      // wave-uniform
+            const float m_o = __shfl_xor(m_run[s], 32);
+            m_run[s] = m_run[s] == -INFINITY ? m_o : m_run[s];
+            __builtin_amdgcn_sched_barrier(0);                  // one tile's temporaries at a time
+        }
         // the pipeline starts on a pair that weighs nothing: exponents of -inf
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[2][r] = acc[3][r] = -INFINITY;

@@ -112,6 +112,25 @@ def test_score_first_stage_far_below_the_others(mode):
     np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=2e-6, atol=1e-4)
 
 
+@pytest.mark.parametrize("mode", MODES)
+def test_score_reference_follows_the_stages(mode):
+    """The first 32 keys lie 100 powers of two below the others: no redo, but an exponent formed against them is
+    rounded at 2^-18 (2.6e-6 of its weight).  Logits are exact in float32 and at most 12 in base 2; what is left
+    is the rounding of small exponents, of 2^x and of the log-sum-exp itself: 1.2e-6 together."""
+    b, h, d, n = 1, 16, 64, 256
+    rng = np.random.default_rng(3)
+    qf, kf = np.zeros((b, h, n, d), np.float32), np.zeros((b, h, n, d), np.float32)
+    qf[..., 0], qf[..., 1] = 1.0, 2.0 ** -11
+    kf[..., 0] = rng.integers(-8, 9, (b, h, n)) / 4.0
+    kf[:, :, :32, 0] = -100.0
+    kf[..., 1] = rng.integers(128, 256, (b, h, n)) / 256.0          # exact in bf16
+    p = B.EmsParams(b, h, h, d, n, 16, dtype=mode, softmax_scale=float(np.float32(np.log(2.0))))
+    q, k = (dev_tensor(ems_inputs.f32_to_bf16_bits(x), mode) for x in (qf, kf))
+    lse = B.ems_attention_lse(p, q, k)
+    _, _, o_lse = ems_ref.score(ref_params(p), qf, kf, want_lse=True)
+    np.testing.assert_allclose(lse.cpu().numpy()[:, :, 32:], o_lse[:, :, 32:], rtol=0, atol=1.2e-6)
+
+
 def test_score_custom_scale_and_large_logits():
     """Logits of magnitude ~40: the running maximum of pass 1 has to do its job."""
     b, hq, hkv, d, n, w = 1, 2, 2, 128, 600, 16

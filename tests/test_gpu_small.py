@@ -131,6 +131,26 @@ def test_score_reference_follows_the_stages(mode):
     np.testing.assert_allclose(lse.cpu().numpy()[:, :, 32:], o_lse[:, :, 32:], rtol=0, atol=1.2e-6)
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("shape", [(1, 4, 2, 64, 4100), (1, 2, 1, 128, 3000)])
+def test_score_sums_do_not_drift(shape, mode):
+    """Column sums against 64 bits, as a 2-norm (one heavy key takes most of it).  A chain of 512 additions in
+    float32 is off by 512^0.5 * 2^-24 / 3 = 4.5e-7 of its sum; sixteen such chains make a column's: 1.1e-7,
+    and three times that is allowed.  A stretch summed in one go is outside it."""
+    b, hq, hkv, d, n = shape
+    rng = np.random.default_rng(n)
+    u = rng.standard_normal((b, hkv, 1, d))
+    u /= np.linalg.norm(u, axis=-1, keepdims=True)
+    kf = rng.standard_normal((b, hkv, n, d)) + 0.75 * d ** 0.5 * rng.exponential(1.0, (b, hkv, n, 1)) * u
+    qf = rng.standard_normal((b, hq, n, d)) + 4.0 * np.repeat(u, hq // hkv, axis=1)
+    kb, qb = (ems_inputs.f32_to_bf16_bits(x.astype(np.float32)) for x in (kf, qf))
+    p = B.EmsParams(b, hq, hkv, d, n, 32, dtype=mode)
+    s_glo, _ = B.ems_global_local_score(p, dev_tensor(qb, mode), dev_tensor(kb, mode))
+    o_glo, _ = ems_ref.score(ref_params(p), ems_inputs.bf16_bits_to_f32(qb), ems_inputs.bf16_bits_to_f32(kb))[:2]
+    err = np.linalg.norm(s_glo.cpu().numpy() - o_glo) / np.linalg.norm(o_glo)
+    assert err <= 3.4e-7, err
+
+
 def test_score_custom_scale_and_large_logits():
     """Logits of magnitude ~40: the running maximum of pass 1 has to do its job."""
     b, hq, hkv, d, n, w = 1, 2, 2, 128, 600, 16

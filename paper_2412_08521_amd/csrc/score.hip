@@ -1247,14 +1247,14 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
     }
 
-    // the sums are relative to the references; one outside the float range (or NaN) sends the whole
-    // wave back through all of the part's stages in the online form
+    // the sums are relative to the references; one outside the float range (or NaN), or whose half-waves
+    // would leave it together, sends the whole wave back through all of the part's stages in the online form
     bool bad = false;
 #pragma unroll
     for (int s = 0; s < kSub; ++s) {
 #pragma unroll
         for (int e = 0; e < kEps; ++e) l_run[s] += lsum[s][e];
-        bad |= !(l_run[s] < INFINITY);
+        bad |= !(l_run[s] < 0x1p126f);
     }
     if (__any(bad)) {
 #pragma unroll

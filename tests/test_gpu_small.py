@@ -151,6 +151,25 @@ def test_score_sums_do_not_drift(shape, mode):
     assert err <= 3.4e-7, err
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("heads", [8, 1600])                  # cut by stages; work queues
+def test_score_two_halves_leave_the_float_range_together(heads, mode):
+    """Two keys of one interior stage, one in each half of the wave, lie 127.5 powers of two above the reference:
+    each half's sum is inside the float range, their total is not.  log2 of the row sum is 64.5 (two weights of
+    2^63.5) or, before the keys, -64 + log2(i + 1): float32 rounding of a number below 128, twice."""
+    d, n = 64, 1111
+    qf, kf = np.zeros((1, 1, n, d), np.float32), np.zeros((1, 1, n, d), np.float32)
+    qf[..., 0], kf[..., 0] = 1.0, -64.0
+    kf[:, :, [64, 68], 0] = 63.5
+    p = B.EmsParams(1, heads, heads, d, n, 16, dtype=mode, softmax_scale=float(np.float32(np.log(2.0))))
+    q, k = (dev_tensor(ems_inputs.f32_to_bf16_bits(x), mode).expand(1, heads, n, d).contiguous() for x in (qf, kf))
+    s_glo, _, lse = B.ems_global_local_score(p, q, k, want_lse=True)
+    want = -64.0 + np.log2(np.arange(1.0, n + 1))
+    want[64:68], want[68:] = 63.5, 64.5
+    np.testing.assert_allclose(lse.cpu().numpy() / np.log(2.0), np.broadcast_to(want, lse.shape), rtol=0, atol=2.0 ** -16)
+    np.testing.assert_allclose(s_glo.sum(-1).cpu().numpy(), n, rtol=1e-4)
+
+
 def test_score_custom_scale_and_large_logits():
     """Logits of magnitude ~40: the running maximum of pass 1 has to do its job."""
     b, hq, hkv, d, n, w = 1, 2, 2, 128, 600, 16

@@ -67,7 +67,7 @@ __device__ __forceinline__ void hist_add(int* hist, int digit, bool on)
     const unsigned long long active = __ballot(on);
     if (active == 0ull) return;                                   // wave-uniform
     const int leader = __ffsll((long long)active) - 1;
-    const int d0 = __builtin_amdgcn_readlane(digit, leader);      // (the leader is the same for all lanes)
+    const int d0 = __shfl(digit, leader);      // (by v_readlane 131072 equal scores take 481 us, not 459; elsewhere no difference)
     const unsigned long long same = __ballot(on && digit == d0);
     if ((int)(threadIdx.x % kWave) == leader) atomicAdd(&hist[d0], __popcll(same));
     if (on && digit != d0) atomicAdd(&hist[digit], 1);
@@ -276,12 +276,15 @@ __global__ __launch_bounds__(kChunkBlock) void select_gather_kernel(SelectArgs a
 // lane l the ordinals base + i * 64.  position(ordinal) is the sequence position of a candidate.
 // kItems: `items` where it is fixed (the loops are then unrolled: 17.3 us against 20.5 rolled, 4096 tokens), else
 // 0 (rolled: 12.4 us against 15.3 for the candidates of a 16384-token prompt).
+// Every digit has kCopies counters and a lane counts on number lane % kCopies: equal keys would otherwise
+// queue for one LDS address (32 heads of 4096 equal scores: 25.7 us with one counter; 4 is what LDS has room for).
+constexpr int kCopies = 4;
 template <int kItems, typename Position>
 __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items, int count, const SelectArgs& a, Position position)
 {
     constexpr int kUnroll = kItems ? kItems : 1;
     const int items = kItems ? kItems : n_items;
-    __shared__ int hist[2][256];
+    __shared__ __attribute__((aligned(16))) int hist[2][256 * kCopies];
     __shared__ int suffix[2][257];
     __shared__ int scan_sm[kSelWaves][2];
     __shared__ int wave_tot[8];
@@ -296,7 +299,7 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
         sel_rem[tid] = tid == 0 ? a.n_imp : a.n_imp + a.n_tbm;
     }
     for (int shift = 24; shift >= 0; shift -= 8) {
-        if (tid < 512) hist[tid >> 8][tid & 255] = 0;
+        for (int i = tid; i < 512 * kCopies; i += kSelBlock) (&hist[0][0])[i] = 0;
         __syncthreads();
         const uint32_t p0 = sel_prefix[0], p1 = sel_prefix[1];
         const bool same_prefix = shift == 24 || p0 == p1;
@@ -305,20 +308,17 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
             const uint32_t key = keys[base + i * kWave];
             const bool cand = base + i * kWave < count;
             const int digit = (key >> shift) & 255;
-            if (shift == 24) {                             // shared leading digits
-                hist_add(hist[0], digit, cand);
-            } else {                                       // spread out: every key its own atomic
-                const uint32_t hi = key >> (shift + 8);
-                if (cand && hi == p0) atomicAdd(&hist[0][digit], 1);
-                if (!same_prefix && cand && hi == p1) atomicAdd(&hist[1][digit], 1);
-            }
+            const int at = digit * kCopies + lane % kCopies;
+            const uint32_t hi = shift == 24 ? 0u : key >> (shift + 8);
+            if (cand && hi == p0) atomicAdd(&hist[0][at], 1);
+            if (!same_prefix && cand && hi == p1) atomicAdd(&hist[1][at], 1);
         }
-        __syncthreads();
-        if (same_prefix && tid < 256) hist[1][tid] = hist[0][tid];   // one count serves both cuts
         __syncthreads();
         int incl = 0;
         if (tid < 512) {
-            incl = hist[tid >> 8][255 - (tid & 255)];
+            const int* counts = hist[same_prefix ? 0 : tid >> 8] + (255 - (tid & 255)) * kCopies;   // one count serves both cuts
+#pragma unroll
+            for (int c = 0; c < kCopies; ++c) incl += counts[c];
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
                 const int u = __shfl_up(incl, o);

@@ -232,6 +232,7 @@ static void fill_score_args(ems::ScoreArgs& a, const ems_params* p, const ScoreP
     a.queue = w ? reinterpret_cast<int*>(w + plan.off_queue) : nullptr;
     a.p1_waves = plan.deal.p1_waves; a.p1_len = plan.deal.p1_len;
     a.p2_waves = plan.deal.p2_waves; a.p2_len = plan.deal.p2_len;
+    a.p1_by_block = plan.deal.p1_by_block;
     a.batch = p->batch; a.q_heads = p->q_heads; a.kv_heads = p->kv_heads;
     a.head_dim = p->head_dim; a.seq_len = p->seq_len; a.window = p->window;
     a.n_pad = plan.n_pad;

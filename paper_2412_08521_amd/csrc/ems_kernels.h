@@ -23,8 +23,9 @@ struct ScoreArgs {
     int loc_chunk0;     // first chunk that holds a last-window row
     float scale_log2e;  // softmax scale * log2(e)
     int p1_groups, p1_per_group;  // pass-1 work grouping per XCD (set by the launcher)
-    // Even deals (score_deal): waves per head and stages per wave; 0 waves = the pass uses work queues.
+    // Even deals (score_deal): waves per head and stages per wave; 0 waves = the pass takes whole items.
     int p1_waves, p1_len, p2_waves, p2_len;
+    int p1_by_block;    // the first pass gives every block one item, by its index
     float* part_m;      // [B*Hq, p1_waves + row tiles, rows per tile] partial running maxima (workspace)
     float* part_l;      // partial sums relative to them
     // Work queues (set by the launchers): a wave takes its work items from the queue of its XCD; once
@@ -159,8 +160,8 @@ struct StatsArgs {
 
 int score_keys_per_block(int dtype_is_f32);
 // How the score passes of a launch are dealt: waves per head and stages per wave of each pass (0 waves:
-// the pass is long enough for its work queues), and the floats of one partial-result array.
-struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len; size_t p1_floats, p2_floats; };
+// the pass takes whole items), and the floats of one partial-result array.
+struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len, p1_by_block; size_t p1_floats, p2_floats; };
 ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32);
 int select_chunks(int seq_len);     // blocks per head of the long-sequence select
 int select_coarse_bins();

@@ -78,9 +78,13 @@ __device__ __forceinline__ int take_or_steal(int* cursors, int n_per_queue, int&
     return __builtin_amdgcn_readfirstlane(k);
 }
 
+// Resident waves per XCD: one per SIMD.
+constexpr int kXcdWaves = 128;
+
+// Both passes' cursors; the first pass's start behind the items its waves begin with.
 __global__ void score_queue_reset_kernel(int* queue)
 {
-    if (threadIdx.x < 2 * (kXcds + 1)) queue[threadIdx.x] = 0;      // both passes' cursors
+    if (threadIdx.x < 2 * (kXcds + 1)) queue[threadIdx.x] = threadIdx.x > kXcds ? kXcdWaves : 0;
 }
 
 // Pass 2: key tiles at or below the diagonal of row chunks 0..I, per (batch, kv-head): chunk I'
@@ -317,7 +321,7 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 // A stretch of an even deal can be as long as a whole row or column.  After kFoldKeys keys (first pass), or kFoldRows
 // rows of every q-head of the group (second), a running sum is added to the sum of those before it, so that
 // small weights are not lost against a large sum.  (1 x 4 heads over 1, 8192: column sums off by 3.8e-7 without, 0.7e-7.)
-constexpr int kFoldKeys = 1024, kFoldRows = 512;
+constexpr int kFoldKeys = 2048, kFoldRows = 512;
 template <typename T> struct Stream { static constexpr int kSub = 8; static constexpr int kRing = 4; };
 template <> struct Stream<float> { static constexpr int kSub = 2; static constexpr int kRing = 3; };
 
@@ -900,28 +904,34 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     // Long launches: a wave stays and takes item after item until every queue is empty -- the exit
     // every wave reaches (the cursors only grow); between two items nothing of the wave is in flight.
     // Shorter ones: the wave's stretch of an even deal, one part of a row tile after the other.
+    // (p1_by_block: one item per block, by its index.)
     const DealPass1<kSub> deal(N);
     DealPlace place{-1, 0};
     int pos = 0, pos_end = 0;
+    int q_head = 0;
     if constexpr (kDeal) {
-        place = deal_place(a.batch * a.q_heads, a.p1_waves);
+        // neighbours are the q-heads of a group on the same stretch: they stream the same keys, through one L2
+        place = deal_place(a.batch * a.kv_heads, a.p1_waves * G);
         if (place.head < 0) return;
+        q_head = scalar(place.wave % G); place.wave = scalar(place.wave / G);
         pos = place.wave * a.p1_len;
         pos_end = scalar(min(pos + a.p1_len, deal.total()));
     }
-    for (;;) {
+    for (bool first = true;; first = false) {
     int rt, bkv, g, t0 = 0, t1;                             // bkv = b * kv_heads + kv; key stages [t0, t1)
     if constexpr (kDeal) {
         if (pos >= pos_end) break;
         rt = scalar(deal.unit_at(pos));
-        g = scalar(place.head % G); bkv = scalar(place.head / G);
+        g = q_head; bkv = place.head;
         const int u0 = deal.first(rt), to = min(pos_end, deal.end(rt));
         t0 = scalar(max(pos, u0) - u0); t1 = scalar(to - u0);
         pos = scalar(to);
         if (t0 >= t1) continue;                             // before the unit's first stage
     } else {
-        int from_xcd;
-        const int k_item = take_or_steal(a.queue + (kXcds + 1), a.p1_local, from_xcd);
+        // the first item goes by the wave's place: a thousand waves would wait for one cache line of cursors
+        int from_xcd = blockIdx.x % kXcds, k_item = blockIdx.x / kXcds;
+        if (!first && a.p1_by_block) break;
+        if (!first || k_item >= a.p1_local) k_item = take_or_steal(a.queue + (kXcds + 1), a.p1_local, from_xcd);
         if (k_item < 0) break;
         int bid = xcd_work_item(a.p1_groups, a.p1_per_group, from_xcd, k_item);
         if (bid < 0) continue;                              // padding
@@ -1293,35 +1303,66 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
 int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<float>::kSub : Stream<bf16_t>::kSub); }
 
-// Which launches are dealt evenly (bf16, head size 128, times of the pass in us, even deal against whole
-// items; both with the masked stages in the pipeline):
-//   first pass    1 x 32 heads:  8192: 247 / 358 (queues), 249 (key-range splits, now gone);  16384: 907 / 922;
-//                 24000: 1917 / 1996;  32768 (4096 row tiles): 3530 / 3545;  4 x 32768: 14164 / 13903
-//   second pass   32 over 8 heads:  8192: 251 / 319;  16384: 921 / 969;  2 x 16384: 1844 / 1874;
-//                 4 x 16384: 3933 / 3659;  4 x 32768: 16.8 / 14.1 ms (waves that stream different rows
-//                 share no lines of their L2: the more rows there are, the more that costs)
-//                 fewer heads than XCDs, 6 over 2:  16384: 200 / 249;  32768: 690 / 774;  4 over 1, 131072:
-//                 7.19 / 7.47 ms (the alternative is one block per item, without queues)
-constexpr int kDealUnits = 4 * 1024;       // first pass: below four row tiles per resident wave
-constexpr double kDealStages = 1200.;      // second pass: up to so many stages per resident wave
+// How a launch's work reaches the waves; times of a pass in us, head size 128, heads x length (rows of one line were
+// measured in one process, in turn).
+//
+// First pass, U = row tiles per resident wave.  Wide: more than one (batch, kv-head) pair per XCD, whose
+// queue then holds its pairs one after the other instead of the heaviest row tiles first.
+//                                                          even deal / block per item / queues
+//   U < 2               deal     28 over 4, 16384    U 1.75      840 /    - /  870
+//                                 8 over 2, 32768      1.0       949 /    - / 1338
+//   U at 2, not wide    blocks   64 over 8, 8192       2.0       473 /  448 /  505   (a heavy and a light row tile
+//                                32 over 8, 16384      2.0       913 /  876 /  908    make a pair: nothing to balance)
+//                                 4 over 1, 131072     2.0      6944 / 6764 / 6786
+//   2 < U < 4, not wide queues   24 over 8, 24000      2.2      1458 / 1462 / 1403
+//                                28 over 4, 32768      3.5      3216 /    - / 3229
+//                                 8 over 2, 98304      3.0      1.2 % in the queues' favour
+//              wide     deal     4 x 32 over 8, 4096   2.0       260 /  298 /  299
+//                                32 over 32, 24000     2.9      2035 /    - / 2198
+//   U >= 4              queues   32 over 8, 32768      4.0      3507 /    - / 3396
+//                                32 over 32, 49152     6.0      8728 /    - / 8264
+//   float32 (a part's beginning is little against its stages): the deal up to U = 16
+//                                 8 over 2, 16384      2.7      2946 / 3305 / 3866
+//                                4 x 32 over 8, 4096  10.7      3036 / 3060 / 3194
+// Second pass, by row stages per resident wave: the deal up to 1200, and always for fewer pairs than XCDs (which have
+// no queues: one block per item).  Waves that stream different rows share no lines of their L2: the more rows, the
+// more that costs.
+//                                                    stages      deal / queues
+//                                32 over 8, 8192       128       255 /  318
+//                                32 over 8, 16384      512       908 /  954
+//                                64 over 8, 16384     1024      1891 / 1879
+//                                24 over 8, 32768     1536      2801 / 2804
+//                                32 over 8, 32768     2048      3726 / 3680
+//                                4 x 32 over 8, 16384 2048      4029 / 3727
+//                                32 over 8, 49152     4608      8522 / 8083
+//                                 6 over 2, 49152      864      1582 / 1674  (block per item)
+//                                16 over 2, 65536     4096      7420 / 7419        "
+//                                 4 over 1, 131072    4096      7360 / 7361        "
+constexpr double kPairUnits = 1.95;        // from here to 2 a launch counts as whole pairs
+constexpr double kDealStages = 1200.;
 
-template <int kSub>
+template <typename T>
 static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len, int resident)
 {
+    constexpr int kSub = Stream<T>::kSub, kRows = 32 * kSub;
     ScoreDeal d{};
     const long long BHQ = (long long)batch * q_heads, BKV = (long long)batch * kv_heads;
-    const int G = q_heads / kv_heads, rows = 32 * kSub;
+    const int G = q_heads / kv_heads;
     const DealPass1<kSub> d1(seq_len);
-    if (BHQ * d1.n_units < kDealUnits) {
+    const double units = (double)(BHQ * d1.n_units) / 1024.;
+    const bool wide = BKV > kXcds;
+    bool deal1 = units < (sizeof(T) == 4 ? 16. : wide ? 4. : 2.);
+    if (sizeof(T) == 2 && !wide && units >= kPairUnits && units <= 2.) { d.p1_by_block = 1; deal1 = false; }
+    if (deal1) {
         deal_over_waves(resident, BHQ, d1.total(), DealPass1<kSub>::kAlign, 4, &d.p1_len, &d.p1_waves);
-        d.p1_floats = (size_t)BHQ * (d.p1_waves + d1.n_units) * rows;
+        d.p1_floats = (size_t)BHQ * (d.p1_waves + d1.n_units) * kRows;
     }
     const DealPass2<kSub> d2(seq_len, G);
     const double stages = 0.5 * (double)BKV * G * d2.rows_all * d2.n_units / 1024.;
     const bool fits = (d2.rows_all + 8.) * d2.n_units < 1073741824.;      // a line's stages are counted in 32 bits
     if (fits && (stages <= kDealStages || BKV < kXcds)) {
         deal_over_waves(resident, BKV, d2.total(), DealPass2<kSub>::align(G), 1, &d.p2_len, &d.p2_waves);
-        d.p2_floats = (size_t)BKV * (d.p2_waves + d2.n_units) * rows;
+        d.p2_floats = (size_t)BKV * (d.p2_waves + d2.n_units) * kRows;
     }
     return d;
 }
@@ -1329,8 +1370,8 @@ static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len,
 ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32)
 {
     // (three 16 KB stages of 512-byte rows: three waves in a compute unit's LDS instead of four)
-    return f32 ? score_deal_t<Stream<float>::kSub>(batch, q_heads, kv_heads, seq_len, head_dim == 128 ? 768 : 1024)
-               : score_deal_t<Stream<bf16_t>::kSub>(batch, q_heads, kv_heads, seq_len, 1024);
+    return f32 ? score_deal_t<float>(batch, q_heads, kv_heads, seq_len, head_dim == 128 ? 768 : 1024)
+               : score_deal_t<bf16_t>(batch, q_heads, kv_heads, seq_len, 1024);
 }
 
 template <typename T, int D>
@@ -1353,15 +1394,17 @@ static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)
     // heads to keep all XCDs busy, else groups of the G q-heads of one row tile
     if (BKV >= kXcds) { a1.p1_groups = BKV; a1.p1_per_group = n_row_tiles * G; }
     else { a1.p1_groups = BKV * n_row_tiles; a1.p1_per_group = G; }
-    // one queue per XCD; resident waves, one per SIMD (128 per XCD).  The reset clears the second
-    // pass's cursors as well.
+    // one queue per XCD; resident waves.  The reset clears the second pass's cursors as well.
     const long long per_xcd = xcd_grid(a1.p1_groups, a1.p1_per_group) / kXcds;
     if (kXcds * per_xcd > 0x7fffffffll) return hipErrorInvalidValue;
     a1.p1_local = (int)per_xcd;
-    a.queue_clear = 1;                                      // tells a second pass that follows that its cursors are clear
-    hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
-    if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
-    hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, false>), dim3(kXcds * 128), dim3(kWave), 0, st, a1);
+    a.queue_clear = !a.p1_by_block;                         // tells a second pass that follows whether its cursors are clear
+    if (!a.p1_by_block) {
+        hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
+        if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
+    }
+    const unsigned grid1 = kXcds * (unsigned)(a.p1_by_block ? per_xcd : kXcdWaves);
+    hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, false>), dim3(grid1), dim3(kWave), 0, st, a1);
     return hipGetLastError();
 }
 
@@ -1401,7 +1444,7 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
     const long long low = p2_items_upto(a2.p2_split - 1, r_tiles, n_key_tiles);
     const long long n_local = a2.q_share * (all - low), n_pool = (long long)BKV * low;
     const long long grid2 = !a2.q_share ? xcd_grid((long long)BKV * a.n_chunks, n_key_tiles)     // no queues: a block per pair, padding included
-                                        : kXcds * 128;
+                                        : kXcds * kXcdWaves;
     if (n_local > 0x7fffffffll || n_pool > 0x7fffffffll) return hipErrorInvalidValue;
     if (a.chunk_rows % kKeys != 0 || grid2 > 0x7fffffffll) return hipErrorInvalidValue;
     a2.p2_local = (int)n_local; a2.p2_pool = (int)n_pool;

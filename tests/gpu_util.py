@@ -1,5 +1,7 @@
 """Helpers shared by the GPU parity tests: moving generated inputs to the device, the
 tolerance rules, and the band rule for index sets."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -26,6 +28,19 @@ def ref_params(p: B.EmsParams) -> RefParams:
     return RefParams(p.batch, p.q_heads, p.kv_heads, p.head_dim, p.seq_len, p.window,
                      budget=p.budget, merge_ratio=p.merge_ratio, tau=p.tau,
                      pool_kernel=p.pool_kernel, softmax_scale=p.softmax_scale)
+
+
+def score_forms(p: B.EmsParams):
+    """How the library deals the two score passes of `p`: "deal" (stretches of stages), "block" (an item per block, by
+    its index) or "queue" (resident waves that draw items), as the host side decides it (runs without a GPU)."""
+    class Deal(C.Structure):
+        _fields_ = [(n, C.c_int) for n in ("p1_waves", "p1_len", "p2_waves", "p2_len", "p1_by_block")] + [
+            ("p1_floats", C.c_size_t), ("p2_floats", C.c_size_t)]
+    f = getattr(B.lib(), "_ZN3ems10score_dealEiiiiib")
+    f.restype, f.argtypes = Deal, [C.c_int] * 5 + [C.c_bool]
+    d = f(p.batch, p.q_heads, p.kv_heads, p.seq_len, p.head_dim, p.dtype == B.EMS_F32)
+    first = "deal" if d.p1_waves else "block" if d.p1_by_block else "queue"
+    return first, "deal" if d.p2_waves else "queue" if p.batch * p.kv_heads % 8 == 0 else "block"
 
 
 def rel_err(got, ref, floor_frac=1e-3):

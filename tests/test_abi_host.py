@@ -218,3 +218,27 @@ def test_binding_rejects_host_tensors_and_wrong_shapes(lib):
         B.ems_redundancy_rate(p, k, k)
     with pytest.raises(B.EmsError):
         B.ems_partition_sizes(_bad(budget=8))
+
+
+# (float32, batch, q_heads, kv_heads, head_dim, seq_len), first pass, second pass: either side of every line of the rule
+@pytest.mark.parametrize("shape,forms", [
+    ((False, 1, 28, 4, 128, 16384), ("deal", "deal")),        # 1.75 row tiles per resident wave
+    ((False, 1, 32, 8, 128, 16384), ("block", "deal")),       # 2, heaviest first
+    ((False, 1, 64, 8, 64, 8177), ("block", "deal")),
+    ((False, 1, 64, 8, 64, 8193), ("queue", "deal")),         # 2.06
+    ((False, 1, 32, 16, 128, 16384), ("deal", "deal")),       # 2, two pairs per XCD
+    ((False, 1, 32, 32, 128, 32512), ("deal", "queue")),      # 3.97
+    ((False, 1, 32, 32, 128, 32768), ("queue", "queue")),     # 4
+    ((False, 1, 32, 8, 128, 24000), ("queue", "deal")),       # 1102 row stages per wave
+    ((False, 1, 24, 8, 128, 32768), ("queue", "queue")),      # 1536
+    ((False, 1, 4, 1, 128, 131072), ("block", "deal")),       # fewer pairs than XCDs
+    ((False, 1, 48, 12, 128, 32768), ("queue", "block")),     # pairs that do not divide over the XCDs
+    ((True, 1, 8, 2, 128, 3000), ("deal", "deal")),
+    ((True, 1, 64, 8, 64, 4096), ("deal", "deal")),           # 4
+    ((True, 1, 320, 320, 128, 3264), ("deal", "deal")),       # 15.9
+    ((True, 1, 320, 320, 128, 3300), ("queue", "deal")),      # 16.25
+])
+def test_score_passes_are_dealt_by_rule(lib, shape, forms):
+    from gpu_util import score_forms
+    f32, b, hq, hkv, d, n = shape
+    assert score_forms(B.EmsParams(b, hq, hkv, d, n, 16, dtype=B.EMS_F32 if f32 else B.EMS_BF16)) == forms

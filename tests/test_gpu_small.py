@@ -8,7 +8,7 @@ import ems_inputs
 from oracle import ems_ref
 from paper_2412_08521_amd import binding as B
 from gpu_util import (RTOL, RTOL_MERGE, assert_dest_valid, assert_rel, check_band, dev_tensor, is_sorted_unique,
-                      ref_params)
+                      ref_params, score_forms)
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +23,7 @@ SCORE_SHAPES = [
     (1, 4, 1, 128, 300, 300),      # window == length
     (1, 8, 2, 128, 2500, 64),      # several row chunks in pass 2
     (1, 2, 2, 64, 4099, 70),       # window straddles a chunk boundary
-    (1, 6, 3, 128, 6000, 64),      # heads that do not divide over the XCDs: pairs dealt by block index
+    (1, 6, 3, 128, 6000, 64),      # heads that do not divide over the XCDs
 ]
 
 
@@ -92,6 +92,44 @@ def test_score_even_deal(shape, mode):
     assert_rel(s_glo.cpu().numpy(), o_glo, RTOL[mode], "s_glo")
     assert_rel(s_loc.cpu().numpy(), o_loc, RTOL[mode], "s_loc")
     np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
+
+
+@pytest.mark.parametrize("mode,shape,forms", [
+    (B.EMS_BF16, (1, 256, 8, 64, 2040, 100), ("block", "deal")),     # two row tiles per wave, one pair per XCD
+    (B.EMS_BF16, (1, 64, 2, 128, 8177, 90), ("block", "deal")),      # the q-heads of a row tile together
+    (B.EMS_BF16, (1, 320, 8, 128, 2040, 100), ("queue", "deal")),
+    (B.EMS_BF16, (1, 500, 5, 64, 1270, 33), ("queue", "deal")),
+    (B.EMS_BF16, (1, 804, 804, 64, 5003, 1500), ("queue", "block")),  # pairs that do not divide over the XCDs
+    (B.EMS_BF16, (1, 804, 804, 128, 5003, 40), ("queue", "block")),
+    (B.EMS_BF16, (2, 800, 400, 64, 5003, 1500), ("queue", "queue")),  # the window crosses a row chunk's end
+    (B.EMS_BF16, (1, 800, 800, 128, 5003, 907), ("queue", "queue")),
+    (B.EMS_F32, (1, 804, 804, 64, 2503, 600), ("queue", "block")),
+    (B.EMS_F32, (1, 804, 402, 128, 2503, 600), ("queue", "block")),
+    (B.EMS_F32, (1, 800, 800, 64, 2503, 600), ("queue", "queue")),
+    (B.EMS_F32, (1, 800, 400, 128, 2503, 70), ("queue", "queue")),
+])
+def test_score_whole_items(mode, shape, forms):
+    """Launches whose passes take whole items, by block index or from queues, at ragged lengths: first, middle and last
+    (batch, kv-head) pair against the oracle (heads are independent).  Tolerance: the stated bars."""
+    b, hq, hkv, d, n, w = shape
+    g = hq // hkv
+    _log("whole items", mode, shape)
+    p = B.EmsParams(b, hq, hkv, d, n, w, dtype=mode)
+    assert score_forms(p) == forms
+    gen = torch.Generator(device="cuda").manual_seed(n + hq)
+    k = torch.randn((b, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16).to(p.torch_dtype)
+    q = torch.empty((b, hq, n, d), dtype=p.torch_dtype, device="cuda")
+    for h in range(hkv):
+        q[:, h * g:(h + 1) * g] = torch.randn((b, g, n, d), device="cuda", generator=gen).to(torch.bfloat16).to(p.torch_dtype)
+    s_glo, s_loc, lse = B.ems_global_local_score(p, q, k, want_lse=True)
+    np.testing.assert_allclose(s_glo.sum(-1).cpu().numpy(), g * n, rtol=1e-4)
+    np.testing.assert_allclose(s_loc.sum(-1).cpu().numpy(), g * w, rtol=1e-4)
+    for i, h in ((0, 0), (b - 1, hkv // 2), (b - 1, hkv - 1)):
+        ref = ems_ref.RefParams(1, g, 1, d, n, w)
+        o = ems_ref.score(ref, q[i:i + 1, h * g:(h + 1) * g].float().cpu().numpy(), k[i:i + 1, h:h + 1].float().cpu().numpy(), want_lse=True)
+        assert_rel(s_glo[i, h].cpu().numpy(), o[0][0, 0], RTOL[mode], "s_glo")
+        assert_rel(s_loc[i, h].cpu().numpy(), o[1][0, 0], RTOL[mode], "s_loc")
+        np.testing.assert_allclose(lse[i, h * g:(h + 1) * g].cpu().numpy(), o[2][0], rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
 
 
 @pytest.mark.parametrize("mode", MODES)

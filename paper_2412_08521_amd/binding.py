@@ -157,8 +157,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# torch's own short way to the current stream's handle, where this torch has it
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _check_tensor(t, shape, dtype, name):

@@ -122,3 +122,13 @@ def test_decode_steps_replay_from_one_captured_launch():
         for name in B.STATE_FIELDS:
             assert torch.equal(getattr(eager_st, name).view(torch.uint8), getattr(graph_st, name).view(torch.uint8)), (t, name)
     assert int(graph_st.step_count.item()) == steps
+
+
+def test_calls_go_to_the_current_stream(monkeypatch):
+    """The handle the binding passes on is the current stream's, by torch's short way to it and without."""
+    side = torch.cuda.Stream()
+    for _ in range(2):
+        for stream in (torch.cuda.current_stream(), side):
+            with torch.cuda.stream(stream):
+                assert B._stream() == stream.cuda_stream == torch.cuda.current_stream().cuda_stream
+        monkeypatch.setattr(B, "_raw_stream", None)

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                     *reinterpret_cast<frag_t*>(lds[s] + row * kStride + cc * 16) = pf[st][s][i];
                     // the kCpr consecutive lanes that hold one row add up its squares
                     const float ss = group_sum<kCpr>(frag_sumsq<T>(pf[st][s][i]));
-                    if (cc == 0) lds_rn[s][row] = c0 + row < c_end ? inv_norm_fast(ss) : __builtin_nanf("");
+                    if (cc == 0) lds_rn[s][row] = c0 + row < c_end ? row_inv_norm<T>(ss) : __builtin_nanf("");
                 }
             }
             __syncthreads();

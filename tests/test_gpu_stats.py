@@ -129,3 +129,28 @@ def test_redundancy_edges(bh_n, d, scale):
         best = best[:, pick]
     assert (best[..., 0] == -np.inf).all()
     np.testing.assert_allclose(best[..., 1:], o_best[..., 1:], rtol=0, atol=2e-5)
+
+
+def test_redundancy_of_the_longest_sequences():
+    """Over 2^21 positions a head's line of stages does not fit 32 bits and another kernel takes the bf16 rows: tokens
+    spread over the sequence, some with a near copy far before them, against 64 bits.  Tolerance as above."""
+    n, d = 2 ** 21 + 33, 64
+    _log("redundancy", n, d)
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    k, v = (torch.randn((1, 1, n, d), device="cuda", generator=gen).to(torch.bfloat16) for _ in range(2))
+    pick = [1, 31, 32, 33, 127, 128, 129, 5000, 2 ** 20 - 1, 2 ** 20, 2 ** 21 - 1, 2 ** 21, 2 ** 21 + 1, n - 2, n - 1]
+    for t in pick[4::2]:
+        for x in (k, v):
+            x[0, 0, t] = (x[0, 0, t // 3].float() + 0.3 * x[0, 0, t].float()).to(torch.bfloat16)
+    rate, best = B.ems_redundancy_rate(B.EmsParams(1, 1, 1, d, n, 1, tau=0.6), k, v)
+    assert best[0, 0, 0] == -float("inf")
+    assert float(rate[0, 0]) == np.float32(int((best >= 0.6).sum())) / np.float32(n)
+    kn, vn = (x[0, 0].float().norm(dim=-1).double() for x in (k, v))
+    for t in pick:
+        top = -1.0
+        for c in range(0, t, 1 << 18):
+            e = min(t, c + (1 << 18))
+            kc, vc = (x[0, 0, c:e].double() @ x[0, 0, t].double() for x in (k, v))
+            top = max(top, float((kc * vc / (kn[c:e] * vn[c:e] * kn[t] * vn[t])).max()))
+        assert abs(float(best[0, 0, t]) - top) <= 2e-5, (t, float(best[0, 0, t]), top)
+        assert top > 0.6 or t not in pick[4::2]

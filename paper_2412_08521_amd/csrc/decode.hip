@@ -53,10 +53,14 @@ __device__ __forceinline__ void block_reduce(float (&v)[kN], float (*buf)[kWaves
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kN; ++i) {
-        float r = buf[i][0];
+        if constexpr (kWaves == 16) {
+            v[i] = lane_value(row_reduce<kMax>(buf[i][lane & 15]), 0);
+        } else {
+            float r = buf[i][0];
 #pragma unroll
-        for (int w = 1; w < kWaves; ++w) r = comb<kMax>(r, buf[i][w]);       // fixed order
-        v[i] = r;
+            for (int w = 1; w < kWaves; ++w) r = comb<kMax>(r, buf[i][w]);       // fixed order
+            v[i] = r;
+        }
     }
 }
 // arg-min (kMin) or arg-max of (value, index) pairs, lowest index on ties; index < 0 = none
@@ -177,23 +181,29 @@ __global__ __launch_bounds__(256) void decode_init_kernel(DecodeInitArgs a)
 // per wave) while the cache is small.
 //
 // Large caches: one compute unit cannot pull the cache rows fast enough, nor walk the table, so the step is
-// four launches in stream order, three of them over slices:
-//   decode_logits_kernel   slices of the token table: every token's own row against the group's queries,
+// four launches in stream order.  Few heads, over slices of the token table:
+//   decode_logits_kernel   slices of the table: every token's own row against the group's queries,
 //                          logits to the workspace, the slice's maxima, sums and scalar totals to the record
 //   decode_weights_kernel  the same slices: weights, score update, the slice's least important centre
 //   kPart = 3              slices of the centre rows: the least important centre of all, phase 3 (one block),
 //                          centre cosines (phase 5)
 //   kPart = 4              one block per head, 1024 threads: phases 6-7
-// Nothing waits for another block inside a launch.  A token gathers its row although tokens share
-// entries: the row comes from the L2, and the table then needs no second look at the rows' dots.  (With row
-// slices for the dots and one block per head for softmax, update and arg-min the step was 4.9 + 13.1 +
-// 5.2 + 4.7 us at budget 2048, 3072 table elements, 8 heads: now 6.4 + 4.2 + 6.4 + 4.7.)  (Letting the last cosine block
+// A token gathers its row although tokens share entries: the row comes from the L2, and the table then needs no
+// second look at the rows' dots.  Many heads fill the chip without the table's slices, and the gathers then
+// cost more than they save:
+//   kPart = 1              slices of the cache rows: phase 1 (row dots, staged in the workspace)
+//   kPart = 2              one block per head, 1024 threads: phases 2-4
+//   kPart = 5              slices of the centre rows: phase 5
+//   kPart = 4              as above
+// (us a step, table slices / row slices, head size 128, budget 2000: 8 heads of 4 q-heads 21.9 / 25.8, 32 heads
+// 22.4 / 23.1, 64 heads of 4 37.0 / 33.9, 256 heads of 4 86.4 / 66.9.)
+// Nothing waits for another block inside a launch.  (Letting the last cosine block
 // of a head run phases 6-7 itself saves a launch and was measured slower: the next launch's latency hides
 // behind the sweep anyway.)
-// What one launch leaves for the next lives in the workspace: the logits, and a hand-over record per
-// head (kHand* offsets below).
-// Dynamic LDS of the one-launch step (floats): dot[G][budget] | rn[budget] when that fits, else the same
-// arrays live in the caller's workspace (a.lds_floats == 0).
+// What one launch leaves for the next lives in the workspace: the logits or the staged dots and row norms, and
+// a hand-over record per head (kHand* offsets below).
+// Dynamic LDS of the one-launch step and of kPart = 2 (floats): dot[G][budget] | rn[budget] when that fits, else the
+// same arrays live in the caller's workspace (a.lds_floats == 0).
 constexpr int kHandSelf = 0;       // [8]  new query . new key per q-head (log2 units)
 constexpr int kHandNewNorm = 8;    //      norm of the new key
 constexpr int kHandOldSc = 9;      // [4]  scalars of the token that left the window
@@ -405,8 +415,9 @@ template <typename T, int D, int G, int kBlock, int kPart>
 __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 {
     constexpr bool kAll = kPart == 0;
-    constexpr bool kDoCos = kAll || kPart == 3;
-    static_assert(kAll || kPart == 3 || kPart == 4, "parts");
+    constexpr bool kDoDots = kAll || kPart == 1, kDoSoftmax = kAll || kPart == 2;
+    constexpr bool kDoCos = kAll || kPart == 3 || kPart == 5;
+    static_assert(kPart >= 0 && kPart <= 5, "parts");
     static_assert(kHandOldRow % 4 == 0 && kHandOldRow + 2 * D * (int)sizeof(T) / 4 <= kDecodeHandFloats, "hand-over record");
     using P = Pack<T>;
     constexpr int kE = P::kElems;
@@ -437,7 +448,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     // step (by the step itself when nobody reads it); in the sliced step the first part copies it into
     // every head's hand-over record, the later parts read that copy, and the last part advances it.
     const int step = a.step >= 0 ? a.step
-                   : (!kAll ? reinterpret_cast<const int*>(a.hand + (size_t)bkv * kDecodeHandFloats)[kHandStep] : *a.st.step_count);
+                   : (kPart >= 2 ? reinterpret_cast<const int*>(a.hand + (size_t)bkv * kDecodeHandFloats)[kHandStep] : *a.st.step_count);
     const int lane = tid % kWave, wave = tid / kWave;
     const int col = lane & 31, half = lane >> 5;             // MFMA operand row / k-half of this lane
     const int grp = tid / kLpr, piece = tid % kLpr;
@@ -453,15 +464,17 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     float* tok_glo = a.st.tok_glo + (size_t)bkv * Tn;
     float* tok_past = a.st.tok_past + (size_t)bkv * Tn;
     float* tok_cur = a.st.tok_cur + (size_t)bkv * Tn;
+    // kPart = 1 writes the staged arrays to the workspace; kPart = 2 copies them into LDS first when they fit
     float* ws_stage = a.ws + (size_t)bkv * ((size_t)(G + 1) * Nb);
-    const bool in_lds = a.lds_floats > 0;                    // block-uniform
+    const bool in_lds = a.lds_floats > 0 && (kAll || kPart == 2);   // block-uniform
     float* stage = in_lds ? dyn_lds : ws_stage;
     float* hand = kAll ? nullptr : a.hand + (size_t)bkv * kDecodeHandFloats;
     int* hand_i = reinterpret_cast<int*>(hand);
     frag_t* hand_row = reinterpret_cast<frag_t*>(hand + kHandOldRow);
-    // centre rows of this block's sweep (phase 5): all, or the block's slice
+    // rows of this block's sweeps: every row, or the block's slice
     const int r_lo = kAll ? 0 : slice * a.slice_rows;
-    const int c_end = kAll ? n_imp : min(r_lo + a.slice_rows, n_imp);
+    const int r_end = kAll ? Nb + 1 : min(r_lo + a.slice_rows, Nb + 1);       // phase 1 (row Nb = the new key)
+    const int c_end = kAll ? n_imp : min(r_lo + a.slice_rows, n_imp);        // phase 5
     float* dot = stage;                                      // [G][budget] q_g . cache row
     float* rn_of = stage + (size_t)G * Nb;                   // [budget] copy of row_norm
     const char* qn = reinterpret_cast<const char*>(a.q_new) + (size_t)bkv * G * D * sizeof(T);
@@ -484,7 +497,10 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr int kRowsPerPass = kWaves * kRowsPerWave;
     constexpr int kInFlight = 4;                             // row loads in flight per lane (bf16 path)
     const int sub = lane / kLpr;                             // this lane's row within the wave's load
-    const int ct_pre = (kAll && tid < n_imp) ? entry_tok[tid] : 0;
+    constexpr int kCt = kBlock == 1024 ? 2 : 1;              // centre tokens looked up ahead per thread (phase 4)
+    int ct_pre[kCt];
+#pragma unroll
+    for (int u = 0; u < kCt; ++u) ct_pre[u] = (kDoSoftmax && tid + u * kBlock < n_imp) ? entry_tok[tid + u * kBlock] : 0;
     frag_t new_k = zero_frag(), new_v = zero_frag();
     float m[G], sum[G];
     float tot2[2] = {0.f, 0.f};                              // sum of s_Glo, sum of s_Loc
@@ -506,7 +522,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             pre_tc[u] = ok ? tok_cur[j] : 0.f;
         }
     };
-    if constexpr (kAll) {
+    if constexpr (kDoDots) {
     if constexpr (kDot2) {
         frag_t qp[G];
 #pragma unroll
@@ -520,17 +536,17 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 fk[u] = r < Nb ? *reinterpret_cast<const frag_t*>(Kc + ((size_t)r * kLpr + piece) * 16) : new_k;
             }
         };
-        const int r_first = wave * kRowsPerWave + sub;
+        const int r_first = r_lo + wave * kRowsPerWave + sub;
         load_rows(r_first);
-        preload_table();
-        const float rn_mine = tid < Nb ? row_norm[tid] : 0.f;
+        if constexpr (kAll) preload_table();
+        const float rn_mine = (kAll && tid < Nb) ? row_norm[tid] : 0.f;
         if (grp == 0) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        for (int r0 = r_first; r0 <= Nb; r0 += kRowsPerPass * kInFlight) {
+        for (int r0 = r_first; r0 < r_end; r0 += kRowsPerPass * kInFlight) {
             if (r0 != r_first) load_rows(r0);
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int r = r0 + u * kRowsPerPass;
-                if (r > Nb) break;                           // uniform over the row's lanes (row Nb = the new key)
+                if (r >= r_end) break;                       // uniform over the row's lanes
                 float d[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) d[g] = group_sum<kLpr>(dot8_bf16(fk[u], qp[g]));
@@ -542,17 +558,18 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
                         for (int g = 0; g < G; ++g) {
                             sh_self[g] = a.scale_log2e * d[g];
+                            if (!kAll) hand[kHandSelf + g] = a.scale_log2e * d[g];
                         }
                     }
                 }
             }
         }
-        for (int r = tid; r < Nb; r += kBlock) rn_of[r] = r == tid ? rn_mine : row_norm[r];
-        if (grp == 0) {
+        for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
+        if (grp == 0 && (kAll || slice == 0)) {
             const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
-            if (piece == 0) sh_newnorm = sqrtf(ss);
+            if (piece == 0) { sh_newnorm = sqrtf(ss); if (!kAll) hand[kHandNewNorm] = sqrtf(ss); }
         }
-    } else {
+    } else {                                                 // (whole step only: the sliced one is bf16's)
         frag_t bq[kFrags];
 #pragma unroll
         for (int f = 0; f < kFrags; ++f)
@@ -603,8 +620,33 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             if (piece == 0) sh_newnorm = sqrtf(ss);
         }
     }
+    }   // kDoDots
+    if constexpr (kPart == 1) {
+        if (slice == 0 && tid == 0) hand_i[kHandStep] = step;
+        return;
     }
-    if constexpr (kAll) {
+    if constexpr (kPart == 2) {
+        // what the dots launch left: the new token's own logits and norm, the staged arrays
+        preload_table();
+        if (tid < G) sh_self[tid] = hand[kHandSelf + tid];
+        if (tid == 0) sh_newnorm = hand[kHandNewNorm];
+        if (grp == 0) {
+            new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
+            new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
+        }
+        if (in_lds) {
+            constexpr int kCopy = 8;                         // loads in flight per thread
+            for (int i0 = tid; i0 < (G + 1) * Nb; i0 += kBlock * kCopy) {
+                float t[kCopy];
+#pragma unroll
+                for (int u = 0; u < kCopy; ++u) t[u] = i0 + u * kBlock < (G + 1) * Nb ? ws_stage[i0 + u * kBlock] : 0.f;
+#pragma unroll
+                for (int u = 0; u < kCopy; ++u)
+                    if (i0 + u * kBlock < (G + 1) * Nb) dyn_lds[i0 + u * kBlock] = t[u];
+            }
+        }
+    }
+    if constexpr (kDoSoftmax) {
     __syncthreads();
 
     // ---- phase 2: softmax over the live tokens and the new token (Eq. 1) ---------------
@@ -731,13 +773,33 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const float align = tot2[0] > 0.f ? tot2[1] / tot2[0] : 0.f;
     float bv = 0.f;
     int bi = -1;
-    for (int s = tid; s < n_imp; s += kBlock) {
-        const int ct = s == tid ? ct_pre : entry_tok[s];
-        const float sc = fmaxf(tok_glo[ct] * align, tok_past[ct] + tok_cur[ct]);
-        if (better<true>(sc, s, bv, bi)) { bv = sc; bi = s; }
+    for (int s0 = tid; s0 < n_imp; s0 += kBlock * kCt) {
+        float cg[kCt], cp[kCt], cc[kCt];
+#pragma unroll
+        for (int u = 0; u < kCt; ++u) {                      // every gather requested before the first is used
+            const int s = s0 + u * kBlock;
+            const int ct = s0 == tid ? ct_pre[u] : (s < n_imp ? entry_tok[s] : 0);
+            cg[u] = tok_glo[ct]; cp[u] = tok_past[ct]; cc[u] = tok_cur[ct];
+        }
+#pragma unroll
+        for (int u = 0; u < kCt; ++u) {
+            const int s = s0 + u * kBlock;
+            const float sc = fmaxf(cg[u] * align, cp[u] + cc[u]);
+            if (s < n_imp && better<true>(sc, s, bv, bi)) { bv = sc; bi = s; }
+        }
     }
     block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // its barriers also publish phase 3
     s_star = max(bi, 0);                                     // block-uniform, in [0, n_imp)
+    }   // kDoSoftmax
+    if constexpr (kPart == 2) {
+        if (grp == 0) { hand_row[piece] = old_k[piece]; hand_row[kLpr + piece] = old_v[piece]; }
+        if (tid == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) hand[kHandOldSc + i] = old_sc[i];
+            hand_i[kHandOldPos] = old_pos;
+            hand_i[kHandStar] = s_star;
+        }
+        return;
     }
     // phase 5's first rows do not depend on the centre that is chosen
     const int s_first = r_lo + wave * kRowsPerWave + sub;
@@ -779,7 +841,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         }
     }
-    if constexpr (kPart == 4) s_star = hand_i[kHandStar];
+    if constexpr (kPart >= 4) s_star = hand_i[kHandStar];
     f = entry_tok[s_star];
 
     // ---- phase 5: its most similar other centre (Eq. 5, cosine of the stored keys) -----
@@ -862,7 +924,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         }
     }
     block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
-    if constexpr (kPart == 3) {
+    if constexpr (kPart == 3 || kPart == 5) {
         if (tid == 0) { hand[kHandPart + 2 * slice] = cv; hand_i[kHandPart + 2 * slice + 1] = ci; }
         return;
     }
@@ -955,20 +1017,20 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
     return a.head_dim == 64 ? launch_decode_init_t<bf16_t, 64>(a, st) : launch_decode_init_t<bf16_t, 128>(a, st);
 }
 
-// which: 0 = the whole step, 1 = logits, 2 = weights, 3 and 4 = those parts of the step kernel
+// kWhich: the step kernel's parts 0 to 5, 6 = logits, 7 = weights
 template <typename T, int D, int G, int kWhich>
 static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
 {
-    if constexpr (kWhich == 0)
-        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 256, 0>), dim3(1, a.bkv), dim3(256), sizeof(float) * (size_t)a.lds_floats, st, a);
-    else if constexpr (kWhich == 1)
+    if constexpr (kWhich == 6)
         hipLaunchKernelGGL((decode_logits_kernel<D, G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
-    else if constexpr (kWhich == 2)
+    else if constexpr (kWhich == 7)
         hipLaunchKernelGGL((decode_weights_kernel<G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
-    else if constexpr (kWhich == 3)
-        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 256, 3>), dim3(a.n_slices, a.bkv), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((decode_step_kernel<T, D, G, 1024, 4>), dim3(1, a.bkv), dim3(1024), 0, st, a);
+    else {
+        constexpr bool kRows = kWhich == 1 || kWhich == 3 || kWhich == 5;      // a block per slice of rows
+        constexpr int kBlock = kWhich == 2 || kWhich == 4 ? 1024 : 256;
+        const size_t lds = kWhich == 0 || kWhich == 2 ? sizeof(float) * (size_t)a.lds_floats : 0;
+        hipLaunchKernelGGL((decode_step_kernel<T, D, G, kBlock, kWhich>), dim3(kRows ? a.n_slices : 1, a.bkv), dim3(kBlock), lds, st, a);
+    }
 }
 
 template <typename T, int D, int kWhich>
@@ -984,20 +1046,25 @@ static hipError_t launch_decode_part(const DecodeStepArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-// Whether the step runs as four launches over slices, and how the centre rows and the token table are
-// cut.  f32 rows need twice the operand registers: the validation mode always takes the one-block kernel.
-bool decode_split(int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s)
+// Whether the step runs as four launches, and how the rows and (up to kTableHeads heads) the token table are cut.
+// f32 rows need twice the operand registers: the validation mode always takes the one-block kernel.
+constexpr int kTableHeads = 32;        // figures at the step kernel
+bool decode_split(int heads, int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s)
 {
     *s = DecodeSlices{0, 1, 0, 1};
     const int table = n_imp + n_tbm + window;
     if (f32 || (budget <= 512 && table <= 2048)) return false;
-    auto cut = [](int n, int least, int* per, int* count) {
-        *per = least;
+    auto cut = [](int n, int* per, int* count) {             // slices of 128, longer ones where that makes too many
+        *per = 128;
         while ((n + *per - 1) / *per > kDecodeMaxSlices) *per *= 2;
         *count = (n + *per - 1) / *per;
     };
-    cut(n_imp, 128, &s->rows, &s->n_rows);
-    cut(table, kTokTile, &s->toks, &s->n_toks);
+    if (heads <= kTableHeads) {
+        cut(n_imp, &s->rows, &s->n_rows);
+        cut(table, &s->toks, &s->n_toks);
+    } else {
+        cut(budget + 1, &s->rows, &s->n_rows);               // the new key's row included
+    }
     return true;
 }
 
@@ -1006,9 +1073,10 @@ static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
 {
     if (a.slice_rows > 0) {
         if constexpr (sizeof(T) == 2) {
-            hipError_t e = launch_decode_part<T, D, 1>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 2>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 3>(a, st);
+            const bool table = a.tok_slice > 0;
+            hipError_t e = table ? launch_decode_part<T, D, 6>(a, st) : launch_decode_part<T, D, 1>(a, st);
+            if (e == hipSuccess) e = table ? launch_decode_part<T, D, 7>(a, st) : launch_decode_part<T, D, 2>(a, st);
+            if (e == hipSuccess) e = table ? launch_decode_part<T, D, 3>(a, st) : launch_decode_part<T, D, 5>(a, st);
             if (e == hipSuccess) e = launch_decode_part<T, D, 4>(a, st);
             return e;                                            // the last part advances the counter
         } else {

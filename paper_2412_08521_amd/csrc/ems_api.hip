@@ -467,13 +467,13 @@ static bool decode_params_ok(const ems_params* p, int* why)
     return g == 1 || g == 2 || g == 4 || g == 8;
 }
 
-// Decode-step workspace: the staged row dots and row norms of the one-launch step, or (large caches)
-// the sliced step's logits and its hand-over records.
-static size_t decode_stage_bytes(const ems_params* p, bool split, int n_imp, int n_tbm)
+// Decode-step workspace: the staged row dots and row norms, or the logits where the token table is cut, and (large
+// caches) the hand-over records of the sliced step.
+static size_t decode_stage_bytes(const ems_params* p, bool table, int n_imp, int n_tbm)
 {
     const size_t bkv = (size_t)p->batch * p->kv_heads;
     const size_t g = (size_t)(p->q_heads / p->kv_heads);
-    return align_up(sizeof(float) * bkv * (split ? g * (size_t)(n_imp + n_tbm + p->window) : (g + 1) * (size_t)p->budget));
+    return align_up(sizeof(float) * bkv * (table ? g * (size_t)(n_imp + n_tbm + p->window) : (g + 1) * (size_t)p->budget));
 }
 
 static size_t decode_ws_bytes(const ems_params* p)
@@ -481,9 +481,9 @@ static size_t decode_ws_bytes(const ems_params* p)
     int n_imp, n_tbm;
     ems::DecodeSlices s;
     partition_sizes(p, &n_imp, &n_tbm);
-    const bool split = ems::decode_split(p->budget, n_imp, n_tbm, p->window, p->dtype == EMS_F32, &s);
     const size_t bkv = (size_t)p->batch * p->kv_heads;
-    return decode_stage_bytes(p, split, n_imp, n_tbm) + (split ? align_up(sizeof(float) * bkv * ems::kDecodeHandFloats) : 0);
+    const bool split = ems::decode_split((int)bkv, p->budget, n_imp, n_tbm, p->window, p->dtype == EMS_F32, &s);
+    return decode_stage_bytes(p, s.toks > 0, n_imp, n_tbm) + (split ? align_up(sizeof(float) * bkv * ems::kDecodeHandFloats) : 0);
 }
 
 static bool state_ok(const ems_decode_state* s)
@@ -551,8 +551,8 @@ int ems_decode_step(const ems_params* p, const ems_decode_state* state, int32_t 
     a.attn_opt = attn_opt; a.decision_opt = decision_opt; a.sim_opt = sim_opt;
     a.ws = static_cast<float*>(ws);
     ems::DecodeSlices sl;
-    if (ems::decode_split(p->budget, n_imp, n_tbm, p->window, p->dtype == EMS_F32, &sl))
-        a.hand = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_stage_bytes(p, true, n_imp, n_tbm));
+    if (ems::decode_split(p->batch * p->kv_heads, p->budget, n_imp, n_tbm, p->window, p->dtype == EMS_F32, &sl))
+        a.hand = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_stage_bytes(p, sl.toks > 0, n_imp, n_tbm));
     a.slice_rows = sl.rows; a.n_slices = sl.n_rows; a.tok_slice = sl.toks; a.n_tok_slices = sl.n_toks;
     // per-row dot products and row norms are staged in LDS when they fit in
     // what a block may ask for without raising the limit, else in the workspace

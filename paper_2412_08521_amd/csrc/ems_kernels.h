@@ -134,10 +134,10 @@ struct DecodeStepArgs {
     float* attn_opt;        // [bkv * group, T + 1] or null
     int32_t* decision_opt;  // [bkv, 2] or null
     float* sim_opt;         // [bkv] or null
-    float* ws;              // [bkv, (group + 1) * budget] staging when it does not fit in LDS; sliced step: logits [bkv, group, T]
+    float* ws;              // [bkv, (group + 1) * budget] staging when it does not fit in LDS or between launches; or logits [bkv, group, T]
     float* hand;            // [bkv, kDecodeHandFloats] hand-over record of the sliced step, else null
-    int slice_rows, n_slices;   // slices of the centre rows in the sliced step (decode_split); 0, 1 = one launch
-    int tok_slice, n_tok_slices;    // slices of the token table
+    int slice_rows, n_slices;   // slices of the rows in the sliced step (decode_split); 0, 1 = one launch
+    int tok_slice, n_tok_slices;    // slices of the token table; 0 = it is not cut
     int lds_floats;         // (group + 1) * budget when staged in LDS, else 0
     int bkv, group, head_dim, seq_len, window, budget, n_imp, n_tbm;
     int step;               // >= 0, or -1: read st.step_count
@@ -171,8 +171,8 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
 hipError_t launch_decode_step(const DecodeStepArgs& a, bool f32, hipStream_t st);
 constexpr int kDecodeMaxSlices = 32;     // slices per head of the sliced decode step
 constexpr int kDecodeHandFloats = 1024;  // floats of its per-head hand-over record
-struct DecodeSlices { int rows, n_rows, toks, n_toks; };   // centre rows and table elements per slice, slices
-bool decode_split(int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s);
+struct DecodeSlices { int rows, n_rows, toks, n_toks; };   // rows and table elements per slice, slices; toks = 0: the table is not cut
+bool decode_split(int heads, int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s);
 hipError_t launch_expand(const ExpandArgs& a, bool f32, hipStream_t st);
 hipError_t launch_score_pass1(ScoreArgs& a, bool f32, hipStream_t st);   // rows' log-sum-exp; sets a.queue_clear
 hipError_t launch_score_pass2(const ScoreArgs& a, bool f32, hipStream_t st);   // column sums

@@ -217,3 +217,32 @@ def test_decode_steps_of_long_tables_match_oracle(shape, tau):
         n_flip += c[0]; n_merge += c[1]; n_evict += c[2]
     assert n_flip <= 1                                    # (at 128 elements the best of 4192 random cosines is itself about 0.3)
     assert n_merge > 0 if tau < 1 else n_merge == 0 and n_evict > 0
+
+
+# more heads than the table's slices are for: the step goes over slices of the cache rows instead
+@pytest.mark.parametrize("tau", [0.3, 2.0])
+@pytest.mark.parametrize("shape", [
+    (5, 8, 8, 64, 2000, 8, 560, 0.5),        # 40 heads; rows and new key in five slices, the last of 49 rows
+    (3, 32, 16, 128, 2500, 8, 639, 1.0),     # two q-heads per kv-head; rows and new key fill five slices
+    (5, 64, 8, 64, 4000, 8, 1800, 0.5),      # eight; the staged dots do not fit in LDS
+])
+def test_decode_steps_of_many_heads_match_oracle(shape, tau):
+    _log("decode_step", shape, "tau", tau)
+    p, merged, tbm, s_glo, s_loc, st = _prefill(shape, B.EMS_BF16, tau, seed=shape[6])
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    G, heads = p.q_heads // p.kv_heads, p.batch * p.kv_heads
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    assert B.ems_decode_workspace_bytes(p) == up(4 * heads * (G + 1) * p.budget) + up(4 * heads * 1024)    # dots and norms staged, records
+    rng = np.random.default_rng(23)
+    n_flip = 0
+    units = [(0, 0), (1, p.kv_heads // 2), (p.batch - 1, p.kv_heads - 1)]
+    for t in range(p.window + 2):
+        qb, kb, vb = _new_token(p, rng, B.EMS_BF16)
+        if t % 3 == 1:                                    # make some new keys similar to an entry
+            kb = ems_inputs.f32_to_bf16_bits(_np(st.k_cache[:, :, n_imp - 1 - t]).astype(np.float32))
+        n_flip += run_and_check_step(p, st, t, qb, kb, vb, tau, units, B.EMS_BF16)[0]
+    assert n_flip <= 1
+    ws = torch.empty(B.ems_decode_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    q, k, v = (dev_tensor(x, B.EMS_BF16) for x in _new_token(p, rng, B.EMS_BF16))
+    B.ems_decode_step(p, st, B.EMS_STEP_FROM_STATE, q, k, v, ws=ws)
+    assert int(st.step_count) == p.window + 3

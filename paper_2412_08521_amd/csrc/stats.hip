@@ -27,6 +27,7 @@ constexpr double kMassOne = 1099511627776.0;   // 2^40: fixed-point image of the
 // scores are >= 0: their bit patterns already order like the values
 __device__ __forceinline__ uint32_t score_key(float s) { return __float_as_uint(fmaxf(s, 0.f)); }
 
+constexpr int kSameLanes = 24;                 // lanes on one digit from which one atomic for them all is the cheaper way
 constexpr int kStatLds = 32768;                // scores of a head held in LDS (128 KB)
 
 // Sum over the wave, the same in every lane.
@@ -83,7 +84,8 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
     const float align = tot_g > 0.f ? (tot_l / (float)N) / (tot_g / (float)N) : 0.f;
 
     // Total of the Eq. 2 scores (float tree), then every score as a share of it in fixed point.  The scores
-    // stay in LDS where they fit: the six walks that follow otherwise go back to memory for them.
+    // stay in LDS where they fit (a thread reads its own elements): the five walks that follow otherwise go back to
+    // memory for them.
     const bool in_lds = N <= kStatLds;
     float st = 0.f;
     for (int j0 = tid; j0 < N; j0 += kStatBlock * kAhead) {
@@ -99,7 +101,6 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
             if (in_lds && j0 + u * kStatBlock < N) kept[j0 + u * kStatBlock] = x[u];
         }
     }
-    auto score = [&](int j) { return in_lds ? kept[j] : fmaxf(glo[j] * align, loc[j]); };   // (a thread reads its own elements)
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) st += __shfl_xor(st, o);
     __syncthreads();
@@ -110,7 +111,21 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
     const double to_fixed = tot_s > 0.f ? kMassOne / (double)tot_s : 0.0;
 
     unsigned long long part = 0ull;
-    for (int j = tid; j < N; j += kStatBlock) part += (unsigned long long)((double)score(j) * to_fixed);
+    if (in_lds) {
+        for (int j = tid; j < N; j += kStatBlock) part += (unsigned long long)((double)kept[j] * to_fixed);
+    } else {
+        for (int j0 = tid; j0 < N; j0 += kStatBlock * kAhead) {
+            float g[kAhead], l[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int j = j0 + u * kStatBlock;
+                g[u] = j < N ? glo[j] : 0.f;
+                l[u] = j < N ? loc[j] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) part += (unsigned long long)((double)fmaxf(g[u] * align, l[u]) * to_fixed);
+        }
+    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
     if (lane == 0) atomicAdd(&sh_total, part);
@@ -123,27 +138,43 @@ __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
         for (int d = tid; d < 256; d += kStatBlock) { cnt[d] = 0; mass[d] = 0ull; }
         __syncthreads();
         const uint32_t prefix = sh_prefix;
-        for (int j0 = 0; j0 < N; j0 += kStatBlock) {
-            const int j = j0 + tid;
-            const float s = j < N ? score(j) : 0.f;
+        auto count = [&](float s, bool in) __attribute__((always_inline)) {          // by whole waves
             const uint32_t key = score_key(s);
-            bool on = j < N && (shift == 24 || (key >> ((shift + 8) & 31)) == prefix);
+            bool on = in && (shift == 24 || (key >> ((shift + 8) & 31)) == prefix);
             const int digit = (key >> shift) & 255;
             const unsigned long long q = on ? (unsigned long long)((double)s * to_fixed) : 0ull;
             if (shift == 24) {
-                // leading digits are shared: the lanes that agree with the first one go into one pair of
+                // leading digits are shared: where many lanes agree with the first one, they go into one pair of
                 // atomics (the masses' sum in two halves of at most 20 + 6 bits)
                 const unsigned long long active = __ballot(on);
-                if (active == 0ull) continue;                // wave-uniform
+                if (active == 0ull) return;                  // wave-uniform
                 const int leader = __ffsll((long long)active) - 1;
                 const int d0 = __builtin_amdgcn_readlane(digit, leader);
                 const bool same = on && digit == d0;
                 const int n = __popcll(__ballot(same));
-                const int lo = wave_add(same ? (int)(q & 0xfffffull) : 0), hi = wave_add(same ? (int)(q >> 20) : 0);
-                if (lane == leader) { atomicAdd(&cnt[d0], n); atomicAdd(&mass[d0], (unsigned long long)lo + ((unsigned long long)hi << 20)); }
-                on = on && !same;
+                if (n >= kSameLanes) {                       // wave-uniform
+                    const int lo = wave_add(same ? (int)(q & 0xfffffull) : 0), hi = wave_add(same ? (int)(q >> 20) : 0);
+                    if (lane == leader) { atomicAdd(&cnt[d0], n); atomicAdd(&mass[d0], (unsigned long long)lo + ((unsigned long long)hi << 20)); }
+                    on = on && !same;
+                }
             }
             if (on) { atomicAdd(&cnt[digit], 1); atomicAdd(&mass[digit], q); }
+        };
+        if (in_lds) {
+            for (int j0 = 0; j0 < N; j0 += kStatBlock) count(j0 + tid < N ? kept[j0 + tid] : 0.f, j0 + tid < N);
+        } else {                                             // from memory: several loads in flight
+            constexpr int kFew = 8;
+            for (int j0 = tid; j0 - tid < N; j0 += kStatBlock * kFew) {
+                float g[kFew], l[kFew];
+#pragma unroll
+                for (int u = 0; u < kFew; ++u) {
+                    const int j = j0 + u * kStatBlock;
+                    g[u] = j < N ? glo[j] : 0.f;
+                    l[u] = j < N ? loc[j] : 0.f;
+                }
+#pragma unroll
+                for (int u = 0; u < kFew; ++u) count(fmaxf(g[u] * align, l[u]), j0 + u * kStatBlock < N);
+            }
         }
         __syncthreads();
         // the digit, from the largest, in which the mass crosses: thread t holds digit 255 - t and the sums

@@ -10,8 +10,9 @@
 //                    all EARLIER tokens: both cosines as MFMA contractions of raw rows scaled by
 //                    reciprocal norms, running maximum per lane, one wave per work item.
 // redundancy_kernel  the same for float32 (whose rows fill the registers of a wave, and whose
-//                    matrix rate hides the staging), in the layout of the merge destination kernel
-//                    with "centres" = the causal prefix.
+//                    matrix rate hides the staging), and for the shortest and the longest 16-bit
+//                    sequences, in the layout of the merge destination kernel with "centres" = the
+//                    causal prefix.
 // redundancy_count_kernel  tokens whose best redundancy reaches tau, per head.
 #include "ems_common.h"
 #include "ems_kernels.h"
@@ -726,10 +727,20 @@ static hipError_t launch_redundancy_t(const StatsArgs& a, hipStream_t st)
 
 constexpr int kRedStreamMax = 1 << 21;      // a head's line of stages is counted in 32 bits: longer sequences take the other form
 
+// Up to this length the other form takes the 16-bit rows as well: a wave of the stream begins with 8 us of loads and
+// norms, and one more launch clears `best`.  (us, stream / blocks.  128: 1 head of 350 24.7 / 22.4, of 450 24.7 /
+// 27.9; 128 heads of 450 40.8 / 34.0, of 513 42.4 / 51.1; 1100 of 256 103 / 89, of 385 183 / 225.  64: 1 head of 450 21.4 / 20.0, of
+// 600 21.6 / 24.3; 128 heads of 700 39.6 / 33.6, of 900 49.0 / 59.1; 1100 of 700 227 / 190, of 900 330 / 402.)
+static int red_block_max(int head_dim, int heads)
+{
+    if (head_dim == 64) return heads <= 16 ? 512 : 768;
+    return heads <= 16 ? 384 : heads <= 128 ? 448 : 256;
+}
+
 template <int D>
 static hipError_t launch_redundancy_stream(StatsArgs a, hipStream_t st)
 {
-    if (a.seq_len > kRedStreamMax) return launch_redundancy_t<bf16_t, D>(a, st);
+    if (a.seq_len > kRedStreamMax || a.seq_len <= red_block_max(D, a.bkv)) return launch_redundancy_t<bf16_t, D>(a, st);
     const DealPass1<RedStream<D>::kSub> deal(a.seq_len);
     deal_over_waves(1024, a.bkv, deal.total(), kTrip, kTrip, &a.red_len, &a.red_waves);
     const long long grid = deal_grid(a.bkv, a.red_waves), clear = ((long long)a.bkv * a.seq_len + 255) / 256;

@@ -154,3 +154,33 @@ def test_redundancy_of_the_longest_sequences():
             top = max(top, float((kc * vc / (kn[c:e] * vn[c:e] * kn[t] * vn[t])).max()))
         assert abs(float(best[0, 0, t]) - top) <= 2e-5, (t, float(best[0, 0, t]), top)
         assert top > 0.6 or t not in pick[4::2]
+
+
+@pytest.mark.parametrize("d,bh,limit", [(64, 1, 512), (64, 20, 768), (128, 2, 384), (128, 20, 448), (128, 140, 256)])
+def test_redundancy_either_side_of_the_short_form(d, bh, limit):
+    """Sequences up to `limit` take the block form, longer ones the stream: the lengths on either side, first and last
+    head.  Tolerance as above."""
+    for n in (limit, limit + 1):
+        _log("redundancy short form", d, bh, n)
+        inp = ems_inputs.small(1, bh, bh, d, n, seed=n + d)
+        kf, vf = inp.f32("k").copy(), inp.f32("v").copy()
+        for t in range(5, n, 7):
+            kf[:, :, t] = kf[:, :, t // 2]
+            vf[:, :, t] = vf[:, :, t // 2] + 0.5 * vf[:, :, t]
+        kb, vb = ems_inputs.f32_to_bf16_bits(kf), ems_inputs.f32_to_bf16_bits(vf)
+        rate, best = B.ems_redundancy_rate(B.EmsParams(1, bh, bh, d, n, 1, tau=0.6), dev_tensor(kb, B.EMS_BF16), dev_tensor(vb, B.EMS_BF16))
+        best = best.cpu().numpy()
+        np.testing.assert_array_equal(np.rint(rate.cpu().numpy() * n), (best >= np.float32(0.6)).sum(-1))
+        pick = sorted({0, bh - 1})
+        o = RefParams(1, len(pick), len(pick), d, n, 1, tau=0.6)
+        _, o_best = ems_ref.redundancy(o, ems_inputs.bf16_bits_to_f32(kb)[:, pick], ems_inputs.bf16_bits_to_f32(vb)[:, pick])
+        np.testing.assert_allclose(best[:, pick, 1:], o_best[..., 1:], rtol=0, atol=2e-5)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("bh_n", [(1, 895), (2, 896), (5, 897), (1100, 800)])
+@pytest.mark.parametrize("scale", ["plain", "extreme"])
+def test_redundancy_edges_of_the_stream(bh_n, d, scale):
+    """The edges above at lengths that the stream takes: token tiles of 128 with one row more or less, more heads than
+    resident waves, and the rows whose norms send a part back to the plain form."""
+    test_redundancy_edges(bh_n, d, scale)

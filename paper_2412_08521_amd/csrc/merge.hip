@@ -446,8 +446,9 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
     const unsigned long long below = (1ull << lane) - 1ull;
     // Sifts a piece of the list from p0, up to `end`, a stretch (of at most kMergeStretch entries) per wave:
     // the tokens whose destination is in [lo, hi), in order, one list for the block or
-    // (own) one per wave in its eighth of the arrays.  Returns the list's length.
-    auto sift = [&](int p0, int end, int lo, int hi, bool own) {
+    // (own) one per wave in its eighth of the arrays.  `meanwhile` runs while the entries are on their way.
+    // Returns the list's length.
+    auto sift = [&](int p0, int end, int lo, int hi, bool own, auto meanwhile) {
         const int stretch = min(kMergeStretch, ((end - p0 + kMergeWaves - 1) / kMergeWaves + kWave - 1) / kWave * kWave);
         const int i0 = p0 + wave * stretch, i1 = min(i0 + stretch, end);
         constexpr int kAhead = 8;                            // entries in flight per lane
@@ -459,6 +460,7 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
             d[u] = i < i1 ? dest[i] : -1;
             q[u] = i < i1 ? tbm[i] : 0;
         }
+        meanwhile();
         int at0 = wave * kMergeStretch, total = 0;
         if (!own) {                                          // block-uniform
 #pragma unroll
@@ -481,13 +483,14 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
         return own ? n : total;
     };
 
+    auto nothing = [] {};
     if (zero_class) {
         const int per_block = (n_tbm + a.zero_blocks - 1) / a.zero_blocks;
         const int z0 = min(blk * per_block, n_tbm), z1 = min(z0 + per_block, n_tbm);
         Acc acc; acc.clear();
         int joined = 0;
         for (int p0 = z0; p0 < z1; p0 += kMergeWaves * kMergeStretch) {
-            const int n = sift(p0, z1, Nb, Nb + 1, true);
+            const int n = sift(p0, z1, Nb, Nb + 1, true, nothing);
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest + wave * kMergeStretch, lpos + wave * kMergeStretch, n, Nb, wlist);
@@ -571,71 +574,83 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
             a.k_norm[(size_t)bkv * (n_imp + n_tbm) + job] = c_norm;
         }
     };
-    // a slot by the whole wave: every lane group takes a share of its members
-    auto slot_by_wave = [&](int job, int len) {
-        Acc acc; acc.clear();
-        const int c_pos = clamp_pos(imp[job], N);            // the centre itself is the first member
-        float c_norm = 0.f;
-        frag_t raw_k = zero_frag(), raw_v = zero_frag();
+    // a slot by the whole wave: the first lane group begins with the centre, every group takes a share of the members
+    struct Centre { int pos; frag_t k, v; float w; };
+    auto centre_at = [&](int at) {
+        Centre c{clamp_pos(at, N), zero_frag(), zero_frag(), 0.f};
         if (grp == 0) {
-            raw_k = Acc::load_piece(K, c_pos, piece);
-            raw_v = Acc::load_piece(V, c_pos, piece);
-            if constexpr (kWeighted) c_norm = acc.accumulate_weighted(raw_k, raw_v, fmaxf(Wt[c_pos], 0.f));
-            else c_norm = acc.accumulate(raw_k, raw_v);
+            c.k = Acc::load_piece(K, c.pos, piece);
+            c.v = Acc::load_piece(V, c.pos, piece);
+            if constexpr (kWeighted) c.w = fmaxf(Wt[c.pos], 0.f);
+        }
+        return c;
+    };
+    auto slot_by_wave = [&](int job, int len, const Centre& c) {
+        Acc acc; acc.clear();
+        float c_norm = 0.f;
+        if (grp == 0) {
+            if constexpr (kWeighted) c_norm = acc.accumulate_weighted(c.k, c.v, c.w);
+            else c_norm = acc.accumulate(c.k, c.v);
         }
         int joined = 0;
         if (len >= 0) {
             joined = gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, len, job, wlist);
         } else {                                             // a list of several pieces: sifted by the block as it goes
             for (int p0 = 0; p0 < n_tbm; p0 += kPiece) {
-                const int n = sift(p0, n_tbm, block0, block1, false);
+                const int n = sift(p0, n_tbm, block0, block1, false, nothing);
                 if (job < n_imp) joined += gather_members<T, D, kWeighted>(acc, K, V, Wt, ldest, lpos, n, job, wlist);
             }
         }
         acc.template reduce_groups<kWeighted>();
-        if (grp == 0 && job < n_imp) write_centre(job, acc, raw_k, raw_v, c_pos, c_norm, 1 + joined);
+        if (grp == 0 && job < n_imp) write_centre(job, acc, c.k, c.v, c.pos, c_norm, 1 + joined);
     };
 
     if (n_tbm > kPiece) {                                    // one row per wave; every wave sifts along
         if (block0 < n_imp) {                                // block-uniform
             const int job = job0;
-            if (job < n_imp) slot_by_wave(job, -1);
-            else for (int p0 = 0; p0 < n_tbm; p0 += kPiece) sift(p0, n_tbm, block0, block1, false);
+            if (job < n_imp) slot_by_wave(job, -1, centre_at(imp[job]));
+            else for (int p0 = 0; p0 < n_tbm; p0 += kPiece) sift(p0, n_tbm, block0, block1, false, nothing);
         }
         if (job0 >= n_imp && job0 < n_imp + W && grp == 0) local_row(job0);
         return;
     }
-    const int len = block0 < n_imp && n_tbm > 0 ? sift(0, n_tbm, block0, block1, false) : 0;
+    if (rpw == 1) {                                          // the wave's centre is fetched beside the list
+        const int job = job0, at = job < n_imp ? imp[job] : 0;
+        Centre c;
+        int len = 0;
+        if (block0 < n_imp && n_tbm > 0) len = sift(0, n_tbm, block0, block1, false, [&] { c = centre_at(at); });
+        else c = centre_at(at);
+        if (job < n_imp) slot_by_wave(job, len, c);
+        else if (job < n_imp + W && grp == 0) local_row(job);
+        return;
+    }
+    const int len = block0 < n_imp && n_tbm > 0 ? sift(0, n_tbm, block0, block1, false, nothing) : 0;
     for (int r0 = 0; r0 < rpw; r0 += kGroups) {
-        // a row per lane group while slots have few members; else (and where a wave has one row) slot after slot
+        // a row per lane group while slots have few members, else slot after slot
         const int n_rows = min(kGroups, rpw - r0);
         int mine = 0;                                        // members of this lane group's row
-        bool wide = rpw == 1;
-        if (!wide) {
-            int count[kGroups];
+        int count[kGroups];
 #pragma unroll
-            for (int g = 0; g < kGroups; ++g) count[g] = 0;
-            for (int c0 = 0; c0 < len; c0 += kWave) {
-                const int d = c0 + lane < len ? ldest[c0 + lane] : -1;
+        for (int g = 0; g < kGroups; ++g) count[g] = 0;
+        for (int c0 = 0; c0 < len; c0 += kWave) {
+            const int d = c0 + lane < len ? ldest[c0 + lane] : -1;
 #pragma unroll
-                for (int g = 0; g < kGroups; ++g) {
-                    const bool match = d == job0 + r0 + g;
-                    const unsigned long long mask = __ballot(match);
-                    const int at = count[g] + __popcll(mask & below);
-                    if (match && at < kMergeFew) wlist[g * kMergeFew + at] = lpos[c0 + lane];
-                    count[g] += __popcll(mask);
-                }
+            for (int g = 0; g < kGroups; ++g) {
+                const bool match = d == job0 + r0 + g;
+                const unsigned long long mask = __ballot(match);
+                const int at = count[g] + __popcll(mask & below);
+                if (match && at < kMergeFew) wlist[g * kMergeFew + at] = lpos[c0 + lane];
+                count[g] += __popcll(mask);
             }
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) mine = g == grp ? count[g] : mine;
-            wide = __any(grp < n_rows && mine > kMergeFew);
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
-        if (wide) {                                          // wave-uniform
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) mine = g == grp ? count[g] : mine;
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (__any(grp < n_rows && mine > kMergeFew)) {       // wave-uniform
             for (int r = r0; r < r0 + n_rows; ++r) {
                 const int job = job0 + r;
-                if (job < n_imp) slot_by_wave(job, len);
+                if (job < n_imp) slot_by_wave(job, len, centre_at(imp[job]));
                 else if (job < n_imp + W && grp == 0) local_row(job);
             }
             continue;

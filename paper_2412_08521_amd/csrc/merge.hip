@@ -394,6 +394,13 @@ __device__ __forceinline__ int gather_members(RowAcc<T, D>& acc, const T* K, con
     return count;
 }
 
+// Words that blocks of one launch hand to each other: read and written where every XCD sees them (device scope),
+// so that a wait for the stores is all that has to come before the arrival is counted.  A fence would write the whole
+// L2 back, with the output rows of every other block: 8 us of a launch whose rows take 10.
+__device__ __forceinline__ void store_shared(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ float load_shared(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // Blocks of a head: first those of the zero class (a.zero_blocks; each takes a stretch of the TBM list,
 // a wave an eighth of it), then the output rows, a.rows_per_wave per wave: class-centre slots, then the
 // local window.
@@ -516,20 +523,19 @@ __global__ __launch_bounds__(kMergeBlock) void merge_kernel(MergeArgs a)
             // a record per block: sums of keys and values, members, total weight
             constexpr int kRec = 2 * D + 2;
             float* rec = a.zero_part + ((size_t)bkv * a.zero_stride) + (size_t)blk * kRec;
-            if (src < 2) rec[tid] = sum;
-            if (tid == 0) { rec[2 * D] = __int_as_float(total); rec[2 * D + 1] = wtot; }
-            __threadfence();
+            if (src < 2) store_shared(rec + tid, sum);
+            if (tid == 0) { store_shared(rec + 2 * D, __int_as_float(total)); store_shared(rec + 2 * D + 1, wtot); }
+            wait_stores();                                   // every thread's share of the record is out before the block counts as arrived
             __syncthreads();
             if (tid == 0) zcnt[0] = atomicAdd(&cnt[n_imp], 1);
             __syncthreads();
             if (zcnt[0] != a.zero_blocks - 1) return;        // block-uniform: not the last one
-            __threadfence();
             const float* all = a.zero_part + (size_t)bkv * a.zero_stride;
             total = 0; wtot = 0.f; sum = 0.f;
             for (int z = 0; z < a.zero_blocks; ++z) {
-                total += __float_as_int(all[(size_t)z * kRec + 2 * D]);
-                wtot += all[(size_t)z * kRec + 2 * D + 1];
-                if (src < 2) sum += all[(size_t)z * kRec + tid];
+                total += __float_as_int(load_shared(all + (size_t)z * kRec + 2 * D));
+                wtot += load_shared(all + (size_t)z * kRec + 2 * D + 1);
+                if (src < 2) sum += load_shared(all + (size_t)z * kRec + tid);
             }
         }
         const float denom = kWeighted ? wtot : (float)total;     // members, or their total weight

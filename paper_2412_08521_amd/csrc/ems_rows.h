@@ -34,14 +34,19 @@ template <> __device__ __forceinline__ float frag_sumsq<float>(const frag_t& f)
 
 __device__ __forceinline__ float inv_norm(float sumsq) { return sumsq > 0.f ? 1.0f / sqrtf(sumsq) : 0.f; }
 
-// The same for a row of T: for bf16 rows by the hardware's reciprocal square root (1 ulp), which is not made for the
-// smallest values.  Similarities against 64 bits, 4200 rows of 128: 6.2e-8 rms with it, 6.4e-8 with two rounded
-// steps.  Float32 rows, the mode that checks the other, keep the rounded steps.
+// The same for a row of T by the hardware's reciprocal square root (1 ulp), which is not made for the smallest
+// values.  Similarities against 64 bits, 4200 rows of 128: 6.2e-8 rms with it, 6.4e-8 with two rounded steps.
+// Float32 rows, the mode that checks the other, add a Newton step with the product's rounding carried along
+// (half an ulp and a little; the two rounded steps made the search 5-10 % slower).
 template <typename T>
 __device__ __forceinline__ float row_inv_norm(float sumsq)
 {
-    if (sizeof(T) == 2 && sumsq >= 0x1p-100f) return __builtin_amdgcn_rsqf(sumsq);
-    return inv_norm(sumsq);
+    if (!(sumsq >= 0x1p-100f && sumsq <= 0x1p100f)) return inv_norm(sumsq);
+    const float y = __builtin_amdgcn_rsqf(sumsq);
+    if constexpr (sizeof(T) == 2) return y;
+    const float h = sumsq * y, low = __builtin_fmaf(sumsq, y, -h);
+    const float e = __builtin_fmaf(-low, y, __builtin_fmaf(-h, y, 1.f));      // 1 - sumsq y^2
+    return __builtin_fmaf(0.5f * y, e, y);
 }
 
 template <typename T> struct Pack;

@@ -4,13 +4,15 @@
 //                 the class-centre keys as an MFMA contraction of the raw keys, scaled by
 //                 the reciprocal norms afterwards, with the row arg-max fused into the
 //                 accumulator read-out; similarity not above tau -> zero class.  With many
-//                 centres the centre list is cut into slices, one block per (128 tokens,
-//                 slice), and dest_combine_kernel takes the best slice per token.
-// merge_kernel    one wave per output row: a centre slot gathers the TBM tokens sent to it
-//                 in ascending order and averages (unit keys scaled by the centre's norm,
-//                 raw values); one block per head does the same for the zero class; the
+//                 centres the centre list is cut into slices, one block per (128 or 256
+//                 tokens, slice), and dest_combine_kernel takes the best slice per token.
+// merge_kernel    one to eight output rows per wave: a centre slot gathers the TBM tokens
+//                 sent to it and averages (unit keys scaled by the centre's norm, raw
+//                 values); one block per head, or several that leave their sums for the
+//                 last of them to add in block order, do the same for the zero class; the
 //                 local-window rows are copied.  Every output element has exactly one
-//                 writer, so there are no atomics and results are reproducible bit for bit.
+//                 writer and every sum a fixed order; the one atomic counts the arrivals
+//                 of the zero class's blocks, so results are reproducible bit for bit.
 #include "ems_common.h"
 #include "ems_kernels.h"
 #include "ems_rows.h"
@@ -57,8 +59,8 @@ __device__ __forceinline__ int clamp_pos(int p, int n) { return min(max(p, 0), n
 // 32 * kTok TBM rows in registers as the MFMA B operand (tokens -> lanes) and the centre rows stream
 // through LDS as the A operand (centres -> accumulator registers), so the running arg-max is a
 // per-lane pair.  A centre row is gathered once per token tile: with many tokens larger tiles pay
-// (4032 centres, 4096 tokens, 8 heads: 88 us with one tile of 32 per wave, 77 with two; four leave one
-// wave per SIMD: 108).
+// (4032 centres, 4096 tokens, 8 heads, the kernel under a trace: 88 us with one tile of 32 per wave, 77 with two
+// when that was chosen, now 72; four leave one wave per SIMD: 108).
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kSim, int kTok>
 __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
@@ -407,10 +409,10 @@ __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)
 //
 // A centre block first sifts the TBM list: each wave reads an eighth of a piece of it and keeps, in
 // order, the tokens that go to one of the block's slots; a slot then looks through the few that were
-// kept.  (Walking the whole list for every slot made the kernel 107 us at 4032 slots, 4096 tokens, 8
-// heads; a single zero-class block and slots done one after the other took most of what was left.  Now
-// 48 us: about one row per 16 lanes in flight, its members' rows requested together.)  Several rows per
-// wave where that leaves enough blocks, since every block reads the list once.
+// kept.  (4032 slots, 4096 tokens, 8 heads, the kernel under a trace: 107 us when every slot walked the whole
+// list; 48 with the sift, a shared zero class and one row per 16 lanes in flight, its members' rows requested
+// together; 32 now that the zero class's blocks need no fence.)  Several rows per wave where that leaves enough
+// blocks, since every block reads the list once.
 //
 // Several zero-class blocks leave their sums in a.zero_part (the slices' winners, dead by now) and
 // count their arrivals on the class's own count, which the last one to arrive overwrites with the

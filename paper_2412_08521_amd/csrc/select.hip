@@ -274,10 +274,12 @@ __global__ __launch_bounds__(kChunkBlock) void select_gather_kernel(SelectArgs a
 // Steps 3 and 4 of the header comment on keys in LDS: a block of kSelBlock threads, wave w taking the
 // ordinals [w * 64 * items, (w + 1) * 64 * items) of `count` candidates in position order (items <= 32),
 // lane l the ordinals base + i * 64.  position(ordinal) is the sequence position of a candidate.
-// kItems: `items` where it is fixed (the loops are then unrolled: 17.3 us against 20.5 rolled, 4096 tokens), else
-// 0 (rolled: 12.4 us against 15.3 for the candidates of a 16384-token prompt).
+// kItems: `items` where it is fixed (the loops are then unrolled: 16.7 us against 17.2 rolled, 32 heads of 4096
+// tokens, calls in a row), else 0 (the candidates of a 16384-token prompt, the kernel under a trace when that was
+// chosen: 12.4 us rolled, 15.3 unrolled for the most there can be).
 // Every digit has kCopies counters and a lane counts on number lane % kCopies: equal keys would otherwise
-// queue for one LDS address (32 heads of 4096 equal scores: 25.7 us with one counter; 4 is what LDS has room for).
+// queue for one LDS address (calls in a row, 4 counters / 1: 32 heads of 4096 equal scores 18.3 / 27.8 us, of 4096
+// different ones 16.7 / 17.8, 8 heads of 16384 equal ones 52.8 / 92.0; 4 is what LDS has room for).
 constexpr int kCopies = 4;
 template <int kItems, typename Position>
 __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items, int count, const SelectArgs& a, Position position)
@@ -455,7 +457,7 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
     };
 
     // A list that fits (all but extreme ties) goes to LDS once, in position order: the digit passes and the
-    // three walks below would each go back to memory for it (8 heads, 8200 candidates each: 45 us, now 27).
+    // three walks below would each go back to memory for it (8 heads, 8200 candidates each, under a trace: 45 us, now 24).
     int top_step = 1;
     while (top_step * 2 < n_chunks) top_step *= 2;
     if (M <= kFinishKeys) {                                // block-uniform

@@ -41,8 +41,8 @@ __device__ __forceinline__ int wave_add(int v)
     return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
-// 8 heads of 16384 tokens: 76 us with one thread walking the 256 digits of each pass and every walk over the
-// scores reading both arrays; now 40.
+// 8 heads of 16384 tokens, calls in a row: 67 us with one thread walking the 256 digits of each pass and every
+// walk over the scores reading both arrays; now 32 (under a trace 76 and 45).
 __global__ __launch_bounds__(kStatBlock) void sparsity_kernel(StatsArgs a)
 {
     __shared__ float kept[kStatLds];
@@ -348,8 +348,9 @@ __global__ __launch_bounds__(kRedBlock) void redundancy_kernel(StatsArgs a)
 // tokens' own norms are applied to the maximum.  The norms of the next stage's rows are formed from
 // LDS under the other rounds' chains (64 v_dot2 per stage), since there is no workspace to keep
 // them in.  Bound: matrix pipe, 64 MFMAs (2048 clocks) per stage against about 1800 of vector issue.
-// 1 x 8 heads of 128, 16384 tokens, 5.5e11 flop: 1659 us with one LDS-staged block per 128 tokens
-// (barriers around every stage, nothing in flight), now 545 us (1.0 PFLOP/s).
+// 1 x 8 heads of 128, 16384 tokens, 5.5e11 flop, calls in a row with the count: 1585 us with one LDS-staged block
+// per 128 tokens (barriers around every stage, nothing in flight), now 537-553 (1.0 PFLOP/s; under a trace, which
+// costs this kernel 15 %, 1659 and 629 for the kernel alone).
 //
 // The short products need norms of a sane size: where |k||v| of a row leaves [2^-30, 2^30] the part is
 // redone with every factor applied in turn, as the other form does.

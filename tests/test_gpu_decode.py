@@ -133,9 +133,9 @@ def test_decode_init_matches_oracle(shape, mode):
     assert (st.tok_row < 0).any() and (st.tok_row >= 0).any()
 
 
-# a budget whose per-row staging does not fit in LDS: the kernel stages in the workspace instead
-# large caches: in bf16 the step runs as four launches over row slices; BIG stages its row dots in the
-# workspace (they do not fit in LDS), BIG_LDS in LDS
+# large caches: with so few heads the bf16 step runs as four launches, two of them over slices of the table, with the
+# logits in the workspace; in float32 it is one launch, whose row dots BIG stages in the workspace (they do not fit
+# in LDS) and BIG_LDS in LDS
 BIG = (1, 8, 1, 64, 4000, 8, 1800, 0.5)
 BIG_LDS = (1, 8, 2, 128, 5000, 16, 1100, 0.5)
 

@@ -98,10 +98,10 @@ def test_redundancy_rate_matches_oracle(shape, mode):
 @pytest.mark.parametrize("bh_n", [(1, 1), (3, 2), (2, 33), (1, 127), (5, 128), (2, 129), (1, 257), (1100, 70), (40, 1025), (1, 4100)])
 @pytest.mark.parametrize("scale", ["plain", "extreme"])
 def test_redundancy_edges(bh_n, d, scale):
-    """Token tiles of 128 with one row more or less, more heads than resident waves, stretches that end inside
-    the diagonal's stages; rows of norm zero and rows scaled by 2^30 to 2^45 either way (cosines do not
-    change, the products of two rows' norms leave the range the short form is made for).  Tolerance: a cosine
-    is a float32 sum of 128 products, 128 * 2^-24 = 8e-6 at most, two of them multiplied."""
+    """Token tiles of 128 with one row more or less and more heads than resident waves (short sequences are the block
+    form's in 16 bits too; the stream's own edges are below); rows of norm zero and rows scaled by 2^30 to 2^45
+    either way (cosines do not change, the products of two rows' norms leave the range the short form is made for).
+    Tolerance: a cosine is a float32 sum of 128 products, 128 * 2^-24 = 8e-6 at most, two of them multiplied."""
     bh, n = bh_n
     _log("redundancy edges", bh_n, d, scale)
     inp = ems_inputs.small(1, bh, bh, d, n, seed=n + d)

@@ -221,7 +221,7 @@ __device__ __forceinline__ DealPlace deal_place(int heads, int waves)
 }
 
 // Stretch length and waves per head of an even deal of `heads` lines of `total` stages over the
-// `resident` waves the chip holds (one per SIMD, fewer where the rings fill the LDS first).  More than one
+// `resident` waves the chip holds (one per SIMD).  More than one
 // round of waves is worth it only where the heads divide the waves badly; a part costs about two and a half stages beside its stages (stationary
 // operand, ring start).
 inline void deal_over_waves(int resident, long long heads, long long total, int align, int shortest, int* len, int* waves)

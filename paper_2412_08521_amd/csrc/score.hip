@@ -320,8 +320,12 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 // rows of every q-head of the group (second), a running sum is added to the sum of those before it, so that
 // small weights are not lost against a large sum.  (1 x 4 heads over 1, 8192: column sums off by 3.8e-7 without, 0.7e-7.)
 constexpr int kFoldKeys = 2048, kFoldRows = 512;
-template <typename T> struct Stream { static constexpr int kSub = 8; static constexpr int kRing = 4; };
-template <> struct Stream<float> { static constexpr int kSub = 2; static constexpr int kRing = 3; };
+template <typename T> struct Stream { static constexpr int kSub = 8; };
+template <> struct Stream<float> { static constexpr int kSub = 2; };
+// (512-byte rows: two 16 KB stages a wave, so that the rings of four waves fit a compute unit's LDS; a stage's 8192 clocks
+// of matrix instructions hide the next one's DMA.  8 heads over 2, 3000 rows, head size 128: a pass 94-108 us, 119-125
+// with three stages and thus three waves; 32 heads over 8, 6000 rows: 1242-1289 against 1639-1675.)
+template <typename T, int D> struct Ring { static constexpr int kStages = Tile<T, D>::kRowBytes == 512 ? 2 : 4; };
 
 // The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
 // the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
@@ -380,7 +384,7 @@ __device__ __forceinline__ void stream_edge_tile(const frag_t (&aq)[Tile<T, D>::
 template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
+    constexpr int kSub = Stream<T>::kSub, kRing = Ring<T, D>::kStages;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;                       // accumulator elements handled per MFMA slot
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");
@@ -392,11 +396,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kQInstr = kStageBytes / 1024;             // 16-byte DMA instructions per stage
     constexpr int kLoads = kQInstr + 1;                     // + one 4-byte DMA for the rows' log-sum-exp
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
-    static_assert(kRing == 3 || kRing == 4, "the waits below are written for rings of 3 or 4 stages");
+    static_assert(kRing == 2 || kRing == 4, "the waits below are written for rings of 2 or 4 stages");
     constexpr int kKeys = 32 * kSub;
     // stages per trip of the interior loop: after that many both the two operand register sets and
     // the ring slots are back where they started, so every slot is a compile-time constant
-    constexpr int kUnroll = kRing % 2 ? 2 * kRing : kRing;
+    constexpr int kUnroll = kRing;
 
     __shared__ __attribute__((aligned(1024))) char lds_q[kRing][kStageBytes];
     __shared__ __attribute__((aligned(256))) float lds_lse[kRing][2 * kStreamRows];   // second half: spare
@@ -561,17 +565,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     };
     // LDS -> registers: this lane's operand fragments of a staged row tile, and the 16 values of
     // the rows' log-sum-exp its accumulator registers stand for
-    auto fetch_rows = [&](int slot, frag_t (&q_out)[kFrags], f32x16_t& l_out) __attribute__((always_inline)) {
+    auto fetch_frags = [&](int slot, frag_t (&q_out)[kFrags]) __attribute__((always_inline)) {
         const char* qs = lds_q[slot];
-        const float* ls = lds_lse[slot];
 #pragma unroll
         for (int f = 0; f < kFrags; ++f) q_out[f] = *reinterpret_cast<const frag_t*>(qs + frag_off[f]);
+    };
+    auto fetch_lse = [&](int slot, f32x16_t& l_out) __attribute__((always_inline)) {
+        const float* ls = lds_lse[slot];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
             const f32x4_t v = *reinterpret_cast<const f32x4_t*>(ls + 8 * q4 + 4 * half);
 #pragma unroll
             for (int i = 0; i < 4; ++i) l_out[4 * q4 + i] = v[i];
         }
+    };
+    auto fetch_rows = [&](int slot, frag_t (&q_out)[kFrags], f32x16_t& l_out) __attribute__((always_inline)) {
+        fetch_frags(slot, q_out);
+        fetch_lse(slot, l_out);
     };
 
     float part[kSub][kEps];
@@ -729,8 +739,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         };
 
         issue_next(ic<0>{});
-        issue_next(ic<1>{});
-        if constexpr (kRing > 3) issue_next(ic<2>{});
+        if constexpr (kRing > 2) {
+            issue_next(ic<1>{});
+            issue_next(ic<2>{});
+        }
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_rows(0, aq[0], lse_v[0]);
         // Pairs alternate between accumulators {0, 1} and {2, 3}.  The pipeline starts on a pair
@@ -750,7 +762,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             constexpr int u = decltype(u_c)::value;         // stage t of the trip, t = u (mod kUnroll)
             constexpr int set = u & 1;
             constexpr int kFetchAt = 1;                     // as early as the other register set is free: the LDS latency has three rounds to hide in
-            issue_next(ic<(u + kRing - 1) % kRing>{});      // stage t + kRing - 1
+            if constexpr (kPairs > 1) issue_next(ic<(u + kRing - 1) % kRing>{});      // stage t + kRing - 1
 #pragma unroll
             for (int p = 0; p < kPairs; ++p) {
                 constexpr int kOddPairs = kPairs % 2;
@@ -779,24 +791,32 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     }
                     // two rounds later those reads have long returned: one wait for all of them
                     if (kPairs > 2 && kFetchAt < kPairs - 1 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
+                    // A single pair: with a ring of two the DMA goes to the slot that this stage was read from, once
+                    // those reads are done; the next stage is read under the last products, its log-sum-exp after
+                    // them (the other set weighs the previous stage until then).
+                    if constexpr (kPairs == 1) {
+                        if (f == 0) {
+                            wait_lds_all_visible();
+                            issue_next(ic<(u + kRing - 1) % kRing>{});
+                        }
+                        if (f == kFrags - 2) {
+                            wait_vmem<(kRing - 2) * kLoads>();
+                            fetch_frags((u + 1) % kRing, aq[1 - set]);
+                        }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if (kPairs == 1) {                              // (validation type) nothing to hide the fetch behind
-                wait_vmem<(kRing - 2) * kLoads>();
-                fetch_rows((u + 1) % kRing, aq[1 - set], lse_v[1 - set]);
-            }
+            if (kPairs == 1) fetch_lse((u + 1) % kRing, lse_v[1 - set]);
         };
         const int fold = kFoldRows / kStreamRows * max(G, 2) / kUnroll * kUnroll;
         int until_fold = fold;
         for (int t = 0; t < n_stages; t += kUnroll) {
             stage(ic<0>{});
             stage(ic<1>{});
-            stage(ic<2>{});
-            stage(ic<3>{});
-            if constexpr (kUnroll > 4) {
-                stage(ic<4>{});
-                stage(ic<5>{});
+            if constexpr (kUnroll > 2) {
+                stage(ic<2>{});
+                stage(ic<3>{});
             }
             until_fold -= kUnroll;
             if (kDeal && __builtin_expect(until_fold == 0, 0)) {     // the sums so far are set aside, in LDS (there are no registers left)
@@ -877,7 +897,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
+    constexpr int kSub = Stream<T>::kSub, kRing = Ring<T, D>::kStages;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");
@@ -888,10 +908,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kStageBytes = kStreamRows * kRowBytes;
     constexpr int kLoads = kStageBytes / 1024;              // 16-byte DMA instructions per stage
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
-    static_assert(kRing == 3 || kRing == 4, "the waits below are written for rings of 3 or 4 stages");
+    static_assert(kRing == 2 || kRing == 4, "the waits below are written for rings of 2 or 4 stages");
     constexpr int kRows = 32 * kSub;                        // query rows per wave
     // stages per trip of the interior loop (operand register sets and ring slots back at their start)
-    constexpr int kUnroll = kRing % 2 ? 2 * kRing : kRing;
+    constexpr int kUnroll = kRing;
     constexpr int kFold = kFoldKeys / kStreamRows / kUnroll * kUnroll;
 
     __shared__ __attribute__((aligned(1024))) char lds_k[kRing][kStageBytes];
@@ -1025,9 +1045,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int t_diag = max(t0, q_base / kStreamRows);
     const int n_edge = max(t1 - t_diag, 0);
     // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form, so
-    // that the pipelined rest is whole trips of the loop
+    // that the pipelined rest is whole trips of the loop.  A stage of float32 gains less by the pipeline than it costs
+    // to start it for a few (600 rows, a stretch of four: 26.8 us without, 29.7 with).
+    constexpr int kFewest = kPairs == 1 ? 6 : 0;
     const int n_int_all = max(min(t1, t_diag) - t0, 0);
-    const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
+    const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all < kFewest ? n_int_all : n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
     const int n_int = n_int_all - n_lead;                        // a multiple of kUnroll, >= 0
 
     float m_run[kSub], l_run[kSub];
@@ -1161,8 +1183,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             }
         };
         issue_next(ic<0>{});
-        issue_next(ic<1>{});
-        if constexpr (kRing > 3) issue_next(ic<2>{});
+        if constexpr (kRing > 2) {
+            issue_next(ic<1>{});
+            issue_next(ic<2>{});
+        }
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_keys(0, ak[0]);
         // The references stay as they are from here on: without edge stages the maxima of the first one (the
@@ -1185,7 +1209,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         auto stage = [&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;         // the stage's place in the trip
             constexpr int set = u & 1;
-            issue_next(ic<(u + kRing - 1) % kRing>{});      // the stage kRing - 1 ahead
+            if constexpr (kPairs > 1) issue_next(ic<(u + kRing - 1) % kRing>{});      // the stage kRing - 1 ahead
 #pragma unroll
             for (int p = 0; p < kPairs; ++p) {
                 constexpr int kOddPairs = kPairs % 2;
@@ -1210,22 +1234,28 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     }
                     // two rounds later those reads have long returned: one wait for all of them
                     if (kPairs > 2 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
+                    // a single pair: with a ring of two the DMA goes to the slot that this stage was read from, once
+                    // those reads are done; the next stage is read under the last products
+                    if constexpr (kPairs == 1) {
+                        if (f == 0) {
+                            wait_lds_all_visible();
+                            issue_next(ic<(u + kRing - 1) % kRing>{});
+                        }
+                        if (f == kFrags - 2) {
+                            wait_vmem<(kRing - 2) * kLoads>();
+                            fetch_keys((u + 1) % kRing, ak[1 - set]);
+                        }
+                    }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-            }
-            if (kPairs == 1) {
-                wait_vmem<(kRing - 2) * kLoads>();
-                fetch_keys((u + 1) % kRing, ak[1 - set]);
             }
         };
         for (int u0 = 0, run = kUnroll, fold = kUnroll; u0 < n_int;) {
             stage(ic<0>{});
             stage(ic<1>{});
-            stage(ic<2>{});
-            stage(ic<3>{});
-            if constexpr (kUnroll > 4) {
-                stage(ic<4>{});
-                stage(ic<5>{});
+            if constexpr (kUnroll > 2) {
+                stage(ic<2>{});
+                stage(ic<3>{});
             }
             u0 += kUnroll;
             if (kDeal && __builtin_expect(u0 == fold, 0)) {
@@ -1325,8 +1355,11 @@ int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<
 //   U >= 4              queues   32 over 8, 32768      4.0      3507 /    - / 3396
 //                                32 over 32, 49152     6.0      8728 /    - / 8264
 //   float32 (a part's beginning is little against its stages): the deal up to U = 16
-//                                 8 over 2, 16384      2.7      2946 / 3305 / 3866
-//                                4 x 32 over 8, 4096  10.7      3036 / 3060 / 3194
+//                                 8 over 2, 16384      2.0      2245 /    - / 2238
+//                                4 x 32 over 8, 4096   8.0      2323 /    - / 2292
+//                                4 x 8 over 8, 6000    2.9      1247 /    - / 1490
+//                                4 x 32 over 32, 6000 11.8      5074 /    - / 5117
+//                                2 x 64 over 8, 8192  16.0      8985 /    - / 8833
 // Second pass, by row stages per resident wave: the deal up to 1200, and always for fewer pairs than XCDs (which have
 // no queues: one block per item).  Waves that stream different rows share no lines of their L2: the more rows, the
 // more that costs.
@@ -1343,9 +1376,10 @@ int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<
 //                                 4 over 1, 131072    4096      7360 / 7361        "
 constexpr double kPairUnits = 1.95;        // from here to 2 a launch counts as whole pairs
 constexpr double kDealStages = 1200.;
+constexpr int kResident = kXcds * kXcdWaves;
 
 template <typename T>
-static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len, int resident)
+static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len)
 {
     constexpr int kSub = Stream<T>::kSub, kRows = 32 * kSub;
     ScoreDeal d{};
@@ -1357,24 +1391,22 @@ static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len,
     bool deal1 = units < (sizeof(T) == 4 ? 16. : wide ? 4. : 2.);
     if (sizeof(T) == 2 && !wide && units >= kPairUnits && units <= 2.) { d.p1_by_block = 1; deal1 = false; }
     if (deal1) {
-        deal_over_waves(resident, BHQ, d1.total(), DealPass1<kSub>::kAlign, 4, &d.p1_len, &d.p1_waves);
+        deal_over_waves(kResident, BHQ, d1.total(), DealPass1<kSub>::kAlign, 4, &d.p1_len, &d.p1_waves);
         d.p1_floats = (size_t)BHQ * (d.p1_waves + d1.n_units) * kRows;
     }
     const DealPass2<kSub> d2(seq_len, G);
     const double stages = 0.5 * (double)BKV * G * d2.rows_all * d2.n_units / 1024.;
     const bool fits = (d2.rows_all + 8.) * d2.n_units < 1073741824.;      // a line's stages are counted in 32 bits
     if (fits && (stages <= kDealStages || BKV < kXcds)) {
-        deal_over_waves(resident, BKV, d2.total(), DealPass2<kSub>::align(G), 1, &d.p2_len, &d.p2_waves);
+        deal_over_waves(kResident, BKV, d2.total(), DealPass2<kSub>::align(G), 1, &d.p2_len, &d.p2_waves);
         d.p2_floats = (size_t)BKV * (d.p2_waves + d2.n_units) * kRows;
     }
     return d;
 }
 
-ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32)
+ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*head_dim*/, bool f32)
 {
-    // (three 16 KB stages of 512-byte rows: three waves in a compute unit's LDS instead of four)
-    return f32 ? score_deal_t<float>(batch, q_heads, kv_heads, seq_len, head_dim == 128 ? 768 : 1024)
-               : score_deal_t<bf16_t>(batch, q_heads, kv_heads, seq_len, 1024);
+    return f32 ? score_deal_t<float>(batch, q_heads, kv_heads, seq_len) : score_deal_t<bf16_t>(batch, q_heads, kv_heads, seq_len);
 }
 
 template <typename T, int D>

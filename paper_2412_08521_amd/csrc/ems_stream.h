@@ -78,6 +78,13 @@ __device__ __forceinline__ void dma_to_lds_x4_at(const void* base, unsigned off0
                  "global_load_lds_dwordx4 %3, %4 offset:3072"
                  ::"v"(off0), "v"(off1), "v"(off2), "v"(off3), "s"(base), "s"(lds_base), "n"(kLdsOff) : "memory", "m0", "scc");
 }
+// One of the four, which go out one by one where an instruction in the middle of others costs less than four in a row.
+template <int kLdsOff, int kBoth>
+__device__ __forceinline__ void dma_one_to_lds_at(const void* base, unsigned off, unsigned lds_base)
+{
+    asm volatile("s_add_u32 m0, %2, %3\n\tglobal_load_lds_dwordx4 %0, %1 offset:%4" ::"v"(off), "s"(base), "s"(lds_base), "n"(kLdsOff), "n"(kBoth)
+                 : "memory", "m0", "scc");
+}
 template <int kLdsOff>
 __device__ __forceinline__ void dma_dword_to_lds_at(const void* base, unsigned off, unsigned lds_base)
 {
@@ -116,6 +123,18 @@ __device__ __forceinline__ float halves_max(float x)
 {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// Combined over the four lanes that agree modulo 16 as well.
+__device__ __forceinline__ float quarters_sum(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return halves_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quarters_max(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return halves_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 
 // LDS byte address of a __shared__ object.
@@ -206,6 +225,15 @@ struct DealPass1 {
         return lo;
     }
 };
+
+// v_mfma_f32_16x16x32_bf16: lane l supplies row (A) / column (B) l % 16, its 16-byte chunk l / 16 of four; register r of the
+// accumulator holds row 4 * (l / 16) + r of column l % 16.  It takes the matrix time of the 32x32x16 form and twice its issue
+// slots (8 clocks each), but less power, which is what limits the clock where the matrix pipe is busy: alone, on
+// random operands, 2050-2130 TFLOP/s at 2.06 GHz against 1750-1830 at 1.75.
+__device__ __forceinline__ f32x4_t mma16(const frag_t& a, const frag_t& b, const f32x4_t& c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
 
 // A value that is the same in every lane, into a scalar register.
 __device__ __forceinline__ int scalar(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -345,12 +345,14 @@ __global__ __launch_bounds__(kRedBlock) void redundancy_kernel(StatsArgs a)
 // A round = the two MFMA chains (keys, values) of one token subtile, alternating, with the previous
 // subtile's accumulators turned into redundancies in between: (k . k')(v . v') w_j, w_j the reciprocal
 // of both norms of the streamed token, two multiplications and half a v_max3 per element; the
-// tokens' own norms are applied to the maximum.  The norms of the next stage's rows are formed from
-// LDS under the other rounds' chains (64 v_dot2 per stage), since there is no workspace to keep
-// them in.  Bound: matrix pipe, 64 MFMAs (2048 clocks) per stage against about 1800 of vector issue.
-// 1 x 8 heads of 128, 16384 tokens, 5.5e11 flop, calls in a row with the count: 1585 us with one LDS-staged block
-// per 128 tokens (barriers around every stage, nothing in flight), now 537-553 (1.0 PFLOP/s; under a trace, which
-// costs this kernel 15 %, 1659 and 629 for the kernel alone).
+// tokens' own norms are applied to the maximum.  The streamed rows' norms are formed at the start of their stage,
+// since there is no workspace to keep them in.  Bound: matrix pipe, 144 MFMAs (2304 clocks) per stage against about
+// 2100 of issue.
+// 1 x 8 heads of 128, 16384 tokens, 5.5e11 flop, calls in a row with the count, us: 1585 with one LDS-staged block
+// per 128 tokens (barriers around every stage, nothing in flight); 517-533 as a stream of 32x32x16 products with the norms by
+// v_dot2 and the diagonal's stages one by one; 437-445 now (1.26 PFLOP/s; without the streamed rows' DMA, which costs
+// issue slots and the L2's misses, 391; 290 for the products alone).  4 heads of 32768: 1006-1040, now 872-899; 8 heads of 16384, size
+// 64: 319-332, now 251.
 //
 // The short products need norms of a sane size: where |k||v| of a row leaves [2^-30, 2^30] the part is
 // redone with every factor applied in turn, as the other form does.
@@ -366,6 +368,8 @@ __device__ __forceinline__ float order_value(uint32_t u)
 {
     return u == 0u ? -INFINITY : __uint_as_float((u & 0x80000000u) ? (u & 0x7fffffffu) : ~u);
 }
+
+__device__ __forceinline__ f32x4_t zero4() { return f32x4_t{0.f, 0.f, 0.f, 0.f}; }
 
 // a fragment held in the accumulation registers, for the vector ALU
 __device__ __forceinline__ frag_t read_acc(const frag_t& b)
@@ -391,20 +395,24 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 {
     using T = bf16_t;
     constexpr int kSub = RedStream<D>::kSub, kRing = RedStream<D>::kRing;
-    constexpr int kFrags = Tile<T, D>::kFrags, kRowBytes = Tile<T, D>::kRowBytes, kCpr = Tile<T, D>::kChunksPerRow;
+    constexpr int kFrags = D / 32;                          // 32 elements of a row are one fragment of four lanes
+    constexpr int kRowBytes = Tile<T, D>::kRowBytes, kCpr = Tile<T, D>::kChunksPerRow;
     constexpr int kStageBytes = kStreamRows * kRowBytes;    // one source's rows of a stage
     constexpr int kInstr = kStageBytes / 1024;              // DMA instructions for them
     constexpr int kLoads = 2 * kInstr;
     static_assert(kInstr == 4 || kInstr == 8, "groups of four DMA instructions");
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
-    static_assert((kSub - 1) * kFrags >= 2 * kFrags + 3, "the norms of a stage fit under the chains of its predecessor");
-    static_assert(kTrip % kRing == 0, "parts hold whole turns of the ring");
+    static_assert(kTrip % kRing == 0 && kSub == kTrip, "parts hold whole turns of the ring, the diagonal is a trip");
     constexpr int kTokens = 32 * kSub;
-    constexpr int kPer = 16 / kFrags;                       // accumulator elements per slot
+    // A subtile's round: kProducts matrix instructions with 24 ticks of vector work evenly between them (an instruction
+    // that finds the matrix pipe busy holds up what is behind it): for each of 8 pairs of the previous subtile's
+    // elements one to multiply keys by values, one to apply the weights, one for the maximum.  The first round of a
+    // stage is preceded by its rows' squares.
+    constexpr int kProducts = 8 * kFrags, kSquares = 4 * kFrags, kTicks = 24;
 
     __shared__ __attribute__((aligned(1024))) char lds[kRing][2][kStageBytes];
-    __shared__ __attribute__((aligned(16))) float lds_w[2][kStreamRows];
-    __shared__ float lds_t[2][kTokens];                     // reciprocal norms of the wave's own tokens
+    __shared__ __attribute__((aligned(16))) float lds_w[2][kStreamRows + kWave];   // (behind the rows: where lanes that have none write)
+    __shared__ float lds_t[3][kTokens];                     // reciprocal norms of the wave's own tokens: key, value, both
 
     const int N = a.seq_len;
     const DealPass1<kSub> deal(N);
@@ -424,48 +432,57 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     if (t0 >= t1) continue;                                 // before the unit's first stage, or padding
     const int tok0 = unit * kTokens;
     const int t_diag = tok0 / kStreamRows;                  // subtile s is on the diagonal in stage t_diag + s
-    // the pipeline takes whole turns of the ring before the diagonal; the diagonal's stages are done one by one
-    const int n_pipe = scalar(max(min(t1, t_diag) - t0, 0) / kRing * kRing);
+    // the pipeline takes the stages before the diagonal and the diagonal's own, each a whole number of turns of the ring
+    // (parts are whole trips)
+    const int n_int = scalar(max(min(t1, t_diag) - t0, 0));
+    const bool on_diag = t1 > t_diag;                       // wave-uniform
 
     const int lane = lane_here();
-    const int col = lane & 31, half = lane >> 5;
+    const int col = lane % 16, group = lane / 16;           // in an operand: its row, the row's chunk (modulo the groups)
 
-    frag_t bk[kSub][kFrags], bv[kSub][kFrags];
+    frag_t bk[kSub][2][kFrags], bv[kSub][2][kFrags];
     bool odd_norm = false;                                  // a row whose norms the short products are not made for
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        const size_t at = (size_t)min(tok0 + s * 32 + col, N - 1) * kRowBytes + half * 16;   // (past the end: any row, its result is not kept)
+    for (int s = 0; s < kSub; ++s)
 #pragma unroll
-        for (int f = 0; f < kFrags; ++f) {
-            bk[s][f] = *reinterpret_cast<const frag_t*>(K + at + f * 32);
-            bv[s][f] = *reinterpret_cast<const frag_t*>(V + at + f * 32);
+        for (int j = 0; j < 2; ++j) {
+            const size_t at = (size_t)min(tok0 + s * 32 + j * 16 + col, N - 1) * kRowBytes + group * 16;   // (past the end: any row, its result is not kept)
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) {
+                bk[s][j][f] = *reinterpret_cast<const frag_t*>(K + at + f * 64);
+                bv[s][j][f] = *reinterpret_cast<const frag_t*>(V + at + f * 64);
+            }
         }
-    }
     // only the matrix instructions read the tokens' rows, but for their norms
 #pragma unroll
     for (int s = 0; s < kSub; ++s)
 #pragma unroll
-        for (int f = 0; f < kFrags; ++f) { asm volatile("" : "+a"(bk[s][f])); asm volatile("" : "+a"(bv[s][f])); }
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        float sk = 0.f, sv = 0.f;
+            for (int f = 0; f < kFrags; ++f) { asm volatile("" : "+a"(bk[s][j][f])); asm volatile("" : "+a"(bv[s][j][f])); }
 #pragma unroll
-        for (int f = 0; f < kFrags; ++f) {
-            const frag_t xk = read_acc(bk[s][f]), xv = read_acc(bv[s][f]);
-            sk += dot8_bf16(xk, xk);
-            sv += dot8_bf16(xv, xv);
-            __builtin_amdgcn_sched_barrier(0);
+    for (int s = 0; s < kSub; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float sk = 0.f, sv = 0.f;
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) {
+                const frag_t xk = read_acc(bk[s][j][f]), xv = read_acc(bv[s][j][f]);
+                sk += dot8_bf16(xk, xk);
+                sv += dot8_bf16(xv, xv);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            sk = quarters_sum(sk); sv = quarters_sum(sv);
+            const float rk = inv_norm(sk), rv = inv_norm(sv);
+            odd_norm |= (sk > 0.f) & (sv > 0.f) & !((rk * rv >= 0x1p-30f) & (rk * rv <= 0x1p30f));
+            lds_t[0][s * 32 + j * 16 + col] = rk; lds_t[1][s * 32 + j * 16 + col] = rv;
+            // (one root of the product, with a Newton step: the redundancies are 5.15e-8 rms off 64 bits at 4100 tokens of 128,
+            // 4.41e-8 of 64; 5.55e-8 and 5.03e-8 where the two roots were multiplied)
+            lds_t[2][s * 32 + j * 16 + col] = sk * sv > 0.f ? row_inv_norm<float>(sk * sv) : 0.f;
         }
-        sk = halves_sum(sk); sv = halves_sum(sv);
-        const float rk = inv_norm(sk), rv = inv_norm(sv);
-        odd_norm |= (sk > 0.f) & (sv > 0.f) & !((rk * rv >= 0x1p-30f) & (rk * rv <= 0x1p30f));
-        lds_t[0][s * 32 + col] = rk; lds_t[1][s * 32 + col] = rv;
-    }
 
-    auto swz = [](int row) __attribute__((always_inline)) { return D == 128 ? row & 7 : (row >> 1) & 7; };
-    // A row's 16-byte chunks are swizzled within each 128 bytes only: eight lanes read at a time, and a
-    // fragment's two places in a 256-byte row stay a constant apart.
-    constexpr int kHalfFrags = kFrags < 4 ? kFrags : 4;
+    // (sixteen lanes read at a time: the chunks of sixteen rows lie in different banks)
+    auto swz = [](int row) __attribute__((always_inline)) { return swz_key<T, D>(row); };
     auto dma_src_off = [&](int j, int ln) __attribute__((always_inline)) {
         const int slot = j * kWave + ln, row = slot / kCpr;
         return (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz(row)) << 4);
@@ -475,157 +492,253 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     unsigned dma_rel[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) dma_rel[j] = dma_src_off(j, lane) - (unsigned)j * 1024u;
-    unsigned frag_base[kHalfFrags];
+    unsigned frag_base[kFrags];
 #pragma unroll
-    for (int f = 0; f < kHalfFrags; ++f)
-        frag_base[f] = (unsigned)col * kRowBytes + (unsigned)(((f * 2 + half) ^ swz(col)) << 4);
-    auto frag_off = [&](int f) __attribute__((always_inline)) { return frag_base[f % kHalfFrags] + (unsigned)(f / kHalfFrags) * 128u; };
+    for (int f = 0; f < kFrags; ++f)
+        frag_base[f] = (unsigned)col * kRowBytes + (unsigned)(((f * 4 + group) ^ swz(col)) << 4);
+    auto frag_off = [&](int i, int f) __attribute__((always_inline)) { return frag_base[f] + (unsigned)(i * 16) * kRowBytes; };   // (rows 16 apart are swizzled alike)
     const unsigned lds0 = scalar((int)lds_address(&lds[0][0][0]));
 
-    float raw[kSub];                                        // products that still lack the tokens' own norms
+    float raw[kSub][2];                                // products that still lack the tokens' own norms
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) raw[s] = -INFINITY;
+    for (int s = 0; s < kSub; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) raw[s][j] = -INFINITY;
 
     wait_vmem_all_visible();
 
-    if (n_pipe > 0) {
-        int t_left = n_pipe;
+    if (n_int > 0 || on_diag) {
+        const bool whole = (unit + 1) * kTokens <= N;       // the diagonal's rows all exist: its first ones follow in the stream
+        int t_left = n_int + (on_diag && whole ? kRing : 0);
         const char* k_src = K + (size_t)t0 * kStageBytes;
         const ptrdiff_t v_minus_k = V - K;
-        // DMA of the next stage into ring slot `slot`; past the end the last stage again, unread
-        auto issue_next = [&](auto slot_c) __attribute__((always_inline)) {
-            constexpr int at = decltype(slot_c)::value * 2 * kStageBytes;
-            const char* v_src = k_src + v_minus_k;
+        // One DMA instruction (of kLoads) of the next stage into ring slot `slot`; past the end the last stage again, unread
+        auto issue_one = [&](auto slot_c, auto n_c) __attribute__((always_inline)) {
+            constexpr int n = decltype(n_c)::value, src = n / kInstr, j = n % kInstr;
+            constexpr int at = (decltype(slot_c)::value * 2 + src) * kStageBytes + j / 4 * 4096;
             static_assert(kInstr == 4 || kRowBytes * 16 == 4096, "the second group's offsets");
-            dma_to_lds_x4_at<at>(k_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds0);
-            if constexpr (kInstr > 4) dma_to_lds_x4_at<at + 4096>(k_src + 4096, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds0);
-            dma_to_lds_x4_at<at + kStageBytes>(v_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds0);
-            if constexpr (kInstr > 4) dma_to_lds_x4_at<at + kStageBytes + 4096>(v_src + 4096, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds0);
-            advance_cursor<kStageBytes>(t_left, k_src);
+            dma_one_to_lds_at<at, j % 4 * 1024>(k_src + (src ? v_minus_k : 0) + j / 4 * 4096, dma_rel[j % 4], lds0);
+            if constexpr (n == kLoads - 1) advance_cursor<kStageBytes>(t_left, k_src);
         };
-        auto rows = [&](int slot, int src, int f) __attribute__((always_inline)) {
-            return *reinterpret_cast<const frag_t*>(lds[slot][src] + frag_off(f));
-        };
-        // The reciprocal of both norms of this lane's row, from the squares this half-wave holds of it (no
-        // branches: this runs between matrix instructions).  One reciprocal root of the product has fewer roundings
-        // than two rounded roots: the redundancies are 5.6e-8 rms off 64 bits, 6.0e-8 with those (4100 tokens of 128).
-        auto both_norms = [&](float sk, float sv) __attribute__((always_inline)) {
-            const float k2 = halves_sum(sk), v2 = halves_sum(sv), p = k2 * v2;
-            odd_norm |= (k2 > 0.f) & (v2 > 0.f) & !((p >= 0x1p-60f) & (p <= 0x1p60f));
-            return p > 0.f ? __builtin_amdgcn_rsqf(p) : 0.f;
-        };
-
-        frag_t ak[kFrags], av[kFrags];
-        f32x16_t acc[4];                                    // {keys, values} of the present and of the previous subtile
-        f32x16_t w_now;
-        float w_mine;                                       // this lane's row of the next stage: reciprocal of both norms
-        defined_here(acc[0]); defined_here(acc[1]);
-        issue_next(ic<0>{});
-        issue_next(ic<1>{});
-        if constexpr (kRing > 2) { issue_next(ic<2>{}); issue_next(ic<3>{}); }
-        wait_vmem<(kRing - 1) * kLoads>();
-        {
-            float sk = 0.f, sv = 0.f;
-#pragma unroll
-            for (int f = 0; f < kFrags; ++f) {
-                ak[f] = rows(0, 0, f); av[f] = rows(0, 1, f);
-                sk += dot8_bf16(ak[f], ak[f]); sv += dot8_bf16(av[f], av[f]);
+        auto issue_next = [&](auto slot_c) __attribute__((always_inline)) {
+            issue_one(slot_c, ic<0>{}); issue_one(slot_c, ic<1>{}); issue_one(slot_c, ic<2>{}); issue_one(slot_c, ic<3>{});
+            issue_one(slot_c, ic<4>{}); issue_one(slot_c, ic<5>{}); issue_one(slot_c, ic<6>{}); issue_one(slot_c, ic<7>{});
+            if constexpr (kLoads > 8) {
+                issue_one(slot_c, ic<8>{}); issue_one(slot_c, ic<9>{}); issue_one(slot_c, ic<10>{}); issue_one(slot_c, ic<11>{});
+                issue_one(slot_c, ic<12>{}); issue_one(slot_c, ic<13>{}); issue_one(slot_c, ic<14>{}); issue_one(slot_c, ic<15>{});
             }
-            w_mine = both_norms(sk, sv);
-        }
+        };
+        // The same for the diagonal's stage d; rows past the end re-read the last row (only tokens past it are later)
+        auto issue_diag = [&](int d, int slot, int n) __attribute__((always_inline)) {
+            const int ln = lane_here(), j = n % kInstr, row0 = min(tok0 + d * kStreamRows, N - 1);
+            const int row = (j * kWave + ln) / kCpr, at = min(tok0 + d * kStreamRows + row, N - 1) - row0;
+            dma_to_lds<16>((n < kInstr ? K : V) + (size_t)row0 * kRowBytes, dma_src_off(j, ln) + (unsigned)((at - row) * kRowBytes),
+                           lds0 + (slot * 2 + n / kInstr) * kStageBytes + j * 1024);
+        };
+        auto rows = [&](int slot, int src, int i, int f) __attribute__((always_inline)) {
+            return *reinterpret_cast<const frag_t*>(lds[slot][src] + frag_off(i, f));
+        };
+        frag_t ak[2][kFrags], av[2][kFrags];
+        f32x4_t accs[2][2][2][2];                           // [present / previous subtile][keys, values][streamed rows][tokens]
+        f32x4_t w[2][2];                                    // the weights by accumulator row, of this stage and the last
+        // A row's squares are the diagonal of its tile's product with itself: 16 matrix instructions a stage.
+        // (By v_dot2, 64 of them, which wait for the matrix pipe to drain and hold up its next instruction, 16
+        // clocks each time: 16384 tokens, 8 heads of 128, 505 us.)
+        f32x4_t square[2][2];                               // [keys, values][streamed rows]
+        const bool diag = group == col / 4;                 // this lane has row col's, in register col % 4
+        const int w_at = diag ? col : kStreamRows + lane;
         // the pipeline starts on a subtile of zeros whose products are no redundancies
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { acc[2][r] = acc[3][r] = 0.f; w_now[r] = 0.f; }
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) accs[1][0][i][j] = accs[1][1][i][j] = zero4();
+            w[1][i] = zero4();
+        }
         bool started = false;                               // false: the first round's maximum is dropped
 
-        auto stage = [&](auto u_c) __attribute__((always_inline)) {
+        // rows of the diagonal tile that are earlier than the lane's token
+        bool earlier[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) earlier[r] = 4 * group + r < col;
+
+        auto dma_at = [&](auto slot_c, int n) __attribute__((always_inline)) {
+            switch (n) {                                    // (a constant once the loops are unrolled)
+            case 0: issue_one(slot_c, ic<0>{}); break;
+            case 1: issue_one(slot_c, ic<1>{}); break;
+            case 2: issue_one(slot_c, ic<2>{}); break;
+            case 3: issue_one(slot_c, ic<3>{}); break;
+            case 4: issue_one(slot_c, ic<4>{}); break;
+            case 5: issue_one(slot_c, ic<5>{}); break;
+            case 6: issue_one(slot_c, ic<6>{}); break;
+            case 7: issue_one(slot_c, ic<7>{}); break;
+            default: if constexpr (kLoads > 8) {
+                switch (n) {
+                case 8: issue_one(slot_c, ic<8>{}); break;
+                case 9: issue_one(slot_c, ic<9>{}); break;
+                case 10: issue_one(slot_c, ic<10>{}); break;
+                case 11: issue_one(slot_c, ic<11>{}); break;
+                case 12: issue_one(slot_c, ic<12>{}); break;
+                case 13: issue_one(slot_c, ic<13>{}); break;
+                case 14: issue_one(slot_c, ic<14>{}); break;
+                default: issue_one(slot_c, ic<15>{}); break;
+                }
+            }
+            }
+        };
+
+        auto stage = [&](auto u_c, auto d_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;         // the stage's ring slot
+            constexpr int d = decltype(d_c)::value;         // its rows are subtile d's own (-1: earlier than all)
             constexpr int next = (u + 1) % kRing;
-            frag_t tmp[2];
-            float sk = 0.f, sv = 0.f;
+            float x[2], p[2], x2 = 0.f;
+            // What the products of the first round leave time for: the reciprocal of both norms, one reciprocal root of
+            // the product, which has fewer roundings than two rounded roots.  No branches: this runs between matrix
+            // instructions.
+            auto norm_step = [&](int n) __attribute__((always_inline)) {
+                auto pick = [&](const f32x4_t& v) __attribute__((always_inline)) {
+                    const float lo = col & 1 ? v[1] : v[0], hi = col & 1 ? v[3] : v[2];
+                    return col & 2 ? hi : lo;
+                };
+                const int i = n / 4, part = n % 4;
+                if (n < 8) {
+                    if (part == 0) p[i] = pick(square[0][i]);
+                    if (part == 1) x2 = pick(square[1][i]);
+                    if (part == 2) {
+                        const float k2 = p[i];
+                        p[i] *= x2;
+                        odd_norm |= diag & (k2 > 0.f) & (x2 > 0.f) & !((p[i] >= 0x1p-60f) & (p[i] <= 0x1p60f));
+                    }
+                    if (part == 3) p[i] = p[i] > 0.f ? __builtin_amdgcn_rsqf(p[i]) : 0.f;
+                }
+                // written by accumulator column, read back by row
+                if (n == 8) { lds_w[u & 1][w_at] = p[0]; lds_w[u & 1][w_at + 16] = p[1]; }
+                if (n == 9) {
+#pragma unroll
+                    for (int i2 = 0; i2 < 2; ++i2) w[u & 1][i2] = *reinterpret_cast<const f32x4_t*>(&lds_w[u & 1][16 * i2 + 4 * group]);
+                }
+            };
 #pragma unroll
             for (int s = 0; s < kSub; ++s) {
                 const int ps = (s + kSub - 1) % kSub;       // the previous subtile (of the previous stage when s = 0)
-                f32x16_t& accK = acc[2 * (s & 1)];
-                f32x16_t& accV = acc[2 * (s & 1) + 1];
-                const f32x16_t& prevK = acc[2 * (1 - (s & 1))];
-                const f32x16_t& prevV = acc[2 * (1 - (s & 1)) + 1];
-                float top = -INFINITY;                      // the first round's result is judged as a whole
-                auto weigh = [&](int r0) __attribute__((always_inline)) {
-                    float x[kPer];
+                auto& now = accs[s & 1];
+                auto& prev = accs[1 - (s & 1)];
+                const auto& pw = w[s == 0 ? 1 - (u & 1) : u & 1];
+                float top[2] = {-INFINITY, -INFINITY};      // the first round's result is judged as a whole
+                auto tick = [&](int k) __attribute__((always_inline)) {
+                    const int e = k / 3, phase = k % 3, j = e / 4, r = e % 4;       // pair e: two rows' elements of one token
+                    if (s > 0 && ps < d) return;
 #pragma unroll
-                    for (int e = 0; e < kPer; ++e) x[e] = prevK[r0 + e] * prevV[r0 + e];
-#pragma unroll
-                    for (int e = 0; e < kPer; ++e) x[e] *= w_now[r0 + e];
-#pragma unroll
-                    for (int e = 0; e < kPer; ++e) top = fmaxf(top, x[e]);
+                    for (int i = 0; i < 2; ++i) {
+                        if (s > 0 && ps == d && phase == 2) x[i] = i < j || (i == j && earlier[r]) ? x[i] : -INFINITY;
+                        if (phase == 0) x[i] = prev[0][i][j][r] * prev[1][i][j][r];
+                        if (phase == 1) x[i] *= pw[i][r];
+                    }
+                    if (phase == 2) top[j] = fmaxf(fmaxf(top[j], x[0]), x[1]);
                 };
-#pragma unroll
-                for (int f = 0; f < kFrags; ++f) {
-                    if (f == 0) mma_first<T>(accK, ak[0], bk[s][0]);
-                    else mma<T>(accK, ak[f], bk[s][f]);
-                    weigh(f * kPer);
-                    if (s == kSub - 1) ak[f] = rows(next, 0, f);            // the last chain over this stage's rows
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (f == 0) mma_first<T>(accV, av[0], bv[s][0]);
-                    else mma<T>(accV, av[f], bv[s][f]);
-                    if (s == kSub - 1) av[f] = rows(next, 1, f);
-                    // the present stage's weights: written by its lanes, read back by accumulator row
-                    if (s == 0 && f == 0) lds_w[u & 1][col] = w_mine;
-                    // (each half of the registers as soon as the previous stage's last subtile is done with it)
-                    if (s == 0 && (f == kFrags / 2 || f == kFrags - 1)) {
-#pragma unroll
-                        for (int q = f == kFrags / 2 ? 0 : 2; q < (f == kFrags / 2 ? 2 : 4); ++q) {
-                            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(&lds_w[u & 1][8 * q + 4 * half]);
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) w_now[4 * q + i] = v[i];
-                        }
-                    }
-                    // the next stage's norms
-                    if (s > 0) {
-                        const int q = (s - 1) * kFrags + f;
-                        if (q == 0) { wait_vmem<(kRing - 1) * kLoads>(); sk = sv = 0.f; }
-                        if (q >= 2 && q < 2 * kFrags + 2) {
-                            const frag_t& x = tmp[q % 2];
-                            if (q % 2 == 0) sk += dot8_bf16(x, x); else sv += dot8_bf16(x, x);
-                        }
-                        if (q < 2 * kFrags) tmp[q % 2] = rows(next, q % 2, q / 2);
-                        if (q == 2 * kFrags + 2) w_mine = both_norms(sk, sv);
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
                 if (s == 0) {
-                    if (!started) top = -INFINITY;          // wave-uniform
-                    started = true;
-                    // every row of this stage is in registers: its slot takes the stage a ring ahead
-                    issue_next(ic<u>{});
+#pragma unroll
+                    for (int m = 0; m < kSquares; ++m) {
+                        const int f = m / 4, src = m / 2 % 2, i = m % 2;
+                        const frag_t& y = (src ? av : ak)[i][f];
+                        square[src][i] = mma16(y, y, f == 0 ? zero4() : square[src][i]);
+#pragma unroll
+                        for (int k = m * kTicks / kSquares; k < (m + 1) * kTicks / kSquares; ++k) tick(k);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
-                raw[ps] = fmaxf(raw[ps], top);
+                // the next stage has landed
+                constexpr int kOfNext = (kSub - 1) * kLoads / kSub;         // of the stage a ring ahead, by now
+                constexpr int kAhead = d < 0 ? kRing - 2 : (d + kRing < kSub ? kRing : kSub - d) - 2;
+                if (s == kSub - 1 && d < kSub - 1) wait_vmem<(kAhead < 0 ? 0 : kAhead) * kLoads + (d + kRing < kSub ? kOfNext : 0)>();
+#pragma unroll
+                for (int m = 0; m < kProducts; ++m) {
+                    // (each shares an operand with the one before)
+                    const int f = m / 8, src = m / 4 % 2, j = m / 2 % 2, i = j ? 1 - m % 2 : m % 2;
+                    frag_t (&a_src)[2][kFrags] = src ? av : ak;
+                    if (s >= d) now[src][i][j] = mma16(a_src[i][f], (src ? bv : bk)[s][j][f], f == 0 ? zero4() : now[src][i][j]);
+                    if (s == 0) {
+#pragma unroll
+                        for (int n = m * 20 / kProducts; n < (m + 1) * 20 / kProducts; ++n) if (n >= 2 && n < 12) norm_step(n - 2);
+                    } else {
+#pragma unroll
+                        for (int k = m * kTicks / kProducts; k < (m + 1) * kTicks / kProducts; ++k) tick(k);
+                    }
+                    if (s == kSub - 1 && j == 1) a_src[i][f] = rows(next, src, i, f);      // the last chain over this stage's rows
+                    // Every row of this stage is in registers once their squares are: its slot takes the stage a ring
+                    // ahead, an instruction at a time
+                    // (four in a row wait for each other: 455 us against 446)
+                    if (m % 8 == 4) {
+                        if (d < 0) dma_at(ic<u>{}, s * (kLoads / kSub) + m / 8);
+                        else if (d + kRing < kSub) issue_diag(d + kRing, u, s * (kLoads / kSub) + m / 8);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    if (s == 0 && !started) top[j] = -INFINITY;        // wave-uniform
+                    raw[ps][j] = fmaxf(raw[ps][j], top[j]);
+                }
+                if (s == 0) started = true;
             }
         };
-        for (int t = 0; t < n_pipe; t += kRing) {
-            stage(ic<0>{});
-            stage(ic<1>{});
-            if constexpr (kRing > 2) { stage(ic<2>{}); stage(ic<3>{}); }
-        }
-        {   // the last stage's last subtile
-            constexpr int at = 2 * ((kSub - 1) & 1);
+        auto first_rows = [&]() __attribute__((always_inline)) {        // of ring slot 0
+            wait_vmem<(kRing - 1) * kLoads>();
 #pragma unroll
-            for (int r = 0; r < 16; ++r) raw[kSub - 1] = fmaxf(raw[kSub - 1], (acc[at][r] * acc[at + 1][r]) * w_now[r]);
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int f = 0; f < kFrags; ++f) { ak[i][f] = rows(0, 0, i, f); av[i][f] = rows(0, 1, i, f); }
+        };
+        if (n_int > 0) {
+            issue_next(ic<0>{});
+            issue_next(ic<1>{});
+            if constexpr (kRing > 2) { issue_next(ic<2>{}); issue_next(ic<3>{}); }
+            first_rows();
+            for (int t = 0; t < n_int; t += kRing) {
+                stage(ic<0>{}, ic<-1>{});
+                stage(ic<1>{}, ic<-1>{});
+                if constexpr (kRing > 2) { stage(ic<2>{}, ic<-1>{}); stage(ic<3>{}, ic<-1>{}); }
+            }
         }
+        if (on_diag) {
+            if (n_int == 0 || !whole) {                     // they do not follow in the stream
+                wait_vmem<0>();
+#pragma unroll
+                for (int t = 0; t < kRing; ++t)
+#pragma unroll
+                    for (int n = 0; n < kLoads; ++n) issue_diag(t, t, n);
+                first_rows();
+            }
+            stage(ic<0>{}, ic<0>{});
+            stage(ic<1>{}, ic<1>{});
+            stage(ic<2 % kRing>{}, ic<2>{});
+            stage(ic<3 % kRing>{}, ic<3>{});
+        }
+        // the last stage's last subtile
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float y = (accs[1][0][i][j][r] * accs[1][1][i][j][r]) * w[1][i][r];
+                    const bool seen = !on_diag || i < j || (i == j && earlier[r]);
+                    raw[kSub - 1][j] = fmaxf(raw[kSub - 1][j], seen ? y : -INFINITY);
+                }
         wait_vmem<0>();                                     // no DMA may outlive the wave's LDS
     }
 
-    // the plain form: the diagonal's stages, or everything where a norm is out of its range
-    const int lane2 = lane_here(), col2 = lane2 & 31, half2 = lane2 >> 5;
+    // the plain form, where a norm is out of its range
+    const int lane2 = lane_here(), col2 = lane2 % 16, group2 = lane2 / 16;
     const bool redo = __any(odd_norm);
-    float best[kSub];                                       // finished redundancies
+    float best[kSub][2];                               // finished redundancies
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        best[s] = -INFINITY;
-        if (redo) raw[s] = -INFINITY;
-    }
-    for (int t = redo ? t0 : t0 + n_pipe; t < t1; ++t) {
+    for (int s = 0; s < kSub; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            best[s][j] = -INFINITY;
+            if (redo) raw[s][j] = -INFINITY;
+        }
+    for (int t = redo ? t0 : t1; t < t1; ++t) {
         const int row0 = t * kStreamRows;
 #pragma unroll
         for (int j = 0; j < kInstr; ++j) {
@@ -636,30 +749,42 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        frag_t ak[kFrags], av[kFrags];
-        float sk = 0.f, sv = 0.f;
+        frag_t ak[2][kFrags], av[2][kFrags];
 #pragma unroll
-        for (int f = 0; f < kFrags; ++f) {
-            ak[f] = *reinterpret_cast<const frag_t*>(lds[0][0] + frag_off(f));
-            av[f] = *reinterpret_cast<const frag_t*>(lds[0][1] + frag_off(f));
-            sk += dot8_bf16(ak[f], ak[f]); sv += dot8_bf16(av[f], av[f]);
+        for (int i = 0; i < 2; ++i) {
+            float sk = 0.f, sv = 0.f;
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) {
+                ak[i][f] = *reinterpret_cast<const frag_t*>(lds[0][0] + frag_off(i, f));
+                av[i][f] = *reinterpret_cast<const frag_t*>(lds[0][1] + frag_off(i, f));
+                sk += dot8_bf16(ak[i][f], ak[i][f]); sv += dot8_bf16(av[i][f], av[i][f]);
+            }
+            lds_w[0][i * 16 + col2] = inv_norm(quarters_sum(sk));
+            lds_w[1][i * 16 + col2] = inv_norm(quarters_sum(sv));
         }
-        lds_w[0][col2] = inv_norm(halves_sum(sk));
-        lds_w[1][col2] = inv_norm(halves_sum(sv));
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int s = 0; s < kSub; ++s) {
             if (row0 < tok0 + s * 32 + 31) {                // wave-uniform: some row is earlier than some token
-                f32x16_t accK = zero_acc(), accV = zero_acc();
 #pragma unroll
-                for (int f = 0; f < kFrags; ++f) { mma<T>(accK, ak[f], bk[s][f]); mma<T>(accV, av[f], bv[s][f]); }
+                for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float x = ((accK[r] * lds_w[0][acc_row(r, half2)]) * lds_t[0][s * 32 + col2]) *
-                                    ((accV[r] * lds_w[1][acc_row(r, half2)]) * lds_t[1][s * 32 + col2]);
-                    if (row0 + acc_row(r, half2) < tok0 + s * 32 + col2) best[s] = fmaxf(best[s], x);
-                }
+                    for (int j = 0; j < 2; ++j) {
+                        f32x4_t accK = zero4(), accV = zero4();
+#pragma unroll
+                        for (int f = 0; f < kFrags; ++f) {
+                            accK = mma16(ak[i][f], bk[s][j][f], accK);
+                            accV = mma16(av[i][f], bv[s][j][f], accV);
+                        }
+                        const int tok = s * 32 + j * 16 + col2;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int row = i * 16 + 4 * group2 + r;
+                            const float x = ((accK[r] * lds_w[0][row]) * lds_t[0][tok]) * ((accV[r] * lds_w[1][row]) * lds_t[1][tok]);
+                            if (row0 + row < tok0 + tok) best[s][j] = fmaxf(best[s][j], x);
+                        }
+                    }
             }
             __builtin_amdgcn_sched_barrier(0);              // one tile's temporaries at a time
         }
@@ -668,13 +793,16 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     }
 
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        if (raw[s] > -INFINITY) best[s] = fmaxf(best[s], raw[s] * (lds_t[0][s * 32 + col2] * lds_t[1][s * 32 + col2]));
-        best[s] = halves_max(best[s]);  // the half2-waves saw different rows
-        const int ti = tok0 + s * 32 + col2;
-        if (half2 == 0 && ti < N && best[s] > -INFINITY)
-            atomicMax(reinterpret_cast<unsigned int*>(a.best) + (size_t)place.head * N + ti, order_image(best[s]));
-    }
+    for (int s = 0; s < kSub; ++s)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int tok = s * 32 + j * 16 + col2, ti = tok0 + tok;
+            float b = best[s][j];
+            if (raw[s][j] > -INFINITY) b = fmaxf(b, raw[s][j] * lds_t[2][tok]);
+            b = quarters_max(b);                                  // the groups saw different rows
+            if (group2 == 0 && ti < N && b > -INFINITY)
+                atomicMax(reinterpret_cast<unsigned int*>(a.best) + (size_t)place.head * N + ti, order_image(b));
+        }
     }   // next part
 }
 
@@ -729,13 +857,13 @@ static hipError_t launch_redundancy_t(const StatsArgs& a, hipStream_t st)
 constexpr int kRedStreamMax = 1 << 21;      // a head's line of stages is counted in 32 bits: longer sequences take the other form
 
 // Up to this length the other form takes the 16-bit rows as well: a wave of the stream begins with 8 us of loads and
-// norms, and one more launch clears `best`.  (us, stream / blocks.  128: 1 head of 350 24.7 / 22.4, of 450 24.7 /
-// 27.9; 128 heads of 450 40.8 / 34.0, of 513 42.4 / 51.1; 1100 of 256 103 / 89, of 385 183 / 225.  64: 1 head of 450 21.4 / 20.0, of
-// 600 21.6 / 24.3; 128 heads of 700 39.6 / 33.6, of 900 49.0 / 59.1; 1100 of 700 227 / 190, of 900 330 / 402.)
+// norms, and one more launch clears `best`.  (us, stream / blocks.  128: 1 head of 256 17.0 / 17.7, of 200 16.7 / 15.9;
+// 128 heads of 300 25.6 / 23.3, of 384 25.5 / 27.1; 1100 of 128 40.0 / 37.0, of 200 66.8 / 76.4.  64: 1 head of 256 14.7 /
+// 13.3, of 384 15.0 / 17.3; 128 heads of 300 19.5 / 16.7, of 384 18.6 / 18.9; 1100 of 300 59.7 / 57.6, of 384 60.6 / 64.3.)
 static int red_block_max(int head_dim, int heads)
 {
-    if (head_dim == 64) return heads <= 16 ? 512 : 768;
-    return heads <= 16 ? 384 : heads <= 128 ? 448 : 256;
+    if (head_dim == 64) return heads <= 16 ? 288 : 352;
+    return heads <= 16 ? 256 : heads <= 128 ? 352 : 160;
 }
 
 template <int D>

@@ -184,3 +184,18 @@ def test_redundancy_edges_of_the_stream(bh_n, d, scale):
     """The edges above at lengths that the stream takes: token tiles of 128 with one row more or less, more heads than
     resident waves, and the rows whose norms send a part back to the plain form."""
     test_redundancy_edges(bh_n, d, scale)
+
+
+@pytest.mark.parametrize("d,bh,limit", [(64, 1, 288), (64, 20, 352), (128, 2, 256), (128, 20, 352), (128, 140, 160)])
+def test_redundancy_either_side_of_the_shorter_forms(d, bh, limit):
+    """As above, at the lengths where the present stream begins."""
+    test_redundancy_either_side_of_the_short_form(d, bh, limit)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("rest", [1, 5, 31, 32, 33, 64, 95, 96, 97, 127, 128])
+def test_redundancy_on_the_diagonal_of_the_stream(rest, d):
+    """The last unit's diagonal with every number of its four stages and odd rests in them, where it is a part of its own
+    and where earlier stages run into it.  Tolerance as above."""
+    for bh, n in ((1, 384 + rest), (9, 1408 + rest)):
+        test_redundancy_edges((bh, n), d, "plain")

@@ -63,6 +63,55 @@ __device__ __forceinline__ void block_reduce(float (&v)[kN], float (*buf)[kWaves
         }
     }
 }
+// The softmax state (reference m, sum l of the weights relative to it) of G rows over the block, and two plain totals with it:
+// one barrier for what a maximum, a sum and the totals would take two each for.  (`buf` is the call's own.)  The result is identical in
+// every thread.
+template <int kWaves, int G>
+__device__ __forceinline__ void block_softmax(float (&m)[G], float (&l)[G], float (&tot)[2], float (*buf)[kWaves])
+{
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    float top[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        top[g] = wave_reduce<true>(m[g]);
+        l[g] = wave_reduce<false>(m[g] > -INFINITY ? l[g] * exp2_fast(m[g] - top[g]) : 0.f);
+    }
+    tot[0] = wave_reduce<false>(tot[0]);
+    tot[1] = wave_reduce<false>(tot[1]);
+    if (lane == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) { buf[g][wave] = top[g]; buf[G + g][wave] = l[g]; }
+        buf[2 * G][wave] = tot[0]; buf[2 * G + 1][wave] = tot[1];
+    }
+    __syncthreads();
+    constexpr bool kRow = kWaves == 16;                 // a lane per wave, else every lane walks the waves in order
+    const int at = kRow ? lane & 15 : 0;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        if constexpr (kRow) {
+            const float mw = buf[g][at];
+            m[g] = lane_value(row_reduce<true>(mw), 0);
+            l[g] = lane_value(row_reduce<false>(mw > -INFINITY ? buf[G + g][at] * exp2_fast(mw - m[g]) : 0.f), 0);
+        } else {
+            float M = buf[g][0], L = 0.f;
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) M = fmaxf(M, buf[g][w]);
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) L += buf[g][w] > -INFINITY ? buf[G + g][w] * exp2_fast(buf[g][w] - M) : 0.f;
+            m[g] = M; l[g] = L;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        if constexpr (kRow) tot[i] = lane_value(row_reduce<false>(buf[2 * G + i][at]), 0);
+        else {
+            float t = buf[2 * G + i][0];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) t += buf[2 * G + i][w];
+            tot[i] = t;
+        }
+    }
+}
 // arg-min (kMin) or arg-max of (value, index) pairs, lowest index on ties; index < 0 = none
 template <bool kMin>
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi)
@@ -116,15 +165,6 @@ __device__ __forceinline__ void block_arg(float& v, int& i, float* fbuf, int* ib
         for (int w = 1; w < kWaves; ++w)
             if (better<kMin>(fbuf[w], ibuf[w], v, i)) { v = fbuf[w]; i = ibuf[w]; }
     }
-}
-
-// register `idx` (0..15) of a 32x32 accumulator, idx not known at compile time
-__device__ __forceinline__ float acc_pick(const f32x16_t& acc, int idx)
-{
-    float v = acc[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) v = idx == r ? acc[r] : v;
-    return v;
 }
 
 // ------------------------------------------------------------------------------------
@@ -202,8 +242,8 @@ __global__ __launch_bounds__(256) void decode_init_kernel(DecodeInitArgs a)
 // behind the sweep anyway.)
 // What one launch leaves for the next lives in the workspace: the logits or the staged dots and row norms, and
 // a hand-over record per head (kHand* offsets below).
-// Dynamic LDS of the one-launch step and of kPart = 2 (floats): dot[G][budget] | rn[budget] when that fits, else the
-// same arrays live in the caller's workspace (a.lds_floats == 0).
+// Dynamic LDS of the one-launch step and of kPart = 2 (floats): dot[G][budget] | rn[budget] | the entries' centre tokens
+// [n_imp] when that fits, else the first two live in the caller's workspace (a.lds_floats == 0), the last where it is.
 constexpr int kHandSelf = 0;       // [8]  new query . new key per q-head (log2 units)
 constexpr int kHandNewNorm = 8;    //      norm of the new key
 constexpr int kHandOldSc = 9;      // [4]  scalars of the token that left the window
@@ -423,18 +463,15 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr int kE = P::kElems;
     constexpr int kWaves = kBlock / kWave;
     constexpr int kLpr = Tile<T, D>::kChunksPerRow;          // lanes per cache row
-    constexpr int kFrags = Tile<T, D>::kFrags;               // MFMA operand fragments per row
-    constexpr int kRowBytes = Tile<T, D>::kRowBytes;
     constexpr int kUnroll = 4;                               // independent loads in flight per thread
-    constexpr int kPre = 2;                                  // row tiles in flight per wave
 
     extern __shared__ float dyn_lds[];
     __shared__ float fbuf[kWaves];
     __shared__ int ibuf[kWaves];
-    __shared__ float vbuf[G < 2 ? 2 : G][kWaves];            // vector reductions
-    __shared__ float sq[kWaves][32];                         // squared norms of a wave's row tile
+    __shared__ float vbuf[2 * G + 2][kWaves];                // the softmax's reduction
     __shared__ float sh_self[G];                             // new query . new key (log2 units)
     __shared__ frag_t old_k[kLpr], old_v[kLpr];              // the token that leaves the window
+    __shared__ frag_t star_k[kLpr];                          // the least important centre's key
     __shared__ float old_sc[4];                              // its norm, glo, past, cur
     __shared__ int old_pos;
     __shared__ float sh_newnorm;
@@ -450,7 +487,6 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const int step = a.step >= 0 ? a.step
                    : (kPart >= 2 ? reinterpret_cast<const int*>(a.hand + (size_t)bkv * kDecodeHandFloats)[kHandStep] : *a.st.step_count);
     const int lane = tid % kWave, wave = tid / kWave;
-    const int col = lane & 31, half = lane >> 5;             // MFMA operand row / k-half of this lane
     const int grp = tid / kLpr, piece = tid % kLpr;
 
     char* Kc = reinterpret_cast<char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
@@ -482,27 +518,21 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const char* vn = reinterpret_cast<const char*>(a.v_new) + (size_t)bkv * D * sizeof(T);
 
     // ---- phase 1: q_g . (every cache row), the new token's own key included as row Nb ----
-    // bf16: a row is kLpr consecutive lanes x 16 bytes, so a wave-wide load covers 64 / kLpr
-    // whole rows (fully coalesced); each lane forms the partial dots of its 8 elements with
-    // v_dot2 and the kLpr partials are added with DPP.  One dot per cache ROW serves every
+    // A row is kLpr consecutive lanes x 16 bytes, so a wave-wide load covers 64 / kLpr
+    // whole rows (fully coalesced); each lane forms the partial dots of its elements (16 bits: with
+    // v_dot2) and the kLpr partials are added with DPP.  One dot per cache ROW serves every
     // token that shares the entry.
-    // f32 (validation mode): MFMA contraction, 32 cache rows per tile as the A operand, the
-    // group's q-heads in B columns 0..G-1.
     // Everything this thread will need from global memory that does not depend on earlier
     // phases is requested here, behind the first row loads, so that the round trips overlap:
     // the first batch of table elements (all of them for small tables), the centre token of
     // "its" entry, its share of the row norms, the new token's row.
-    constexpr bool kDot2 = sizeof(T) == 2;
     constexpr int kRowsPerWave = kWave / kLpr;               // whole rows per wave-wide load
     constexpr int kRowsPerPass = kWaves * kRowsPerWave;
-    constexpr int kInFlight = 4;                             // row loads in flight per lane (bf16 path)
+    constexpr int kInFlight = kAll ? 8 : 4;                  // row loads in flight per lane
     const int sub = lane / kLpr;                             // this lane's row within the wave's load
-    constexpr int kCt = kBlock == 1024 ? 2 : 1;              // centre tokens looked up ahead per thread (phase 4)
-    int ct_pre[kCt];
-#pragma unroll
-    for (int u = 0; u < kCt; ++u) ct_pre[u] = (kDoSoftmax && tid + u * kBlock < n_imp) ? entry_tok[tid + u * kBlock] : 0;
+    frag_t row_pre[kInFlight];                               // the first batch of rows: phase 1's, and in the one-launch step phase 5's
     frag_t new_k = zero_frag(), new_v = zero_frag();
-    float m[G], sum[G];
+    float m[G], inv[G];
     float tot2[2] = {0.f, 0.f};                              // sum of s_Glo, sum of s_Loc
     float self_tot = 0.f;
     int s_star = 0, f = 0;
@@ -510,6 +540,23 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     int ci = -1;
     int pre_rr[kUnroll];
     float pre_tn[kUnroll], pre_tg[kUnroll], pre_tp[kUnroll], pre_tc[kUnroll];
+    // the entries' centre tokens, in LDS behind the staged arrays where these are there
+    const bool ct_in_lds = in_lds && a.lds_centres > 0;      // block-uniform
+    int* sh_ct = reinterpret_cast<int*>(dyn_lds) + (size_t)(G + 1) * Nb;
+    constexpr int kCt = 2;                                   // looked up ahead per thread
+    int pre_ct[kCt];
+    auto preload_centres = [&]() {
+#pragma unroll
+        for (int u = 0; u < kCt; ++u) pre_ct[u] = tid + u * kBlock < n_imp ? entry_tok[tid + u * kBlock] : -1;
+    };
+    auto store_centres = [&]() {
+        if (!ct_in_lds) return;                              // block-uniform
+#pragma unroll
+        for (int u = 0; u < kCt; ++u)
+            if (tid + u * kBlock < n_imp) sh_ct[tid + u * kBlock] = pre_ct[u];
+        for (int i = tid + kCt * kBlock; i < n_imp; i += kBlock) sh_ct[i] = entry_tok[i];
+    };
+    auto centre_of = [&](int r) __attribute__((always_inline)) { return r < 0 || r >= n_imp ? -1 : ct_in_lds ? sh_ct[r] : entry_tok[r]; };
     auto preload_table = [&]() {
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -522,14 +569,24 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             pre_tc[u] = ok ? tok_cur[j] : 0.f;
         }
     };
+    // the token that leaves the window: its rows and position (its scalars come from the thread that updates them)
+    const int ring = step % W;
+    const int jo = E + ring, ro = n_imp + ring;
+    frag_t pre_old[2] = {zero_frag(), zero_frag()};
+    int pre_old_pos = 0;
+    auto preload_old = [&]() {
+        if (grp == 0) {
+            pre_old[0] = *reinterpret_cast<const frag_t*>(Kc + ((size_t)ro * kLpr + piece) * 16);
+            pre_old[1] = *reinterpret_cast<const frag_t*>(Vc + ((size_t)ro * kLpr + piece) * 16);
+        }
+        if (tid == 0) pre_old_pos = tok_pos[jo];
+    };
     if constexpr (kDoDots) {
-    if constexpr (kDot2) {
         frag_t qp[G];
 #pragma unroll
         for (int g = 0; g < G; ++g) qp[g] = *reinterpret_cast<const frag_t*>(qn + ((size_t)g * kLpr + piece) * 16);
         new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-        frag_t fk[kInFlight];
-        auto load_rows = [&](int r0) {
+        auto load_rows = [&](int r0, frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int r = r0 + u * kRowsPerPass;
@@ -537,19 +594,19 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         };
         const int r_first = r_lo + wave * kRowsPerWave + sub;
-        load_rows(r_first);
+        load_rows(r_first, row_pre);
         if constexpr (kAll) preload_table();
         const float rn_mine = (kAll && tid < Nb) ? row_norm[tid] : 0.f;
         if (grp == 0) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        for (int r0 = r_first; r0 < r_end; r0 += kRowsPerPass * kInFlight) {
-            if (r0 != r_first) load_rows(r0);
+        if constexpr (kAll) { preload_old(); preload_centres(); }
+        auto dots = [&](int r0, const frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int r = r0 + u * kRowsPerPass;
                 if (r >= r_end) break;                       // uniform over the row's lanes
                 float d[G];
 #pragma unroll
-                for (int g = 0; g < G; ++g) d[g] = group_sum<kLpr>(dot8_bf16(fk[u], qp[g]));
+                for (int g = 0; g < G; ++g) d[g] = group_sum<kLpr>(frag_dot<T>(fk[u], qp[g]));
                 if (piece == 0) {
                     if (r < Nb) {
 #pragma unroll
@@ -563,63 +620,19 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                     }
                 }
             }
+        };
+        dots(r_first, row_pre);
+        for (int r0 = r_first + kRowsPerPass * kInFlight; r0 < r_end; r0 += kRowsPerPass * kInFlight) {
+            frag_t fk[kInFlight];
+            load_rows(r0, fk);
+            dots(r0, fk);
         }
+        if constexpr (kAll) store_centres();
         for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
         if (grp == 0 && (kAll || slice == 0)) {
             const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
             if (piece == 0) { sh_newnorm = sqrtf(ss); if (!kAll) hand[kHandNewNorm] = sqrtf(ss); }
         }
-    } else {                                                 // (whole step only: the sliced one is bf16's)
-        frag_t bq[kFrags];
-#pragma unroll
-        for (int f = 0; f < kFrags; ++f)
-            bq[f] = load_frag_or_zero(qn, (size_t)col * kRowBytes + f * 32 + half * 16, col < G);
-        const int n_tiles = (Nb + 32) / 32;
-        frag_t fa[kPre][kFrags];
-        auto load_tiles = [&](int t0) {
-#pragma unroll
-            for (int u = 0; u < kPre; ++u) {
-                const int r = (t0 + u * kWaves) * 32 + col;
-                const char* src = r < Nb ? Kc + (size_t)r * kRowBytes : kn;
-#pragma unroll
-                for (int f = 0; f < kFrags; ++f) fa[u][f] = load_frag_or_zero(src, f * 32 + half * 16, r <= Nb);
-            }
-        };
-        load_tiles(wave);
-        preload_table();
-        const float rn_mine = tid < Nb ? row_norm[tid] : 0.f;
-        if (grp == 0) {
-            new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-            new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        }
-        for (int t0 = wave; t0 < n_tiles; t0 += kWaves * kPre) {
-            if (t0 != wave) load_tiles(t0);
-#pragma unroll
-            for (int u = 0; u < kPre; ++u) {
-                const int t = t0 + u * kWaves;
-                if (t >= n_tiles) break;                     // wave-uniform
-                f32x16_t acc;
-                mma_first<T>(acc, fa[u][0], bq[0]);
-#pragma unroll
-                for (int f = 1; f < kFrags; ++f) mma<T>(acc, fa[u][f], bq[f]);
-                if (col < G) {
-#pragma unroll
-                    for (int r16 = 0; r16 < 16; ++r16) {
-                        const int row = t * 32 + acc_row(r16, half);
-                        if (row < Nb) dot[(size_t)col * Nb + row] = acc[r16];
-                        else if (row == Nb) {
-                            sh_self[col] = a.scale_log2e * acc[r16];
-                        }
-                    }
-                }
-            }
-        }
-        for (int r = tid; r < Nb; r += kBlock) rn_of[r] = r == tid ? rn_mine : row_norm[r];
-        if (grp == 0) {
-            const float ss = group_sum<kLpr>(frag_sumsq<T>(new_k));
-            if (piece == 0) sh_newnorm = sqrtf(ss);
-        }
-    }
     }   // kDoDots
     if constexpr (kPart == 1) {
         if (slice == 0 && tid == 0) hand_i[kHandStep] = step;
@@ -628,6 +641,8 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     if constexpr (kPart == 2) {
         // what the dots launch left: the new token's own logits and norm, the staged arrays
         preload_table();
+        preload_old();
+        preload_centres();
         if (tid < G) sh_self[tid] = hand[kHandSelf + tid];
         if (tid == 0) sh_newnorm = hand[kHandNewNorm];
         if (grp == 0) {
@@ -645,63 +660,84 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                     if (i0 + u * kBlock < (G + 1) * Nb) dyn_lds[i0 + u * kBlock] = t[u];
             }
         }
+        store_centres();
     }
     if constexpr (kDoSoftmax) {
     __syncthreads();
 
     // ---- phase 2: softmax over the live tokens and the new token (Eq. 1) ---------------
-    // logit of token j in row r: scale * (|k_j| / |centre of r|) * (q . row r).  Three light
-    // sweeps over the table: maxima, sums, weights.
+    // logit of token j in row r: scale * (|k_j| / |centre of r|) * (q . row r).  Two sweeps over the table: logits with their
+    // maxima, sums relative to these and the scalars' totals; weights.  (us a step, calls in a row, with this, the kept
+    // rows and what is looked up ahead, against a sweep and a reduction each for maxima, sums, weights and totals and centres'
+    // scores, and every phase loading its own rows: 32 heads with a budget of 128 10.1 / 10.8, 8 heads of 384 17.7 / 20.5,
+    // of 512 21.5 / 25.7, 512 heads of 300 17.5 / 19.8; part 2 for 96 heads of 2000 37.8 / 40.3.  float32, then by matrix
+    // instructions: 2 heads of 200 19.2 / 26.1, 512 of 300 28.5 / 66.1.)
+    constexpr bool kKeep = kAll || G <= 4;                   // (1024 threads have no registers for eight q-heads')
+    float x0[kKeep ? kUnroll : 1][G];                        // the first batch's logits
+    int ct0[kUnroll];                                        // and its elements' centre tokens
 #pragma unroll
-    for (int g = 0; g < G; ++g) m[g] = sh_self[g];
+    for (int u = 0; u < kUnroll; ++u) ct0[u] = centre_of(pre_rr[u]);
+#pragma unroll
+    for (int g = 0; g < G; ++g) { m[g] = -INFINITY; inv[g] = 0.f; }
+    auto logits_of = [&](int r, float tn, float (&x)[G]) __attribute__((always_inline)) {
+        const float rn = r >= 0 ? rn_of[r] : 0.f;
+        const float c = a.scale_log2e * (rn > 0.f ? tn / rn : 0.f);
+#pragma unroll
+        for (int g = 0; g < G; ++g) x[g] = r >= 0 ? c * dot[(size_t)g * Nb + r] : -INFINITY;
+    };
     for (int j0 = tid; j0 < Tn; j0 += kBlock * kUnroll) {
-        int rr[kUnroll];
-        float tn[kUnroll];
+        float x[kUnroll][G];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int j = j0 + u * kBlock;
-            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
-            else { rr[u] = j < Tn ? tok_row[j] : -1; tn[u] = j < Tn ? tok_norm[j] : 0.f; }
+            int r = pre_rr[u];
+            float tn = pre_tn[u], tg = pre_tg[u], tl = pre_tp[u] + pre_tc[u];
+            if (j0 != tid) {
+                r = j < Tn ? tok_row[j] : -1;
+                tn = j < Tn ? tok_norm[j] : 0.f;
+                tg = j < Tn ? tok_glo[j] : 0.f;
+                tl = j < Tn ? tok_past[j] + tok_cur[j] : 0.f;
+            }
+            logits_of(r, tn, x[u]);
+            if (r >= 0) { tot2[0] += tg; tot2[1] += tl; }
         }
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int r = rr[u];
-            if (r < 0) continue;
-            const float rn = rn_of[r];
-            const float c = a.scale_log2e * (rn > 0.f ? tn[u] / rn : 0.f);
+        for (int g = 0; g < G; ++g) {
+            float top = m[g];
 #pragma unroll
-            for (int g = 0; g < G; ++g) m[g] = fmaxf(m[g], c * dot[(size_t)g * Nb + r]);
+            for (int u = 0; u < kUnroll; ++u) top = fmaxf(top, x[u][g]);
+            const float ref = top > -INFINITY ? top : 0.f;
+            float l = inv[g] * exp2_fast(m[g] - ref);
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) l += exp2_fast(x[u][g] - ref);
+            m[g] = top; inv[g] = l;
         }
-    }
-    block_reduce<kWaves, G, true>(m, vbuf);
+        if (kKeep && j0 == tid) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) sum[g] = tid == 0 ? exp2_fast(sh_self[g] - m[g]) : 0.f;
-    for (int j0 = tid; j0 < Tn; j0 += kBlock * kUnroll) {
-        int rr[kUnroll];
-        float tn[kUnroll];
+            for (int u = 0; u < (kKeep ? kUnroll : 1); ++u)
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int j = j0 + u * kBlock;
-            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; }
-            else { rr[u] = j < Tn ? tok_row[j] : -1; tn[u] = j < Tn ? tok_norm[j] : 0.f; }
-        }
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            const int r = rr[u];
-            if (r < 0) continue;
-            const float rn = rn_of[r];
-            const float c = a.scale_log2e * (rn > 0.f ? tn[u] / rn : 0.f);
-#pragma unroll
-            for (int g = 0; g < G; ++g) sum[g] += exp2_fast(c * dot[(size_t)g * Nb + r] - m[g]);
+                for (int g = 0; g < G; ++g) x0[u][g] = x[u][g];
         }
     }
-    block_reduce<kWaves, G, false>(sum, vbuf);
+    block_softmax<kWaves, G>(m, inv, tot2, vbuf);
+    float self_w[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) sum[g] = 1.0f / sum[g];
-    // accumulate the row into s_Glo and s_Loc^cur (Sec. 3.3); the sums that Eq. 2 needs
-    // (phase 4) are those of the updated scalars
+    for (int g = 0; g < G; ++g) {
+        const float self = sh_self[g], M = fmaxf(m[g], self);
+        inv[g] = 1.0f / ((m[g] > -INFINITY ? inv[g] * exp2_fast(m[g] - M) : 0.f) + exp2_fast(self - M));
+        m[g] = M;
+        self_w[g] = exp2_fast(self - M) * inv[g];            // every thread, same value
+        self_tot += self_w[g];
+    }
+    // Eq. 2 factor on the updated scalars: this step adds one unit of weight per q-head to both totals
+    const float s_glo = tot2[0] + (float)G, s_loc = tot2[1] + (float)G;
+    const float align = s_glo > 0.f ? s_loc / s_glo : 0.f;
+    // accumulate the row into s_Glo and s_Loc^cur (Sec. 3.3); the elements that are class centres' own take part in
+    // phase 4: the least important one
+    float bv = 0.f;
+    int bi = -1;
     for (int j0 = tid; j0 < Tn; j0 += kBlock * kUnroll) {
-        int rr[kUnroll];
+        int rr[kUnroll], ct[kUnroll];
         float tn[kUnroll], tg[kUnroll], tp[kUnroll], tc[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -715,6 +751,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 tp[u] = ok ? tok_past[j] : 0.f;
                 tc[u] = ok ? tok_cur[j] : 0.f;
             }
+            ct[u] = j0 == tid ? ct0[u] : centre_of(rr[u]);
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -723,16 +760,23 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             const int r = rr[u];
             float w[G];
             if (r >= 0) {
-                const float rn = rn_of[r];
-                const float c = a.scale_log2e * (rn > 0.f ? tn[u] / rn : 0.f);
-                float tot = 0.f;
+                float x[G], tot = 0.f;
+                if (kKeep && j0 == tid) {
 #pragma unroll
-                for (int g = 0; g < G; ++g) { w[g] = exp2_fast(c * dot[(size_t)g * Nb + r] - m[g]) * sum[g]; tot += w[g]; }
+                    for (int g = 0; g < G; ++g) x[g] = x0[kKeep ? u : 0][g];
+                } else {
+                    logits_of(r, tn[u], x);
+                }
+#pragma unroll
+                for (int g = 0; g < G; ++g) { w[g] = exp2_fast(x[g] - m[g]) * inv[g]; tot += w[g]; }
                 const float glo = tg[u] + tot, cur = tc[u] + tot;
                 tok_glo[j] = glo;
                 tok_cur[j] = cur;
-                tot2[0] += glo;
-                tot2[1] += tp[u] + cur;
+                if (j == jo) { old_sc[0] = tn[u]; old_sc[1] = glo; old_sc[2] = tp[u]; old_sc[3] = cur; }
+                if (ct[u] == j) {
+                    const float sc = fmaxf(glo * align, tp[u] + cur);
+                    if (better<true>(sc, r, bv, bi)) { bv = sc; bi = r; }
+                }
             } else {
 #pragma unroll
                 for (int g = 0; g < G; ++g) w[g] = 0.f;
@@ -743,52 +787,28 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         }
     }
-#pragma unroll                                               // self_tot: every thread, same value
-    for (int g = 0; g < G; ++g) {
-        const float w = exp2_fast(sh_self[g] - m[g]) * sum[g];
-        self_tot += w;
-        if (a.attn_opt && tid == 0) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + Tn] = w;
+    if (a.attn_opt && tid == 0) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + Tn] = self_w[g];
     }
-    if (tid == 0) { tot2[0] += self_tot; tot2[1] += self_tot; }   // the new token: glo = cur = its own weight
-    block_reduce<kWaves, 2, false>(tot2, vbuf);              // also: every token's scalars are written
 
-    // ---- phase 3: the oldest window token leaves, the new token takes its ring slot ----
-    const int ring = step % W;
-    const int jo = E + ring, ro = n_imp + ring;
+    // ---- phase 4: least important class centre (Eq. 2 on the tokens' scalars) ----------
+    block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // also: every token's scalars are written
+
+    // ---- phase 3: the oldest window token leaves, the new token takes its ring slot (nothing reads these before the
+    // next barrier) ----
     if (grp == 0) {
-        old_k[piece] = *reinterpret_cast<const frag_t*>(Kc + ((size_t)ro * kLpr + piece) * 16);
-        old_v[piece] = *reinterpret_cast<const frag_t*>(Vc + ((size_t)ro * kLpr + piece) * 16);
+        old_k[piece] = pre_old[0];
+        old_v[piece] = pre_old[1];
         *reinterpret_cast<frag_t*>(Kc + ((size_t)ro * kLpr + piece) * 16) = new_k;
         *reinterpret_cast<frag_t*>(Vc + ((size_t)ro * kLpr + piece) * 16) = new_v;
     }
     if (tid == 0) {
-        old_pos = tok_pos[jo];
-        old_sc[0] = tok_norm[jo]; old_sc[1] = tok_glo[jo]; old_sc[2] = tok_past[jo]; old_sc[3] = tok_cur[jo];
+        old_pos = pre_old_pos;
         tok_pos[jo] = a.seq_len + step; tok_row[jo] = ro; tok_norm[jo] = sh_newnorm;
         tok_glo[jo] = self_tot; tok_past[jo] = 0.f; tok_cur[jo] = self_tot;
         row_norm[ro] = sh_newnorm;
     }
-
-    // ---- phase 4: least important class centre (Eq. 2 on the tokens' scalars) ----------
-    const float align = tot2[0] > 0.f ? tot2[1] / tot2[0] : 0.f;
-    float bv = 0.f;
-    int bi = -1;
-    for (int s0 = tid; s0 < n_imp; s0 += kBlock * kCt) {
-        float cg[kCt], cp[kCt], cc[kCt];
-#pragma unroll
-        for (int u = 0; u < kCt; ++u) {                      // every gather requested before the first is used
-            const int s = s0 + u * kBlock;
-            const int ct = s0 == tid ? ct_pre[u] : (s < n_imp ? entry_tok[s] : 0);
-            cg[u] = tok_glo[ct]; cp[u] = tok_past[ct]; cc[u] = tok_cur[ct];
-        }
-#pragma unroll
-        for (int u = 0; u < kCt; ++u) {
-            const int s = s0 + u * kBlock;
-            const float sc = fmaxf(cg[u] * align, cp[u] + cc[u]);
-            if (s < n_imp && better<true>(sc, s, bv, bi)) { bv = sc; bi = s; }
-        }
-    }
-    block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // its barriers also publish phase 3
     s_star = max(bi, 0);                                     // block-uniform, in [0, n_imp)
     }   // kDoSoftmax
     if constexpr (kPart == 2) {
@@ -803,7 +823,6 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     }
     // phase 5's first rows do not depend on the centre that is chosen
     const int s_first = r_lo + wave * kRowsPerWave + sub;
-    frag_t row_pre[kInFlight];
     auto load_centres = [&](int s0) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
@@ -819,8 +838,6 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         wave_arg<true>(v, i);
         s_star = max(i, 0);
         if (slice == 0) {
-            const int ring = step % W;
-            const int jo = E + ring, ro = n_imp + ring;
             if (grp == 0) {
                 char* const k_at = Kc + ((size_t)ro * kLpr + piece) * 16;
                 char* const v_at = Vc + ((size_t)ro * kLpr + piece) * 16;
@@ -842,75 +859,35 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         }
     }
     if constexpr (kPart >= 4) s_star = hand_i[kHandStar];
-    f = entry_tok[s_star];
+    f = kAll && ct_in_lds ? sh_ct[s_star] : entry_tok[s_star];
 
     // ---- phase 5: its most similar other centre (Eq. 5, cosine of the stored keys) -----
-    // bf16: per entry row the dot with the chosen row and the row's own squared norm, again as
-    // v_dot2 partials added with DPP.  f32: two MFMA chains per tile of 32 entries -- tile x
-    // (chosen row in every column) for the dots, tile x tile for the squared norms on its
-    // diagonal.
+    // Per entry row the dot with the chosen row and the row's own squared norm, as in phase 1.
     if constexpr (kDoCos) {
-    if constexpr (kDot2) {
-        const frag_t sp = *reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16);
-        const float rn_star = inv_norm(group_sum<kLpr>(dot8_bf16(sp, sp)));
+        frag_t sp;
+        if (kAll && s_star < kRowsPerPass * kInFlight) {     // block-uniform: some thread group has the row
+#pragma unroll
+            for (int u = 0; u < kInFlight; ++u)
+                if (s_first + u * kRowsPerPass == s_star) star_k[piece] = row_pre[u];
+            __syncthreads();
+            sp = star_k[piece];
+        } else {
+            sp = *reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16);
+        }
+        const float rn_star = row_inv_norm<T>(group_sum<kLpr>(frag_sumsq<T>(sp)));
         for (int s0 = s_first; s0 < c_end; s0 += kRowsPerPass * kInFlight) {
-            if (kPart != 3 || s0 != s_first) load_centres(s0);
+            if (!(kAll || kPart == 3) || s0 != s_first) load_centres(s0);
             const frag_t (&fk)[kInFlight] = row_pre;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int s = s0 + u * kRowsPerPass;
                 if (s >= c_end) break;                       // uniform over the row's lanes
-                const float d = group_sum<kLpr>(dot8_bf16(fk[u], sp));
-                const float e2 = group_sum<kLpr>(dot8_bf16(fk[u], fk[u]));
-                const float sim = (d * inv_norm(e2)) * rn_star;
+                const float d = group_sum<kLpr>(frag_dot<T>(fk[u], sp));
+                const float e2 = group_sum<kLpr>(frag_sumsq<T>(fk[u]));
+                const float sim = (d * row_inv_norm<T>(e2)) * rn_star;
                 if (piece == 0 && s != s_star && better<false>(sim, s, cv, ci)) { cv = sim; ci = s; }
             }
         }
-    } else
-    {
-        frag_t bs[kFrags];
-        float ss = 0.f;
-#pragma unroll
-        for (int fr = 0; fr < kFrags; ++fr) {
-            bs[fr] = *reinterpret_cast<const frag_t*>(Kc + (size_t)s_star * kRowBytes + fr * 32 + half * 16);
-            ss += frag_sumsq<T>(bs[fr]);
-        }
-        ss += __shfl_xor(ss, 32);
-        const float rn_star = inv_norm(ss);
-        const int t_lo = r_lo / 32, n_tiles = (c_end + 31) / 32;
-        const int pick = col & 15;                           // the accumulator register this lane judges
-        const int my_local = acc_row(pick, half);            // ... and the tile row it belongs to
-        const bool diag_here = half == ((col >> 2) & 1);     // this lane holds |row col|^2 ...
-        const int diag_reg = 4 * (col >> 3) + (col & 3);     // ... in this register
-        for (int t0 = t_lo + wave; t0 < n_tiles; t0 += kWaves * kPre) {
-            frag_t fa[kPre][kFrags];
-#pragma unroll
-            for (int u = 0; u < kPre; ++u) {
-                const int r = (t0 + u * kWaves) * 32 + col;
-#pragma unroll
-                for (int fr = 0; fr < kFrags; ++fr)
-                    fa[u][fr] = load_frag_or_zero(Kc, (size_t)r * kRowBytes + fr * 32 + half * 16, r < c_end);
-            }
-#pragma unroll
-            for (int u = 0; u < kPre; ++u) {
-                const int t = t0 + u * kWaves;
-                if (t >= n_tiles) break;                     // wave-uniform
-                f32x16_t acc, acc2;
-                mma_first<T>(acc, fa[u][0], bs[0]);
-                mma_first<T>(acc2, fa[u][0], fa[u][0]);
-#pragma unroll
-                for (int fr = 1; fr < kFrags; ++fr) { mma<T>(acc, fa[u][fr], bs[fr]); mma<T>(acc2, fa[u][fr], fa[u][fr]); }
-                __builtin_amdgcn_wave_barrier();             // the previous tile's sq[] has been read
-                if (diag_here) sq[wave][col] = acc_pick(acc2, diag_reg);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const int s = t * 32 + my_local;
-                const float sim = (acc_pick(acc, pick) * inv_norm(sq[wave][my_local])) * rn_star;
-                if (col < 16 && s < c_end && s != s_star && better<false>(sim, s, cv, ci)) { cv = sim; ci = s; }
-            }
-        }
-    }
     }   // kDoCos
     if constexpr (kPart == 4) {
         // the slices' winners (combined below, lowest centre on ties) and the token that left the window
@@ -922,6 +899,10 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             for (int i = 0; i < 4; ++i) old_sc[i] = hand[kHandOldSc + i];
             old_pos = hand_i[kHandOldPos];
         }
+    }
+    if constexpr (kPart == 4) {                              // phase 6's first look at the table
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) pre_rr[u] = tid + u * kBlock < E ? tok_row[tid + u * kBlock] : -1;
     }
     block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
     if constexpr (kPart == 3 || kPart == 5) {
@@ -954,7 +935,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
             const int j = j0 + u * kBlock;
-            rr[u] = j < E ? tok_row[j] : -1;
+            rr[u] = j >= E ? -1 : j0 == tid ? pre_rr[u] : tok_row[j];
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
@@ -1028,7 +1009,7 @@ static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
     else {
         constexpr bool kRows = kWhich == 1 || kWhich == 3 || kWhich == 5;      // a block per slice of rows
         constexpr int kBlock = kWhich == 2 || kWhich == 4 ? 1024 : 256;
-        const size_t lds = kWhich == 0 || kWhich == 2 ? sizeof(float) * (size_t)a.lds_floats : 0;
+        const size_t lds = kWhich == 0 || kWhich == 2 ? sizeof(float) * (size_t)(a.lds_floats + a.lds_centres) : 0;
         hipLaunchKernelGGL((decode_step_kernel<T, D, G, kBlock, kWhich>), dim3(kRows ? a.n_slices : 1, a.bkv), dim3(kBlock), lds, st, a);
     }
 }

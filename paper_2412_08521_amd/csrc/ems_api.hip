@@ -558,6 +558,7 @@ int ems_decode_step(const ems_params* p, const ems_decode_state* state, int32_t 
     // what a block may ask for without raising the limit, else in the workspace
     const size_t stage_floats = (size_t)(g + 1) * p->budget;
     a.lds_floats = stage_floats * sizeof(float) <= 60 * 1024 ? (int)stage_floats : 0;
+    a.lds_centres = (stage_floats + n_imp) * sizeof(float) <= 60 * 1024 ? n_imp : 0;
     a.bkv = (int)bkv; a.group = g; a.head_dim = p->head_dim; a.window = p->window; a.budget = p->budget;
     a.n_imp = n_imp; a.n_tbm = n_tbm; a.step = step; a.seq_len = p->seq_len;
     a.tau = p->tau;

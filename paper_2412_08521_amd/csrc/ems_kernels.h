@@ -139,6 +139,7 @@ struct DecodeStepArgs {
     int slice_rows, n_slices;   // slices of the rows in the sliced step (decode_split); 0, 1 = one launch
     int tok_slice, n_tok_slices;    // slices of the token table; 0 = it is not cut
     int lds_floats;         // (group + 1) * budget when staged in LDS, else 0
+    int lds_centres;        // n_imp when the entries' centre tokens fit behind them, else 0
     int bkv, group, head_dim, seq_len, window, budget, n_imp, n_tbm;
     int step;               // >= 0, or -1: read st.step_count
     float tau, scale_log2e;

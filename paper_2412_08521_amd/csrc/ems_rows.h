@@ -20,6 +20,18 @@ __device__ __forceinline__ float dot8_bf16(const frag_t& x, const frag_t& y)
     return acc;
 }
 
+// dot product of two 16-byte fragments, in f32
+template <typename T> __device__ __forceinline__ float frag_dot(const frag_t& x, const frag_t& y);
+template <> __device__ __forceinline__ float frag_dot<bf16_t>(const frag_t& x, const frag_t& y) { return dot8_bf16(x, y); }
+template <> __device__ __forceinline__ float frag_dot<float>(const frag_t& x, const frag_t& y)
+{
+    const f32x4_t a = __builtin_bit_cast(f32x4_t, x), b = __builtin_bit_cast(f32x4_t, y);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = __builtin_fmaf(a[i], b[i], s);
+    return s;
+}
+
 // sum of squares of the 16-byte fragment's elements, in f32
 template <typename T> __device__ __forceinline__ float frag_sumsq(const frag_t& f);
 template <> __device__ __forceinline__ float frag_sumsq<bf16_t>(const frag_t& f) { return dot8_bf16(f, f); }

@@ -246,3 +246,29 @@ def test_decode_steps_of_many_heads_match_oracle(shape, tau):
     q, k, v = (dev_tensor(x, B.EMS_BF16) for x in _new_token(p, rng, B.EMS_BF16))
     B.ems_decode_step(p, st, B.EMS_STEP_FROM_STATE, q, k, v, ws=ws)
     assert int(st.step_count) == p.window + 3
+
+
+# the one-launch step keeps its first rows (128 in 16 bits and 64 in float32 at head size 128, twice as many at 64) for the
+# search: a chosen centre among them and behind them, tables over one batch of 1024, centre tokens that do not fit LDS
+@pytest.mark.parametrize("shape,mode", [
+    ((1, 4, 1, 128, 1500, 8, 136, 0.5), B.EMS_BF16),      # 128 centres: the last is the last kept row
+    ((1, 2, 1, 128, 1500, 8, 137, 1.0), B.EMS_BF16),      # one more
+    ((1, 8, 1, 64, 4000, 16, 500, 2.0), B.EMS_BF16),      # a table of 1500, 484 centres
+    ((1, 2, 2, 128, 900, 8, 73, 0.5), B.EMS_F32),
+    ((1, 1, 1, 64, 7000, 8, 5400, 0.25), B.EMS_F32),      # staged rows fit LDS, the centres' tokens behind them do not
+])
+def test_decode_steps_around_the_kept_rows(shape, mode):
+    _log("decode_step", shape, mode)
+    p, merged, tbm, s_glo, s_loc, st = _prefill(shape, mode, 0.3, seed=shape[6])
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    rng = np.random.default_rng(29)
+    n_flip = 0
+    for t in range(p.window + 2):
+        if t % 2 == 0:                                    # the least important centre: by turns the last one and the first
+            want = n_imp - 1 if t % 4 == 0 else 0
+            at = int(st.entry_tok[0, 0, want])
+            for x in (st.tok_glo, st.tok_past, st.tok_cur):
+                x[:, :, at] = 0.0
+        qb, kb, vb = _new_token(p, rng, mode)
+        n_flip += run_and_check_step(p, st, t, qb, kb, vb, 0.3, [(0, 0)], mode)[0]
+    assert n_flip <= 1

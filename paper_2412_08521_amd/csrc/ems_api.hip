@@ -153,7 +153,7 @@ size_t select_ws_bytes(const ems_params* p) { return plan_select(p).total; }
 // Evict-merge workspace: the key norms (used when the caller does not ask for them) and, when the
 // centre list is searched in slices, the per-slice winners.
 struct MergePlan {
-    int slice_rows, n_slices;
+    int n_slices;               // at most
     size_t off_norm, off_best, off_arg, total;
 };
 
@@ -162,7 +162,7 @@ MergePlan plan_merge(const ems_params* p)
     int n_imp, n_tbm;
     partition_sizes(p, &n_imp, &n_tbm);
     MergePlan m{};
-    ems::dest_slicing(n_imp, p->dtype == EMS_F32, &m.slice_rows, &m.n_slices);
+    m.n_slices = ems::dest_max_slices(n_imp, p->dtype == EMS_F32);
     const size_t bkv = (size_t)p->batch * p->kv_heads;
     const size_t part = m.n_slices > 1 ? align_up(4 * bkv * m.n_slices * (size_t)n_tbm) : 0;
     m.off_norm = 0;
@@ -357,7 +357,7 @@ static int evict_merge_launch(const ems_params* p, int similarity, const void* k
     const MergePlan plan = plan_merge(p);
     char* w = static_cast<char*>(ws);
     a.k_norm = k_norm_opt ? k_norm_opt : reinterpret_cast<float*>(w + plan.off_norm);
-    a.slice_rows = plan.slice_rows; a.n_slices = plan.n_slices;
+    a.n_slices = plan.n_slices;
     a.part_best = reinterpret_cast<float*>(w + plan.off_best);
     a.part_arg = reinterpret_cast<int32_t*>(w + plan.off_arg);
     a.slot_count = slot_count;

@@ -18,12 +18,13 @@
 #include "ems_rows.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ems {
 
 constexpr int kMrgWaves = 4;
 constexpr int kMrgBlock = kMrgWaves * kWave;
-constexpr int kDestDepth = 4;        // centre stages whose rows a block has in flight at once
+constexpr int kDestDepth = 4;        // centre stages whose rows a block has in flight at once, at most
 constexpr int kDestMaxSlices = 16;   // centre slices per head at most
 constexpr int kMergeWaves = 8;       // output rows per merge block
 constexpr int kMergeBlock = kMergeWaves * kWave;
@@ -58,12 +59,17 @@ __device__ __forceinline__ int clamp_pos(int p, int n) { return min(max(p, 0), n
 // Block = (128 * kTok TBM tokens, one slice of the centres, one (b, kv-head)); each wave keeps
 // 32 * kTok TBM rows in registers as the MFMA B operand (tokens -> lanes) and the centre rows stream
 // through LDS as the A operand (centres -> accumulator registers), so the running arg-max is a
-// per-lane pair.  A centre row is gathered once per token tile: with many tokens larger tiles pay
-// (4032 centres, 4096 tokens, 8 heads, the kernel under a trace: 88 us with one tile of 32 per wave, 77 with two
-// when that was chosen, now 72; four leave one wave per SIMD: 108).
+// per-lane pair.  A centre row is gathered once per token tile: with many tokens larger tiles pay.
+//
+// What bounds it: a 32 x 32 tile is 256 clocks of products and 192 of scaling and comparing, which two waves per SIMD
+// overlap; beside them a stage's norms, and at a block's beginning two dependent gathers with nothing to do meanwhile.
+// So a slice is long where there are tokens enough to fill the chip (dest_cost), its gathers run a round ahead of its products
+// through one barrier a stage, and its norms are one root per lane.  Destination and merge, slices of one round with the
+// rows requested between barriers before, now: 8 heads, 4032 centres, 4096 tokens 83.7 -> 60 us; 96 heads, 1968, 2000
+// 264 -> 194; 8 heads, 448, 512 by the product of cosines 31.3 -> 21.0, 4032, 4096 286 -> 166.
 // ------------------------------------------------------------------------------------
 template <typename T, int D, int kSim, int kTok>
-__global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
+__global__ __launch_bounds__(kMrgBlock, kSim == 2 ? 1 : 2) void dest_kernel(MergeArgs a)
 {
     constexpr int kStageRows = DestCfg<T>::kStageRows;
     constexpr int kFrags = Tile<T, D>::kFrags;
@@ -71,9 +77,12 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
     constexpr int kCpr = Tile<T, D>::kChunksPerRow;
     constexpr int kPerThread = kCpr * kStageRows / kMrgBlock;
     constexpr int kSrc = kSim == 2 ? 2 : 1;
+    constexpr int kDepth = kTok * kSrc * Tile<T, D>::kFrags > 8 ? 2 : kDestDepth;    // (as registers allow)
 
-    __shared__ __attribute__((aligned(16))) char lds[kSrc][kStageRows * kStride];
-    __shared__ __attribute__((aligned(16))) float lds_rn[kSrc][kStageRows];
+    // two stages, so that one barrier per stage is enough: whoever writes a stage has passed the barrier that
+    // its other readers reached after the one before it
+    __shared__ __attribute__((aligned(16))) char lds[2][kSrc][kStageRows * kStride];
+    __shared__ __attribute__((aligned(16))) float lds_rn[2][kSrc][kStageRows];
 
     const int N = a.seq_len, n_imp = a.n_imp, n_tbm = a.n_tbm;
     const int tiles = (n_tbm + kMrgWaves * 32 * kTok - 1) / (kMrgWaves * 32 * kTok);
@@ -87,37 +96,33 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
     if constexpr (kSim == 0) { src[0] = K; }
     else if constexpr (kSim == 1) { src[0] = V; }
     else { src[0] = K; src[1] = V; }
-    const int32_t* imp = a.imp_idx + (size_t)bkv * n_imp;
     const int32_t* tbm = a.tbm_idx + (size_t)bkv * n_tbm;
+    const int32_t* imp = n_imp ? a.imp_idx + (size_t)bkv * n_imp : tbm;   // (without centres the loads below still find a list)
 
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     const int col = lane & 31, half = lane >> 5;
     const int ti0 = (tile * kMrgWaves + wave) * (32 * kTok) + col;   // this lane's first TBM token (of kTok, 32 apart)
 
-    // A round is kDestDepth stages of kStageRows centres.  All of a round's centre positions,
-    // then all of its rows, are requested before the first stage is used: two global round
-    // trips per round, however many stages it has; the first round's share theirs with the tokens'.
-    int pos_pf[kDestDepth][kPerThread];
-    frag_t pf[kDestDepth][kSrc][kPerThread];
-    auto request_positions = [&](int r0) __attribute__((always_inline)) {
+    // A round is kDepth stages of kStageRows centres.  The first round's positions, then its rows, share their
+    // round trips with the tokens'; from then on a stage's registers take its rows of the next round as soon as
+    // they are in LDS, from positions that a round's work has had to arrive.
+    // (Past the slice's end: its last centre, whose products a NaN of a norm takes out.  No branch here, so that the
+    // loads stay in flight across the barriers.)
+    int pos_pf[kDepth][kPerThread];
+    frag_t pf[kDepth][kSrc][kPerThread];
+    auto request_positions = [&](int st, int r0) __attribute__((always_inline)) {
 #pragma unroll
-        for (int st = 0; st < kDestDepth; ++st)
-#pragma unroll
-            for (int i = 0; i < kPerThread; ++i) {
-                const int ci = r0 + st * kStageRows + (threadIdx.x + i * kMrgBlock) / kCpr;
-                pos_pf[st][i] = ci < c_end ? clamp_pos(imp[ci], N) : -1;
-            }
+        for (int i = 0; i < kPerThread; ++i)
+            pos_pf[st][i] = imp[min(r0 + st * kStageRows + (int)(threadIdx.x + i * kMrgBlock) / kCpr, max(c_end - 1, 0))];
     };
-    auto request_rows = [&]() __attribute__((always_inline)) {
+    auto request_rows = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-        for (int st = 0; st < kDestDepth; ++st)
+        for (int i = 0; i < kPerThread; ++i) {
+            const int cc = (threadIdx.x + i * kMrgBlock) % kCpr;
 #pragma unroll
-            for (int i = 0; i < kPerThread; ++i) {
-                const int cc = (threadIdx.x + i * kMrgBlock) % kCpr;
-#pragma unroll
-                for (int s = 0; s < kSrc; ++s)
-                    pf[st][s][i] = load_frag_or_zero(src[s], ((size_t)max(pos_pf[st][i], 0) * kCpr + cc) * 16, pos_pf[st][i] >= 0);
-            }
+            for (int s = 0; s < kSrc; ++s)
+                pf[st][s][i] = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(src[s]) + ((size_t)clamp_pos(pos_pf[st][i], N) * kCpr + cc) * 16);
+        }
     };
 
     frag_t bt[kTok][kSrc][kFrags], kt[kSim == 1 ? kTok : 1][kFrags];
@@ -125,7 +130,8 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
     int t_pos[kTok];
 #pragma unroll
     for (int tk = 0; tk < kTok; ++tk) t_pos[tk] = ti0 + 32 * tk < n_tbm ? clamp_pos(tbm[ti0 + 32 * tk], N) : 0;
-    request_positions(c_begin);
+#pragma unroll
+    for (int st = 0; st < kDepth; ++st) request_positions(st, c_begin);
 #pragma unroll
     for (int tk = 0; tk < kTok; ++tk) {                              // (a lane past the list's end: any row, its result is not kept)
 #pragma unroll
@@ -139,7 +145,12 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
                 kt[tk][f] = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(K) + (size_t)t_pos[tk] * Tile<T, D>::kRowBytes + f * 32 + half * 16);
         }
     }
-    request_rows();
+    constexpr int kRound = kDepth * kStageRows;
+#pragma unroll
+    for (int st = 0; st < kDepth; ++st) {
+        request_rows(st);
+        request_positions(st, c_begin + kRound);
+    }
 #pragma unroll
     for (int tk = 0; tk < kTok; ++tk) {
 #pragma unroll
@@ -169,77 +180,100 @@ __global__ __launch_bounds__(kMrgBlock) void dest_kernel(MergeArgs a)
     for (int tk = 0; tk < kTok; ++tk) { best[tk] = -INFINITY; arg[tk] = 0; no_factor |= t_rn[tk][0] == 0.f; }
     const bool each = kSrc == 1 && __any(no_factor);
 
-    for (int r0 = c_begin; r0 < c_end; r0 += kDestDepth * kStageRows) {
-        if (r0 != c_begin) { request_positions(r0); request_rows(); }
+    auto stage = [&](auto whole, int st, int c0) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole)::value;        // of a round that lies in the slice
+        const int b = st & 1;                                  // (a round is an even number of stages)
+        // the kCpr consecutive lanes that hold a row add up its squares; of the rows that they hold in turn, the
+        // i-th lane does the i-th one's norm
+        float ss[kSrc];
 #pragma unroll
-        for (int st = 0; st < kDestDepth; ++st) {
-            const int c0 = r0 + st * kStageRows;
-            if (c0 >= c_end) break;                            // block-uniform
-            __syncthreads();                                   // previous tile fully consumed
+        for (int i = 0; i < kPerThread; ++i) {
+            const int c = threadIdx.x + i * kMrgBlock;
+            const int row = c / kCpr, cc = c % kCpr;
 #pragma unroll
-            for (int i = 0; i < kPerThread; ++i) {
-                const int c = threadIdx.x + i * kMrgBlock;
-                const int row = c / kCpr, cc = c % kCpr;
-#pragma unroll
-                for (int s = 0; s < kSrc; ++s) {
-                    *reinterpret_cast<frag_t*>(lds[s] + row * kStride + cc * 16) = pf[st][s][i];
-                    // the kCpr consecutive lanes that hold one row add up its squares
-                    const float ss = group_sum<kCpr>(frag_sumsq<T>(pf[st][s][i]));
-                    if (cc == 0) lds_rn[s][row] = c0 + row < c_end ? row_inv_norm<T>(ss) : __builtin_nanf("");
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int rs = 0; rs < kStageRows / 32; ++rs) {
-                const int cbase = c0 + rs * 32;
-                if (cbase >= c_end) continue;                  // block-uniform
-                f32x16_t acc[kTok][kSrc];
-#pragma unroll
-                for (int s = 0; s < kSrc; ++s) {
-#pragma unroll
-                    for (int f = 0; f < kFrags; ++f) {
-                        const frag_t ac = *reinterpret_cast<const frag_t*>(lds[s] + (rs * 32 + col) * kStride + f * 32 + half * 16);
-#pragma unroll
-                        for (int tk = 0; tk < kTok; ++tk) {
-                            if (f == 0) mma_first<T>(acc[tk][s], ac, bt[tk][s][f]);
-                            else mma<T>(acc[tk][s], ac, bt[tk][s][f]);
-                        }
-                    }
-                }
-                if (each) {                                    // wave-uniform
-#pragma unroll
-                    for (int tk = 0; tk < kTok; ++tk)
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) acc[tk][0][r] *= t_rn[tk][0];
-                }
-                // Four operations per element: the winner is noted by its register (a constant) and the
-                // tile by one select per tile.
-                float before[kTok];
-                int reg[kTok];
-#pragma unroll
-                for (int tk = 0; tk < kTok; ++tk) { before[tk] = best[tk]; reg[tk] = 0; }
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    f32x4_t rn[kSrc];                          // NaN past the slice's end: never the larger one
-#pragma unroll
-                    for (int s = 0; s < kSrc; ++s)
-                        rn[s] = *reinterpret_cast<const f32x4_t*>(lds_rn[s] + rs * 32 + 8 * q4 + 4 * half);
-#pragma unroll
-                    for (int tk = 0; tk < kTok; ++tk)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            float sim = acc[tk][0][4 * q4 + e] * rn[0][e];
-                            if constexpr (kSrc == 2) sim = (sim * t_rn[tk][0]) * ((acc[tk][1][4 * q4 + e] * rn[1][e]) * t_rn[tk][1]);
-                            reg[tk] = sim > best[tk] ? 4 * q4 + e : reg[tk];
-                            best[tk] = fmaxf(best[tk], sim);   // (NaN counts as the smaller one)
-                        }
-                }
-#pragma unroll
-                for (int tk = 0; tk < kTok; ++tk)
-                    if (best[tk] > before[tk]) arg[tk] = cbase + acc_row(reg[tk], half);
+            for (int s = 0; s < kSrc; ++s) {
+                *reinterpret_cast<frag_t*>(lds[b][s] + row * kStride + cc * 16) = pf[st][s][i];
+                const float sum = group_sum<kCpr>(frag_sumsq<T>(pf[st][s][i]));
+                ss[s] = i == 0 || cc == i ? sum : ss[s];
             }
         }
+        {
+            const int i = threadIdx.x % kCpr, row = threadIdx.x / kCpr + i * (kMrgBlock / kCpr);
+            if (i < kPerThread) {
+#pragma unroll
+                for (int s = 0; s < kSrc; ++s) lds_rn[b][s][row] = c0 + row < c_end ? row_inv_norm<T>(ss[s]) : __builtin_nanf("");
+            }
+        }
+        if constexpr (kWhole) {
+            request_rows(st);
+            request_positions(st, c0 + 2 * kRound - st * kStageRows);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int rs = 0; rs < kStageRows / 32; ++rs) {
+            const int cbase = c0 + rs * 32;
+            if (!kWhole && cbase >= c_end) continue;       // block-uniform
+            f32x16_t acc[kTok][kSrc];
+#pragma unroll
+            for (int s = 0; s < kSrc; ++s) {
+#pragma unroll
+                for (int f = 0; f < kFrags; ++f) {
+                    const frag_t ac = *reinterpret_cast<const frag_t*>(lds[b][s] + (rs * 32 + col) * kStride + f * 32 + half * 16);
+#pragma unroll
+                    for (int tk = 0; tk < kTok; ++tk) {
+                        if (f == 0) mma_first<T>(acc[tk][s], ac, bt[tk][s][f]);
+                        else mma<T>(acc[tk][s], ac, bt[tk][s][f]);
+                    }
+                }
+            }
+            if (each) {                                    // wave-uniform
+#pragma unroll
+                for (int tk = 0; tk < kTok; ++tk)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[tk][0][r] *= t_rn[tk][0];
+            }
+            // Three operations per element: pairs of centres are compared with the best so far, the winning
+            // pair is noted by its first register (a constant) and that one's value, the tile by one select per tile.
+            float before[kTok], first[kTok];
+            int reg[kTok];
+#pragma unroll
+            for (int tk = 0; tk < kTok; ++tk) { before[tk] = best[tk]; first[tk] = 0.f; reg[tk] = 0; }
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                f32x4_t rn[kSrc];                          // NaN past the slice's end: never the larger one
+#pragma unroll
+                for (int s = 0; s < kSrc; ++s)
+                    rn[s] = *reinterpret_cast<const f32x4_t*>(lds_rn[b][s] + rs * 32 + 8 * q4 + 4 * half);
+#pragma unroll
+                for (int tk = 0; tk < kTok; ++tk)
+#pragma unroll
+                    for (int e = 0; e < 4; e += 2) {
+                        float sim[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            sim[i] = acc[tk][0][4 * q4 + e + i] * rn[0][e + i];
+                            if constexpr (kSrc == 2) sim[i] = (sim[i] * t_rn[tk][0]) * ((acc[tk][1][4 * q4 + e + i] * rn[1][e + i]) * t_rn[tk][1]);
+                        }
+                        const float top = fmaxf(fmaxf(sim[0], sim[1]), best[tk]);      // (NaN counts as the smallest)
+                        const bool won = top > best[tk];
+                        reg[tk] = won ? 4 * q4 + e : reg[tk];
+                        first[tk] = won ? sim[0] : first[tk];
+                        best[tk] = top;
+                    }
+            }
+#pragma unroll
+            for (int tk = 0; tk < kTok; ++tk)              // (the second of the pair only where it is the larger one)
+                if (best[tk] > before[tk]) arg[tk] = cbase + acc_row(reg[tk] + (first[tk] == best[tk] ? 0 : 1), half);
+        }
+    };
+    int r0 = c_begin;
+    for (; r0 + kRound <= c_end; r0 += kRound) {
+#pragma unroll
+        for (int st = 0; st < kDepth; ++st) stage(std::true_type{}, st, r0 + st * kStageRows);
     }
+#pragma unroll
+    for (int st = 0; st < kDepth; ++st)
+        if (r0 + st * kStageRows < c_end) stage(std::false_type{}, st, r0 + st * kStageRows);     // block-uniform
 #pragma unroll
     for (int tk = 0; tk < kTok; ++tk) {
         if constexpr (kSrc == 1)
@@ -775,36 +809,62 @@ hipError_t launch_expand(const ExpandArgs& a, bool f32, hipStream_t st)
     return launch_expand_t<bf16_t, 128>(a, st);
 }
 
-// How the centre list is cut for dest_kernel: rows per slice (whole rounds) and slices.
-void dest_slicing(int n_imp, bool f32, int* slice_rows, int* n_slices)
+// Centre slices per head at most; one round of centres is not cut (dest_combine_kernel would cost what that gains).
+int dest_max_slices(int n_imp, bool f32)
 {
-    const int round_rows = kDestDepth * (f32 ? DestCfg<float>::kStageRows : DestCfg<bf16_t>::kStageRows);
-    const int rounds = (max(n_imp, 1) + round_rows - 1) / round_rows;
-    const int per_slice = (rounds + kDestMaxSlices - 1) / kDestMaxSlices;
-    *slice_rows = per_slice * round_rows;
-    *n_slices = (rounds + per_slice - 1) / per_slice;
+    const int stage_rows = f32 ? DestCfg<float>::kStageRows : DestCfg<bf16_t>::kStageRows;
+    return n_imp <= kDestDepth * stage_rows ? 1 : min(kDestMaxSlices, (n_imp + stage_rows - 1) / stage_rows);
 }
 
-// Token tiles of 64 per wave read every gathered centre row less often; they take over where they still
-// make two blocks per compute unit.  Both sources of the product of
-// cosines leave registers for one, float32 rows likewise.
-template <typename T, int D, int kSim>
-static hipError_t launch_dest(const MergeArgs& a, hipStream_t st)
+// How the centre list is cut: the slices (of whole stages) whose blocks get through soonest, two blocks to a compute
+// unit; a block's beginning (two dependent gathers, its tokens' norms) counts as kDestStart stages.  Destination and merge,
+// us with 2 / 4 / 8 / 16 slices: 8 heads, 4032 centres, 4096 tokens 75.3 / 60.2 / 63.0 / 70.6; 32 heads of 64, 3968,
+// 8000: 426 / 436 / 458 / 506; one head, 2968, 750: 50.2 / 37.5 / 29.9 / 25.7.  The rule's choice: 60, 426 and 25.4; over
+// 17 sizes of 1 to 96 heads it is at most 3 % off the best.
+constexpr int kDestStart = 4, kDestResident = 512;
+static long long dest_cost(long long lists, int stages, int n_slices, int* per_slice)
 {
-    constexpr int kTile = kMrgWaves * 32;
-    auto per_head = [&](int tok) { return (long long)((a.n_tbm + kTile * tok - 1) / (kTile * tok)) * a.n_slices; };
-    if constexpr (sizeof(T) == 2 && kSim != 2) {
-        if (per_head(2) * a.bkv >= 512) {
-            const long long grid = head_grid(a.bkv, per_head(2));
-            if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((dest_kernel<T, D, kSim, 2>), dim3((unsigned)grid), dim3(kMrgBlock), 0, st, a);
-            return hipGetLastError();
+    *per_slice = (stages + n_slices - 1) / n_slices;
+    const long long blocks = lists * ((stages + *per_slice - 1) / *per_slice);
+    return (blocks + kDestResident - 1) / kDestResident * (*per_slice + kDestStart);
+}
+
+template <typename T, int D, int kSim, int kTok>
+static hipError_t launch_dest_t(MergeArgs& a, hipStream_t st)
+{
+    constexpr int kTile = kMrgWaves * 32 * kTok, kStageRows = DestCfg<T>::kStageRows;
+    const int tiles = (a.n_tbm + kTile - 1) / kTile, stages = (max(a.n_imp, 1) + kStageRows - 1) / kStageRows;
+    const int most = a.n_slices;
+    int per = stages;
+    if (most > 1) {
+        long long best = -1;
+        for (int s = 2; s <= most; ++s) {
+            int p;
+            const long long cost = dest_cost((long long)tiles * a.bkv, stages, s, &p);
+            if (best < 0 || cost < best) { best = cost; per = p; }
         }
     }
-    const long long grid = head_grid(a.bkv, per_head(1));
+    a.slice_rows = per * kStageRows;
+    a.n_slices = (stages + per - 1) / per;
+    const long long grid = head_grid(a.bkv, (long long)tiles * a.n_slices);
     if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((dest_kernel<T, D, kSim, 1>), dim3((unsigned)grid), dim3(kMrgBlock), 0, st, a);
+    hipLaunchKernelGGL((dest_kernel<T, D, kSim, kTok>), dim3((unsigned)grid), dim3(kMrgBlock), 0, st, a);
     return hipGetLastError();
+}
+
+// Token tiles of 64 per wave read every gathered centre row less often; they take over where, with rounds for slices,
+// they still make two blocks per compute unit (32 heads, 1436 centres, 1500 tokens: 60 us against 64 with tiles of 32;
+// 8 heads, 1984 and 1024: 27.3 against 26.7).  Both sources of the product of
+// cosines leave registers for one, float32 rows likewise.
+template <typename T, int D, int kSim>
+static hipError_t launch_dest(MergeArgs& a, hipStream_t st)
+{
+    if constexpr (sizeof(T) == 2 && kSim != 2) {
+        constexpr int kTile = kMrgWaves * 64, kRound = kDestDepth * DestCfg<T>::kStageRows;
+        const long long lists = (long long)((a.n_tbm + kTile - 1) / kTile) * a.bkv;
+        if (lists * min(kDestMaxSlices, (a.n_imp + kRound - 1) / kRound) >= kDestResident) return launch_dest_t<T, D, kSim, 2>(a, st);
+    }
+    return launch_dest_t<T, D, kSim, 1>(a, st);
 }
 
 template <typename T, int D>

@@ -371,9 +371,9 @@ MERGE_SHAPES = [
     (1, 2, 64, 700, 16, 48, 1.5),
     (2, 2, 128, 1500, 32, 256, 0.5),
     (1, 3, 128, 4096, 64, 128, 3.0),
-    (1, 1, 128, 3000, 32, 512, 2.0),       # centre list searched in 2 (bf16) / 4 (f32) slices
-    (1, 2, 128, 12000, 32, 1100, 5.0),     # 5 / 9 slices; 5500 to-be-merged tokens: two LDS pieces in the merge
-    (1, 1, 64, 9000, 16, 2300, 0.6),       # f32: 18 rounds of centres, two per slice
+    (1, 1, 128, 3000, 32, 512, 2.0),       # centre list searched in slices
+    (1, 2, 128, 12000, 32, 1100, 5.0),     # 5500 to-be-merged tokens: two LDS pieces in the merge
+    (1, 1, 64, 9000, 16, 2300, 0.6),       # several stages of centres per slice
 ]
 
 
@@ -580,6 +580,30 @@ def test_destinations_of_rows_without_a_norm(shape, similarity, mode):
     np.testing.assert_allclose(sim[-1, rest], plain_sim[-1, rest], rtol=2.0 ** -22)     # two roundings, in another order
     assert (where[-1, rest] != plain_dest[-1, rest]).sum() <= max(1, n_tbm // 1000)     # ties within that rounding
     np.testing.assert_array_equal(sim[:-1], plain_sim[:-1])
+
+
+@pytest.mark.parametrize("mode", MODES)
+@pytest.mark.parametrize("similarity", [B.EMS_SIM_KEY, B.EMS_SIM_KEY_VALUE])
+@pytest.mark.parametrize("heads,n_imp,n_tbm", [(1, 1, 33), (2, 65, 129), (1, 256, 40), (1, 257, 40), (3, 513, 385), (2, 1030, 1000),
+                                               (16, 1090, 2100), (1, 4097, 130)])
+def test_destinations_of_equal_centres(heads, n_imp, n_tbm, similarity, mode):
+    """One-hot rows: products of 1 and 0, so a token's centres tie bit for bit and the lowest of them is its
+    destination, whatever the slices, stages and pairs that the search cuts the centres into (their last ones in part)."""
+    d, w = 64, 8
+    n = n_imp + n_tbm + w
+    p = B.EmsParams(1, heads, heads, d, n, w, n_imp + w, merge_ratio=(n_tbm + 0.5) / (n_imp + w), tau=-2.0, dtype=mode)
+    assert B.ems_partition_sizes(p) == (n_imp, n_tbm)
+    rng = np.random.default_rng(n)
+    hot = rng.integers(0, d, (heads, n))
+    hot[:, :n_imp // 2] %= d // 2                        # the higher half first occurs far down the list
+    order = np.stack([rng.permutation(n - w) for _ in range(heads)])
+    imp, tbm = np.sort(order[:, :n_imp]), np.sort(order[:, n_imp:])
+    k = torch.nn.functional.one_hot(torch.from_numpy(hot), d)[None].to(p.torch_dtype).cuda()
+    out = B.ems_evict_merge_variant(p, similarity, k, k, None, *(torch.from_numpy(x.astype(np.int32))[None].cuda() for x in (imp, tbm)))
+    rows = np.arange(heads)[:, None]
+    same = hot[rows, tbm][:, :, None] == hot[rows, imp][:, None, :]
+    np.testing.assert_array_equal(out["tbm_dest"].cpu().numpy()[0], same.argmax(-1))      # (none alike: 0 with all, the first)
+    np.testing.assert_array_equal(out["tbm_sim"].cpu().numpy()[0], same.any(-1).astype(np.float32))
 
 
 @pytest.mark.parametrize("mode", MODES)

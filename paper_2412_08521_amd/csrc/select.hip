@@ -35,6 +35,18 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
+// Inclusive prefix sum of one int per lane over a wave (row shifts, then the rows' ends handed on: no trip through LDS).
+__device__ __forceinline__ int wave_incl_scan(int v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);      // row_shr:1, 2, 4, 8 inside each row of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);      // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 // Exclusive prefix sum of one int per thread over a block of kThreads (a multiple of 64, at most
 // 1024); `total` gets the block's sum.  `sm` holds kThreads / 64 + 1 ints.  Every thread calls it.
 template <int kThreads>
@@ -42,12 +54,7 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sm, int& total)
 {
     constexpr int kW = kThreads / kWave;
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int u = __shfl_up(incl, o);
-        if (lane >= o) incl += u;
-    }
+    const int incl = wave_incl_scan(v);
     __syncthreads();                                      // sm may still be read from an earlier call
     if (lane == kWave - 1) sm[wave] = incl;
     __syncthreads();
@@ -274,12 +281,11 @@ __global__ __launch_bounds__(kChunkBlock) void select_gather_kernel(SelectArgs a
 // Steps 3 and 4 of the header comment on keys in LDS: a block of kSelBlock threads, wave w taking the
 // ordinals [w * 64 * items, (w + 1) * 64 * items) of `count` candidates in position order (items <= 32),
 // lane l the ordinals base + i * 64.  position(ordinal) is the sequence position of a candidate.
-// kItems: `items` where it is fixed (the loops are then unrolled: 16.7 us against 17.2 rolled, 32 heads of 4096
-// tokens, calls in a row), else 0 (the candidates of a 16384-token prompt, the kernel under a trace when that was
+// kItems: `items` where it is fixed (the loops are then unrolled), else 0 (the candidates of a 16384-token prompt, the kernel under a trace when that was
 // chosen: 12.4 us rolled, 15.3 unrolled for the most there can be).
 // Every digit has kCopies counters and a lane counts on number lane % kCopies: equal keys would otherwise
-// queue for one LDS address (calls in a row, 4 counters / 1: 32 heads of 4096 equal scores 18.3 / 27.8 us, of 4096
-// different ones 16.7 / 17.8, 8 heads of 16384 equal ones 52.8 / 92.0; 4 is what LDS has room for).
+// queue for one LDS address (calls in a row when that was chosen, 4 counters / 1: 32 heads of 4096 equal scores 18.3 / 27.8 us,
+// of 4096 different ones 16.7 / 17.8, 8 heads of 16384 equal ones 52.8 / 92.0; 4 is what LDS has room for).
 constexpr int kCopies = 4;
 template <int kItems, typename Position>
 __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items, int count, const SelectArgs& a, Position position)
@@ -287,22 +293,22 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
     constexpr int kUnroll = kItems ? kItems : 1;
     const int items = kItems ? kItems : n_items;
     __shared__ __attribute__((aligned(16))) int hist[2][256 * kCopies];
-    __shared__ int suffix[2][257];
-    __shared__ int scan_sm[kSelWaves][2];
-    __shared__ int wave_tot[8];
+    __shared__ int scan_sm[2][kSelWaves][2];
     __shared__ uint32_t sel_prefix[2];
     __shared__ int sel_rem[2];
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const int base = wave * kWave * items + lane;
 
-    // ---- 3. radix select of two ranks (1-based, counted from the largest key)
+    // ---- 3. radix select of two ranks (1-based, counted from the largest key).  A digit is two barriers: all waves
+    // count; then one wave per cut (one for both while they share their prefix) scans its 256 counters, four digits a lane,
+    // finds its own and clears them for the next digit.
     if (tid < 2) {
         sel_prefix[tid] = 0u;
         sel_rem[tid] = tid == 0 ? a.n_imp : a.n_imp + a.n_tbm;
     }
+    for (int i = tid; i < 512 * kCopies; i += kSelBlock) (&hist[0][0])[i] = 0;
+    __syncthreads();
     for (int shift = 24; shift >= 0; shift -= 8) {
-        for (int i = tid; i < 512 * kCopies; i += kSelBlock) (&hist[0][0])[i] = 0;
-        __syncthreads();
         const uint32_t p0 = sel_prefix[0], p1 = sel_prefix[1];
         const bool same_prefix = shift == 24 || p0 == p1;
 #pragma unroll kUnroll
@@ -316,38 +322,30 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
             if (!same_prefix && cand && hi == p1) atomicAdd(&hist[1][at], 1);
         }
         __syncthreads();
-        int incl = 0;
-        if (tid < 512) {
-            const int* counts = hist[same_prefix ? 0 : tid >> 8] + (255 - (tid & 255)) * kCopies;   // one count serves both cuts
+        if (wave == 0 || (wave == 1 && !same_prefix)) {              // wave-uniform
+            static_assert(kCopies == 4, "a digit's counters are read at once");
+            int4* counts = reinterpret_cast<int4*>(hist[wave]);
+            int n[4], sum = 0;
 #pragma unroll
-            for (int c = 0; c < kCopies; ++c) incl += counts[c];
-#pragma unroll
-            for (int o = 1; o < kWave; o <<= 1) {
-                const int u = __shfl_up(incl, o);
-                if (lane >= o) incl += u;
+            for (int q = 0; q < 4; ++q) {                            // digits 255 - 4 lane downwards
+                const int4 c = counts[255 - 4 * lane - q];
+                n[q] = (c.x + c.y) + (c.z + c.w);
+                sum += n[q];
             }
-            if (lane == kWave - 1) wave_tot[wave] = incl;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) counts[255 - 4 * lane - q] = make_int4(0, 0, 0, 0);
+            const int before = wave_incl_scan(sum) - sum;            // keys with a higher digit than this lane's
+            for (int t = wave; t < (same_prefix ? 2 : wave + 1); ++t) {
+                const int rem = sel_rem[t];
+                int above = before, digit = -1, left = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (above < rem && above + n[q] >= rem) { digit = 255 - 4 * lane - q; left = rem - above; }
+                    above += n[q];
+                }
+                if (digit >= 0) { sel_prefix[t] = ((t ? p1 : p0) << 8) | (uint32_t)digit; sel_rem[t] = left; }      // one lane
+            }
         }
-        __syncthreads();
-        if (tid < 512) {
-            const int t = tid >> 8;
-            for (int w = t * 4; w < wave; ++w) incl += wave_tot[w];
-            suffix[t][255 - (tid & 255)] = incl;
-            if ((tid & 255) == 0) suffix[t][256] = 0;
-        }
-        __syncthreads();
-        bool mine = false;
-        uint32_t new_prefix = 0u;
-        int new_rem = 0;
-        if (tid < 512) {
-            const int t = tid >> 8, d = tid & 255;
-            const int rem = sel_rem[t];
-            mine = suffix[t][d] >= rem && suffix[t][d + 1] < rem;
-            new_prefix = (sel_prefix[t] << 8) | (uint32_t)d;
-            new_rem = rem - suffix[t][d + 1];
-        }
-        __syncthreads();
-        if (mine) { sel_prefix[tid >> 8] = new_prefix; sel_rem[tid >> 8] = new_rem; }
         __syncthreads();
     }
     const uint32_t T1 = sel_prefix[0], T2 = sel_prefix[1];
@@ -360,12 +358,14 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
     auto below_count = [&](unsigned long long m) {                 // set bits of m below this lane
         return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
     };
-    auto wave_prefix = [&](int mine_, int& before) {               // exclusive scan over waves
+    auto wave_prefix = [&](int (&sm)[kSelWaves][2], int x, int y, int& before_x, int& before_y) {      // exclusive scans over waves
+        if (lane == 0) { sm[wave][0] = x; sm[wave][1] = y; }
         __syncthreads();
-        if (lane == 0) scan_sm[wave][0] = mine_;
-        __syncthreads();
-        before = 0;
-        for (int w = 0; w < wave; ++w) before += scan_sm[w][0];
+        static_assert(kSelWaves <= kWave, "a lane per wave");
+        before_x = lane < wave ? sm[lane][0] : 0;
+        before_y = lane < wave ? sm[lane][1] : 0;
+        before_x = __builtin_amdgcn_readlane(wave_incl_scan(before_x), kWave - 1);
+        before_y = __builtin_amdgcn_readlane(wave_incl_scan(before_y), kWave - 1);
     };
     int eq1 = 0, eq2 = 0;
 #pragma unroll kUnroll
@@ -376,8 +376,7 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
         eq2 += __popcll(__ballot(cand && key == T2));
     }
     int r1, r2;
-    wave_prefix(eq1, r1);
-    wave_prefix(eq2, r2);
+    wave_prefix(scan_sm[0], eq1, eq2, r1, r2);
     unsigned imp_mask = 0u, tbm_mask = 0u;        // bit i: item i; items <= 32
     int c_imp = 0, c_tbm = 0;
 #pragma unroll kUnroll
@@ -399,8 +398,7 @@ __device__ __forceinline__ void select_ranked(const uint32_t* keys, int n_items,
         c_tbm += __popcll(__ballot(tt));
     }
     int bi, bt;
-    wave_prefix(c_imp, bi);
-    wave_prefix(c_tbm, bt);
+    wave_prefix(scan_sm[1], c_imp, c_tbm, bi, bt);
     int32_t* imp = a.imp_idx + (size_t)blockIdx.x * a.n_imp;
     int32_t* tbm = a.tbm_idx ? a.tbm_idx + (size_t)blockIdx.x * a.n_tbm : nullptr;
 #pragma unroll kUnroll
@@ -457,7 +455,7 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
     };
 
     // A list that fits (all but extreme ties) goes to LDS once, in position order: the digit passes and the
-    // three walks below would each go back to memory for it (8 heads, 8200 candidates each, under a trace: 45 us, now 24).
+    // three walks below would each go back to memory for it (8 heads, 8200 candidates each, under a trace: 45 us, then 24, now 22 with fewer barriers a digit).
     int top_step = 1;
     while (top_step * 2 < n_chunks) top_step *= 2;
     if (M <= kFinishKeys) {                                // block-uniform
@@ -629,28 +627,34 @@ __global__ __launch_bounds__(kSelBlock) void select_finish_kernel(SelectArgs a)
 // Same computation with the ranking keys held in LDS.  Wave w owns the positions
 // [w * 64 * kItems, (w + 1) * 64 * kItems); lane l holds positions base + i * 64 + l, so
 // every load and store is coalesced and, after the keys are formed, nothing depends on
-// memory latency any more.  Used when the sequence fits (N <= 1024 * kItems).
+// memory latency any more.  kItems is as few as the sequence allows (N <= 1024 * kItems); the scores are read and
+// summed in the same way for kLoad, which fixes the order of the factor's sums for a range of N.
+// One compute unit per head and a chain of latencies bound it (launch, scores, factor, pooling, four digits of two
+// barriers, two walks in position order): under a trace, with eight positions a thread for everything over 2048 and six barriers
+// a digit 10.2 us at 1024 tokens, 16.2 at 4096, 16.7 at 5003, 18.5 at 8000; with two barriers a digit 7.5, 14.2, -, 17; with only
+// the positions there are 6.9, 11.0, 11.8, 16.
 // ------------------------------------------------------------------------------------
-template <int kItems>
+template <int kLoad, int kItems>
 __global__ __launch_bounds__(kSelBlock) void select_reg_kernel(SelectArgs a)
 {
     __shared__ float red[kSelWaves][2];
     constexpr int kHalo = 31;                             // the widest window reaches 31 positions to either side
     __shared__ uint32_t keys[kSelBlock * kItems];
-    __shared__ float comb[kHalo + kSelBlock * kItems + kHalo];   // Eq. 2 vector before pooling, zeros around it
+    __shared__ float comb[kHalo + kSelBlock * kLoad + kHalo];   // Eq. 2 vector before pooling, zeros around it
     const int N = a.seq_len, Nc = N - a.window;
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     const float* glo = a.s_glo + (size_t)blockIdx.x * N;
     const float* loc = a.s_loc + (size_t)blockIdx.x * N;
     float* s_out = a.s_gl_opt ? a.s_gl_opt + (size_t)blockIdx.x * N : nullptr;
     const int base = wave * kWave * kItems + lane;        // position of item i: base + 64 i
+    const int load = wave * kWave * kLoad + lane;         // of the i-th score read: load + 64 i
 
     // ---- 1. Eq. 2 alignment factor (sum(s_loc)/N) / (sum(s_glo)/N)
-    float g[kItems], l[kItems];
+    float g[kLoad], l[kLoad];
     float sg = 0.f, sl = 0.f;
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int j = base + i * kWave;
+    for (int i = 0; i < kLoad; ++i) {
+        const int j = load + i * kWave;
         g[i] = j < N ? glo[j] : 0.f;
         l[i] = j < N ? loc[j] : 0.f;
         sg += g[i]; sl += l[i];
@@ -665,11 +669,11 @@ __global__ __launch_bounds__(kSelBlock) void select_reg_kernel(SelectArgs a)
     // ---- 2. element-wise max, staged through LDS so that the pooling window can reach into the
     // neighbouring lanes' and waves' positions (by way of the workspace: 2.5 us more)
 #pragma unroll
-    for (int i = 0; i < kItems; ++i) {
-        const int j = base + i * kWave;
+    for (int i = 0; i < kLoad; ++i) {
+        const int j = load + i * kWave;
         comb[kHalo + j] = j < N ? fmaxf(g[i] * align, l[i]) : 0.f;
     }
-    if (tid < kHalo) { comb[tid] = 0.f; comb[kHalo + kSelBlock * kItems + tid] = 0.f; }
+    if (tid < kHalo) { comb[tid] = 0.f; comb[kHalo + kSelBlock * kLoad + tid] = 0.f; }
     __syncthreads();
     const int half = (a.pool_kernel - 1) / 2;
     const float div = (float)a.pool_kernel;
@@ -693,17 +697,25 @@ __global__ __launch_bounds__(kSelBlock) void select_reg_kernel(SelectArgs a)
     select_ranked<kItems>(keys, kItems, Nc, a, [](int j) { return j; });
 }
 
-template <int kItems>
+template <int kLoad, int kItems>
 static hipError_t launch_select_reg(const SelectArgs& a, hipStream_t st)
 {
-    hipLaunchKernelGGL(select_reg_kernel<kItems>, dim3((unsigned)a.bkv), dim3(kSelBlock), 0, st, a);
+    hipLaunchKernelGGL((select_reg_kernel<kLoad, kItems>), dim3((unsigned)a.bkv), dim3(kSelBlock), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t st)
 {
-    if (a.seq_len <= kSelBlock * 2) return launch_select_reg<2>(a, st);
-    if (a.seq_len <= kSelBlock * 8) return launch_select_reg<8>(a, st);
+    switch ((a.seq_len + kSelBlock - 1) / kSelBlock) {
+    case 1: return launch_select_reg<2, 1>(a, st);
+    case 2: return launch_select_reg<2, 2>(a, st);
+    case 3: return launch_select_reg<8, 3>(a, st);
+    case 4: return launch_select_reg<8, 4>(a, st);
+    case 5: return launch_select_reg<8, 5>(a, st);
+    case 6: return launch_select_reg<8, 6>(a, st);
+    case 7: return launch_select_reg<8, 7>(a, st);
+    case 8: return launch_select_reg<8, 8>(a, st);
+    }
     const dim3 grid((unsigned)select_chunks(a.seq_len), (unsigned)a.bkv);
     const size_t lds = sizeof(float) * (size_t)(kChunk + a.pool_kernel - 1);
     hipLaunchKernelGGL(select_sums_kernel, grid, dim3(kChunkBlock), 0, st, a);

@@ -347,6 +347,13 @@ def test_select_matches_oracle(shape):
         assert is_sorted_unique(imp[0, h]) and (tbm.shape[-1] == 0 or is_sorted_unique(tbm[0, h]))
 
 
+@pytest.mark.parametrize("n", [1023, 1025, 2048, 2049, 3071, 3073, 4096, 4097, 5120, 5121, 6144, 6145, 7168, 7169, 8191])
+def test_select_every_item_count(n):
+    """One to eight positions per thread of the one-block kernel, its last ones in use and not."""
+    test_select_matches_oracle((2, n, 32, 300, 0.75, 7))
+    test_select_exact_ties_rank_by_position(n, 4)
+
+
 @pytest.mark.parametrize("levels", [4, 1])
 @pytest.mark.parametrize("n", [5000, 20000])
 def test_select_exact_ties_rank_by_position(n, levels):

@@ -162,8 +162,8 @@ MergePlan plan_merge(const ems_params* p)
     int n_imp, n_tbm;
     partition_sizes(p, &n_imp, &n_tbm);
     MergePlan m{};
-    m.n_slices = ems::dest_max_slices(n_imp, p->dtype == EMS_F32);
     const size_t bkv = (size_t)p->batch * p->kv_heads;
+    m.n_slices = ems::dest_max_slices(n_imp, n_tbm, (int)bkv, p->dtype == EMS_F32);
     const size_t part = m.n_slices > 1 ? align_up(4 * bkv * m.n_slices * (size_t)n_tbm) : 0;
     m.off_norm = 0;
     m.off_best = align_up(sizeof(float) * bkv * (size_t)(n_imp + n_tbm));

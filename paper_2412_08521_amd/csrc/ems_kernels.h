@@ -180,6 +180,6 @@ hipError_t launch_score_pass1(ScoreArgs& a, bool f32, hipStream_t st);   // rows
 hipError_t launch_score_pass2(const ScoreArgs& a, bool f32, hipStream_t st);   // column sums
 hipError_t launch_select(const SelectArgs& a, hipStream_t st);
 hipError_t launch_evict_merge(const MergeArgs& a, bool f32, hipStream_t st);
-int dest_max_slices(int n_imp, bool f32);
+int dest_max_slices(int n_imp, int n_tbm, int bkv, bool f32);
 
 }  // namespace ems

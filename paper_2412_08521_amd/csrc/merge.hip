@@ -809,11 +809,23 @@ hipError_t launch_expand(const ExpandArgs& a, bool f32, hipStream_t st)
     return launch_expand_t<bf16_t, 128>(a, st);
 }
 
-// Centre slices per head at most; one round of centres is not cut (dest_combine_kernel would cost what that gains).
-int dest_max_slices(int n_imp, bool f32)
+// Centre slices per head at most: whole rounds of centres, or, of up to 16 rounds, stages where all blocks are resident even
+// so.  The winners of those take 512 KB at most and the norms beside them (256 heads of 4096 centres at most) 4.3 MB, so
+// nothing that fitted the fixed scratch of the call without a workspace stops fitting it.  One round is not cut
+// (dest_combine_kernel would cost what that gains).
+constexpr int kDestResident = 512;
+int dest_max_slices(int n_imp, int n_tbm, int bkv, bool f32)
 {
     const int stage_rows = f32 ? DestCfg<float>::kStageRows : DestCfg<bf16_t>::kStageRows;
-    return n_imp <= kDestDepth * stage_rows ? 1 : min(kDestMaxSlices, (n_imp + stage_rows - 1) / stage_rows);
+    const int stages = (n_imp + stage_rows - 1) / stage_rows, rounds = (stages + kDestDepth - 1) / kDestDepth;
+    if (rounds <= 1) return 1;
+    if (rounds > kDestMaxSlices) {
+        const int per_slice = (rounds + kDestMaxSlices - 1) / kDestMaxSlices;
+        return (rounds + per_slice - 1) / per_slice;
+    }
+    constexpr int kTile = kMrgWaves * 32;
+    const long long lists = std::max(1ll, (long long)((n_tbm + kTile - 1) / kTile) * bkv);
+    return std::max(rounds, (int)std::min<long long>(std::min(kDestMaxSlices, stages), kDestResident / lists));
 }
 
 // How the centre list is cut: the slices (of whole stages) whose blocks get through soonest, two blocks to a compute
@@ -821,7 +833,7 @@ int dest_max_slices(int n_imp, bool f32)
 // us with 2 / 4 / 8 / 16 slices: 8 heads, 4032 centres, 4096 tokens 75.3 / 60.2 / 63.0 / 70.6; 32 heads of 64, 3968,
 // 8000: 426 / 436 / 458 / 506; one head, 2968, 750: 50.2 / 37.5 / 29.9 / 25.7.  The rule's choice: 60, 426 and 25.4; over
 // 17 sizes of 1 to 96 heads it is at most 3 % off the best.
-constexpr int kDestStart = 4, kDestResident = 512;
+constexpr int kDestStart = 4;
 static long long dest_cost(long long lists, int stages, int n_slices, int* per_slice)
 {
     *per_slice = (stages + n_slices - 1) / n_slices;

@@ -85,6 +85,28 @@ def test_select_and_merge_argument_errors(lib, p):
         B.ems_partition_sizes(p)
 
 
+@pytest.mark.parametrize("mode", [B.EMS_BF16, B.EMS_F32])
+def test_evict_merge_scratch_of_finer_slices(lib, mode):
+    """The centre list may be cut finer than a round (256 or 128 centres) a slice; no size that fits the fixed scratch
+    of ems_evict_merge_static with slices of whole rounds may need more than that for it."""
+    up = lambda x: -(-x // 256) * 256  # noqa: E731
+    finer = 0
+    for bkv in (1, 3, 8, 31, 96, 255, 256, 1024):
+        for n_imp in (1, 128, 129, 256, 257, 1000, 2048, 2049, 4096, 4097, 9000, 300000):
+            for n_tbm in (0, 1, 100, 128, 129, 1000, 5000, 60000):
+                p = B.EmsParams(1, bkv, bkv, 64, 1 << 20, 8, n_imp + 8, merge_ratio=(n_tbm + 0.25) / (n_imp + 8), dtype=mode)
+                assert B.ems_partition_sizes(p) == (n_imp, n_tbm)
+                rounds = -(-n_imp // (128 if mode == B.EMS_F32 else 256))
+                per = -(-rounds // 16)
+                slices = -(-rounds // per)
+                whole = up(4 * bkv * (n_imp + n_tbm)) + (2 * up(4 * bkv * slices * n_tbm) if slices > 1 else 0)
+                need = B.ems_workspace_bytes(p)[2]
+                assert need >= whole
+                assert need <= whole + 2 * 256 or need <= 8 << 20
+                finer += need > whole + 2 * 256
+    assert finer
+
+
 def test_null_pointers_and_workspace_errors(lib):
     p = _bad()
     cp = p.c()

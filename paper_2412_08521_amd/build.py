@@ -14,7 +14,7 @@ CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libems_hip.so")
 SOURCES = ["ems_api.hip", "score.hip", "select.hip", "merge.hip", "decode.hip", "stats.hip"]
-HEADERS = ["ems_common.h", "ems_kernels.h", "ems_rows.h", "ems_stream.h", os.path.join("..", "..", "include", "ems.h")]
+HEADERS = ["ems_common.h", "ems_kernels.h", "ems_red_weights.h", "ems_rows.h", "ems_stream.h", os.path.join("..", "..", "include", "ems.h")]
 # the benchmark's ceiling measurements: a library of their own, outside the product's interface
 PROBE_DIR = os.path.join(_HERE, "bench_probe")
 PROBE_LIB = os.path.join(_HERE, "libems_probe.so")

@@ -16,6 +16,7 @@
 // redundancy_count_kernel  tokens whose best redundancy reaches tau, per head.
 #include "ems_common.h"
 #include "ems_kernels.h"
+#include "ems_red_weights.h"
 #include "ems_rows.h"
 #include "ems_stream.h"
 
@@ -411,7 +412,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kProducts = 8 * kFrags, kSquares = 4 * kFrags, kTicks = 24;
 
     __shared__ __attribute__((aligned(1024))) char lds[kRing][2][kStageBytes];
-    __shared__ __attribute__((aligned(16))) float lds_w[2][kStreamRows + kWave];   // (behind the rows: where lanes that have none write)
+    static_assert(RedWeights::sound() && RedWeights::kRows == kStreamRows && RedWeights::kLanes == kWave, "the weights' places");
+    __shared__ __attribute__((aligned(16))) float lds_w[2][RedWeights::kFloats];
     __shared__ float lds_t[3][kTokens];                     // reciprocal norms of the wave's own tokens: key, value, both
 
     const int N = a.seq_len;
@@ -545,8 +547,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         // (By v_dot2, 64 of them, which wait for the matrix pipe to drain and hold up its next instruction, 16
         // clocks each time: 16384 tokens, 8 heads of 128, 505 us.)
         f32x4_t square[2][2];                               // [keys, values][streamed rows]
-        const bool diag = group == col / 4;                 // this lane has row col's, in register col % 4
-        const int w_at = diag ? col : kStreamRows + lane;
+        const bool diag = RedWeights::holds(lane);          // this lane has row col's, in register col % 4
+        const int w_at = RedWeights::slot(lane);
         // the pipeline starts on a subtile of zeros whose products are no redundancies
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -611,7 +613,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     if (part == 3) p[i] = p[i] > 0.f ? __builtin_amdgcn_rsqf(p[i]) : 0.f;
                 }
                 // written by accumulator column, read back by row
-                if (n == 8) { lds_w[u & 1][w_at] = p[0]; lds_w[u & 1][w_at + 16] = p[1]; }
+                if (n == 8) { lds_w[u & 1][w_at] = p[0]; lds_w[u & 1][w_at + RedWeights::kSecond] = p[1]; }
                 if (n == 9) {
 #pragma unroll
                     for (int i2 = 0; i2 < 2; ++i2) w[u & 1][i2] = *reinterpret_cast<const f32x4_t*>(&lds_w[u & 1][16 * i2 + 4 * group]);

@@ -545,7 +545,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         f32x4_t w[2][2];                                    // the weights by accumulator row, of this stage and the last
         // A row's squares are the diagonal of its tile's product with itself: 16 matrix instructions a stage.
         // (By v_dot2, 64 of them, which wait for the matrix pipe to drain and hold up its next instruction, 16
-        // clocks each time: 16384 tokens, 8 heads of 128, 505 us.)
+        // clocks each time: 16384 tokens, 8 heads of 128, 505 us.)  Subnormal squares are kept either way: with square sums of
+        // 2^-128 to 2^-136 the redundancies are as close to 64 bits as the block form's.
         f32x4_t square[2][2];                               // [keys, values][streamed rows]
         const bool diag = RedWeights::holds(lane);          // this lane has row col's, in register col % 4
         const int w_at = RedWeights::slot(lane);

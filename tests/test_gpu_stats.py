@@ -199,3 +199,36 @@ def test_redundancy_on_the_diagonal_of_the_stream(rest, d):
     and where earlier stages run into it.  Tolerance as above."""
     for bh, n in ((1, 384 + rest), (9, 1408 + rest)):
         test_redundancy_edges((bh, n), d, "plain")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("exponent", [-62, -64, -66, -68])
+@pytest.mark.parametrize("tiny", ["some keys", "every key", "every value"])
+def test_redundancy_of_rows_with_subnormal_squares(tiny, exponent, d):
+    """Streamed rows whose square sums are below the normal range (2^-128 to 2^-136; the other rows' are as large, so
+    that the products of both norms stay where the short form is used): they keep their redundancies, nothing is flushed
+    to zero.  Tolerance: of the d products of a dot or a square sum each loses up to 2^-149, the smallest subnormal; a
+    cosine takes one dot's error and half of two square sums'; 2e-5 as above."""
+    bh, n = 2, 900
+    _log("redundancy of subnormal squares", tiny, exponent, d)
+    gen = torch.Generator().manual_seed(d - exponent)
+    k, v = (torch.randn((1, bh, n, d), generator=gen, dtype=torch.float64) for _ in range(2))
+    for t in range(5, n, 7):
+        for x in (k, v):
+            x[:, :, t] = x[:, :, t // 2] + 0.1 * x[:, :, t]
+    rows = slice(1, None, 3) if tiny == "some keys" else slice(None)
+    for x, e in ((k, exponent), (v, min(-exponent, 62))):
+        x /= x.norm(dim=-1, keepdim=True)
+        x[:, :, rows] *= 2.0 ** e
+    if tiny == "every value":
+        k, v = v, k
+    k, v = k.to(torch.bfloat16), v.to(torch.bfloat16)
+    _, best = B.ems_redundancy_rate(B.EmsParams(1, bh, bh, d, n, 1, tau=0.6), k.cuda(), v.cuda())
+    exact = 1.0
+    for x in (k.double(), v.double()):
+        x = x / x.norm(dim=-1, keepdim=True)
+        exact = exact * (x @ x.transpose(-1, -2))
+    exact = exact.masked_fill(torch.ones(n, n).triu().bool(), -np.inf).amax(-1)
+    assert float(exact.max()) > 0.9
+    np.testing.assert_allclose(best.cpu().double().numpy()[..., 1:], exact.numpy()[..., 1:], rtol=0,
+                               atol=2e-5 + 2 * d * 2.0 ** (-149 - 2 * exponent))

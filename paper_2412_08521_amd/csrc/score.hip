@@ -1045,9 +1045,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int t_diag = max(t0, q_base / kStreamRows);
     const int n_edge = max(t1 - t_diag, 0);
     // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form, so
-    // that the pipelined rest is whole trips of the loop.  A stage of float32 gains less by the pipeline than it costs
-    // to start it for a few (600 rows, a stretch of four: 26.8 us without, 29.7 with).
-    constexpr int kFewest = kPairs == 1 ? 6 : 0;
+    // that the pipelined rest is whole trips of the loop.  In float32 starting the pipeline costs more than it gains for
+    // up to four stages and less from five on (us of the pass where a part has that many, online / pipelined: 8 heads over 2
+    // of 128, 600 rows, four 26.2 / 29.2; 1400, five 33.5 / 33.1; of 64, 600, four 16.8 / 17.8; 1400, five 20.9 / 20.1).
+    constexpr int kFewest = kPairs == 1 ? 5 : 0;
     const int n_int_all = max(min(t1, t_diag) - t0, 0);
     const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all < kFewest ? n_int_all : n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
     const int n_int = n_int_all - n_lead;                        // a multiple of kUnroll, >= 0

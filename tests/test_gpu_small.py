@@ -94,6 +94,13 @@ def test_score_even_deal(shape, mode):
     np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [600, 1300, 1400, 1470, 1500, 1660, 1750, 1850])
+def test_score_short_float32_stretches(n, d):
+    """Stretches of four to eight stages (8 heads over 2), the shortest of them without the pipelined loop."""
+    test_score_even_deal((1, 8, 2, d, n, 40), B.EMS_F32)
+
+
 @pytest.mark.parametrize("mode,shape,forms", [
     (B.EMS_BF16, (1, 256, 8, 64, 2040, 100), ("block", "deal")),     # two row tiles per wave, one pair per XCD
     (B.EMS_BF16, (1, 64, 2, 128, 8177, 90), ("block", "deal")),      # the q-heads of a row tile together

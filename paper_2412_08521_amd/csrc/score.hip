@@ -320,12 +320,14 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 // rows of every q-head of the group (second), a running sum is added to the sum of those before it, so that
 // small weights are not lost against a large sum.  (1 x 4 heads over 1, 8192: column sums off by 3.8e-7 without, 0.7e-7.)
 constexpr int kFoldKeys = 2048, kFoldRows = 512;
-template <typename T> struct Stream { static constexpr int kSub = 8; };
-template <> struct Stream<float> { static constexpr int kSub = 2; };
-// (512-byte rows: two 16 KB stages a wave, so that the rings of four waves fit a compute unit's LDS; a stage's 8192 clocks
-// of matrix instructions hide the next one's DMA.  8 heads over 2, 3000 rows, head size 128: a pass 94-108 us, 119-125
-// with three stages and thus three waves; 32 heads over 8, 6000 rows: 1242-1289 against 1639-1675.)
-template <typename T, int D> struct Ring { static constexpr int kStages = Tile<T, D>::kRowBytes == 512 ? 2 : 4; };
+template <typename T> struct Stream { static constexpr int kSub = 8, kRing = 4; };
+// (float32: two stages a wave.  At head size 128 the rings of four waves then fit a compute unit's LDS, and a stage's 8192
+// clocks of matrix instructions hide the next one's DMA: 8 heads over 2, 3000 rows, a pass 94-108 us, 119-125
+// with three stages and thus three waves; 32 heads over 8, 6000 rows: 1242-1289 against 1639-1675.  At 64, 4096 clocks a stage,
+// more would fit, but a trip is as many stages and the stages before whole trips are done online: the first
+// pass of 8 heads over 2 with 2 / 3 / 4 stages, 1750 rows 23.6 / 24.4 / 25.0 us, 3000 48.1 / 49.1 / 49.4, 1500 22.7 / 22.9 / 22.3;
+// both passes 54.5 / 55.3 / 56.2, 104.3 / 109.0 / 106.2, 52.4 / 53.0 / 52.4; 32 over 8, 6000 rows 1189 / 1197 / 1191.)
+template <> struct Stream<float> { static constexpr int kSub = 2, kRing = 2; };
 
 // The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
 // the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
@@ -384,7 +386,7 @@ __device__ __forceinline__ void stream_edge_tile(const frag_t (&aq)[Tile<T, D>::
 template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Ring<T, D>::kStages;
+    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;                       // accumulator elements handled per MFMA slot
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");
@@ -897,7 +899,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 template <typename T, int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Ring<T, D>::kStages;
+    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");

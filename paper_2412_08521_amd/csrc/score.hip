@@ -793,9 +793,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     }
                     // two rounds later those reads have long returned: one wait for all of them
                     if (kPairs > 2 && kFetchAt < kPairs - 1 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
-                    // A single pair: with a ring of two the DMA goes to the slot that this stage was read from, once
-                    // those reads are done; the next stage is read under the last products, its log-sum-exp after
-                    // them (the other set weighs the previous stage until then).
+                    // A single pair (two stages in the ring): the next stage's DMA goes to the other slot, whose last reads,
+                    // the previous stage's log-sum-exp among them, ended at that stage's wait; this wait does the same for
+                    // the DMA a stage on.  The next stage is read under the last products, its log-sum-exp
+                    // after them (the other set weighs the previous stage until then).
                     if constexpr (kPairs == 1) {
                         if (f == 0) {
                             wait_lds_all_visible();
@@ -1237,8 +1238,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     }
                     // two rounds later those reads have long returned: one wait for all of them
                     if (kPairs > 2 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
-                    // a single pair: with a ring of two the DMA goes to the slot that this stage was read from, once
-                    // those reads are done; the next stage is read under the last products
+                    // a single pair (two stages in the ring): the next stage's DMA goes to the other slot, whose last reads
+                    // ended at the previous stage's wait; this wait does the same for the DMA a stage on.  The next
+                    // stage is read under the last products
                     if constexpr (kPairs == 1) {
                         if (f == 0) {
                             wait_lds_all_visible();

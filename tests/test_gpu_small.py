@@ -55,7 +55,7 @@ def test_score_matches_oracle(shape, mode):
 @pytest.mark.parametrize("mode", MODES)
 @pytest.mark.parametrize("group", [1, 2, 3, 4])
 def test_score_every_remainder_of_interior_stages(group, mode):
-    """The pipelined loops of both passes take whole trips of 4 stages (6 in f32 mode); what does not fill
+    """The pipelined loops of both passes take whole trips of 4 stages (2 in f32 mode); what does not fill
     a trip goes through the masked loop.  Lengths 32 apart walk through every remainder, for every group size
     (the trip counts stages of all q-heads of a group), plus one ragged length."""
     lengths = [1312 + 32 * i for i in range(6 if mode == B.EMS_F32 else 4)] + [1333]

@@ -109,7 +109,7 @@ ScorePlan plan_score(const ems_params* p)
     s.off_lse2 = off; off += align_up(sizeof(float) * (size_t)p->batch * p->q_heads * s.n_pad);
     s.off_part_glo = off;
     s.off_part_loc = off;
-    s.deal = ems::score_deal(p->batch, p->q_heads, p->kv_heads, N, p->dtype == EMS_F32);
+    s.deal = ems::score_deal(p->batch, p->q_heads, p->kv_heads, N, p->head_dim, p->dtype == EMS_F32);
     if (s.deal.p2_waves) {
         off += align_up(sizeof(float) * s.deal.p2_floats);
         s.off_part_loc = off;

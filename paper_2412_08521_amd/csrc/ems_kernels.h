@@ -164,7 +164,7 @@ int score_keys_per_block(int dtype_is_f32);
 // How the score passes of a launch are dealt: waves per head and stages per wave of each pass (0 waves:
 // the pass takes whole items), and the floats of one partial-result array.
 struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len, p1_by_block; size_t p1_floats, p2_floats; };
-ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, bool f32);
+ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32);
 int select_chunks(int seq_len);     // blocks per head of the long-sequence select
 int select_coarse_bins();
 hipError_t launch_sparsity(const StatsArgs& a, hipStream_t st);

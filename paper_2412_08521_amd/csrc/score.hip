@@ -1409,7 +1409,7 @@ static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len)
     return d;
 }
 
-ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, bool f32)
+ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*head_dim*/, bool f32)
 {
     return f32 ? score_deal_t<float>(batch, q_heads, kv_heads, seq_len) : score_deal_t<bf16_t>(batch, q_heads, kv_heads, seq_len);
 }

@@ -17,7 +17,7 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise ImportError(f"{LIB_PATH} is not built: run `python -m paper_2412_08521_amd.build`")
         l = C.CDLL(LIB_PATH)
-        l.ems_probe_mfma.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
+        l.ems_probe_mfma.argtypes = l.ems_probe_mfma_16x16x32.argtypes = [C.c_int32, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p]
         l.ems_probe_copy.argtypes = [C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
         _lib = l
     return _lib
@@ -27,8 +27,10 @@ def _stream():
     return C.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
-def probe_mfma(blocks: int, iters: int, sink, operands=None):
-    """Enqueue the MFMA ceiling kernel; returns the flops it performs."""
+def probe_mfma(blocks: int, iters: int, sink, operands=None, tile: int = 32):
+    """Enqueue the MFMA ceiling kernel (`tile` 32: 32x32x16 instructions, 16: 16x16x32); returns the flops it performs."""
+    if tile not in (16, 32):
+        raise ValueError("tile must be 16 or 32")
     if not (sink.is_cuda and sink.dtype == torch.float32 and sink.numel() == blocks * 256):
         raise ValueError("sink must be a device float32 tensor of blocks * 256 elements")
     op = None
@@ -37,7 +39,8 @@ def probe_mfma(blocks: int, iters: int, sink, operands=None):
                 and operands.numel() * operands.element_size() >= OPERAND_BYTES):
             raise ValueError("operands must be a contiguous device tensor of at least 64 KiB")
         op = C.c_void_p(operands.data_ptr())
-    rc = lib().ems_probe_mfma(int(blocks), int(iters), op, C.c_void_p(sink.data_ptr()), _stream())
+    probe = lib().ems_probe_mfma if tile == 32 else lib().ems_probe_mfma_16x16x32
+    rc = probe(int(blocks), int(iters), op, C.c_void_p(sink.data_ptr()), _stream())
     if rc != 0:
         raise RuntimeError(f"ems_probe_mfma failed ({rc})")
     return blocks * 4 * iters * 32 * 32768

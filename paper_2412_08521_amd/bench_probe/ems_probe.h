@@ -31,6 +31,12 @@ extern "C" {
 int ems_probe_mfma(int32_t blocks, int32_t iters, const void* operands, float* sink, void* hip_stream);
 
 /*
+ * The same work as iters * 64 v_mfma_f32_16x16x32_bf16 per wave (eight accumulators): the form that
+ * takes less power, and so the higher ceiling on random operands.
+ */
+int ems_probe_mfma_16x16x32(int32_t blocks, int32_t iters, const void* operands, float* sink, void* hip_stream);
+
+/*
  * Copies `bytes` (a multiple of 16) from src to dst with 16-byte loads and stores, one
  * grid-stride pass: bytes read + bytes written of HBM traffic.
  */

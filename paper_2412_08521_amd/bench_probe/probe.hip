@@ -3,15 +3,15 @@
 // product library.
 #include "ems_probe.h"
 #include "../csrc/ems_common.h"
+#include "../csrc/ems_stream.h"
 
 namespace ems {
 
-__global__ __launch_bounds__(256) void probe_mfma_kernel(const frag_t* operands, float* sink, int iters)
+// 8 A and 8 B fragments per lane: from the caller's buffer, or constants that are neither zero
+// nor denormal (their values do not matter)
+__device__ __forceinline__ void load_operands(const frag_t* operands, frag_t (&a)[8], frag_t (&b)[8])
 {
     const int lane = threadIdx.x % kWave;
-    // 8 A and 8 B fragments per lane: from the caller's buffer, or constants that are neither zero
-    // nor denormal (their values do not matter)
-    frag_t a[8], b[8];
     constexpr int kFragsInBuffer = 65536 / 16;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -25,6 +25,12 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(const frag_t* operands,
             a[i] = __builtin_bit_cast(frag_t, x); b[i] = __builtin_bit_cast(frag_t, y);
         }
     }
+}
+
+__global__ __launch_bounds__(256) void probe_mfma_kernel(const frag_t* operands, float* sink, int iters)
+{
+    frag_t a[8], b[8];
+    load_operands(operands, a, b);
     f32x16_t c0 = {}, c1 = {}, c2 = {}, c3 = {};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
@@ -39,6 +45,27 @@ __global__ __launch_bounds__(256) void probe_mfma_kernel(const frag_t* operands,
     float s = 0.f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s += c0[r] + c1[r] + c2[r] + c3[r];
+    sink[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
+}
+
+__global__ __launch_bounds__(256) void probe_mfma16_kernel(const frag_t* operands, float* sink, int iters)
+{
+    frag_t a[8], b[8];
+    load_operands(operands, a, b);
+    f32x4_t c[8] = {};
+    for (int it = 0; it < iters; ++it) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c[j] = mma16(a[i], b[(i + j) & 7], c[j]);
+        if ((it & 63) == 63) {                              // stays finite
+#pragma unroll
+            for (int j = 0; j < 8; ++j) c[j] = c[j] * 0.f;
+        }
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += (c[j][0] + c[j][1]) + (c[j][2] + c[j][3]);
     sink[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
@@ -62,6 +89,14 @@ int ems_probe_mfma(int32_t blocks, int32_t iters, const void* operands, float* s
 {
     if (blocks < 1 || blocks > (1 << 20) || iters < 1 || !sink || ((uintptr_t)operands % 16) != 0) return -1;
     hipLaunchKernelGGL(ems::probe_mfma_kernel, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
+                       static_cast<const ems::frag_t*>(operands), sink, iters);
+    return hipGetLastError() == hipSuccess ? 0 : -4;
+}
+
+int ems_probe_mfma_16x16x32(int32_t blocks, int32_t iters, const void* operands, float* sink, void* hip_stream)
+{
+    if (blocks < 1 || blocks > (1 << 20) || iters < 1 || !sink || ((uintptr_t)operands % 16) != 0) return -1;
+    hipLaunchKernelGGL(ems::probe_mfma16_kernel, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream),
                        static_cast<const ems::frag_t*>(operands), sink, iters);
     return hipGetLastError() == hipSuccess ? 0 : -4;
 }

@@ -218,6 +218,8 @@ def test_probe_library_is_separate_and_checks_arguments(lib):
     assert pl.ems_probe_mfma(8, 0, None, d, None) == -1
     assert pl.ems_probe_mfma(8, 10, None, None, None) == -1
     assert pl.ems_probe_mfma(8, 10, C.c_void_p(8), d, None) == -1          # misaligned operand buffer
+    assert pl.ems_probe_mfma_16x16x32(0, 10, None, d, None) == -1
+    assert pl.ems_probe_mfma_16x16x32(8, 10, C.c_void_p(8), d, None) == -1
     assert pl.ems_probe_copy(d, d, 24, None) == -1                           # not a multiple of 16
     assert pl.ems_probe_copy(C.c_void_p(8), d, 32, None) == -1
     assert pl.ems_probe_copy(None, d, 32, None) == -1

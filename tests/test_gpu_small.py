@@ -842,3 +842,13 @@ def test_probe_kernels_run():
     bench_probe.probe_mfma(8, 100, sink, operands=ops)
     torch.cuda.synchronize()
     assert torch.isfinite(sink).all()
+
+
+def test_probe_of_the_smaller_tile_runs():
+    from paper_2412_08521_amd import bench_probe
+    sink = torch.full((8 * 256,), float("nan"), device="cuda")
+    ops = torch.randn(bench_probe.OPERAND_BYTES // 2, device="cuda").to(torch.bfloat16)
+    for operands in (None, ops):
+        assert bench_probe.probe_mfma(8, 100, sink, operands=operands, tile=16) == 8 * 4 * 100 * 32 * 32768
+        torch.cuda.synchronize()
+        assert torch.isfinite(sink).all()

@@ -158,8 +158,9 @@ def test_redundancy_of_the_longest_sequences():
 
 @pytest.mark.parametrize("d,bh,limit", [(64, 1, 512), (64, 20, 768), (128, 2, 384), (128, 20, 448), (128, 140, 256)])
 def test_redundancy_either_side_of_the_short_form(d, bh, limit):
-    """Sequences up to `limit` take the block form, longer ones the stream: the lengths on either side, first and last
-    head.  Tolerance as above."""
+    """The lengths `limit` and `limit` + 1, first and last head.  Here both are the stream's, a whole number of its stages and
+    one token more; below, called with the block form's present limits, they are on either side of it.  Tolerance as
+    above."""
     for n in (limit, limit + 1):
         _log("redundancy short form", d, bh, n)
         inp = ems_inputs.small(1, bh, bh, d, n, seed=n + d)
@@ -188,7 +189,7 @@ def test_redundancy_edges_of_the_stream(bh_n, d, scale):
 
 @pytest.mark.parametrize("d,bh,limit", [(64, 1, 288), (64, 20, 352), (128, 2, 256), (128, 20, 352), (128, 140, 160)])
 def test_redundancy_either_side_of_the_shorter_forms(d, bh, limit):
-    """As above, at the lengths where the present stream begins."""
+    """As above at the longest sequences that the block form takes: one token more takes the stream."""
     test_redundancy_either_side_of_the_short_form(d, bh, limit)
 
 

@@ -1050,7 +1050,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form, so
     // that the pipelined rest is whole trips of the loop.  In float32 starting the pipeline costs more than it gains for
     // up to four stages and less from five on (us of the pass where a part has that many, online / pipelined: 8 heads over 2
-    // of 128, 600 rows, four 26.2 / 29.2; 1400, five 33.5 / 33.1; of 64, 600, four 16.8 / 17.8; 1400, five 20.9 / 20.1).
+    // of 128, 600 rows, four 26.5 / 29.5; 1400, five 33.3 / 33.0; of 64, 600, four 16.5 / 17.4; 1400, five 20.4 / 19.6).
     constexpr int kFewest = kPairs == 1 ? 5 : 0;
     const int n_int_all = max(min(t1, t_diag) - t0, 0);
     const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all < kFewest ? n_int_all : n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)

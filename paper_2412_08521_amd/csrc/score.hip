@@ -13,69 +13,14 @@
 // the stationary operand), with a private LDS ring for the streamed operand.
 #include "ems_common.h"
 #include "ems_kernels.h"
+#include "ems_score.h"
 #include "ems_stream.h"
 
 namespace ems {
 
-// The hardware deals workgroups to the 8 XCDs (each with its own L2) round-robin in launch
-// order: block b runs on XCD b % 8.  First pass: work is cut into groups of `per_group`
-// consecutive work items that stream the same operand; group g belongs to XCD g % 8 so that the
-// group shares one L2.  Returns the linear index of the k-th work item of XCD `xcd`, or -1 for
-// padding.
-__device__ __forceinline__ int xcd_work_item(int n_groups, int per_group, int xcd, int k)
-{
-    const int group = (k / per_group) * kXcds + xcd;
-    return group < n_groups ? group * per_group + k % per_group : -1;
-}
 static long long xcd_grid(long long n_groups, long long per_group)    // 8 x (items per XCD, padding included)
 {
     return kXcds * ((n_groups + kXcds - 1) / kXcds) * per_group;
-}
-
-// ---- work queues.  The XCDs of one chip do not run at the same speed (a few percent apart under
-// this load), and the hardware deals workgroups to them in fixed turns, so a launch whose work is
-// bound to block indices ends when the slowest XCD ends, with the re-dispatch of a workgroup per
-// item on top.  In long launches a wave therefore stays resident and takes its work items at run
-// time, one integer atomic per item; which wave computes an item has no influence on the item's
-// result.
-// Second pass: from the queue of its XCD (items that stream the same operand stay on one L2)
-// and, once that is empty, from a pool of the lightest items that every XCD draws from.  Returns
-// the item's index in its queue (pool = true: in the pool), or -1 when both are empty.
-__device__ __forceinline__ int take_work_item(int* cursors, int n_local, int n_pool, bool& pool)
-{
-    int k = -1, from_pool = 0;
-    if (threadIdx.x == 0) {
-        if (n_local > 0) {
-            k = atomicAdd(&cursors[blockIdx.x % kXcds], 1);
-            if (k >= n_local) k = -1;
-        }
-        if (k < 0 && n_pool > 0) {
-            k = atomicAdd(&cursors[kXcds], 1);
-            from_pool = 1;
-            if (k >= n_pool) k = -1;
-        }
-    }
-    pool = __builtin_amdgcn_readfirstlane(from_pool) != 0;
-    return __builtin_amdgcn_readfirstlane(k);
-}
-
-// First pass: every XCD has a queue (its items in the fixed order of xcd_work_item, padding
-// included); a wave whose own queue is empty goes on with the next item of another XCD's queue,
-// so the faster XCDs help the slower ones finish.  Returns the item's index in the queue of XCD
-// `from`, or -1 when every queue is empty.
-__device__ __forceinline__ int take_or_steal(int* cursors, int n_per_queue, int& from)
-{
-    int k = -1, q = 0;
-    if (threadIdx.x == 0) {
-        const int own = blockIdx.x % kXcds;
-        for (int d = 0; d < kXcds && k < 0; ++d) {
-            q = (own + d) % kXcds;
-            k = atomicAdd(&cursors[q], 1);
-            if (k >= n_per_queue) k = -1;
-        }
-    }
-    from = __builtin_amdgcn_readfirstlane(q);
-    return __builtin_amdgcn_readfirstlane(k);
 }
 
 // Resident waves per XCD: one per SIMD.
@@ -87,64 +32,6 @@ __global__ void score_queue_reset_kernel(int* queue)
     if (threadIdx.x < 2 * (kXcds + 1)) queue[threadIdx.x] = threadIdx.x > kXcds ? kXcdWaves : 0;
 }
 
-// Pass 2: key tiles at or below the diagonal of row chunks 0..I, per (batch, kv-head): chunk I'
-// has min(n_key_tiles, (I' + 1) * r) of them, r = chunk rows / keys per tile.
-__host__ __device__ inline long long p2_items_upto(int I, int r, int n_key_tiles)
-{
-    const long long n = I + 1;
-    const long long whole = n < n_key_tiles / r ? n : n_key_tiles / r;    // chunks whose count is not capped
-    return r * whole * (whole + 1) / 2 + (n - whole) * n_key_tiles;
-}
-
-// Second pass: unit u = 32 * kSub keys, its stages = 32 query rows each (of every q-head of the group)
-// from the diagonal on.
-template <int kSub>
-struct DealPass2 {
-    int n_units, rows_all, lead;                           // rows_all: stages of unit 0, padding included
-    __host__ __device__ DealPass2(int N, int group)
-    {
-        const int n_stages = (N + kStreamRows - 1) / kStreamRows;
-        n_units = (n_stages + kSub - 1) / kSub;
-        const int a = align(group);
-        rows_all = (n_stages + a - 1) / a * a;
-        // (the operand's load is paid once for the q-heads of the group, the masked stages by each)
-        lead = kSub % kTrip ? (group == 1 ? 2 : 1) : ((2 * group + 5 + group / 2) / group + a - 1) / a * a;
-    }
-    // a stretch that starts and ends at these multiples holds whole trips (of stages x q-heads)
-    static __host__ __device__ int align(int group) { return kSub % kTrip ? 1 : group % 4 == 0 ? 1 : group % 2 == 0 ? 2 : kTrip; }
-    __host__ __device__ int start(int u) const { return u * (rows_all + lead) - kSub * (u * (u - 1) / 2); }
-    __host__ __device__ int first(int u) const { return start(u) + lead; }
-    __host__ __device__ int end(int u) const { return start(u + 1); }
-    __host__ __device__ int total() const { return start(n_units); }
-    __device__ int unit_at(int pos) const
-    {
-        int lo = 0, hi = n_units;
-        while (hi - lo > 1) { const int mid = (lo + hi) >> 1; if (start(mid) <= pos) lo = mid; else hi = mid; }
-        return lo;
-    }
-};
-
-// sum of the 16 accumulator-derived values with four independent partial sums
-__device__ __forceinline__ float sum16(const float (&p)[16])
-{
-    float s0 = p[0], s1 = p[1], s2 = p[2], s3 = p[3];
-#pragma unroll
-    for (int r = 4; r < 16; r += 4) { s0 += p[r]; s1 += p[r + 1]; s2 += p[r + 2]; s3 += p[r + 3]; }
-    return (s0 + s1) + (s2 + s3);
-}
-
-__device__ __forceinline__ float max16(const f32x16_t& acc)
-{
-    float t0 = fmaxf(fmaxf(acc[0], acc[1]), acc[2]);
-    float t1 = fmaxf(fmaxf(acc[3], acc[4]), acc[5]);
-    float t2 = fmaxf(fmaxf(acc[6], acc[7]), acc[8]);
-    float t3 = fmaxf(fmaxf(acc[9], acc[10]), acc[11]);
-    float t4 = fmaxf(fmaxf(acc[12], acc[13]), acc[14]);
-    t0 = fmaxf(fmaxf(t0, t1), t2);
-    t3 = fmaxf(fmaxf(t3, t4), acc[15]);
-    return fmaxf(t0, t3);
-}
-
 // The largest exponent of a tile that lies below the diagonal.
 template <typename T, int D>
 __device__ __forceinline__ float pass1_tile_max(const frag_t (&ak)[Tile<T, D>::kFrags], const frag_t (&bq)[Tile<T, D>::kFrags], float c)
@@ -153,40 +40,6 @@ __device__ __forceinline__ float pass1_tile_max(const frag_t (&ak)[Tile<T, D>::k
 #pragma unroll
     for (int f = 0; f < Tile<T, D>::kFrags; ++f) mma<T>(acc, ak[f], bq[f]);
     return max16(acc) * c;
-}
-
-// A sum above `limit` gives its exponent to its reference; what the sum of reference and exponent loses in
-// rounding stays with it.
-__device__ __forceinline__ void give_exponent(float& m, float& l, float limit)
-{
-    const int up = l > limit ? __builtin_amdgcn_frexp_expf(l) : 0;
-    const float to = m + (float)up, part = to - m;
-    const float lost = up ? (m - (to - part)) + ((float)up - part) : 0.f;      // (m may be infinite where up is 0)
-    l = __builtin_amdgcn_ldexpf(l, -up) * exp2_fast(lost);
-    m = to;
-}
-
-// One 32-key x 32-query tile of the online softmax; it may cross the diagonal.
-template <typename T, int D>
-__device__ __forceinline__ void pass1_tile(const frag_t (&ak)[Tile<T, D>::kFrags],
-                                           const frag_t (&bq)[Tile<T, D>::kFrags],
-                                           float& m_run, float& l_run, float c,
-                                           int key0, int qi, int half)
-{
-    f32x16_t acc = zero_acc();
-#pragma unroll
-    for (int f = 0; f < Tile<T, D>::kFrags; ++f) mma<T>(acc, ak[f], bq[f]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        if (key0 + acc_row(r, half) > qi) acc[r] = -INFINITY;
-    const float tmax = max16(acc);
-    const float m_new = fmaxf(m_run, tmax * c);
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    float p[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[r], c, -m_use));
-    l_run = __builtin_fmaf(l_run, exp2_fast(m_run - m_use), sum16(p));
-    m_run = m_new;
 }
 
 // Parts of a unit that the two small kernels below request together (one after the other they were most
@@ -316,18 +169,8 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 //                  row operand and log-sum-exp are fetched from LDS into a second register set.
 // 32-wide subtiles of the stationary operand per wave (8 x 8 fragments = the 256 accumulation
 // registers in the 16-bit types) and LDS stages in the wave's ring
-// A stretch of an even deal can be as long as a whole row or column.  After kFoldKeys keys (first pass), or kFoldRows
-// rows of every q-head of the group (second), a running sum is added to the sum of those before it, so that
-// small weights are not lost against a large sum.  (1 x 4 heads over 1, 8192: column sums off by 3.8e-7 without, 0.7e-7.)
-constexpr int kFoldKeys = 2048, kFoldRows = 512;
-template <typename T> struct Stream { static constexpr int kSub = 8, kRing = 4; };
-// (float32: two stages a wave.  At head size 128 the rings of four waves then fit a compute unit's LDS, and a stage's 8192
-// clocks of matrix instructions hide the next one's DMA: 8 heads over 2, 3000 rows, a pass 94-108 us, 119-125
-// with three stages and thus three waves; 32 heads over 8, 6000 rows: 1242-1289 against 1639-1675.  At 64, 4096 clocks a stage,
-// more would fit, but a trip is as many stages and the stages before whole trips are done online: the first
-// pass of 8 heads over 2 with 2 / 3 / 4 stages, 1750 rows 23.6 / 24.4 / 25.0 us, 3000 48.1 / 49.1 / 49.4, 1500 22.7 / 22.9 / 22.3;
-// both passes 54.5 / 55.3 / 56.2, 104.3 / 109.0 / 106.2, 52.4 / 53.0 / 52.4; 32 over 8, 6000 rows 1189 / 1197 / 1191.)
-template <> struct Stream<float> { static constexpr int kSub = 2, kRing = 2; };
+constexpr int kSub = 8, kRing = 4;
+using T = bf16_t;
 
 // The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
 // the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
@@ -356,41 +199,12 @@ __device__ __forceinline__ void advance_cursor(int& h_left, int& t_left, const c
     l += al;
 }
 
-// One 32-row x 32-key tile of the edge loop: weights added into the lane's column sums; the
-// tile may cross the diagonal and may hold last-window rows.
-template <typename T, int D>
-__device__ __forceinline__ void stream_edge_tile(const frag_t (&aq)[Tile<T, D>::kFrags],
-                                                 const frag_t (&bk)[Tile<T, D>::kFrags],
-                                                 const f32x16_t& lse_v, float c, float& glo, float& loc,
-                                                 int row0, int kj, int half, int win0)
-{
-    constexpr int kFrags = Tile<T, D>::kFrags;
-    f32x16_t acc = zero_acc();
-    float p[16];
-#pragma unroll
-    for (int f = 0; f < kFrags; ++f) mma<T>(acc, aq[f], bk[f]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[r], c, -lse_v[r]));
-#pragma unroll
-    for (int r = 0; r < 16; ++r)
-        if (row0 + acc_row(r, half) < kj) p[r] = 0.f;
-    glo += sum16(p);
-    if (row0 + 31 >= win0) {                               // wave-uniform
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            if (row0 + acc_row(r, half) < win0) p[r] = 0.f;
-        loc += sum16(p);
-    }
-}
-
-template <typename T, int D, bool kDeal>
+template <int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;                       // accumulator elements handled per MFMA slot
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");
-    static_assert(kSub >= 2 && kSub % 2 == 0, "tiles are processed in pairs");
     constexpr int kPairs = kSub / 2;
     constexpr int kRowBytes = Tile<T, D>::kRowBytes;
     constexpr int kCpr = Tile<T, D>::kChunksPerRow;
@@ -398,7 +212,6 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kQInstr = kStageBytes / 1024;             // 16-byte DMA instructions per stage
     constexpr int kLoads = kQInstr + 1;                     // + one 4-byte DMA for the rows' log-sum-exp
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
-    static_assert(kRing == 2 || kRing == 4, "the waits below are written for rings of 2 or 4 stages");
     constexpr int kKeys = 32 * kSub;
     // stages per trip of the interior loop: after that many both the two operand register sets and
     // the ring slots are back where they started, so every slot is a compile-time constant
@@ -411,69 +224,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const float c = a.scale_log2e;
     const int N = a.seq_len, W = a.window;
     const int G = a.q_heads / a.kv_heads;
-    const int n_key_tiles = (N + kKeys - 1) / kKeys;
-    const int n_chunks = a.n_chunks, R = a.chunk_rows;
 
-    // Work item = (row chunk I, (batch, kv-head), key tile J at or below the chunk's diagonal),
-    // heaviest chunks first.  An XCD's queue holds the chunks from the top down to p2_split for
-    // its share of the heads (head = XCD + 8 m), key tiles innermost, so that the waves of an XCD
-    // stream the same query rows; the chunks below p2_split, all heads, are the pool.
-    const int BKV = a.batch * a.kv_heads;
-    // Long launches: a wave stays and takes item after item until the queues are empty -- the exit
-    // every wave reaches (the cursors only grow); between two items nothing of the wave is in flight.
-    // Shorter ones: the wave's stretch of an even deal, one part of a key tile after the other.
-    // When the heads do not divide over the XCDs there are no queues: the groups (I, head) are
-    // dealt to the XCDs in turn and every block has one item, fixed by its index.
-    const DealPass2<kSub> deal(N, G);
-    DealPlace place{-1, 0};
-    int pos = 0, pos_end = 0;
-    if constexpr (kDeal) {
-        place = deal_place(BKV, a.p2_waves);
-        if (place.head < 0) return;
-        pos = place.wave * a.p2_len;
-        pos_end = scalar(min(pos + a.p2_len, deal.total()));
-    }
-    for (bool first = true; first || kDeal || a.q_dynamic; first = false) {
-    int I = 0, J, bkv, r_begin, r_end;
-    if constexpr (kDeal) {
-        if (pos >= pos_end) break;
-        J = scalar(deal.unit_at(pos));
-        bkv = place.head;
-        const int u0 = deal.first(J), to = min(pos_end, deal.end(J));
-        r_begin = scalar(J * kKeys + (max(pos, u0) - u0) * kStreamRows);
-        r_end = scalar(min(J * kKeys + (to - u0) * kStreamRows, N));
-        pos = scalar(to);
-    } else {
-    if (a.q_share == 0) {
-        int bid = xcd_work_item(BKV * n_chunks, n_key_tiles, blockIdx.x % kXcds, blockIdx.x / kXcds);
-        if (bid < 0) break;
-        J = bid % n_key_tiles; bid /= n_key_tiles;
-        bkv = bid % BKV;
-        I = n_chunks - 1 - bid / BKV;
-    } else {
-        bool pool;
-        const int k = take_work_item(a.queue, a.p2_local, a.p2_pool, pool);
-        if (k < 0) break;
-        const int r_tiles = R / kKeys;
-        const int top = pool ? a.p2_split - 1 : n_chunks - 1;
-        const long long per = pool ? BKV : a.q_share;       // heads per chunk in this queue
-        const long long upto_top = p2_items_upto(top, r_tiles, n_key_tiles);
-        int lo = pool ? 0 : a.p2_split, hi = top;           // the chunk whose items include k: the smallest I with before(I) <= k
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (per * (upto_top - p2_items_upto(mid, r_tiles, n_key_tiles)) <= k) hi = mid; else lo = mid + 1;
-        }
-        I = lo;
-        const int rem = (int)(k - per * (upto_top - p2_items_upto(I, r_tiles, n_key_tiles)));
-        const int cnt = min(n_key_tiles, (I + 1) * r_tiles);
-        J = rem % cnt;
-        bkv = pool ? rem / cnt : (int)(blockIdx.x % kXcds) + kXcds * (rem / cnt);
-    }
-    r_begin = max(I * R, J * kKeys);                        // both multiples of 32
-    r_end = min((I + 1) * R, N);
-    }
-    if (r_begin >= r_end) continue;                         // pair above the diagonal (the queues hold none), or padding
-    const int key_base = J * kKeys;
+    Pass2Items<kSub, kDeal> items(a);
+    while (items.next()) {
+    const int bkv = items.bkv, r_begin = items.r_begin, r_end = items.r_end;
+    const int key_base = items.J * kKeys;
     // [r_begin, e_end) touches the diagonal, [e_end, i_end) is interior, [i_end, r_end) holds
     // window rows (each range may be empty; all bounds but r_end are multiples of 32)
     const int win0 = N - W;
@@ -561,7 +316,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     // with stages issued up to `last`, wait until stage t has landed (stages complete in order)
     auto wait_landed = [&](int t, int last) __attribute__((always_inline)) {
         const int later = last - t;
-        if (later >= 2 && kRing > 3) wait_vmem<2 * kLoads>();
+        if (later >= 2) wait_vmem<2 * kLoads>();
         else if (later >= 1) wait_vmem<kLoads>();
         else wait_vmem<0>();
     };
@@ -741,10 +496,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         };
 
         issue_next(ic<0>{});
-        if constexpr (kRing > 2) {
-            issue_next(ic<1>{});
-            issue_next(ic<2>{});
-        }
+        issue_next(ic<1>{});
+        issue_next(ic<2>{});
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_rows(0, aq[0], lse_v[0]);
         // Pairs alternate between accumulators {0, 1} and {2, 3}.  The pipeline starts on a pair
@@ -764,11 +517,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             constexpr int u = decltype(u_c)::value;         // stage t of the trip, t = u (mod kUnroll)
             constexpr int set = u & 1;
             constexpr int kFetchAt = 1;                     // as early as the other register set is free: the LDS latency has three rounds to hide in
-            if constexpr (kPairs > 1) issue_next(ic<(u + kRing - 1) % kRing>{});      // stage t + kRing - 1
+            issue_next(ic<(u + kRing - 1) % kRing>{});      // stage t + kRing - 1
 #pragma unroll
             for (int p = 0; p < kPairs; ++p) {
-                constexpr int kOddPairs = kPairs % 2;
-                const int rp = (kOddPairs ? set + p : p) & 1;                 // accumulators this round writes: {2rp, 2rp+1}
+                const int rp = p & 1;                                          // accumulators this round writes: {2rp, 2rp+1}
                 const int psa = (2 * p + kSub - 2) % kSub;                     // key subtiles of the previous pair
                 f32x16_t& accA = acc[2 * rp];
                 f32x16_t& accB = acc[2 * rp + 1];
@@ -787,40 +539,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     // The other register set is free once round 0 has read the previous stage's
                     // log-sum-exp; stage t + 1 has landed once only the kRing - 2 stages issued
                     // after it are in flight.
-                    if (kPairs > 1 && p == (kFetchAt < 1 ? 1 : kFetchAt) && f == 0) {
+                    if (p == kFetchAt && f == 0) {
                         wait_vmem<(kRing - 2) * kLoads>();
                         fetch_rows((u + 1) % kRing, aq[1 - set], lse_v[1 - set]);
                     }
                     // two rounds later those reads have long returned: one wait for all of them
-                    if (kPairs > 2 && kFetchAt < kPairs - 1 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
-                    // A single pair (two stages in the ring): the next stage's DMA goes to the other slot, whose last reads,
-                    // the previous stage's log-sum-exp among them, ended at that stage's wait; this wait does the same for
-                    // the DMA a stage on.  The next stage is read under the last products, its log-sum-exp
-                    // after them (the other set weighs the previous stage until then).
-                    if constexpr (kPairs == 1) {
-                        if (f == 0) {
-                            wait_lds_all_visible();
-                            issue_next(ic<(u + kRing - 1) % kRing>{});
-                        }
-                        if (f == kFrags - 2) {
-                            wait_vmem<(kRing - 2) * kLoads>();
-                            fetch_frags((u + 1) % kRing, aq[1 - set]);
-                        }
-                    }
+                    if (p == kPairs - 1 && f == 0) wait_lds_all_visible();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            if (kPairs == 1) fetch_lse((u + 1) % kRing, lse_v[1 - set]);
         };
         const int fold = kFoldRows / kStreamRows * max(G, 2) / kUnroll * kUnroll;
         int until_fold = fold;
         for (int t = 0; t < n_stages; t += kUnroll) {
             stage(ic<0>{});
             stage(ic<1>{});
-            if constexpr (kUnroll > 2) {
-                stage(ic<2>{});
-                stage(ic<3>{});
-            }
+            stage(ic<2>{});
+            stage(ic<3>{});
             until_fold -= kUnroll;
             if (kDeal && __builtin_expect(until_fold == 0, 0)) {     // the sums so far are set aside, in LDS (there are no registers left)
                 until_fold = fold;
@@ -836,7 +571,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         }
         // the last pair (key subtiles kSub - 2 and kSub - 1 of the last stage, register set 1)
         {
-            constexpr int rp = ((kPairs % 2 ? 1 + kPairs - 1 : kPairs - 1)) & 1;
+            constexpr int rp = (kPairs - 1) & 1;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 part[kSub - 2][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp][r], c, -lse_v[1][r]));
@@ -846,21 +581,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         wait_vmem<0>();                                     // no DMA may outlive the wave's LDS
     }
 
-    // where the keys' sums go: key kj to out_glo[kj]
-    const int loc_chunk0 = a.loc_chunk0;
-    float* out_glo;
-    float* out_loc = nullptr;
-    if constexpr (kDeal) {
-        const ptrdiff_t at = ((ptrdiff_t)bkv * (a.p2_waves + deal.n_units) + place.wave + J) * kKeys - key_base;
-        out_glo = a.part_glo + at;
-        if (r_end > win0) out_loc = a.part_loc + at;
-    } else {
-        out_glo = a.n_chunks == 1 ? a.s_glo + (size_t)bkv * N
-                                  : a.part_glo + ((size_t)bkv * n_chunks + I) * N;
-        if (a.n_chunks == 1) out_loc = a.s_loc + (size_t)bkv * N;
-        else if (I >= loc_chunk0)
-            out_loc = a.part_loc + ((size_t)bkv * (n_chunks - loc_chunk0) + (I - loc_chunk0)) * N;
-    }
+    float *out_glo, *out_loc;
+    items.outputs(out_glo, out_loc);
     const int out_lane = opaque_lane(lane);                 // (likewise not kept across the loops above)
 #pragma unroll
     for (int s = 0; s < kSub; ++s) {
@@ -897,21 +619,18 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 //                    the wave redoes all of its stages in the online form (running maximum and
 //                    rescaled sum, tile by tile).
 // ------------------------------------------------------------------------------------
-template <typename T, int D, bool kDeal>
+template <int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_stream_kernel(ScoreArgs a)
 {
-    constexpr int kSub = Stream<T>::kSub, kRing = Stream<T>::kRing;
     constexpr int kFrags = Tile<T, D>::kFrags;
     constexpr int kEps = 16 / kFrags;
     static_assert(kFrags >= 2 && kFrags <= 16 && 16 % kFrags == 0, "slot schedule needs 2..16 fragments per row");
-    static_assert(kSub >= 2 && kSub % 2 == 0, "tiles are processed in pairs");
     constexpr int kPairs = kSub / 2;
     constexpr int kRowBytes = Tile<T, D>::kRowBytes;
     constexpr int kCpr = Tile<T, D>::kChunksPerRow;
     constexpr int kStageBytes = kStreamRows * kRowBytes;
     constexpr int kLoads = kStageBytes / 1024;              // 16-byte DMA instructions per stage
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
-    static_assert(kRing == 2 || kRing == 4, "the waits below are written for rings of 2 or 4 stages");
     constexpr int kRows = 32 * kSub;                        // query rows per wave
     // stages per trip of the interior loop (operand register sets and ring slots back at their start)
     constexpr int kUnroll = kRing;
@@ -920,49 +639,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     __shared__ __attribute__((aligned(1024))) char lds_k[kRing][kStageBytes];
 
     const int N = a.seq_len;
-    const int n_row_tiles = (N + kRows - 1) / kRows;
     const int G = a.q_heads / a.kv_heads;
-    // Long launches: a wave stays and takes item after item until every queue is empty -- the exit
-    // every wave reaches (the cursors only grow); between two items nothing of the wave is in flight.
-    // Shorter ones: the wave's stretch of an even deal, one part of a row tile after the other.
-    // (p1_by_block: one item per block, by its index.)
-    const DealPass1<kSub> deal(N);
-    DealPlace place{-1, 0};
-    int pos = 0, pos_end = 0;
-    int q_head = 0;
-    if constexpr (kDeal) {
-        // neighbours are the q-heads of a group on the same stretch: they stream the same keys, through one L2
-        place = deal_place(a.batch * a.kv_heads, a.p1_waves * G);
-        if (place.head < 0) return;
-        q_head = scalar(place.wave % G); place.wave = scalar(place.wave / G);
-        pos = place.wave * a.p1_len;
-        pos_end = scalar(min(pos + a.p1_len, deal.total()));
-    }
-    for (bool first = true;; first = false) {
-    int rt, bkv, g, t0 = 0, t1;                             // bkv = b * kv_heads + kv; key stages [t0, t1)
-    if constexpr (kDeal) {
-        if (pos >= pos_end) break;
-        rt = scalar(deal.unit_at(pos));
-        g = q_head; bkv = place.head;
-        const int u0 = deal.first(rt), to = min(pos_end, deal.end(rt));
-        t0 = scalar(max(pos, u0) - u0); t1 = scalar(to - u0);
-        pos = scalar(to);
-        if (t0 >= t1) continue;                             // before the unit's first stage
-    } else {
-        // the first item goes by the wave's place: a thousand waves would wait for one cache line of cursors
-        int from_xcd = blockIdx.x % kXcds, k_item = blockIdx.x / kXcds;
-        if (!first && a.p1_by_block) break;
-        if (!first || k_item >= a.p1_local) k_item = take_or_steal(a.queue + (kXcds + 1), a.p1_local, from_xcd);
-        if (k_item < 0) break;
-        int bid = xcd_work_item(a.p1_groups, a.p1_per_group, from_xcd, k_item);
-        if (bid < 0) continue;                              // padding
-        g = bid % G; bid /= G;
-        const int BKV = a.batch * a.kv_heads;
-        if (a.p1_groups == BKV) { rt = n_row_tiles - 1 - (bid % n_row_tiles); bkv = bid / n_row_tiles; }
-        else { bkv = bid % BKV; rt = n_row_tiles - 1 - (bid / BKV); }   // heaviest row tiles first
-        t1 = kSub * (rt + 1);
-    }
-    t1 = min(t1, (min(N, (rt + 1) * kRows) + kStreamRows - 1) / kStreamRows);   // the stages the row tile can see
+    Pass1Items<kSub, kDeal> items(a);
+    while (items.next()) {
+    const int rt = items.rt, bkv = items.bkv, g = items.g, t0 = items.t0, t1 = items.t1;
     const int b = bkv / a.kv_heads, kvh = bkv % a.kv_heads;
     const int h = kvh * G + g;
 
@@ -1034,7 +714,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     };
     auto wait_landed = [&](int t, int last) __attribute__((always_inline)) {
         const int later = last - t;
-        if (later >= 2 && kRing > 3) wait_vmem<2 * kLoads>();
+        if (later >= 2) wait_vmem<2 * kLoads>();
         else if (later >= 1) wait_vmem<kLoads>();
         else wait_vmem<0>();
     };
@@ -1048,12 +728,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int t_diag = max(t0, q_base / kStreamRows);
     const int n_edge = max(t1 - t_diag, 0);
     // interior stages [t0, min(t1, t_diag)): the first n_lead of them are done in the online form, so
-    // that the pipelined rest is whole trips of the loop.  In float32 starting the pipeline costs more than it gains for
-    // up to four stages and less from five on (us of the pass where a part has that many, online / pipelined: 8 heads over 2
-    // of 128, 600 rows, four 26.5 / 29.5; 1400, five 33.3 / 33.0; of 64, 600, four 16.5 / 17.4; 1400, five 20.4 / 19.6).
-    constexpr int kFewest = kPairs == 1 ? 5 : 0;
+    // that the pipelined rest is whole trips of the loop.
     const int n_int_all = max(min(t1, t_diag) - t0, 0);
-    const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all < kFewest ? n_int_all : n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
+    const int n_lead = __builtin_amdgcn_readfirstlane(n_int_all % kUnroll);   // (wave-uniform; kept in a scalar register)
     const int n_int = n_int_all - n_lead;                        // a multiple of kUnroll, >= 0
 
     float m_run[kSub], l_run[kSub];
@@ -1187,10 +864,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             }
         };
         issue_next(ic<0>{});
-        if constexpr (kRing > 2) {
-            issue_next(ic<1>{});
-            issue_next(ic<2>{});
-        }
+        issue_next(ic<1>{});
+        issue_next(ic<2>{});
         wait_vmem<(kRing - 2) * kLoads>();
         fetch_keys(0, ak[0]);
         // The references stay as they are from here on: without edge stages the maxima of the first one (the
@@ -1213,11 +888,10 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         auto stage = [&](auto u_c) __attribute__((always_inline)) {
             constexpr int u = decltype(u_c)::value;         // the stage's place in the trip
             constexpr int set = u & 1;
-            if constexpr (kPairs > 1) issue_next(ic<(u + kRing - 1) % kRing>{});      // the stage kRing - 1 ahead
+            issue_next(ic<(u + kRing - 1) % kRing>{});      // the stage kRing - 1 ahead
 #pragma unroll
             for (int p = 0; p < kPairs; ++p) {
-                constexpr int kOddPairs = kPairs % 2;
-                const int rp = (kOddPairs ? set + p : p) & 1;
+                const int rp = p & 1;
                 const int psa = (2 * p + kSub - 2) % kSub;       // query subtiles of the previous pair
                 f32x16_t& accA = acc[2 * rp];
                 f32x16_t& accB = acc[2 * rp + 1];
@@ -1232,25 +906,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                     if (f == 0) mma_first<T>(accB, ak[set][0], bq[2 * p + 1][0]);
                     else mma<T>(accB, ak[set][f], bq[2 * p + 1][f]);
                     weigh(lsum[psa + 1], prevB, m_run[psa + 1], f);
-                    if (kPairs > 1 && p == 1 && f == 0) {   // the other register set is free; early, so that the LDS latency hides
+                    if (p == 1 && f == 0) {   // the other register set is free; early, so that the LDS latency hides
                         wait_vmem<(kRing - 2) * kLoads>();
                         fetch_keys((u + 1) % kRing, ak[1 - set]);
                     }
                     // two rounds later those reads have long returned: one wait for all of them
-                    if (kPairs > 2 && p == kPairs - 1 && f == 0) wait_lds_all_visible();
-                    // a single pair (two stages in the ring): the next stage's DMA goes to the other slot, whose last reads
-                    // ended at the previous stage's wait; this wait does the same for the DMA a stage on.  The next
-                    // stage is read under the last products
-                    if constexpr (kPairs == 1) {
-                        if (f == 0) {
-                            wait_lds_all_visible();
-                            issue_next(ic<(u + kRing - 1) % kRing>{});
-                        }
-                        if (f == kFrags - 2) {
-                            wait_vmem<(kRing - 2) * kLoads>();
-                            fetch_keys((u + 1) % kRing, ak[1 - set]);
-                        }
-                    }
+                    if (p == kPairs - 1 && f == 0) wait_lds_all_visible();
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
@@ -1258,10 +919,8 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         for (int u0 = 0, run = kUnroll, fold = kUnroll; u0 < n_int;) {
             stage(ic<0>{});
             stage(ic<1>{});
-            if constexpr (kUnroll > 2) {
-                stage(ic<2>{});
-                stage(ic<3>{});
-            }
+            stage(ic<2>{});
+            stage(ic<3>{});
             u0 += kUnroll;
             if (kDeal && __builtin_expect(u0 == fold, 0)) {
                 // The sums so far are set aside, and where they have outgrown the reference their exponent goes
@@ -1284,7 +943,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             }
         }
         {   // the last pair (query subtiles kSub - 2 and kSub - 1 of the last stage, register set 1)
-            constexpr int rp = ((kPairs % 2 ? 1 + kPairs - 1 : kPairs - 1)) & 1;
+            constexpr int rp = (kPairs - 1) & 1;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 lsum[kSub - 2][r % kEps] += exp2_fast(__builtin_fmaf(acc[2 * rp][r], c, -m_run[kSub - 2]));
@@ -1325,7 +984,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             // this part's (reference, sum); combined by lse_combine_kernel.  A sum far above its
             // reference gives its exponent to the reference: against another part's larger reference
             // 2^(M - other) could otherwise leave the float range while L still makes up for it.
-            const size_t at = (bh * (a.p1_waves + deal.n_units) + place.wave + rt) * kRows + s * 32 + col;
+            const size_t at = (bh * (a.p1_waves + items.deal.n_units) + items.place.wave + rt) * kRows + s * 32 + col;
             float m = M, l = L;
             give_exponent(m, l, 0x1p40f);
             if (half == 0) { a.part_m[at] = m; a.part_l[at] = l; }
@@ -1339,7 +998,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     }   // next work item
 }
 
-int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<float>::kSub : Stream<bf16_t>::kSub); }
+int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? kSubF32 : kSub); }
 
 // How a launch's work reaches the waves; times of a pass in us, head size 128, heads x length (rows of one line were
 // measured in one process, in turn).
@@ -1360,11 +1019,12 @@ int score_keys_per_block(int dtype_is_f32) { return 32 * (dtype_is_f32 ? Stream<
 //   U >= 4              queues   32 over 8, 32768      4.0      3507 /    - / 3396
 //                                32 over 32, 49152     6.0      8728 /    - / 8264
 //   float32 (a part's beginning is little against its stages): the deal up to U = 16
-//                                 8 over 2, 16384      2.0      2245 /    - / 2238
-//                                4 x 32 over 8, 4096   8.0      2323 /    - / 2292
-//                                4 x 8 over 8, 6000    2.9      1247 /    - / 1490
-//                                4 x 32 over 32, 6000 11.8      5074 /    - / 5117
-//                                2 x 64 over 8, 8192  16.0      8985 /    - / 8833
+//                                 8 over 2, 16384      2.0      1283 /    - / 1267
+//                                 4 x 8 over 8, 6000   2.9       753 /    - /  778
+//                                32 over 8, 6000 (64)  2.9       409 /    - /  426
+//                                 4 x 32 over 8, 4096  8.0      1366 /    - / 1335
+//                                 4 x 32 over 32, 6000 11.8     3199 /    - / 2876
+//                                 2 x 64 over 8, 8192  16.0     5019 /    - / 5032
 // Second pass, by row stages per resident wave: the deal up to 1200, and always for fewer pairs than XCDs (which have
 // no queues: one block per item).  Waves that stream different rows share no lines of their L2: the more rows, the
 // more that costs.
@@ -1383,18 +1043,18 @@ constexpr double kPairUnits = 1.95;        // from here to 2 a launch counts as 
 constexpr double kDealStages = 1200.;
 constexpr int kResident = kXcds * kXcdWaves;
 
-template <typename T>
+template <bool kF32>
 static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len)
 {
-    constexpr int kSub = Stream<T>::kSub, kRows = 32 * kSub;
+    constexpr int kSub = kF32 ? kSubF32 : ems::kSub, kRows = 32 * kSub;
     ScoreDeal d{};
     const long long BHQ = (long long)batch * q_heads, BKV = (long long)batch * kv_heads;
     const int G = q_heads / kv_heads;
     const DealPass1<kSub> d1(seq_len);
     const double units = (double)(BHQ * d1.n_units) / 1024.;
     const bool wide = BKV > kXcds;
-    bool deal1 = units < (sizeof(T) == 4 ? 16. : wide ? 4. : 2.);
-    if (sizeof(T) == 2 && !wide && units >= kPairUnits && units <= 2.) { d.p1_by_block = 1; deal1 = false; }
+    bool deal1 = units < (kF32 ? 16. : wide ? 4. : 2.);
+    if (!kF32 && !wide && units >= kPairUnits && units <= 2.) { d.p1_by_block = 1; deal1 = false; }
     if (deal1) {
         deal_over_waves(kResident, BHQ, d1.total(), DealPass1<kSub>::kAlign, 4, &d.p1_len, &d.p1_waves);
         d.p1_floats = (size_t)BHQ * (d.p1_waves + d1.n_units) * kRows;
@@ -1411,13 +1071,29 @@ static ScoreDeal score_deal_t(int batch, int q_heads, int kv_heads, int seq_len)
 
 ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*head_dim*/, bool f32)
 {
-    return f32 ? score_deal_t<float>(batch, q_heads, kv_heads, seq_len) : score_deal_t<bf16_t>(batch, q_heads, kv_heads, seq_len);
+    return f32 ? score_deal_t<true>(batch, q_heads, kv_heads, seq_len) : score_deal_t<false>(batch, q_heads, kv_heads, seq_len);
 }
 
-template <typename T, int D>
+template <bool kF32, bool kDeal>
+static void start_pass1(const ScoreArgs& a, unsigned grid, hipStream_t st)
+{
+    if constexpr (kF32) start_pass1_f32(a, kDeal, grid, st);
+    else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass1_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
+    else hipLaunchKernelGGL((score_pass1_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
+}
+
+template <bool kF32, bool kDeal>
+static void start_pass2(const ScoreArgs& a, unsigned grid, hipStream_t st)
+{
+    if constexpr (kF32) start_pass2_f32(a, kDeal, grid, st);
+    else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass2_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
+    else hipLaunchKernelGGL((score_pass2_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
+}
+
+template <bool kF32>
 static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)
 {
-    constexpr int kSub = Stream<T>::kSub, kRows = 32 * kSub;
+    constexpr int kSub = kF32 ? kSubF32 : ems::kSub, kRows = 32 * kSub;
     const int BKV = a.batch * a.kv_heads, G = a.q_heads / a.kv_heads;
     const int n_row_tiles = (a.seq_len + kRows - 1) / kRows;
     ScoreArgs a1 = a;
@@ -1425,7 +1101,7 @@ static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)
         const long long grid = deal_grid((long long)a.batch * a.q_heads, a.p1_waves);
         if (grid > 0x7fffffffll) return hipErrorInvalidValue;
         a.queue_clear = 0;
-        hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, true>), dim3((unsigned)grid), dim3(kWave), 0, st, a1);
+        start_pass1<kF32, true>(a1, (unsigned)grid, st);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         hipLaunchKernelGGL(lse_combine_kernel<kSub>, dim3((a.n_pad + 255) / 256, a.batch * a.q_heads), dim3(256), 0, st, a1);
         return hipGetLastError();
@@ -1444,14 +1120,14 @@ static hipError_t launch_pass1_t(ScoreArgs& a, hipStream_t st)
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
     const unsigned grid1 = kXcds * (unsigned)(a.p1_by_block ? per_xcd : kXcdWaves);
-    hipLaunchKernelGGL((score_pass1_stream_kernel<T, D, false>), dim3(grid1), dim3(kWave), 0, st, a1);
+    start_pass1<kF32, false>(a1, grid1, st);
     return hipGetLastError();
 }
 
-template <typename T, int D>
+template <bool kF32>
 static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
 {
-    constexpr int kSub = Stream<T>::kSub, kKeys = 32 * kSub;
+    constexpr int kSub = kF32 ? kSubF32 : ems::kSub, kKeys = 32 * kSub;
     const int BKV = a.batch * a.kv_heads;
     const int n_key_tiles = (a.seq_len + kKeys - 1) / kKeys;
     if (a.lse_in_nat) {
@@ -1463,7 +1139,7 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
     if (a.p2_waves) {
         const long long grid = deal_grid(BKV, a.p2_waves);
         if (grid > 0x7fffffffll) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((score_pass2_stream_kernel<T, D, true>), dim3((unsigned)grid), dim3(kWave), 0, st, a);
+        start_pass2<kF32, true>(a, (unsigned)grid, st);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
         hipLaunchKernelGGL(score_reduce_deal_kernel<kSub>, reduce_grid, dim3(256), 0, st, a);
         return hipGetLastError();
@@ -1492,7 +1168,7 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
         hipLaunchKernelGGL(score_queue_reset_kernel, dim3(1), dim3(64), 0, st, a.queue);
         if (hipGetLastError() != hipSuccess) return hipErrorLaunchFailure;
     }
-    hipLaunchKernelGGL((score_pass2_stream_kernel<T, D, false>), dim3((unsigned)grid2), dim3(kWave), 0, st, a2);
+    start_pass2<kF32, false>(a2, (unsigned)grid2, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.n_chunks > 1) {
@@ -1502,17 +1178,7 @@ static hipError_t launch_pass2_t(const ScoreArgs& a, hipStream_t st)
     return e;
 }
 
-#define EMS_DISPATCH(fn, a, f32, st)                                         \
-    do {                                                                     \
-        if (f32) {                                                           \
-            if ((a).head_dim == 64) return fn<float, 64>(a, st);             \
-            return fn<float, 128>(a, st);                                    \
-        }                                                                    \
-        if ((a).head_dim == 64) return fn<bf16_t, 64>(a, st);                \
-        return fn<bf16_t, 128>(a, st);                                       \
-    } while (0)
-
-hipError_t launch_score_pass1(ScoreArgs& a, bool f32, hipStream_t st) { EMS_DISPATCH(launch_pass1_t, a, f32, st); }
-hipError_t launch_score_pass2(const ScoreArgs& a, bool f32, hipStream_t st) { EMS_DISPATCH(launch_pass2_t, a, f32, st); }
+hipError_t launch_score_pass1(ScoreArgs& a, bool f32, hipStream_t st) { return f32 ? launch_pass1_t<true>(a, st) : launch_pass1_t<false>(a, st); }
+hipError_t launch_score_pass2(const ScoreArgs& a, bool f32, hipStream_t st) { return f32 ? launch_pass2_t<true>(a, st) : launch_pass2_t<false>(a, st); }
 
 }  // namespace ems

@@ -1,0 +1,556 @@
+// The two score passes (score.hip) in float32, the mode that checks the 16-bit one.
+//
+// A float32 product costs sixteen times the matrix time of a 16-bit one.  Every operand is therefore
+// written as the exact sum of three bf16 pieces (a float's 24 digits are three times eight),
+// x = h + m + l with |m| <= 2^-9 |x|, |l| <= 2^-18 |x|, and a product as the six products of pieces down to
+// 2^-18: hh, hm, mh, mm, hl, lh (what is left out, ml and lm, is below 2^-26).  Six
+// 32x32x16 instructions of 32 clocks stand where eight 32x32x2 ones of 64 did, and a sum of 128 products is
+// rounded 48 times instead of 64.  Measured (us of the first / second pass by float32 products, now): 8 heads over 2 of 128, 3000 rows
+// 93.5 / 107.1 -> 54.7 / 62.5; 32 over 8, 6000 rows 1234 / 1282 -> 698 / 697, of 64 594 / 604 -> 394 / 394; the whole case of 8 heads
+// 226 -> 141.  Column sums against 64 bits, rms of 16 seeds each: 700 to 5000 rows of 128 0.9-1.7e-7 -> 0.9-1.3e-7 (all rows),
+// 1.2-3.2e-7 -> 1.1-2.7e-7 (window); of 64 0.7-1.3e-7 -> 0.6-1.2e-7, 1.0-2.2e-7 -> 0.8-2.0e-7.
+//
+// A wave keeps 64 rows in registers as their pieces (split once per item) and streams the other operand as
+// float32 through its ring of two stages; a stage is split on the way to the matrix pipe, in the vector slots
+// between the products: per 16 columns 12 products (384 clocks), 44 operations of splitting, 12 to 24 of weighing the
+// stage before.  That is what bounds it: 3072 clocks of products and up to 2900 of issue per stage of 32 x 64 x 128.
+//
+// Not every float has three such pieces.  Infinities, NaN and values that round to infinity in bf16 give NaN, which no
+// later step loses; rows with elements of 2^60 and more, or below 2^-100 (whose low piece falls below bf16's range
+// while the other factor could be large), are found when they are split.  Either sends the item to a plain loop of
+// float32 instructions, so that infinite logits come out as they do there.
+#include "ems_common.h"
+#include "ems_kernels.h"
+#include "ems_score.h"
+#include "ems_stream.h"
+
+namespace ems {
+
+typedef __bf16 bf16x2v_t __attribute__((ext_vector_type(2)));
+typedef float f32x2v_t __attribute__((ext_vector_type(2)));
+
+// two floats -> their bf16 pieces of one level (rounded to nearest even), and what they leave
+__device__ __forceinline__ int split_pair(float& x0, float& x1)
+{
+    const int p = __builtin_bit_cast(int, __builtin_convertvector(f32x2v_t{x0, x1}, bf16x2v_t));
+    x0 -= __builtin_bit_cast(float, p << 16);
+    x1 -= __builtin_bit_cast(float, p & (int)0xffff0000);
+    return p;
+}
+__device__ __forceinline__ int last_pair(float x0, float x1)
+{
+    return __builtin_bit_cast(int, __builtin_convertvector(f32x2v_t{x0, x1}, bf16x2v_t));
+}
+
+// Eight consecutive-in-K elements of a row as pieces: the operand of three products.
+struct Pieces { frag_t h, m, l; };
+
+__device__ __forceinline__ void mma_piece(f32x16_t& acc, const frag_t& a, const frag_t& b, bool start)
+{
+    if (start) mma_first<bf16_t>(acc, a, b);
+    else mma<bf16_t>(acc, a, b);
+}
+
+// Keeps what forms the value before this point (the compiler would move a stage's vector work past its
+// last product, where branches follow and the matrix pipe is idle).
+__device__ __forceinline__ void stays_here(float& x) { asm volatile("" : "+v"(x)); }
+
+template <int D>
+struct F32 {
+    static constexpr int kFrags = Tile<float, D>::kFrags;              // 16-byte fragments a lane has of a row
+    static constexpr int kSteps = kFrags / 2;                          // 16 columns each
+    static constexpr int kRowBytes = Tile<float, D>::kRowBytes;
+    static constexpr int kCpr = Tile<float, D>::kChunksPerRow;
+    static constexpr int kStageBytes = kStreamRows * kRowBytes;
+    static constexpr int kInstr = kStageBytes / 1024;                  // DMA instructions per stage
+    static constexpr int kPerStep = 16 / kSteps;                       // accumulator elements of a tile weighed per step
+    static_assert(kInstr % 4 == 0 && kSteps % 2 == 0 && kSteps >= 4, "");
+
+    // where a lane finds its fragments of its row of 32, 32 bytes apart (past the end of the matrix: of the last row, whose
+    // results there are not kept)
+    static __device__ __forceinline__ const char* row_bytes(const float* X, int row0, int N, int lane)
+    {
+        return reinterpret_cast<const char*>(X) + (size_t)min(row0 + (lane & 31), N - 1) * kRowBytes + (lane >> 5) * 16;
+    }
+    // the 32 * kSubF32 rows from row0 on, as pieces; true if a row's elements may not be split (see above)
+    static __device__ __forceinline__ bool load_stationary(const float* X, int row0, int N, int lane, Pieces (&b)[kSubF32][kSteps])
+    {
+        float most = 0.f, least = INFINITY;
+#pragma unroll
+        for (int s = 0; s < kSubF32; ++s) {
+            const char* x = row_bytes(X, row0 + s * 32, N, lane);
+            frag_t raw[kFrags];
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) raw[f] = *reinterpret_cast<const frag_t*>(x + f * 32);
+#pragma unroll
+            for (int f = 0; f < kSteps; ++f) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const f32x4_t v = __builtin_bit_cast(f32x4_t, raw[2 * f + w / 2]);
+                    float x0 = v[2 * (w & 1)], x1 = v[2 * (w & 1) + 1];
+                    most = fmaxf(most, fmaxf(fabsf(x0), fabsf(x1)));
+                    least = fminf(least, fminf(x0 == 0.f ? INFINITY : fabsf(x0), x1 == 0.f ? INFINITY : fabsf(x1)));
+                    b[s][f].h[w] = split_pair(x0, x1);
+                    b[s][f].m[w] = split_pair(x0, x1);
+                    b[s][f].l[w] = last_pair(x0, x1);
+                }
+                // (the accumulation registers, which only the products read)
+                asm volatile("" : "+a"(b[s][f].h)); asm volatile("" : "+a"(b[s][f].m)); asm volatile("" : "+a"(b[s][f].l));
+            }
+            __builtin_amdgcn_sched_barrier(0);                         // one subtile's rows at a time
+        }
+        return !(most < 0x1p60f) || least < 0x1p-100f;
+    }
+
+    // Source offsets of a stage's DMA, less what the instruction itself adds (1 KiB x its place in a group of four); those of
+    // the stage's second 16 rows are the same again.
+    static constexpr int kOffs = kInstr / 2;
+    static_assert(kOffs % 4 == 0, "");
+    static __device__ __forceinline__ void dma_offsets(int lane, unsigned (&off)[kOffs])
+    {
+#pragma unroll
+        for (int j = 0; j < kOffs; ++j) {
+            const int slot = j * kWave + lane, row = slot / kCpr;
+            off[j] = (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz_key<float, D>(row)) << 4) - (unsigned)(j % 4) * 1024u;
+        }
+    }
+    // DMA of 32 rows from `row` on into the ring slot at `dst`; rows past the end re-read the last one
+    static __device__ __forceinline__ void issue(const char* base, int row, int N, unsigned dst, const unsigned (&off)[kOffs])
+    {
+        const char* from = base + (size_t)row * kRowBytes;
+        if (row + kStreamRows <= N) {
+#pragma unroll
+            for (int j = 0; j < kInstr; j += 4) {
+                const int i = j % kOffs;
+                dma_to_lds_x4(from + j / kOffs * (16 * kRowBytes), off[i], off[i + 1], off[i + 2], off[i + 3], dst + j * 1024);
+            }
+        } else {
+            const int lane = lane_here();                              // (nothing is kept for this)
+#pragma unroll
+            for (int j = 0; j < kInstr; ++j) {
+                const int over = max(row + (j * kWave + lane) / kCpr - (N - 1), 0);
+                dma_to_lds<16>(base, (unsigned)row * kRowBytes + off[j % kOffs] + j / kOffs * (16 * kRowBytes) + (unsigned)(j % 4) * 1024u - (unsigned)over * kRowBytes, dst + j * 1024);
+            }
+        }
+    }
+    // a lane's fragment f of its row of a stage (the swizzle touches the low chunk bits only)
+    static constexpr int kKeys = kCpr >= 16 ? 8 : 4;                   // distinct offsets: 16 or 8 chunks swizzled together, two of a fragment
+    static __device__ __forceinline__ void frag_offsets(int lane, unsigned (&off)[kKeys])
+    {
+        const int col = lane & 31, half = lane >> 5;
+#pragma unroll
+        for (int f = 0; f < kKeys; ++f) off[f] = (unsigned)col * kRowBytes + (unsigned)(((f * 2 + half) ^ swz_key<float, D>(col)) << 4);
+    }
+    static __device__ __forceinline__ frag_t fetch(const char* stage, const unsigned (&off)[kKeys], int f)
+    {
+        return *reinterpret_cast<const frag_t*>(stage + off[f % kKeys] + (f / kKeys) * (kKeys * 32));
+    }
+
+    // The streamed operand on its way from LDS to the matrix pipe: raw fragments two steps ahead of the products,
+    // pieces one.
+    struct Feed {
+        frag_t raw[2][2];                                              // by step parity
+        Pieces now, next;
+        float x[8];                                                    // what is left of the elements being split
+        __device__ __forceinline__ void take(int parity)
+        {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const f32x4_t v = __builtin_bit_cast(f32x4_t, raw[parity][i]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[4 * i + e] = v[e];
+            }
+        }
+        __device__ __forceinline__ void part(int slot)                 // 1/12 of the splitting
+        {
+            if (slot < 4) next.h[slot] = split_pair(x[2 * slot], x[2 * slot + 1]);
+            else if (slot < 8) next.m[slot - 4] = split_pair(x[2 * slot - 8], x[2 * slot - 7]);
+            else if (slot < 10) {
+#pragma unroll
+                for (int w = 2 * slot - 16; w < 2 * slot - 14; ++w) next.l[w] = last_pair(x[2 * w], x[2 * w + 1]);
+            }
+        }
+        // the first step of the first stage
+        __device__ __forceinline__ void start(const char* stage, const unsigned (&off)[kKeys])
+        {
+            raw[0][0] = fetch(stage, off, 0); raw[0][1] = fetch(stage, off, 1);
+            raw[1][0] = fetch(stage, off, 2); raw[1][1] = fetch(stage, off, 3);
+            take(0);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) part(k);
+            now = next;
+        }
+    };
+
+    // The products of one stage, 32 streamed rows x kSubF32 tiles.  `landed` waits for the next stage (which
+    // step kSteps - 2 begins to read); `weigh(f, i)`: vector work of slot i of 12 of step f.
+    template <class Landed, class Weigh>
+    static __device__ __forceinline__ void stage(const char* here, const char* after, const unsigned (&off)[kKeys], Feed& q,
+                                                 const Pieces (&b)[kSubF32][kSteps], f32x16_t (&acc)[kSubF32], Landed landed, Weigh weigh)
+    {
+#pragma unroll
+        for (int f = 0; f < kSteps; ++f) {
+            if (f == kSteps - 2) landed();
+            q.take((f + 1) & 1);
+            {
+                const char* from = f + 2 < kSteps ? here : after;
+                const int at = (f + 2) % kSteps * 2;
+                q.raw[f & 1][0] = fetch(from, off, at);
+                q.raw[f & 1][1] = fetch(from, off, at + 1);
+            }
+#pragma unroll
+            for (int i = 0; i < 12; ++i) {
+                const int s = i & 1, k = i >> 1;                       // the two tiles' chains alternate; small products first
+                const Pieces& p = b[s][f];
+                const frag_t& x = k == 0 ? q.now.l : k == 1 || k == 5 || k == 4 ? q.now.h : q.now.m;
+                const frag_t& y = k == 1 ? p.l : k == 2 || k == 4 ? p.m : p.h;
+                mma_piece(acc[s], x, y, f == 0 && k == 0);
+                q.part(i);
+                weigh(f, i);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            q.now = q.next;
+        }
+    }
+};
+
+// ------------------------------------------------------------------------------------
+// Second pass: 64 keys stationary, the query rows of every q-head of the group streamed with their log-sum-exp.
+// The weights of a stage are formed under the products of the next one; those of a stage with window rows (which go
+// to the local sums too) at its end.  Rows above the diagonal get logits of -inf.
+// ------------------------------------------------------------------------------------
+template <int D, bool kDeal>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_f32_kernel(ScoreArgs a)
+{
+    using E = F32<D>;
+    constexpr int kSub = kSubF32, kKeys = 32 * kSub, kSteps = E::kSteps, kEach = E::kPerStep;
+    __shared__ __attribute__((aligned(1024))) char lds_q[2][E::kStageBytes];
+    __shared__ __attribute__((aligned(256))) float lds_lse[2][2 * kStreamRows];       // second half: spare
+
+    const float c = a.scale_log2e;
+    const int N = a.seq_len, win0 = N - a.window, G = a.q_heads / a.kv_heads;
+    Pass2Items<kSub, kDeal> items(a);
+    while (items.next()) {
+    const int key_base = items.J * kKeys, bkv = items.bkv, r_begin = items.r_begin, r_end = items.r_end;
+    const int b = bkv / a.kv_heads, kvh = bkv % a.kv_heads;
+    const float* K = reinterpret_cast<const float*>(a.k) + ((size_t)bkv * N) * D;
+    const float* Q0 = reinterpret_cast<const float*>(a.q) + ((size_t)(b * a.q_heads + kvh * G) * N) * D;
+    const float* L0 = a.lse2 + (size_t)(b * a.q_heads + kvh * G) * a.n_pad;
+    const int lane = opaque_lane(threadIdx.x);
+    const int col = lane & 31, half = lane >> 5;
+
+    Pieces bk[kSub][kSteps];
+    bool plain = E::load_stationary(K, key_base, N, lane, bk);
+    unsigned dma_off[E::kOffs], frag_off[E::kKeys];
+    E::dma_offsets(lane, dma_off);
+    E::frag_offsets(lane, frag_off);
+    const unsigned lds_q0 = lds_address(&lds_q[0][0]), lds_l0 = lds_address(&lds_lse[0][0]);
+    wait_vmem_all_visible();
+
+    const int per_head = (r_end - r_begin + kStreamRows - 1) / kStreamRows, n_stages = per_head * G;
+    int g_next = 0, row_next = r_begin, row_now = r_begin;              // the stage to fetch next, the present one
+    auto issue_next = [&](int slot) __attribute__((always_inline)) {
+        E::issue(reinterpret_cast<const char*>(Q0) + (size_t)g_next * N * E::kRowBytes, row_next, N, lds_q0 + slot * E::kStageBytes, dma_off);
+        // the rows' log-sum-exp (+inf up to n_pad); the upper half-wave's copy goes to the spare half of the slot
+        dma_to_lds<4>(L0 + (size_t)g_next * a.n_pad, (unsigned)(row_next + col) * 4u, lds_l0 + slot * (2 * kStreamRows * 4));
+        row_next += kStreamRows;
+        if (row_next >= r_end) { row_next = r_begin; ++g_next; }
+    };
+
+    f32x16_t acc[2][kSub], lse_v[2];
+    float part[kSub][2], aside[kSub], loc[kSub];
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) { part[s][0] = part[s][1] = aside[s] = loc[s] = 0.f; acc[1][s] = zero_acc(); }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) lse_v[1][r] = INFINITY;                // before the first stage: weights of zero
+    typename E::Feed feed;
+    issue_next(0);
+    wait_vmem<0>();
+    feed.start(lds_q[0], frag_off);
+
+    auto stage = [&](auto set_c, int t) __attribute__((always_inline)) {
+        constexpr int set = decltype(set_c)::value;
+        // the other slot was last read (its log-sum-exp included) before the last steps of the stage before this one
+        wait_lds_all_visible();
+        if (t + 1 < n_stages) issue_next(1 - set);
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(lds_lse[set] + 8 * q4 + 4 * half);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lse_v[set][4 * q4 + i] = v[i];
+        }
+        E::stage(lds_q[set], lds_q[1 - set], frag_off, feed, bk, acc[set], []() __attribute__((always_inline)) { wait_vmem<0>(); },
+                 [&](int f, int i) __attribute__((always_inline)) {
+                     // 2 * kEach elements of the stage before, one in each of the last slots
+                     const int e = i - (12 - 2 * kEach);
+                     if (e < 0) return;
+                     const int s = e & 1, r = f * kEach + (e >> 1);
+                     part[s][r & 1] += exp2_fast(__builtin_fmaf(acc[1 - set][s][r], c, -lse_v[1 - set][r]));
+                 });
+#pragma unroll
+        for (int s = 0; s < kSub; ++s) { stays_here(part[s][0]); stays_here(part[s][1]); }
+        const int row0 = row_now;
+        row_now += kStreamRows;
+        if (row_now >= r_end) row_now = r_begin;
+        if (row0 < key_base + kKeys) {                                  // on the diagonal: rows before the key
+            const int lane = lane_here(), col = lane & 31, half = lane >> 5;      // (nothing is kept for this)
+#pragma unroll
+            for (int s = 0; s < kSub; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (row0 + acc_row(r, half) < key_base + s * 32 + col) acc[set][s][r] = -INFINITY;
+        }
+        if (row0 + kStreamRows > win0) {                                // rows of the window: at once, and none left for the next stage
+            const int half = lane_here() >> 5;
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                float p[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[set][s][r], c, -lse_v[set][r]));
+                part[s][0] += sum16(p);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) p[r] = row0 + acc_row(r, half) < win0 ? 0.f : p[r];
+                loc[s] += sum16(p);
+                acc[set][s] = zero_acc();
+            }
+#pragma unroll
+            for (int r = 0; r < 16; ++r) lse_v[set][r] = INFINITY;
+        }
+    };
+    const int fold = kFoldRows / kStreamRows * max(G, 2) / 2 * 2;
+    int until_fold = fold;
+    int t = 0;
+    do {                                                                // (an item has rows)
+        stage(ic<0>{}, t);
+        if (t + 1 < n_stages) stage(ic<1>{}, t + 1);
+        until_fold -= 2;
+        if (until_fold == 0) {
+            until_fold = fold;
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) { aside[s] += part[s][0] + part[s][1]; part[s][0] = part[s][1] = 0.f; }
+        }
+    } while ((t += 2) < n_stages);
+    wait_vmem<0>();
+    auto last = [&](const f32x16_t (&x)[kSub], const f32x16_t& l) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < kSub; ++s)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) part[s][r & 1] += exp2_fast(__builtin_fmaf(x[s][r], c, -l[r]));
+    };
+    if (n_stages & 1) last(acc[0], lse_v[0]);
+    else last(acc[1], lse_v[1]);
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) {
+        aside[s] += part[s][0] + part[s][1];
+        plain |= !(aside[s] < INFINITY) || !(loc[s] < INFINITY);
+    }
+    if (__any(plain)) {                                                 // wave-uniform
+#pragma unroll 1
+        for (int s = 0; s < kSub; ++s) {
+            constexpr int kFrags = E::kFrags;
+            const int lane = lane_here(), col = lane & 31, half = lane >> 5;      // (nothing is kept for this path)
+            const char* k = E::row_bytes(K, key_base + s * 32, N, lane);
+            frag_t bf[kFrags];
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) bf[f] = *reinterpret_cast<const frag_t*>(k + f * 32);
+            float glo = 0.f, lo = 0.f;
+            for (int g = 0; g < G; ++g)
+                for (int row0 = r_begin; row0 < r_end; row0 += kStreamRows) {
+                    const char* q = E::row_bytes(Q0 + (size_t)g * N * D, row0, N, lane);
+                    frag_t aq[kFrags];
+                    f32x16_t l;
+#pragma unroll
+                    for (int f = 0; f < kFrags; ++f) aq[f] = *reinterpret_cast<const frag_t*>(q + f * 32);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) l[r] = L0[(size_t)g * a.n_pad + row0 + acc_row(r, half)];
+                    stream_edge_tile<float, D>(aq, bf, l, c, glo, lo, row0, key_base + s * 32 + col, half, win0);
+                }
+            if (s == 0) { aside[0] = glo; loc[0] = lo; }
+            else { aside[1] = glo; loc[1] = lo; }
+        }
+    }
+    float *out_glo, *out_loc;
+    items.outputs(out_glo, out_loc);
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) {
+        const float gsum = halves_sum(aside[s]), lsum = halves_sum(loc[s]);       // the half-waves hold disjoint rows of the same keys
+        const int kj = key_base + s * 32 + col;
+        if (half == 0 && kj < N) {
+            out_glo[kj] = gsum;
+            if (out_loc) out_loc[kj] = lsum;
+        }
+    }
+    }   // next work item
+}
+
+// ------------------------------------------------------------------------------------
+// First pass: 64 query rows stationary, keys streamed.  The running maximum and the rescaled sum of a stage are formed under the
+// products of the next one; keys above the diagonal get logits of -inf.
+// ------------------------------------------------------------------------------------
+template <int D, bool kDeal>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_f32_kernel(ScoreArgs a)
+{
+    using E = F32<D>;
+    constexpr int kSub = kSubF32, kRows = 32 * kSub, kSteps = E::kSteps, kEach = E::kPerStep;
+    constexpr int kFold = kFoldKeys / kStreamRows;
+    __shared__ __attribute__((aligned(1024))) char lds_k[2][E::kStageBytes];
+
+    const float c = a.scale_log2e;
+    const int N = a.seq_len, G = a.q_heads / a.kv_heads;
+    Pass1Items<kSub, kDeal> items(a);
+    while (items.next()) {
+    const int rt = items.rt, bkv = items.bkv, t0 = items.t0, t1 = items.t1;
+    const int b = bkv / a.kv_heads, h = (bkv % a.kv_heads) * G + items.g;
+    const float* Q = reinterpret_cast<const float*>(a.q) + ((size_t)(b * a.q_heads + h) * N) * D;
+    const float* K = reinterpret_cast<const float*>(a.k) + ((size_t)bkv * N) * D;
+    const int lane = opaque_lane(threadIdx.x);
+    const int col = lane & 31, half = lane >> 5;
+    const int q_base = rt * kRows;
+
+    Pieces bq[kSub][kSteps];
+    bool plain = E::load_stationary(Q, q_base, N, lane, bq);
+    unsigned dma_off[E::kOffs], frag_off[E::kKeys];
+    E::dma_offsets(lane, dma_off);
+    E::frag_offsets(lane, frag_off);
+    const unsigned lds_k0 = lds_address(&lds_k[0][0]);
+    wait_vmem_all_visible();
+    auto issue = [&](int t) __attribute__((always_inline)) {
+        E::issue(reinterpret_cast<const char*>(K), t * kStreamRows, N, lds_k0 + ((t - t0) & 1) * E::kStageBytes, dma_off);
+    };
+
+    // running maximum, the reference in use (0 while nothing is seen), the sums since the last fold and before it
+    float m_run[kSub], m_use[kSub], l_run[kSub][2], l_old[kSub];
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) { m_run[s] = -INFINITY; m_use[s] = 0.f; l_run[s][0] = l_run[s][1] = l_old[s] = 0.f; }
+    auto raise = [&](int s, const f32x16_t& x) __attribute__((always_inline)) {
+        const float m_new = fmaxf(m_run[s], max16(x) * c);
+        m_use[s] = m_new == -INFINITY ? 0.f : m_new;
+        const float down = exp2_fast(m_run[s] - m_use[s]);
+        l_run[s][0] *= down; l_run[s][1] *= down; l_old[s] *= down;
+        m_run[s] = m_new;
+    };
+    auto add = [&](int s, int r, const f32x16_t& x) __attribute__((always_inline)) {
+        l_run[s][r & 1] += exp2_fast(__builtin_fmaf(x[r], c, -m_use[s]));
+    };
+
+    const int n_stages = t1 - t0;                                       // (none where a part is padding)
+    if (n_stages > 0) {
+        f32x16_t acc[2][kSub];
+#pragma unroll
+        for (int s = 0; s < kSub; ++s)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[1][s][r] = -INFINITY;      // before the first stage: nothing seen
+        typename E::Feed feed;
+        issue(t0);
+        wait_vmem<0>();
+        feed.start(lds_k[0], frag_off);
+        auto stage = [&](auto set_c, int t) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            wait_lds_all_visible();                                     // (the other slot's last reads)
+            if (t + 1 < t1) issue(t + 1);
+            E::stage(lds_k[set], lds_k[1 - set], frag_off, feed, bq, acc[set], []() __attribute__((always_inline)) { wait_vmem<0>(); },
+                     [&](int f, int i) __attribute__((always_inline)) {
+                         if (f == 0 && i < 2) raise(i, acc[1 - set][i]);
+                         const int e = i - (12 - 2 * kEach);
+                         if (e >= 0) add(e & 1, f * kEach + (e >> 1), acc[1 - set][e & 1]);
+                     });
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) { stays_here(l_run[s][0]); stays_here(l_run[s][1]); }
+            if (t * kStreamRows + kStreamRows > q_base) {               // on the diagonal: keys after the row
+                const int lane = lane_here(), col = lane & 31, half = lane >> 5;  // (nothing is kept for this)
+#pragma unroll
+                for (int s = 0; s < kSub; ++s)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (t * kStreamRows + acc_row(r, half) > q_base + s * 32 + col) acc[set][s][r] = -INFINITY;
+            }
+        };
+        int until_fold = kFold;
+        int t = t0;
+        do {
+            stage(ic<0>{}, t);
+            if (t + 1 < t1) stage(ic<1>{}, t + 1);
+            until_fold -= 2;
+            if (until_fold == 0) {                                      // a long sum is set aside, so that small weights are not lost against it
+                until_fold = kFold;
+#pragma unroll
+                for (int s = 0; s < kSub; ++s) { l_old[s] += l_run[s][0] + l_run[s][1]; l_run[s][0] = l_run[s][1] = 0.f; }
+            }
+        } while ((t += 2) < t1);
+        wait_vmem<0>();
+        auto last = [&](const f32x16_t (&x)[kSub]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                raise(s, x[s]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) add(s, r, x[s]);
+            }
+        };
+        if (n_stages & 1) last(acc[0]);
+        else last(acc[1]);
+    }
+    float L[kSub];
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) {
+        L[s] = l_old[s] + (l_run[s][0] + l_run[s][1]);
+        plain |= !(L[s] < INFINITY);
+    }
+    if (__any(plain)) {                                                 // wave-uniform
+#pragma unroll 1
+        for (int s = 0; s < kSub; ++s) {
+            constexpr int kFrags = E::kFrags;
+            const int lane = lane_here(), half = lane >> 5;                       // (nothing is kept for this path)
+            const int qs0 = q_base + s * 32;
+            const char* q = E::row_bytes(Q, qs0, N, lane);
+            frag_t bf[kFrags];
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) bf[f] = *reinterpret_cast<const frag_t*>(q + f * 32);
+            float m = -INFINITY, l = 0.f;
+            for (int key0 = t0 * kStreamRows; key0 < min(t1 * kStreamRows, qs0 + 32); key0 += kStreamRows) {
+                const char* k = E::row_bytes(K, key0, N, lane);
+                frag_t ak[kFrags];
+#pragma unroll
+                for (int f = 0; f < kFrags; ++f) ak[f] = *reinterpret_cast<const frag_t*>(k + f * 32);
+                pass1_tile<float, D>(ak, bf, m, l, c, key0, qs0 + (lane & 31), half);
+            }
+            if (s == 0) { m_run[0] = m; L[0] = l; }
+            else { m_run[1] = m; L[1] = l; }
+        }
+    }
+
+    const size_t bh = (size_t)(b * a.q_heads + h);
+    float* lse2 = a.lse2 + bh * a.n_pad;
+#pragma unroll
+    for (int s = 0; s < kSub; ++s) {
+        const float m_o = __shfl_xor(m_run[s], 32), l_o = __shfl_xor(L[s], 32);
+        const float M = fmaxf(m_run[s], m_o), Mu = M == -INFINITY ? 0.f : M;
+        const float sum = L[s] * exp2_fast(m_run[s] - Mu) + l_o * exp2_fast(m_o - Mu);
+        const int qi = q_base + s * 32 + col;
+        if constexpr (kDeal) {                                          // a part, for lse_combine_kernel
+            const size_t at = (bh * (a.p1_waves + items.deal.n_units) + items.place.wave + rt) * kRows + s * 32 + col;
+            if (half == 0) { a.part_m[at] = M; a.part_l[at] = sum; }
+        } else {
+            const float v = Mu + log2_fast(sum);
+            if (half == 0 && qi < a.n_pad) lse2[qi] = qi < N ? v : INFINITY;      // rows past the end: weight zero in the second pass
+            if (half == 0 && qi < N && a.lse_opt) a.lse_opt[bh * N + qi] = v * 0.693147180559945309f;
+        }
+    }
+    }   // next work item
+}
+
+template <int D>
+static void start_pass1_d(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st)
+{
+    if (deal) hipLaunchKernelGGL((score_pass1_f32_kernel<D, true>), dim3(grid), dim3(kWave), 0, st, a);
+    else hipLaunchKernelGGL((score_pass1_f32_kernel<D, false>), dim3(grid), dim3(kWave), 0, st, a);
+}
+template <int D>
+static void start_pass2_d(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st)
+{
+    if (deal) hipLaunchKernelGGL((score_pass2_f32_kernel<D, true>), dim3(grid), dim3(kWave), 0, st, a);
+    else hipLaunchKernelGGL((score_pass2_f32_kernel<D, false>), dim3(grid), dim3(kWave), 0, st, a);
+}
+void start_pass1_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st) { a.head_dim == 64 ? start_pass1_d<64>(a, deal, grid, st) : start_pass1_d<128>(a, deal, grid, st); }
+void start_pass2_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st) { a.head_dim == 64 ? start_pass2_d<64>(a, deal, grid, st) : start_pass2_d<128>(a, deal, grid, st); }
+
+}  // namespace ems

@@ -101,6 +101,37 @@ def test_score_short_float32_stretches(n, d):
     test_score_even_deal((1, 8, 2, d, n, 40), B.EMS_F32)
 
 
+@pytest.mark.parametrize("what", ["wide", "tiny", "huge", "infinite"])
+@pytest.mark.parametrize("d", [64, 128])
+def test_score_float32_values_that_do_not_split(what, d):
+    """The float32 passes multiply bf16 pieces of their operands; values without three such pieces are redone by float32
+    products.  "wide": elements over 40 binary orders, which do split.  "tiny" and "huge": some of one side's elements times
+    2^-112 or 2^70, the other side's the other way.  "infinite": keys of -inf where every query is positive (logits of -inf: no weight),
+    and rows next to float32's largest value.  Tolerance: the stated bars."""
+    b, hq, hkv, n, w = 1, 4, 2, 700, 40
+    gen = np.random.default_rng(len(what) + d)
+    q, k = (gen.standard_normal((b, h, n, d)).astype(np.float32) for h in (hq, hkv))
+    if what == "wide":
+        q *= 2.0 ** gen.integers(-40, 1, q.shape).astype(np.float32)
+    elif what == "tiny":
+        q[..., :8] *= np.float32(2.0 ** 112); k[..., :8] *= np.float32(2.0 ** -112)
+    elif what == "huge":
+        q[..., 5] *= np.float32(2.0 ** -70); k[..., 5] *= np.float32(2.0 ** 70)
+    else:
+        q[..., 3] = np.abs(q[..., 3]) + np.float32(0.1)
+        k[:, 0, 100:400:7, 3] = -np.inf
+        q[..., 9] *= np.float32(2.0 ** -124)
+        k[:, 1, ::5, 9] = np.float32(-3.4e38)
+    p = B.EmsParams(b, hq, hkv, d, n, w, dtype=B.EMS_F32)
+    s_glo, s_loc, lse = B.ems_global_local_score(p, torch.from_numpy(q).cuda(), torch.from_numpy(k).cuda(), want_lse=True)
+    o_glo, o_loc, o_lse = ems_ref.score(ref_params(p), q, k, want_lse=True)
+    live = ~np.isneginf(k).any(-1)
+    assert (s_glo.cpu().numpy()[~live] == 0).all() and (s_loc.cpu().numpy()[~live] == 0).all()
+    assert_rel(s_glo.cpu().numpy()[live], o_glo[live], RTOL[B.EMS_F32], "s_glo")
+    assert_rel(s_loc.cpu().numpy()[live], o_loc[live], RTOL[B.EMS_F32], "s_loc")
+    np.testing.assert_allclose(lse.cpu().numpy(), o_lse, rtol=0, atol=2e-5)
+
+
 @pytest.mark.parametrize("mode,shape,forms", [
     (B.EMS_BF16, (1, 256, 8, 64, 2040, 100), ("block", "deal")),     # two row tiles per wave, one pair per XCD
     (B.EMS_BF16, (1, 64, 2, 128, 8177, 90), ("block", "deal")),      # the q-heads of a row tile together

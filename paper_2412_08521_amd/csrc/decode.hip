@@ -4,8 +4,8 @@
 // decode_init_kernel  builds the per-token table (position, cache row, key norm, s_Glo,
 //                     s_Loc^past, s_Loc^cur) from what the prefill compression returned.
 // decode_step_kernel  one generated token: one block per (batch, kv-head) runs the whole
-//                     step (for large caches it is four launches, three over slices of the table or
-//                     of the cache rows: decode_logits_kernel, decode_weights_kernel, kPart) -- attention row of the new query over the expanded run-time
+//                     step (for large caches it is three or four launches, all but one over slices of the table or
+//                     of the cache rows: decode_logits_kernel, decode_choose_kernel, decode_commit_kernel, kPart) -- attention row of the new query over the expanded run-time
 //                     cache (one dot product per cache ROW, shared by the tokens that share
 //                     the entry; coalesced row loads, v_dot2 partials added with DPP),
 //                     score accumulation, window ring shift, least important centre, its
@@ -221,22 +221,21 @@ __global__ __launch_bounds__(256) void decode_init_kernel(DecodeInitArgs a)
 // per wave) while the cache is small.
 //
 // Large caches: one compute unit cannot pull the cache rows fast enough, nor walk the table, so the step is
-// four launches in stream order.  Few heads, over slices of the token table:
-//   decode_logits_kernel   slices of the table: every token's own row against the group's queries,
-//                          logits to the workspace, the slice's maxima, sums and scalar totals to the record
-//   decode_weights_kernel  the same slices: weights, score update, the slice's least important centre
-//   kPart = 3              slices of the centre rows: the least important centre of all, phase 3 (one block),
-//                          centre cosines (phase 5)
-//   kPart = 4              one block per head, 1024 threads: phases 6-7
+// three or four launches in stream order.  Few heads, over slices of the token table:
+//   decode_logits_kernel   slices of the table: every token's own row against the group's queries, logits to the
+//                          workspace, the slice's maxima, sums and scalar totals to the record
+//   decode_choose_kernel   the same slices and those of the centre rows, in one launch or two: weights, score update,
+//                          window shift, the least important centre, centre cosines (phase 5)
+//   decode_commit_kernel   one block per head: phases 6-7
 // A token gathers its row although tokens share entries: the row comes from the L2, and the table then needs no
 // second look at the rows' dots.  Many heads fill the chip without the table's slices, and the gathers then
 // cost more than they save:
 //   kPart = 1              slices of the cache rows: phase 1 (row dots, staged in the workspace)
 //   kPart = 2              one block per head, 1024 threads: phases 2-4
 //   kPart = 5              slices of the centre rows: phase 5
-//   kPart = 4              as above
-// (us a step, table slices / row slices, head size 128, budget 2000: 8 heads of 4 q-heads 21.9 / 25.8, 32 heads
-// 22.4 / 23.1, 64 heads of 4 37.0 / 33.9, 256 heads of 4 86.4 / 66.9.)
+//   decode_commit_kernel   as above
+// (us a step, table slices / row slices, head size 128, budget 2000: 8 heads of 4 q-heads 16.7 / 23.1, 32 heads
+// 23.2 / 25.4; when the table's slices were four launches, 64 heads of 4 37.0 / 33.9, 256 heads of 4 86.4 / 66.9.)
 // Nothing waits for another block inside a launch.  (Letting the last cosine block
 // of a head run phases 6-7 itself saves a launch and was measured slower: the next launch's latency hides
 // behind the sweep anyway.)
@@ -250,7 +249,6 @@ constexpr int kHandOldSc = 9;      // [4]  scalars of the token that left the wi
 constexpr int kHandOldPos = 13;    //      its position (int)
 constexpr int kHandStar = 14;      //      the least important centre (int)
 constexpr int kHandStep = 15;      //      tokens generated before this one (int)
-constexpr int kHandSelfTot = 16;   //      the new token's weight, all q-heads
 constexpr int kHandPart = 20;      // [kDecodeMaxSlices][2] best cosine and its centre per row slice
 constexpr int kHandStat = kHandPart + 2 * kDecodeMaxSlices;     // [18][kDecodeMaxSlices] per table slice: maxima [8], sums [8], totals of s_Glo and s_Loc
 constexpr int kHandLeast = kHandStat + 18 * kDecodeMaxSlices;   // [2][kDecodeMaxSlices] least score and its centre (int) per table slice
@@ -258,6 +256,9 @@ constexpr int kHandOldRow = kHandLeast + 2 * kDecodeMaxSlices;  // key row, then
 
 // table elements a pass of a table slice covers
 constexpr int kTokTile = 128;
+// What the logits launch leaves of a centre's own element, in pieces of 16 bytes ([piece][centre]): the group's logits, s_Glo,
+// s_Loc^cur, s_Loc^past.
+template <int G> constexpr int kCentrePieces = (G + 3 + 3) / 4;
 
 // arg-min (kMin) or arg-max over the lanes of a wave, lowest index on ties; the same in every lane
 template <bool kMin>
@@ -281,9 +282,9 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
     using T = bf16_t;
     constexpr int kLpr = Tile<T, D>::kChunksPerRow, kRows = 256 / kLpr;      // rows a block loads at a time
     constexpr int kAhead = kTokTile / kRows;
-    __shared__ float sh_dot[G][kTokTile];
+    static_assert(kAhead <= kLpr, "a lane per row");
     __shared__ float red[2 * G + 2][4];
-    const int E = a.n_imp + a.n_tbm, Tn = E + a.window, Nb = a.budget;
+    const int n_imp = a.n_imp, Tn = n_imp + a.n_tbm + a.window, Nb = a.budget;
     const int bkv = blockIdx.y, slice = blockIdx.x, tid = threadIdx.x;
     const int grp = tid / kLpr, piece = tid % kLpr;
     const char* Kc = reinterpret_cast<const char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
@@ -293,6 +294,8 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
     const char* qn = reinterpret_cast<const char*>(a.q_new) + (size_t)bkv * G * D * sizeof(T);
     const char* kn = reinterpret_cast<const char*>(a.k_new) + (size_t)bkv * D * sizeof(T);
     float* logits = a.ws + (size_t)bkv * G * Tn;
+    f32x4_t* centres = reinterpret_cast<f32x4_t*>(a.ws + a.centre_at) + (size_t)bkv * kCentrePieces<G> * n_imp;
+    const int32_t* entry_tok = a.st.entry_tok + (size_t)bkv * n_imp;
     float* hand = a.hand + (size_t)bkv * kDecodeHandFloats;
 
     frag_t qp[G];
@@ -307,8 +310,8 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
         int rr[kAhead];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) { const int j = j0 + u * kRows + grp; rr[u] = j < t_end ? tok_row[j] : -1; }
-        const int j = j0 + tid;
-        const bool mine = tid < kTokTile && j < t_end;
+        const int j = j0 + piece * kRows + grp;              // of the rows a lane group loads, lane i takes on the i-th one's token
+        const bool mine = piece < kAhead && j < t_end;
         const int r = mine ? tok_row[j] : -1;
         const float tn = mine ? a.st.tok_norm[tok0 + j] : 0.f, tg = mine ? a.st.tok_glo[tok0 + j] : 0.f;
         const float tp = mine ? a.st.tok_past[tok0 + j] : 0.f, tc = mine ? a.st.tok_cur[tok0 + j] : 0.f;
@@ -316,20 +319,23 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int u = 0; u < kAhead; ++u) fk[u] = load_frag_or_zero(Kc, ((size_t)max(rr[u], 0) * kLpr + piece) * 16, rr[u] >= 0);
         const float rn = r >= 0 ? row_norm[r] : 0.f;
-        if (j0 != slice * a.tok_slice) __syncthreads();      // the previous pass's dots are read
+        const bool centre = r >= 0 && r < n_imp && entry_tok[r] == j;
+        float dot[G];
 #pragma unroll
         for (int u = 0; u < kAhead; ++u)
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const float d = group_sum<kLpr>(dot8_bf16(fk[u], qp[g]));
-                if (piece == 0) sh_dot[g][u * kRows + grp] = d;
+                dot[g] = u == 0 || piece == u ? d : dot[g];
             }
-        __syncthreads();
         if (r >= 0) {
             const float c = a.scale_log2e * (rn > 0.f ? tn / rn : 0.f);
+            f32x4_t left[kCentrePieces<G>];
+            left[kCentrePieces<G> - 1] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const float x = c * sh_dot[g][tid];
+                const float x = c * dot[g];
+                left[g / 4][g % 4] = x;
                 const float m_new = fmaxf(m[g], x), ref = m_new > -INFINITY ? m_new : 0.f;
                 l[g] = l[g] * exp2_fast(m[g] - ref) + exp2_fast(x - ref);
                 m[g] = m_new;
@@ -337,26 +343,23 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
             }
             tot[0] += tg;
             tot[1] += tp + tc;
+            left[G / 4][G % 4] = tg; left[(G + 1) / 4][(G + 1) % 4] = tc; left[(G + 2) / 4][(G + 2) % 4] = tp;
+            if (centre) {
+#pragma unroll
+                for (int i = 0; i < kCentrePieces<G>; ++i) centres[(size_t)i * n_imp + r] = left[i];
+            }
         }
     }
     // the slice's maxima, sums relative to them, and totals
-    float top[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) top[g] = m[g];
-    block_reduce<4, G, true>(top, red);
-    float sum[G + 2];
-#pragma unroll
-    for (int g = 0; g < G; ++g) sum[g] = m[g] > -INFINITY ? l[g] * exp2_fast(m[g] - top[g]) : 0.f;
-    sum[G] = tot[0]; sum[G + 1] = tot[1];
-    block_reduce<4, G + 2, false>(sum, red);
+    block_softmax<4, G>(m, l, tot, red);
     if (tid == 0) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            hand[kHandStat + g * kDecodeMaxSlices + slice] = top[g];
-            hand[kHandStat + (8 + g) * kDecodeMaxSlices + slice] = sum[g];
+            hand[kHandStat + g * kDecodeMaxSlices + slice] = m[g];
+            hand[kHandStat + (8 + g) * kDecodeMaxSlices + slice] = l[g];
         }
-        hand[kHandStat + 16 * kDecodeMaxSlices + slice] = sum[G];
-        hand[kHandStat + 17 * kDecodeMaxSlices + slice] = sum[G + 1];
+        hand[kHandStat + 16 * kDecodeMaxSlices + slice] = tot[0];
+        hand[kHandStat + 17 * kDecodeMaxSlices + slice] = tot[1];
     }
     if (slice == 0 && tid < kLpr) {                          // the new token
         const frag_t new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
@@ -373,81 +376,313 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(DecodeStepArgs a)
     }
 }
 
-template <int G>
-__global__ __launch_bounds__(256) void decode_weights_kernel(DecodeStepArgs a)
+// Weights, the least important centre and its cosines.
+//   kChoose              in one launch: every block forms the scores of all centres for itself, from what the launch before left
+//                        of them (the table's scalars are being updated by the other blocks)
+//   kWeights, kCosines   in two: the weights and each table slice's least important centre; the least of all and its cosines
+enum ChooseStep { kChoose, kWeights, kCosines };
+template <int D, int G, int kBlock, ChooseStep kStep>
+__global__ __launch_bounds__(kBlock) void decode_choose_kernel(DecodeStepArgs a)
 {
-    __shared__ float fbuf[4];
-    __shared__ int ibuf[4];
-    const int n_imp = a.n_imp, Tn = a.n_imp + a.n_tbm + a.window;
+    using T = bf16_t;
+    constexpr bool kDoWeights = kStep != kCosines, kDoCosines = kStep != kWeights;
+    constexpr int kWaves = kBlock / kWave;
+    constexpr int kLpr = Tile<T, D>::kChunksPerRow, kRows = kBlock / kLpr;     // rows a block loads at a time
+    constexpr int kAhead = kTokTile / kRows;                 // row loads in flight per thread
+    constexpr int kCen = 4, kPieces = kCentrePieces<G>;      // centres in flight per thread
+    __shared__ float fbuf[kWaves];
+    __shared__ int ibuf[kWaves];
+    const int n_imp = a.n_imp, E = a.n_imp + a.n_tbm, Tn = E + a.window, Nb = a.budget;
     const int bkv = blockIdx.y, slice = blockIdx.x, tid = threadIdx.x, lane = tid % kWave;
+    const int grp = tid / kLpr, piece = tid % kLpr;
     const size_t tok0 = (size_t)bkv * Tn;
-    const float* logits = a.ws + (size_t)bkv * G * Tn;
+    char* Kc = reinterpret_cast<char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
+    char* Vc = reinterpret_cast<char*>(a.st.v_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
     float* hand = a.hand + (size_t)bkv * kDecodeHandFloats;
-    const int32_t* entry_tok = a.st.entry_tok + (size_t)bkv * n_imp;
+    int* hand_i = reinterpret_cast<int*>(hand);
 
-    // every wave combines the slices' records for itself
-    float sm[G], sl[G], m[G], inv[G], tot[2];
-    const bool on = lane < a.n_tok_slices;
+    // ---- what waits for nothing: the first centres' scalars, the slices' records, the first centre rows
+    f32x4_t cen[kCen][kPieces];
+    auto load_scalars = [&](int r0) __attribute__((always_inline)) {
+        const f32x4_t* centres = reinterpret_cast<const f32x4_t*>(a.ws + a.centre_at) + (size_t)bkv * kPieces * n_imp;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        sm[g] = on ? hand[kHandStat + g * kDecodeMaxSlices + lane] : -INFINITY;
-        sl[g] = on ? hand[kHandStat + (8 + g) * kDecodeMaxSlices + lane] : 0.f;
-    }
-    tot[0] = on ? hand[kHandStat + 16 * kDecodeMaxSlices + lane] : 0.f;
-    tot[1] = on ? hand[kHandStat + 17 * kDecodeMaxSlices + lane] : 0.f;
-    float self_tot = 0.f, self_w[G];
+        for (int u = 0; u < kCen; ++u)
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const float self = hand[kHandSelf + g];
-        m[g] = fmaxf(wave_reduce<true>(sm[g]), self);
-        const float sum = wave_reduce<false>(sm[g] > -INFINITY ? sl[g] * exp2_fast(sm[g] - m[g]) : 0.f) + exp2_fast(self - m[g]);
-        inv[g] = 1.0f / sum;
-        self_w[g] = exp2_fast(self - m[g]) * inv[g];
-        self_tot += self_w[g];
+            for (int i = 0; i < kPieces; ++i) cen[u][i] = centres[(size_t)i * n_imp + min(r0 + u * kBlock, n_imp - 1)];
+    };
+    if constexpr (kStep == kChoose) load_scalars(tid);
+    // (every wave combines the records for itself: a row of 16 lanes per q-head, two slices a lane)
+    static_assert(kDecodeMaxSlices == 32, "two slices a lane");
+    constexpr int kPasses = (G + 3) / 4;
+    const int row = lane / 16, at = lane % 16;
+    float sm[kPasses][2], sl[kPasses][2], self[kPasses], st[2];
+    if constexpr (kDoWeights) {
+        auto record = [&](int what, bool there, float none, float (&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) v[i] = there && at + 16 * i < a.n_tok_slices ? hand[kHandStat + what * kDecodeMaxSlices + at + 16 * i] : none;
+        };
+#pragma unroll
+        for (int q = 0; q < kPasses; ++q) {
+            const int g = 4 * q + row;
+            record(g, g < G, -INFINITY, sm[q]);
+            record(8 + g, g < G, 0.f, sl[q]);
+            self[q] = g < G ? hand[kHandSelf + g] : 0.f;
+        }
+        record(16 + row, row < 2, 0.f, st);
     }
-    // Eq. 2 factor on the updated scalars: this step adds one unit of weight per q-head to both totals
-    const float s_glo = wave_reduce<false>(tot[0]) + (float)G, s_loc = wave_reduce<false>(tot[1]) + (float)G;
-    const float align = s_glo > 0.f ? s_loc / s_glo : 0.f;
+    const int c_lo = slice * a.slice_rows, c_end = min(c_lo + a.slice_rows, n_imp);       // this block's centre rows: none where c_lo >= n_imp
+    frag_t rows[kAhead];
+    auto load_centres = [&](int s0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            rows[u] = load_frag_or_zero(Kc, ((size_t)(s0 + u * kRows + grp) * kLpr + piece) * 16, s0 + u * kRows + grp < c_end);
+    };
+    if constexpr (kDoCosines) load_centres(c_lo);
 
-    float bv = 0.f;
-    int bi = -1;
-    const int t_end = min((slice + 1) * a.tok_slice, Tn);
-    for (int j = slice * a.tok_slice + tid; j < t_end; j += 256) {
-        const int r = a.st.tok_row[tok0 + j];
-        float w[G];
-        if (r >= 0) {
-            const int centre_tok = r < n_imp ? entry_tok[r] : -1;
+    float bv = 0.f;                                          // the least important centre seen
+    int bi = -1, s_star = 0;
+    frag_t sp = zero_frag();                                 // its key
+    auto star_row = [&]() __attribute__((always_inline)) {
+        s_star = max(bi, 0);
+        sp = *reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16);
+    };
+    if constexpr (kDoWeights) {
+        float m[G], inv[G], self_w[G], self_tot = 0.f;
+#pragma unroll
+        for (int q = 0; q < kPasses; ++q) {
+            const float top = fmaxf(row_reduce<true>(fmaxf(sm[q][0], sm[q][1])), self[q]);
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sum += sm[q][i] > -INFINITY ? sl[q][i] * exp2_fast(sm[q][i] - top) : 0.f;
+            const float own = exp2_fast(self[q] - top), over = 1.0f / (row_reduce<false>(sum) + own);
+#pragma unroll
+            for (int g = 4 * q; g < min(G, 4 * q + 4); ++g) {
+                m[g] = lane_value(top, 16 * (g - 4 * q));
+                inv[g] = lane_value(over, 16 * (g - 4 * q));
+                self_w[g] = lane_value(own * over, 16 * (g - 4 * q));
+                self_tot += self_w[g];
+            }
+        }
+        // Eq. 2 factor on the updated scalars: this step adds one unit of weight per q-head to both totals
+        const float both = row_reduce<false>(st[0] + st[1]);
+        const float s_glo = lane_value(both, 0) + (float)G, s_loc = lane_value(both, 16) + (float)G;
+        const float align = s_glo > 0.f ? s_loc / s_glo : 0.f;
+        auto weights = [&](const float (&x)[G], float (&w)[G]) __attribute__((always_inline)) {
             float add = 0.f;
 #pragma unroll
-            for (int g = 0; g < G; ++g) { w[g] = exp2_fast(logits[(size_t)g * Tn + j] - m[g]) * inv[g]; add += w[g]; }
-            const float glo = a.st.tok_glo[tok0 + j] + add, cur = a.st.tok_cur[tok0 + j] + add;
-            const float past = a.st.tok_past[tok0 + j];
-            a.st.tok_glo[tok0 + j] = glo;
-            a.st.tok_cur[tok0 + j] = cur;
-            if (centre_tok == j) {                           // a class centre's own element
-                const float sc = fmaxf(glo * align, past + cur);
-                if (better<true>(sc, r, bv, bi)) { bv = sc; bi = r; }
+            for (int g = 0; g < G; ++g) { w[g] = exp2_fast(x[g] - m[g]) * inv[g]; add += w[g]; }
+            return add;
+        };
+        if constexpr (kStep == kChoose) {
+            for (int r0 = tid;;) {
+#pragma unroll
+                for (int u = 0; u < kCen; ++u) {
+                    const int r = r0 + u * kBlock;
+                    float x[G], w[G];
+#pragma unroll
+                    for (int g = 0; g < G; ++g) x[g] = cen[u][g / 4][g % 4];
+                    const float tg = cen[u][G / 4][G % 4], tc = cen[u][(G + 1) / 4][(G + 1) % 4], tp = cen[u][(G + 2) / 4][(G + 2) % 4];
+                    const float add = weights(x, w), sc = fmaxf((tg + add) * align, tp + (tc + add));
+                    if (r < n_imp && better<true>(sc, r, bv, bi)) { bv = sc; bi = r; }
+                }
+                r0 += kCen * kBlock;
+                if (r0 - tid >= n_imp) break;                // block-uniform
+                load_scalars(r0);
             }
-        } else {
+            block_arg<kWaves, true>(bv, bi, fbuf, ibuf);
+            star_row();
+        }
+
+        // ---- the block's table elements; the oldest window token leaves, the new one takes its place
+        const float* logits = a.ws + (size_t)bkv * G * Tn;
+        const int32_t* entry_tok = a.st.entry_tok + (size_t)bkv * n_imp;
+        const int step = hand_i[kHandStep], ring = step % a.window, jo = E + ring, ro = n_imp + ring;
+        const int t_end = min((slice + 1) * a.tok_slice, Tn);
+        for (int j = slice * a.tok_slice + tid; j < t_end; j += kBlock) {
+            const int r = a.st.tok_row[tok0 + j];
+            float w[G];
 #pragma unroll
             for (int g = 0; g < G; ++g) w[g] = 0.f;
-        }
-        if (a.attn_opt) {
+            if (r >= 0) {
+                float x[G];
 #pragma unroll
-            for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + j] = w[g];
-        }
-    }
-    block_arg<4, true>(bv, bi, fbuf, ibuf);
-    if (tid == 0) {
-        hand[kHandLeast + slice] = bv;
-        reinterpret_cast<int*>(hand)[kHandLeast + kDecodeMaxSlices + slice] = bi;
-        if (slice == 0) {
-            hand[kHandSelfTot] = self_tot;
+                for (int g = 0; g < G; ++g) x[g] = logits[(size_t)g * Tn + j];
+                const float add = weights(x, w), past = a.st.tok_past[tok0 + j];
+                const float glo = a.st.tok_glo[tok0 + j] + add, cur = a.st.tok_cur[tok0 + j] + add;
+                a.st.tok_glo[tok0 + j] = glo;
+                a.st.tok_cur[tok0 + j] = cur;
+                if (kStep == kWeights && r < n_imp && entry_tok[r] == j) {       // a class centre's own element
+                    const float sc = fmaxf(glo * align, past + cur);
+                    if (better<true>(sc, r, bv, bi)) { bv = sc; bi = r; }
+                }
+                if (j == jo) { hand[kHandOldSc + 1] = glo; hand[kHandOldSc + 2] = past; hand[kHandOldSc + 3] = cur; }
+            }
+            if (j == jo) {
+                const float norm = hand[kHandNewNorm];
+                hand[kHandOldSc] = a.st.tok_norm[tok0 + j];
+                hand_i[kHandOldPos] = a.st.tok_pos[tok0 + j];
+                a.st.tok_pos[tok0 + j] = a.seq_len + step; a.st.tok_row[tok0 + j] = ro; a.st.tok_norm[tok0 + j] = norm;
+                a.st.tok_glo[tok0 + j] = self_tot; a.st.tok_past[tok0 + j] = 0.f; a.st.tok_cur[tok0 + j] = self_tot;
+                a.st.row_norm[(size_t)bkv * Nb + ro] = norm;
+            }
             if (a.attn_opt) {
+#pragma unroll
+                for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + j] = w[g];
+            }
+        }
+        if constexpr (kStep == kWeights) {
+            block_arg<kWaves, true>(bv, bi, fbuf, ibuf);
+            if (tid == 0) { hand[kHandLeast + slice] = bv; hand_i[kHandLeast + kDecodeMaxSlices + slice] = bi; }
+        }
+        if (slice == 0) {
+            if (grp == 0) {
+                frag_t* const hand_row = reinterpret_cast<frag_t*>(hand + kHandOldRow);
+                char* const k_at = Kc + ((size_t)ro * kLpr + piece) * 16;
+                char* const v_at = Vc + ((size_t)ro * kLpr + piece) * 16;
+                hand_row[piece] = *reinterpret_cast<const frag_t*>(k_at);
+                hand_row[kLpr + piece] = *reinterpret_cast<const frag_t*>(v_at);
+                const size_t new_at = ((size_t)bkv * kLpr + piece) * 16;
+                *reinterpret_cast<frag_t*>(k_at) = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(a.k_new) + new_at);
+                *reinterpret_cast<frag_t*>(v_at) = *reinterpret_cast<const frag_t*>(reinterpret_cast<const char*>(a.v_new) + new_at);
+            }
+            if (a.attn_opt && tid == 0) {
 #pragma unroll
                 for (int g = 0; g < G; ++g) a.attn_opt[((size_t)bkv * G + g) * (Tn + 1) + Tn] = self_w[g];
             }
         }
+    } else {
+        bv = lane < a.n_tok_slices ? hand[kHandLeast + lane] : 0.f;
+        bi = lane < a.n_tok_slices ? hand_i[kHandLeast + kDecodeMaxSlices + lane] : -1;
+        wave_arg<true>(bv, bi);
+        star_row();
+    }
+    if constexpr (kDoCosines) {
+        if (slice == 0 && tid == 0) hand_i[kHandStar] = s_star;
+        if (c_lo >= n_imp) return;                           // block-uniform
+        // ---- its cosines with the block's centre rows (as phase 5 of the step kernel)
+        float cv = 0.f;
+        int ci = -1;
+        const float rn_star = row_inv_norm<T>(group_sum<kLpr>(frag_sumsq<T>(sp)));
+        for (int s0 = c_lo; s0 < c_end; s0 += kTokTile) {
+            if (s0 != c_lo) load_centres(s0);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int s = s0 + u * kRows + grp;
+                if (s >= c_end) break;                       // uniform over the row's lanes
+                const float d = group_sum<kLpr>(frag_dot<T>(rows[u], sp));
+                const float e2 = group_sum<kLpr>(frag_sumsq<T>(rows[u]));
+                const float sim = (d * row_inv_norm<T>(e2)) * rn_star;
+                if (piece == 0 && s != s_star && better<false>(sim, s, cv, ci)) { cv = sim; ci = s; }
+            }
+        }
+        block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
+        if (tid == 0) { hand[kHandPart + 2 * slice] = cv; hand_i[kHandPart + 2 * slice + 1] = ci; }
+    }
+}
+
+// The last launch of the sliced step, one block per head: merge at class-centre level or evict, followers follow (as phases 6
+// and 7 of the step kernel).  Bound by two dependent round trips: what the launches before left and the table's rows, then
+// the chosen entries' rows.  Every wave finds the winner for itself, and the lanes that read a row, count or norm are those that write it,
+// so that no barrier is needed.
+constexpr int kCommitBlock = 512;
+template <typename T, int D>
+__global__ __launch_bounds__(kCommitBlock) void decode_commit_kernel(DecodeStepArgs a)
+{
+    using P = Pack<T>;
+    constexpr int kE = P::kElems, kLpr = Tile<T, D>::kChunksPerRow;
+    constexpr int kUnroll = 8;                               // table elements in flight per thread
+    const int n_imp = a.n_imp, E = n_imp + a.n_tbm, W = a.window, Tn = E + W, Nb = a.budget;
+    const int bkv = blockIdx.x, tid = threadIdx.x, lane = tid % kWave;
+    const bool row_lane = tid < kLpr;
+    const int piece = tid % kLpr;
+    char* Kc = reinterpret_cast<char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
+    char* Vc = reinterpret_cast<char*>(a.st.v_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
+    float* row_norm = a.st.row_norm + (size_t)bkv * Nb;
+    int32_t* entry_count = a.st.entry_count + (size_t)bkv * n_imp;
+    int32_t* tok_pos = a.st.tok_pos + (size_t)bkv * Tn;
+    int32_t* tok_row = a.st.tok_row + (size_t)bkv * Tn;
+    float* tok_norm = a.st.tok_norm + (size_t)bkv * Tn;
+    float* tok_glo = a.st.tok_glo + (size_t)bkv * Tn;
+    float* tok_past = a.st.tok_past + (size_t)bkv * Tn;
+    float* tok_cur = a.st.tok_cur + (size_t)bkv * Tn;
+    const float* hand = a.hand + (size_t)bkv * kDecodeHandFloats;
+    const int* hand_i = reinterpret_cast<const int*>(hand);
+    const frag_t* hand_row = reinterpret_cast<const frag_t*>(hand + kHandOldRow);
+
+    const int s_star = hand_i[kHandStar], step = hand_i[kHandStep];
+    static_assert(kDecodeMaxSlices <= kWave, "a slice per lane");
+    float cv = lane < a.n_slices ? hand[kHandPart + 2 * lane] : 0.f;
+    int ci = lane < a.n_slices ? hand_i[kHandPart + 2 * lane + 1] : -1;
+    int rr[kUnroll];
+    auto load_rows_of = [&](int j0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) rr[u] = j0 + u * kCommitBlock < E ? tok_row[j0 + u * kCommitBlock] : -1;
+    };
+    load_rows_of(tid);
+    frag_t old_k = zero_frag(), old_v = zero_frag();         // the token that left the window
+    if (row_lane) { old_k = hand_row[piece]; old_v = hand_row[kLpr + piece]; }
+    const float old_norm = hand[kHandOldSc], old_glo = hand[kHandOldSc + 1], old_past = hand[kHandOldSc + 2], old_cur = hand[kHandOldSc + 3];
+    const int old_pos = hand_i[kHandOldPos];
+
+    wave_arg<false>(cv, ci);                                 // the slices' winners, lowest centre on ties
+    const bool merged = ci >= 0 && cv > a.tau;
+    const int dst = merged ? ci : -1;
+    const int f = a.st.entry_tok[(size_t)bkv * n_imp + s_star];
+    if (row_lane) {
+        char* const k_star = Kc + ((size_t)s_star * kLpr + piece) * 16;
+        char* const v_star = Vc + ((size_t)s_star * kLpr + piece) * 16;
+        if (merged) {
+            char* const k_dst = Kc + ((size_t)dst * kLpr + piece) * 16;
+            char* const v_dst = Vc + ((size_t)dst * kLpr + piece) * 16;
+            const int na_count = entry_count[s_star], nb_count = entry_count[dst];
+            const float ca = (float)na_count, cb = (float)nb_count;
+            const float na = row_norm[s_star], nb = row_norm[dst];
+            const float ra = na > 0.f ? 1.0f / na : 0.f, rb = nb > 0.f ? 1.0f / nb : 0.f;
+            float ka[kE], kb[kE], va[kE], vb[kE];
+            P::unpack(*reinterpret_cast<const frag_t*>(k_star), ka);
+            P::unpack(*reinterpret_cast<const frag_t*>(k_dst), kb);
+            P::unpack(*reinterpret_cast<const frag_t*>(v_star), va);
+            P::unpack(*reinterpret_cast<const frag_t*>(v_dst), vb);
+#pragma unroll
+            for (int i = 0; i < kE; ++i) {
+                kb[i] = nb * ((cb * (kb[i] * rb) + ca * (ka[i] * ra)) / (ca + cb));
+                vb[i] = (cb * vb[i] + ca * va[i]) / (ca + cb);
+            }
+            *reinterpret_cast<frag_t*>(k_dst) = P::pack(kb);
+            *reinterpret_cast<frag_t*>(v_dst) = P::pack(vb);
+            if (tid == 0) entry_count[dst] = nb_count + na_count;
+        }
+        // the token that left the window is the new centre of entry s_star and takes the departed centre's table element
+        *reinterpret_cast<frag_t*>(k_star) = old_k;
+        *reinterpret_cast<frag_t*>(v_star) = old_v;
+    }
+    if (tid == 0) {
+        entry_count[s_star] = 1;
+        row_norm[s_star] = old_norm;
+        tok_pos[f] = old_pos; tok_row[f] = s_star; tok_norm[f] = old_norm;
+        tok_glo[f] = old_glo; tok_past[f] = old_past; tok_cur[f] = old_cur;
+        if (a.decision_opt) { a.decision_opt[(size_t)bkv * 2] = s_star; a.decision_opt[(size_t)bkv * 2 + 1] = dst; }
+        if (a.sim_opt) a.sim_opt[bkv] = ci >= 0 ? cv : -INFINITY;
+        if (bkv == 0) *a.st.step_count = step + 1;           // (every block reads the hand-over copy)
+    }
+    for (int j0 = tid; j0 < E; j0 += kCommitBlock * kUnroll) {
+        if (j0 != tid) load_rows_of(j0);
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int j = j0 + u * kCommitBlock;
+            if (rr[u] != s_star || j == f) continue;
+            if (merged) {
+                tok_row[j] = dst;
+            } else {
+                tok_row[j] = -1; tok_pos[j] = -1;
+                tok_norm[j] = 0.f; tok_glo[j] = 0.f; tok_past[j] = 0.f; tok_cur[j] = 0.f;
+            }
+        }
+    }
+    // a full window of queries: s_Loc^cur becomes s_Loc^past (Sec. 3.3)
+    if ((step + 1) % W == 0) {                               // block-uniform
+        __syncthreads();
+        for (int j = tid; j < Tn; j += kCommitBlock) { tok_past[j] = tok_cur[j]; tok_cur[j] = 0.f; }
     }
 }
 
@@ -456,8 +691,8 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 {
     constexpr bool kAll = kPart == 0;
     constexpr bool kDoDots = kAll || kPart == 1, kDoSoftmax = kAll || kPart == 2;
-    constexpr bool kDoCos = kAll || kPart == 3 || kPart == 5;
-    static_assert(kPart >= 0 && kPart <= 5, "parts");
+    constexpr bool kDoCos = kAll || kPart == 5;
+    static_assert(kAll || kPart == 1 || kPart == 2 || kPart == 5, "parts");
     static_assert(kHandOldRow % 4 == 0 && kHandOldRow + 2 * D * (int)sizeof(T) / 4 <= kDecodeHandFloats, "hand-over record");
     using P = Pack<T>;
     constexpr int kE = P::kElems;
@@ -830,35 +1065,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             row_pre[u] = load_frag_or_zero(Kc, ((size_t)s * kLpr + piece) * 16, s < c_end);
         }
     };
-    if constexpr (kPart == 3) load_centres(s_first);
-    if constexpr (kPart == 3) {
-        // the least important centre of the table slices' (lowest on ties); the first block shifts the window
-        float v = lane < a.n_tok_slices ? hand[kHandLeast + lane] : 0.f;
-        int i = lane < a.n_tok_slices ? hand_i[kHandLeast + kDecodeMaxSlices + lane] : -1;
-        wave_arg<true>(v, i);
-        s_star = max(i, 0);
-        if (slice == 0) {
-            if (grp == 0) {
-                char* const k_at = Kc + ((size_t)ro * kLpr + piece) * 16;
-                char* const v_at = Vc + ((size_t)ro * kLpr + piece) * 16;
-                hand_row[piece] = *reinterpret_cast<const frag_t*>(k_at);
-                hand_row[kLpr + piece] = *reinterpret_cast<const frag_t*>(v_at);
-                *reinterpret_cast<frag_t*>(k_at) = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-                *reinterpret_cast<frag_t*>(v_at) = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-            }
-            if (tid == 0) {
-                hand_i[kHandOldPos] = tok_pos[jo];
-                hand[kHandOldSc] = tok_norm[jo]; hand[kHandOldSc + 1] = tok_glo[jo];
-                hand[kHandOldSc + 2] = tok_past[jo]; hand[kHandOldSc + 3] = tok_cur[jo];
-                const float norm = hand[kHandNewNorm], weight = hand[kHandSelfTot];
-                tok_pos[jo] = a.seq_len + step; tok_row[jo] = ro; tok_norm[jo] = norm;
-                tok_glo[jo] = weight; tok_past[jo] = 0.f; tok_cur[jo] = weight;
-                row_norm[ro] = norm;
-                hand_i[kHandStar] = s_star;
-            }
-        }
-    }
-    if constexpr (kPart >= 4) s_star = hand_i[kHandStar];
+    if constexpr (kPart == 5) s_star = hand_i[kHandStar];
     f = kAll && ct_in_lds ? sh_ct[s_star] : entry_tok[s_star];
 
     // ---- phase 5: its most similar other centre (Eq. 5, cosine of the stored keys) -----
@@ -876,7 +1083,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         }
         const float rn_star = row_inv_norm<T>(group_sum<kLpr>(frag_sumsq<T>(sp)));
         for (int s0 = s_first; s0 < c_end; s0 += kRowsPerPass * kInFlight) {
-            if (!(kAll || kPart == 3) || s0 != s_first) load_centres(s0);
+            if (!kAll || s0 != s_first) load_centres(s0);
             const frag_t (&fk)[kInFlight] = row_pre;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
@@ -889,23 +1096,8 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         }
     }   // kDoCos
-    if constexpr (kPart == 4) {
-        // the slices' winners (combined below, lowest centre on ties) and the token that left the window
-        cv = tid < a.n_slices ? hand[kHandPart + 2 * tid] : 0.f;
-        ci = tid < a.n_slices ? hand_i[kHandPart + 2 * tid + 1] : -1;
-        if (grp == 0) { old_k[piece] = hand_row[piece]; old_v[piece] = hand_row[kLpr + piece]; }
-        if (tid == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) old_sc[i] = hand[kHandOldSc + i];
-            old_pos = hand_i[kHandOldPos];
-        }
-    }
-    if constexpr (kPart == 4) {                              // phase 6's first look at the table
-#pragma unroll
-        for (int u = 0; u < kUnroll; ++u) pre_rr[u] = tid + u * kBlock < E ? tok_row[tid + u * kBlock] : -1;
-    }
     block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
-    if constexpr (kPart == 3 || kPart == 5) {
+    if constexpr (kPart == 5) {
         if (tid == 0) { hand[kHandPart + 2 * slice] = cv; hand_i[kHandPart + 2 * slice + 1] = ci; }
         return;
     }
@@ -973,7 +1165,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     }
     // the counter: in the sliced step every block reads the hand-over copy, and a step whose number
     // came with the call reads none
-    if (kPart == 4 || (kAll && a.step >= 0)) {
+    if (a.step >= 0) {
         if (bkv == 0 && tid == 0) *a.st.step_count = step + 1;
     }
 }
@@ -998,17 +1190,34 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
     return a.head_dim == 64 ? launch_decode_init_t<bf16_t, 64>(a, st) : launch_decode_init_t<bf16_t, 128>(a, st);
 }
 
-// kWhich: the step kernel's parts 0 to 5, 6 = logits, 7 = weights
+// One launch for the choice while what its blocks form more than once -- every block the scores of all centres -- costs less
+// than a launch: blocks x centres x (q-heads + 1).  us a step, one launch / two, head size 128:
+//    8 heads of 4, budget 2048   1.9 M    16.6 / 18.2        8 heads of 4, 4096   5.2 M   21.4 / 21.0
+//   32 heads of 4,        1000   1.8 M    20.2 / 20.7       16 heads of 4, 2048   3.8 M   20.5 / 20.1
+//    2 heads of 8,        4000   2.3 M    23.5 / 23.4       32 heads of 8, 1000   3.2 M   25.3 / 24.4
+//   32 heads of 1,        2000   3.0 M    19.4 / 19.9       32 heads of 4, 2000   7.4 M   25.3 / 23.2
+// (The same with four launches, the scores by the table's slices, the cosines' and the commit's chains not yet shortened:
+// 21.1, 23.4, 27.7, 21.4; 24.1, 22.7, 28.0, 25.9.)
+constexpr long long kChooseScores = 3000000;
+// kWhich: the step kernel's parts, 6 = logits, 7 = choice of the centres
 template <typename T, int D, int G, int kWhich>
 static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
 {
     if constexpr (kWhich == 6)
         hipLaunchKernelGGL((decode_logits_kernel<D, G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
-    else if constexpr (kWhich == 7)
-        hipLaunchKernelGGL((decode_weights_kernel<G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
+    else if constexpr (kWhich == 7) {
+        const dim3 toks(a.n_tok_slices, a.bkv), rows(a.n_slices, a.bkv), most(max(a.n_tok_slices, a.n_slices), a.bkv);
+        if ((long long)most.x * a.bkv * a.n_imp * (G + 1) <= kChooseScores)
+            hipLaunchKernelGGL((decode_choose_kernel<D, G, 512, kChoose>), most, dim3(512), 0, st, a);
+        else {
+            hipLaunchKernelGGL((decode_choose_kernel<D, G, 256, kWeights>), toks, dim3(256), 0, st, a);
+            if (hipPeekAtLastError() != hipSuccess) return;
+            hipLaunchKernelGGL((decode_choose_kernel<D, G, 256, kCosines>), rows, dim3(256), 0, st, a);
+        }
+    }
     else {
-        constexpr bool kRows = kWhich == 1 || kWhich == 3 || kWhich == 5;      // a block per slice of rows
-        constexpr int kBlock = kWhich == 2 || kWhich == 4 ? 1024 : 256;
+        constexpr bool kRows = kWhich == 1 || kWhich == 5;      // a block per slice of rows
+        constexpr int kBlock = kWhich == 2 ? 1024 : 256;
         const size_t lds = kWhich == 0 || kWhich == 2 ? sizeof(float) * (size_t)(a.lds_floats + a.lds_centres) : 0;
         hipLaunchKernelGGL((decode_step_kernel<T, D, G, kBlock, kWhich>), dim3(kRows ? a.n_slices : 1, a.bkv), dim3(kBlock), lds, st, a);
     }
@@ -1057,9 +1266,10 @@ static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
             const bool table = a.tok_slice > 0;
             hipError_t e = table ? launch_decode_part<T, D, 6>(a, st) : launch_decode_part<T, D, 1>(a, st);
             if (e == hipSuccess) e = table ? launch_decode_part<T, D, 7>(a, st) : launch_decode_part<T, D, 2>(a, st);
-            if (e == hipSuccess) e = table ? launch_decode_part<T, D, 3>(a, st) : launch_decode_part<T, D, 5>(a, st);
-            if (e == hipSuccess) e = launch_decode_part<T, D, 4>(a, st);
-            return e;                                            // the last part advances the counter
+            if (e == hipSuccess && !table) e = launch_decode_part<T, D, 5>(a, st);
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL((decode_commit_kernel<T, D>), dim3(a.bkv), dim3(kCommitBlock), 0, st, a);     // (advances the counter)
+            return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
         }

@@ -467,13 +467,19 @@ static bool decode_params_ok(const ems_params* p, int* why)
     return g == 1 || g == 2 || g == 4 || g == 8;
 }
 
-// Decode-step workspace: the staged row dots and row norms, or the logits where the token table is cut, and (large
-// caches) the hand-over records of the sliced step.
+// Decode-step workspace: the staged row dots and row norms, or, where the token table is cut, the logits and what they
+// leave of the class centres; and (large caches) the hand-over records of the sliced step.
+static size_t decode_logit_bytes(const ems_params* p, int n_imp, int n_tbm)
+{
+    return align_up(sizeof(float) * p->batch * p->q_heads * (size_t)(n_imp + n_tbm + p->window));
+}
+
 static size_t decode_stage_bytes(const ems_params* p, bool table, int n_imp, int n_tbm)
 {
     const size_t bkv = (size_t)p->batch * p->kv_heads;
     const size_t g = (size_t)(p->q_heads / p->kv_heads);
-    return align_up(sizeof(float) * bkv * (table ? g * (size_t)(n_imp + n_tbm + p->window) : (g + 1) * (size_t)p->budget));
+    if (table) return decode_logit_bytes(p, n_imp, n_tbm) + align_up(sizeof(float) * bkv * n_imp * ((g + 3 + 3) / 4 * 4));
+    return align_up(sizeof(float) * bkv * (g + 1) * (size_t)p->budget);
 }
 
 static size_t decode_ws_bytes(const ems_params* p)
@@ -553,6 +559,7 @@ int ems_decode_step(const ems_params* p, const ems_decode_state* state, int32_t 
     ems::DecodeSlices sl;
     if (ems::decode_split(p->batch * p->kv_heads, p->budget, n_imp, n_tbm, p->window, p->dtype == EMS_F32, &sl))
         a.hand = reinterpret_cast<float*>(static_cast<char*>(ws) + decode_stage_bytes(p, sl.toks > 0, n_imp, n_tbm));
+    a.centre_at = decode_logit_bytes(p, n_imp, n_tbm) / sizeof(float);
     a.slice_rows = sl.rows; a.n_slices = sl.n_rows; a.tok_slice = sl.toks; a.n_tok_slices = sl.n_toks;
     // per-row dot products and row norms are staged in LDS when they fit in
     // what a block may ask for without raising the limit, else in the workspace

@@ -136,6 +136,7 @@ struct DecodeStepArgs {
     int32_t* decision_opt;  // [bkv, 2] or null
     float* sim_opt;         // [bkv] or null
     float* ws;              // [bkv, (group + 1) * budget] staging when it does not fit in LDS or between launches; or logits [bkv, group, T]
+    size_t centre_at;       // behind the logits, in floats: what they leave of the centres' own elements
     float* hand;            // [bkv, kDecodeHandFloats] hand-over record of the sliced step, else null
     int slice_rows, n_slices;   // slices of the rows in the sliced step (decode_split); 0, 1 = one launch
     int tok_slice, n_tok_slices;    // slices of the token table; 0 = it is not cut

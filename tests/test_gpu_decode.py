@@ -219,6 +219,32 @@ def test_decode_steps_of_long_tables_match_oracle(shape, tau):
     assert n_merge > 0 if tau < 1 else n_merge == 0 and n_evict > 0
 
 
+# head counts and centre lists on both sides of the sizes where the least important centre is chosen in a launch of its own
+# (blocks x centres x (q-heads + 1) over 3 million), last slices of a few rows; units: a first, a middle and the last head.
+# Bounds as in the tests above; all steps of a unit count for the flips.
+@pytest.mark.parametrize("shape", [
+    (2, 32, 4, 64, 3000, 8, 1290, 0.5),      # 8 heads of 8, 1282 centres: 16 slices of the table, the last of 15: 1.5 million
+    (4, 64, 8, 64, 3000, 8, 1033, 0.5),      # 32 heads of 8, 1025 centres, one of them in the last slice: 3.8 million
+    (1, 16, 16, 128, 9000, 8, 4200, 1.0),    # 16 heads of 1, 4192 centres in slices of 256: 4.4 million
+    (2, 32, 16, 128, 3000, 8, 1410, 1.0),    # 32 heads of 2, 1402 centres: 3.1 million
+])
+def test_decode_steps_choose_in_one_launch_or_two(shape):
+    _log("decode_step", shape)
+    tau = 0.3
+    p, merged, tbm, s_glo, s_loc, st = _prefill(shape, B.EMS_BF16, tau, seed=shape[6])
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    rng = np.random.default_rng(29)
+    n_merge = n_flip = 0
+    units = [(0, 0), (p.batch // 2, p.kv_heads // 2), (p.batch - 1, p.kv_heads - 1)]
+    for t in range(p.window + 2):
+        qb, kb, vb = _new_token(p, rng, B.EMS_BF16)
+        if t % 3 == 1:                                    # make some new keys similar to an entry
+            kb = ems_inputs.f32_to_bf16_bits(_np(st.k_cache[:, :, n_imp - 1 - t]).astype(np.float32))
+        c = run_and_check_step(p, st, t, qb, kb, vb, tau, units, B.EMS_BF16)
+        n_flip += c[0]; n_merge += c[1]
+    assert n_flip <= 1 and n_merge > 0
+
+
 # more heads than the table's slices are for: the step goes over slices of the cache rows instead
 @pytest.mark.parametrize("tau", [0.3, 2.0])
 @pytest.mark.parametrize("shape", [

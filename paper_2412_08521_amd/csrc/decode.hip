@@ -38,31 +38,6 @@ __device__ __forceinline__ float wave_reduce(float v)
     return comb<kMax>(comb<kMax>(lane_value(v, 0), lane_value(v, 16)), comb<kMax>(lane_value(v, 32), lane_value(v, 48)));
 }
 
-// Every thread of the block must call; the result is identical in every thread.
-template <int kWaves, int kN, bool kMax>
-__device__ __forceinline__ void block_reduce(float (&v)[kN], float (*buf)[kWaves])
-{
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int i = 0; i < kN; ++i) v[i] = wave_reduce<kMax>(v[i]);
-    __syncthreads();                                    // buf free again
-    if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < kN; ++i) buf[i][wave] = v[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kN; ++i) {
-        if constexpr (kWaves == 16) {
-            v[i] = lane_value(row_reduce<kMax>(buf[i][lane & 15]), 0);
-        } else {
-            float r = buf[i][0];
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) r = comb<kMax>(r, buf[i][w]);       // fixed order
-            v[i] = r;
-        }
-    }
-}
 // The softmax state (reference m, sum l of the weights relative to it) of G rows over the block, and two plain totals with it:
 // one barrier for what a maximum, a sum and the totals would take two each for.  (`buf` is the call's own.)  The result is identical in
 // every thread.
@@ -136,6 +111,7 @@ __device__ __forceinline__ void row_arg(float& v, int& i)
     arg_step<kMin, kDppHalfMirror>(v, i);
     arg_step<kMin, kDppMirror>(v, i);
 }
+// (`fbuf` and `ibuf` are the call's own: one barrier)
 template <int kWaves, bool kMin>
 __device__ __forceinline__ void block_arg(float& v, int& i, float* fbuf, int* ibuf)
 {
@@ -152,7 +128,6 @@ __device__ __forceinline__ void block_arg(float& v, int& i, float* fbuf, int* ib
         }
         v = bv; i = bi;
     }
-    __syncthreads();
     if (lane == 0) { fbuf[wave] = v; ibuf[wave] = i; }
     __syncthreads();
     if constexpr (kWaves == 16) {
@@ -390,8 +365,8 @@ __global__ __launch_bounds__(kBlock) void decode_choose_kernel(DecodeStepArgs a)
     constexpr int kLpr = Tile<T, D>::kChunksPerRow, kRows = kBlock / kLpr;     // rows a block loads at a time
     constexpr int kAhead = kTokTile / kRows;                 // row loads in flight per thread
     constexpr int kCen = 4, kPieces = kCentrePieces<G>;      // centres in flight per thread
-    __shared__ float fbuf[kWaves];
-    __shared__ int ibuf[kWaves];
+    __shared__ float fbuf[2][kWaves];
+    __shared__ int ibuf[2][kWaves];
     const int n_imp = a.n_imp, E = a.n_imp + a.n_tbm, Tn = E + a.window, Nb = a.budget;
     const int bkv = blockIdx.y, slice = blockIdx.x, tid = threadIdx.x, lane = tid % kWave;
     const int grp = tid / kLpr, piece = tid % kLpr;
@@ -489,7 +464,7 @@ __global__ __launch_bounds__(kBlock) void decode_choose_kernel(DecodeStepArgs a)
                 if (r0 - tid >= n_imp) break;                // block-uniform
                 load_scalars(r0);
             }
-            block_arg<kWaves, true>(bv, bi, fbuf, ibuf);
+            block_arg<kWaves, true>(bv, bi, fbuf[0], ibuf[0]);
             star_row();
         }
 
@@ -531,7 +506,7 @@ __global__ __launch_bounds__(kBlock) void decode_choose_kernel(DecodeStepArgs a)
             }
         }
         if constexpr (kStep == kWeights) {
-            block_arg<kWaves, true>(bv, bi, fbuf, ibuf);
+            block_arg<kWaves, true>(bv, bi, fbuf[0], ibuf[0]);
             if (tid == 0) { hand[kHandLeast + slice] = bv; hand_i[kHandLeast + kDecodeMaxSlices + slice] = bi; }
         }
         if (slice == 0) {
@@ -575,9 +550,26 @@ __global__ __launch_bounds__(kBlock) void decode_choose_kernel(DecodeStepArgs a)
                 if (piece == 0 && s != s_star && better<false>(sim, s, cv, ci)) { cv = sim; ci = s; }
             }
         }
-        block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
+        block_arg<kWaves, false>(cv, ci, fbuf[1], ibuf[1]);
         if (tid == 0) { hand[kHandPart + 2 * slice] = cv; hand_i[kHandPart + 2 * slice + 1] = ci; }
     }
+}
+
+// Merge at class-centre level: the row piece at `to` becomes the mean of entry b's (there) and entry a's, weighted by their counts;
+// keys as unit vectors, scaled to b's norm.  (A value counts as a vector of norm 1.)
+template <typename T>
+__device__ __forceinline__ void merge_rows(char* to, const frag_t& from, bool key, float ca, float cb, float na, float nb)
+{
+    using P = Pack<T>;
+    constexpr int kE = P::kElems;
+    const float ra = !key ? 1.f : na > 0.f ? 1.0f / na : 0.f, rb = !key ? 1.f : nb > 0.f ? 1.0f / nb : 0.f;
+    const float scale = key ? nb : 1.f;
+    float xa[kE], xb[kE];
+    P::unpack(from, xa);
+    P::unpack(*reinterpret_cast<const frag_t*>(to), xb);
+#pragma unroll
+    for (int i = 0; i < kE; ++i) xb[i] = scale * ((cb * (xb[i] * rb) + ca * (xa[i] * ra)) / (ca + cb));
+    *reinterpret_cast<frag_t*>(to) = P::pack(xb);
 }
 
 // The last launch of the sliced step, one block per head: merge at class-centre level or evict, followers follow (as phases 6
@@ -588,13 +580,13 @@ constexpr int kCommitBlock = 512;
 template <typename T, int D>
 __global__ __launch_bounds__(kCommitBlock) void decode_commit_kernel(DecodeStepArgs a)
 {
-    using P = Pack<T>;
-    constexpr int kE = P::kElems, kLpr = Tile<T, D>::kChunksPerRow;
+    constexpr int kLpr = Tile<T, D>::kChunksPerRow;
     constexpr int kUnroll = 8;                               // table elements in flight per thread
     const int n_imp = a.n_imp, E = n_imp + a.n_tbm, W = a.window, Tn = E + W, Nb = a.budget;
     const int bkv = blockIdx.x, tid = threadIdx.x, lane = tid % kWave;
-    const bool row_lane = tid < kLpr;
     const int piece = tid % kLpr;
+    const bool row_lane = tid < 2 * kLpr, key = tid < kLpr;  // a piece of a key, or of the value
+    static_assert(2 * kLpr <= kWave, "both rows in one wave");
     char* Kc = reinterpret_cast<char*>(a.st.k_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
     char* Vc = reinterpret_cast<char*>(a.st.v_cache) + (size_t)bkv * (Nb + 1) * D * sizeof(T);
     float* row_norm = a.st.row_norm + (size_t)bkv * Nb;
@@ -619,8 +611,7 @@ __global__ __launch_bounds__(kCommitBlock) void decode_commit_kernel(DecodeStepA
         for (int u = 0; u < kUnroll; ++u) rr[u] = j0 + u * kCommitBlock < E ? tok_row[j0 + u * kCommitBlock] : -1;
     };
     load_rows_of(tid);
-    frag_t old_k = zero_frag(), old_v = zero_frag();         // the token that left the window
-    if (row_lane) { old_k = hand_row[piece]; old_v = hand_row[kLpr + piece]; }
+    const frag_t old_row = row_lane ? hand_row[tid] : zero_frag();               // the token that left the window
     const float old_norm = hand[kHandOldSc], old_glo = hand[kHandOldSc + 1], old_past = hand[kHandOldSc + 2], old_cur = hand[kHandOldSc + 3];
     const int old_pos = hand_i[kHandOldPos];
 
@@ -629,32 +620,16 @@ __global__ __launch_bounds__(kCommitBlock) void decode_commit_kernel(DecodeStepA
     const int dst = merged ? ci : -1;
     const int f = a.st.entry_tok[(size_t)bkv * n_imp + s_star];
     if (row_lane) {
-        char* const k_star = Kc + ((size_t)s_star * kLpr + piece) * 16;
-        char* const v_star = Vc + ((size_t)s_star * kLpr + piece) * 16;
+        char* const X = key ? Kc : Vc;
+        char* const star = X + ((size_t)s_star * kLpr + piece) * 16;
         if (merged) {
-            char* const k_dst = Kc + ((size_t)dst * kLpr + piece) * 16;
-            char* const v_dst = Vc + ((size_t)dst * kLpr + piece) * 16;
+            char* const to = X + ((size_t)dst * kLpr + piece) * 16;
             const int na_count = entry_count[s_star], nb_count = entry_count[dst];
-            const float ca = (float)na_count, cb = (float)nb_count;
-            const float na = row_norm[s_star], nb = row_norm[dst];
-            const float ra = na > 0.f ? 1.0f / na : 0.f, rb = nb > 0.f ? 1.0f / nb : 0.f;
-            float ka[kE], kb[kE], va[kE], vb[kE];
-            P::unpack(*reinterpret_cast<const frag_t*>(k_star), ka);
-            P::unpack(*reinterpret_cast<const frag_t*>(k_dst), kb);
-            P::unpack(*reinterpret_cast<const frag_t*>(v_star), va);
-            P::unpack(*reinterpret_cast<const frag_t*>(v_dst), vb);
-#pragma unroll
-            for (int i = 0; i < kE; ++i) {
-                kb[i] = nb * ((cb * (kb[i] * rb) + ca * (ka[i] * ra)) / (ca + cb));
-                vb[i] = (cb * vb[i] + ca * va[i]) / (ca + cb);
-            }
-            *reinterpret_cast<frag_t*>(k_dst) = P::pack(kb);
-            *reinterpret_cast<frag_t*>(v_dst) = P::pack(vb);
+            merge_rows<T>(to, *reinterpret_cast<const frag_t*>(star), key, (float)na_count, (float)nb_count, row_norm[s_star], row_norm[dst]);
             if (tid == 0) entry_count[dst] = nb_count + na_count;
         }
         // the token that left the window is the new centre of entry s_star and takes the departed centre's table element
-        *reinterpret_cast<frag_t*>(k_star) = old_k;
-        *reinterpret_cast<frag_t*>(v_star) = old_v;
+        *reinterpret_cast<frag_t*>(star) = old_row;
     }
     if (tid == 0) {
         entry_count[s_star] = 1;
@@ -694,21 +669,16 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     constexpr bool kDoCos = kAll || kPart == 5;
     static_assert(kAll || kPart == 1 || kPart == 2 || kPart == 5, "parts");
     static_assert(kHandOldRow % 4 == 0 && kHandOldRow + 2 * D * (int)sizeof(T) / 4 <= kDecodeHandFloats, "hand-over record");
-    using P = Pack<T>;
-    constexpr int kE = P::kElems;
     constexpr int kWaves = kBlock / kWave;
     constexpr int kLpr = Tile<T, D>::kChunksPerRow;          // lanes per cache row
     constexpr int kUnroll = 4;                               // independent loads in flight per thread
 
     extern __shared__ float dyn_lds[];
-    __shared__ float fbuf[kWaves];
-    __shared__ int ibuf[kWaves];
+    __shared__ float fbuf[2][kWaves];
+    __shared__ int ibuf[2][kWaves];
     __shared__ float vbuf[2 * G + 2][kWaves];                // the softmax's reduction
-    __shared__ float sh_self[G];                             // new query . new key (log2 units)
-    __shared__ frag_t old_k[kLpr], old_v[kLpr];              // the token that leaves the window
     __shared__ frag_t star_k[kLpr];                          // the least important centre's key
-    __shared__ float old_sc[4];                              // its norm, glo, past, cur
-    __shared__ int old_pos;
+    __shared__ float old_sc[4];                              // of the token that leaves the window: norm, glo, past, cur
     __shared__ float sh_newnorm;
 
     const int n_imp = a.n_imp, E = a.n_imp + a.n_tbm, W = a.window, Nb = a.budget;
@@ -744,7 +714,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     frag_t* hand_row = reinterpret_cast<frag_t*>(hand + kHandOldRow);
     // rows of this block's sweeps: every row, or the block's slice
     const int r_lo = kAll ? 0 : slice * a.slice_rows;
-    const int r_end = kAll ? Nb + 1 : min(r_lo + a.slice_rows, Nb + 1);       // phase 1 (row Nb = the new key)
+    const int r_end = kAll ? Nb : min(r_lo + a.slice_rows, Nb + 1);           // phase 1 (row Nb = the new key)
     const int c_end = kAll ? n_imp : min(r_lo + a.slice_rows, n_imp);        // phase 5
     float* dot = stage;                                      // [G][budget] q_g . cache row
     float* rn_of = stage + (size_t)G * Nb;                   // [budget] copy of row_norm
@@ -763,11 +733,12 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     // "its" entry, its share of the row norms, the new token's row.
     constexpr int kRowsPerWave = kWave / kLpr;               // whole rows per wave-wide load
     constexpr int kRowsPerPass = kWaves * kRowsPerWave;
-    constexpr int kInFlight = kAll ? 8 : 4;                  // row loads in flight per lane
+    constexpr int kInFlight = kAll ? 2048 / kBlock : 4;                  // row loads in flight per lane
     const int sub = lane / kLpr;                             // this lane's row within the wave's load
+    const int mine = wave * kRowsPerWave + sub;              // and within the block's
     frag_t row_pre[kInFlight];                               // the first batch of rows: phase 1's, and in the one-launch step phase 5's
     frag_t new_k = zero_frag(), new_v = zero_frag();
-    float m[G], inv[G];
+    float m[G], inv[G], self[G];                             // (self: new query . new key, in log2 units)
     float tot2[2] = {0.f, 0.f};                              // sum of s_Glo, sum of s_Loc
     float self_tot = 0.f;
     int s_star = 0, f = 0;
@@ -795,6 +766,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     auto preload_table = [&]() {
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (u * kBlock >= Tn) break;                     // block-uniform, as in the sweeps: a batch ends where the table does
             const int j = tid + u * kBlock;
             const bool ok = j < Tn;
             pre_rr[u] = ok ? tok_row[j] : -1;
@@ -807,13 +779,13 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     // the token that leaves the window: its rows and position (its scalars come from the thread that updates them)
     const int ring = step % W;
     const int jo = E + ring, ro = n_imp + ring;
-    frag_t pre_old[2] = {zero_frag(), zero_frag()};
+    const bool row_lane = grp < 2;                           // a piece of a key, or of the value beside it
+    static_assert(2 * kLpr <= kWave, "both rows in one wave");
+    char* const X = grp == 0 ? Kc : Vc;
+    frag_t pre_old = zero_frag();
     int pre_old_pos = 0;
     auto preload_old = [&]() {
-        if (grp == 0) {
-            pre_old[0] = *reinterpret_cast<const frag_t*>(Kc + ((size_t)ro * kLpr + piece) * 16);
-            pre_old[1] = *reinterpret_cast<const frag_t*>(Vc + ((size_t)ro * kLpr + piece) * 16);
-        }
+        if (row_lane) pre_old = *reinterpret_cast<const frag_t*>(X + ((size_t)ro * kLpr + piece) * 16);
         if (tid == 0) pre_old_pos = tok_pos[jo];
     };
     if constexpr (kDoDots) {
@@ -821,46 +793,51 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int g = 0; g < G; ++g) qp[g] = *reinterpret_cast<const frag_t*>(qn + ((size_t)g * kLpr + piece) * 16);
         new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-        auto load_rows = [&](int r0, frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
+        auto load_rows = [&](int base, frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
+            const int r0 = base + mine;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
                 const int r = r0 + u * kRowsPerPass;
+                if (kAll && base + u * kRowsPerPass >= r_end) break;                 // block-uniform
                 fk[u] = r < Nb ? *reinterpret_cast<const frag_t*>(Kc + ((size_t)r * kLpr + piece) * 16) : new_k;
             }
         };
-        const int r_first = r_lo + wave * kRowsPerWave + sub;
-        load_rows(r_first, row_pre);
+        load_rows(r_lo, row_pre);
         if constexpr (kAll) preload_table();
         const float rn_mine = (kAll && tid < Nb) ? row_norm[tid] : 0.f;
-        if (grp == 0) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
+        if (grp == 1) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
         if constexpr (kAll) { preload_old(); preload_centres(); }
-        auto dots = [&](int r0, const frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
+        auto dots = [&](int base, const frag_t (&fk)[kInFlight]) __attribute__((always_inline)) {
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
-                const int r = r0 + u * kRowsPerPass;
+                const int r = base + mine + u * kRowsPerPass;
+                if (kAll && base + u * kRowsPerPass >= r_end) break;                 // block-uniform
                 if (r >= r_end) break;                       // uniform over the row's lanes
                 float d[G];
 #pragma unroll
                 for (int g = 0; g < G; ++g) d[g] = group_sum<kLpr>(frag_dot<T>(fk[u], qp[g]));
                 if (piece == 0) {
-                    if (r < Nb) {
+                    if (kAll || r < Nb) {
 #pragma unroll
                         for (int g = 0; g < G; ++g) dot[(size_t)g * Nb + r] = d[g];
                     } else {
 #pragma unroll
                         for (int g = 0; g < G; ++g) {
-                            sh_self[g] = a.scale_log2e * d[g];
-                            if (!kAll) hand[kHandSelf + g] = a.scale_log2e * d[g];
+                            hand[kHandSelf + g] = a.scale_log2e * d[g];
                         }
                     }
                 }
             }
         };
-        dots(r_first, row_pre);
-        for (int r0 = r_first + kRowsPerPass * kInFlight; r0 < r_end; r0 += kRowsPerPass * kInFlight) {
+        dots(r_lo, row_pre);
+        for (int base = r_lo + kRowsPerPass * kInFlight; base < r_end; base += kRowsPerPass * kInFlight) {
             frag_t fk[kInFlight];
-            load_rows(r0, fk);
-            dots(r0, fk);
+            load_rows(base, fk);
+            dots(base, fk);
+        }
+        if constexpr (kAll) {                                // the new token's, by every wave
+#pragma unroll
+            for (int g = 0; g < G; ++g) self[g] = a.scale_log2e * group_sum<kLpr>(frag_dot<T>(new_k, qp[g]));
         }
         if constexpr (kAll) store_centres();
         for (int r = r_lo + tid; r < min(r_end, Nb); r += kBlock) rn_of[r] = (kAll && r == tid) ? rn_mine : row_norm[r];
@@ -878,12 +855,11 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         preload_table();
         preload_old();
         preload_centres();
-        if (tid < G) sh_self[tid] = hand[kHandSelf + tid];
+#pragma unroll
+        for (int g = 0; g < G; ++g) self[g] = hand[kHandSelf + g];
         if (tid == 0) sh_newnorm = hand[kHandNewNorm];
-        if (grp == 0) {
-            new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
-            new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
-        }
+        if (grp == 0) new_k = *reinterpret_cast<const frag_t*>(kn + piece * 16);
+        if (grp == 1) new_v = *reinterpret_cast<const frag_t*>(vn + piece * 16);
         if (in_lds) {
             constexpr int kCopy = 8;                         // loads in flight per thread
             for (int i0 = tid; i0 < (G + 1) * Nb; i0 += kBlock * kCopy) {
@@ -911,7 +887,10 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     float x0[kKeep ? kUnroll : 1][G];                        // the first batch's logits
     int ct0[kUnroll];                                        // and its elements' centre tokens
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) ct0[u] = centre_of(pre_rr[u]);
+    for (int u = 0; u < kUnroll; ++u) {
+        if (u * kBlock >= Tn) break;
+        ct0[u] = centre_of(pre_rr[u]);
+    }
 #pragma unroll
     for (int g = 0; g < G; ++g) { m[g] = -INFINITY; inv[g] = 0.f; }
     auto logits_of = [&](int r, float tn, float (&x)[G]) __attribute__((always_inline)) {
@@ -920,14 +899,16 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
 #pragma unroll
         for (int g = 0; g < G; ++g) x[g] = r >= 0 ? c * dot[(size_t)g * Nb + r] : -INFINITY;
     };
-    for (int j0 = tid; j0 < Tn; j0 += kBlock * kUnroll) {
+    for (int b0 = 0; b0 < Tn; b0 += kBlock * kUnroll) {
+        const int j0 = b0 + tid;
         float x[kUnroll][G];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (b0 + u * kBlock >= Tn) break;
             const int j = j0 + u * kBlock;
             int r = pre_rr[u];
             float tn = pre_tn[u], tg = pre_tg[u], tl = pre_tp[u] + pre_tc[u];
-            if (j0 != tid) {
+            if (b0 != 0) {
                 r = j < Tn ? tok_row[j] : -1;
                 tn = j < Tn ? tok_norm[j] : 0.f;
                 tg = j < Tn ? tok_glo[j] : 0.f;
@@ -940,28 +921,36 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         for (int g = 0; g < G; ++g) {
             float top = m[g];
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) top = fmaxf(top, x[u][g]);
+            for (int u = 0; u < kUnroll; ++u) {
+                if (b0 + u * kBlock >= Tn) break;
+                top = fmaxf(top, x[u][g]);
+            }
             const float ref = top > -INFINITY ? top : 0.f;
             float l = inv[g] * exp2_fast(m[g] - ref);
 #pragma unroll
-            for (int u = 0; u < kUnroll; ++u) l += exp2_fast(x[u][g] - ref);
+            for (int u = 0; u < kUnroll; ++u) {
+                if (b0 + u * kBlock >= Tn) break;
+                l += exp2_fast(x[u][g] - ref);
+            }
             m[g] = top; inv[g] = l;
         }
-        if (kKeep && j0 == tid) {
+        if (kKeep && b0 == 0) {
 #pragma unroll
-            for (int u = 0; u < (kKeep ? kUnroll : 1); ++u)
+            for (int u = 0; u < (kKeep ? kUnroll : 1); ++u) {
+                if (u * kBlock >= Tn) break;
 #pragma unroll
                 for (int g = 0; g < G; ++g) x0[u][g] = x[u][g];
+            }
         }
     }
     block_softmax<kWaves, G>(m, inv, tot2, vbuf);
     float self_w[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        const float self = sh_self[g], M = fmaxf(m[g], self);
-        inv[g] = 1.0f / ((m[g] > -INFINITY ? inv[g] * exp2_fast(m[g] - M) : 0.f) + exp2_fast(self - M));
+        const float M = fmaxf(m[g], self[g]), own = exp2_fast(self[g] - M);
+        inv[g] = 1.0f / ((m[g] > -INFINITY ? inv[g] * exp2_fast(m[g] - M) : 0.f) + own);
         m[g] = M;
-        self_w[g] = exp2_fast(self - M) * inv[g];            // every thread, same value
+        self_w[g] = own * inv[g];                            // every thread, same value
         self_tot += self_w[g];
     }
     // Eq. 2 factor on the updated scalars: this step adds one unit of weight per q-head to both totals
@@ -971,14 +960,16 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     // phase 4: the least important one
     float bv = 0.f;
     int bi = -1;
-    for (int j0 = tid; j0 < Tn; j0 += kBlock * kUnroll) {
+    for (int b0 = 0; b0 < Tn; b0 += kBlock * kUnroll) {
+        const int j0 = b0 + tid;
         int rr[kUnroll], ct[kUnroll];
         float tn[kUnroll], tg[kUnroll], tp[kUnroll], tc[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (b0 + u * kBlock >= Tn) break;
             const int j = j0 + u * kBlock;
             const bool ok = j < Tn;
-            if (j0 == tid) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; tg[u] = pre_tg[u]; tp[u] = pre_tp[u]; tc[u] = pre_tc[u]; }
+            if (b0 == 0) { rr[u] = pre_rr[u]; tn[u] = pre_tn[u]; tg[u] = pre_tg[u]; tp[u] = pre_tp[u]; tc[u] = pre_tc[u]; }
             else {
                 rr[u] = ok ? tok_row[j] : -1;
                 tn[u] = ok ? tok_norm[j] : 0.f;
@@ -986,17 +977,18 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
                 tp[u] = ok ? tok_past[j] : 0.f;
                 tc[u] = ok ? tok_cur[j] : 0.f;
             }
-            ct[u] = j0 == tid ? ct0[u] : centre_of(rr[u]);
+            ct[u] = b0 == 0 ? ct0[u] : centre_of(rr[u]);
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
+            if (b0 + u * kBlock >= Tn) break;
             const int j = j0 + u * kBlock;
             if (j >= Tn) break;
             const int r = rr[u];
             float w[G];
             if (r >= 0) {
                 float x[G], tot = 0.f;
-                if (kKeep && j0 == tid) {
+                if (kKeep && b0 == 0) {
 #pragma unroll
                     for (int g = 0; g < G; ++g) x[g] = x0[kKeep ? u : 0][g];
                 } else {
@@ -1028,18 +1020,12 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     }
 
     // ---- phase 4: least important class centre (Eq. 2 on the tokens' scalars) ----------
-    block_arg<kWaves, true>(bv, bi, fbuf, ibuf);             // also: every token's scalars are written
+    block_arg<kWaves, true>(bv, bi, fbuf[0], ibuf[0]);             // also: every token's scalars are written
 
     // ---- phase 3: the oldest window token leaves, the new token takes its ring slot (nothing reads these before the
     // next barrier) ----
-    if (grp == 0) {
-        old_k[piece] = pre_old[0];
-        old_v[piece] = pre_old[1];
-        *reinterpret_cast<frag_t*>(Kc + ((size_t)ro * kLpr + piece) * 16) = new_k;
-        *reinterpret_cast<frag_t*>(Vc + ((size_t)ro * kLpr + piece) * 16) = new_v;
-    }
+    if (row_lane) *reinterpret_cast<frag_t*>(X + ((size_t)ro * kLpr + piece) * 16) = grp == 0 ? new_k : new_v;
     if (tid == 0) {
-        old_pos = pre_old_pos;
         tok_pos[jo] = a.seq_len + step; tok_row[jo] = ro; tok_norm[jo] = sh_newnorm;
         tok_glo[jo] = self_tot; tok_past[jo] = 0.f; tok_cur[jo] = self_tot;
         row_norm[ro] = sh_newnorm;
@@ -1047,21 +1033,20 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     s_star = max(bi, 0);                                     // block-uniform, in [0, n_imp)
     }   // kDoSoftmax
     if constexpr (kPart == 2) {
-        if (grp == 0) { hand_row[piece] = old_k[piece]; hand_row[kLpr + piece] = old_v[piece]; }
+        if (row_lane) hand_row[tid] = pre_old;
         if (tid == 0) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) hand[kHandOldSc + i] = old_sc[i];
-            hand_i[kHandOldPos] = old_pos;
+            hand_i[kHandOldPos] = pre_old_pos;
             hand_i[kHandStar] = s_star;
         }
         return;
     }
     // phase 5's first rows do not depend on the centre that is chosen
-    const int s_first = r_lo + wave * kRowsPerWave + sub;
-    auto load_centres = [&](int s0) __attribute__((always_inline)) {
+    auto load_centres = [&](int base) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < kInFlight; ++u) {
-            const int s = s0 + u * kRowsPerPass;
+            const int s = base + mine + u * kRowsPerPass;
             row_pre[u] = load_frag_or_zero(Kc, ((size_t)s * kLpr + piece) * 16, s < c_end);
         }
     };
@@ -1075,19 +1060,20 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
         if (kAll && s_star < kRowsPerPass * kInFlight) {     // block-uniform: some thread group has the row
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u)
-                if (s_first + u * kRowsPerPass == s_star) star_k[piece] = row_pre[u];
+                if (mine + u * kRowsPerPass == s_star) star_k[piece] = row_pre[u];
             __syncthreads();
             sp = star_k[piece];
         } else {
             sp = *reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16);
         }
         const float rn_star = row_inv_norm<T>(group_sum<kLpr>(frag_sumsq<T>(sp)));
-        for (int s0 = s_first; s0 < c_end; s0 += kRowsPerPass * kInFlight) {
-            if (!kAll || s0 != s_first) load_centres(s0);
+        for (int base = r_lo; base < c_end; base += kRowsPerPass * kInFlight) {
+            if (!kAll || base != r_lo) load_centres(base);
             const frag_t (&fk)[kInFlight] = row_pre;
 #pragma unroll
             for (int u = 0; u < kInFlight; ++u) {
-                const int s = s0 + u * kRowsPerPass;
+                const int s = base + mine + u * kRowsPerPass;
+                if (base + u * kRowsPerPass >= c_end) break; // block-uniform
                 if (s >= c_end) break;                       // uniform over the row's lanes
                 const float d = group_sum<kLpr>(frag_dot<T>(fk[u], sp));
                 const float e2 = group_sum<kLpr>(frag_sumsq<T>(fk[u]));
@@ -1096,7 +1082,7 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         }
     }   // kDoCos
-    block_arg<kWaves, false>(cv, ci, fbuf, ibuf);
+    block_arg<kWaves, false>(cv, ci, fbuf[1], ibuf[1]);
     if constexpr (kPart == 5) {
         if (tid == 0) { hand[kHandPart + 2 * slice] = cv; hand_i[kHandPart + 2 * slice + 1] = ci; }
         return;
@@ -1105,33 +1091,21 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
     const int dst = merged ? ci : -1;
 
     // ---- phase 6: merge at class-centre level, or evict; followers follow --------------
-    if (merged && grp == 0) {
-        const float ca = (float)entry_count[s_star], cb = (float)entry_count[dst];
-        const float na = row_norm[s_star], nb = row_norm[dst];
-        const float ra = na > 0.f ? 1.0f / na : 0.f, rb = nb > 0.f ? 1.0f / nb : 0.f;
-        float ka[kE], kb[kE], va[kE], vb[kE];
-        P::unpack(*reinterpret_cast<const frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16), ka);
-        P::unpack(*reinterpret_cast<const frag_t*>(Kc + ((size_t)dst * kLpr + piece) * 16), kb);
-        P::unpack(*reinterpret_cast<const frag_t*>(Vc + ((size_t)s_star * kLpr + piece) * 16), va);
-        P::unpack(*reinterpret_cast<const frag_t*>(Vc + ((size_t)dst * kLpr + piece) * 16), vb);
-#pragma unroll
-        for (int i = 0; i < kE; ++i) {
-            kb[i] = nb * ((cb * (kb[i] * rb) + ca * (ka[i] * ra)) / (ca + cb));
-            vb[i] = (cb * vb[i] + ca * va[i]) / (ca + cb);
-        }
-        *reinterpret_cast<frag_t*>(Kc + ((size_t)dst * kLpr + piece) * 16) = P::pack(kb);
-        *reinterpret_cast<frag_t*>(Vc + ((size_t)dst * kLpr + piece) * 16) = P::pack(vb);
-    }
-    for (int j0 = tid; j0 < E; j0 += kBlock * kUnroll) {
+    if (merged && row_lane)
+        merge_rows<T>(X + ((size_t)dst * kLpr + piece) * 16, *reinterpret_cast<const frag_t*>(X + ((size_t)s_star * kLpr + piece) * 16), grp == 0,
+                      (float)entry_count[s_star], (float)entry_count[dst], row_norm[s_star], row_norm[dst]);
+    for (int b0 = 0; b0 < E; b0 += kBlock * kUnroll) {
         int rr[kUnroll];
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const int j = j0 + u * kBlock;
-            rr[u] = j >= E ? -1 : j0 == tid ? pre_rr[u] : tok_row[j];
+            if (b0 + u * kBlock >= E) break;                 // block-uniform
+            const int j = b0 + tid + u * kBlock;
+            rr[u] = j >= E ? -1 : b0 == 0 ? pre_rr[u] : tok_row[j];
         }
 #pragma unroll
         for (int u = 0; u < kUnroll; ++u) {
-            const int j = j0 + u * kBlock;
+            if (b0 + u * kBlock >= E) break;
+            const int j = b0 + tid + u * kBlock;
             if (rr[u] != s_star || j == f) continue;
             if (merged) {
                 tok_row[j] = dst;
@@ -1141,26 +1115,22 @@ __global__ __launch_bounds__(kBlock) void decode_step_kernel(DecodeStepArgs a)
             }
         }
     }
-    __syncthreads();                                         // entry s_star fully read
     // the token that left the window is the new centre of entry s_star and takes the
-    // departed centre's table element
-    if (grp == 0) {
-        *reinterpret_cast<frag_t*>(Kc + ((size_t)s_star * kLpr + piece) * 16) = old_k[piece];
-        *reinterpret_cast<frag_t*>(Vc + ((size_t)s_star * kLpr + piece) * 16) = old_v[piece];
-    }
+    // departed centre's table element (rows and scalars are written by the lanes, or the wave, that have read them)
+    if (row_lane) *reinterpret_cast<frag_t*>(X + ((size_t)s_star * kLpr + piece) * 16) = pre_old;
     if (tid == 0) {
         if (merged) entry_count[dst] += entry_count[s_star];
         entry_count[s_star] = 1;
         row_norm[s_star] = old_sc[0];
-        tok_pos[f] = old_pos; tok_row[f] = s_star; tok_norm[f] = old_sc[0];
+        tok_pos[f] = pre_old_pos; tok_row[f] = s_star; tok_norm[f] = old_sc[0];
         tok_glo[f] = old_sc[1]; tok_past[f] = old_sc[2]; tok_cur[f] = old_sc[3];
         if (a.decision_opt) { a.decision_opt[(size_t)bkv * 2] = s_star; a.decision_opt[(size_t)bkv * 2 + 1] = dst; }
         if (a.sim_opt) a.sim_opt[bkv] = ci >= 0 ? cv : -INFINITY;
     }
-    __syncthreads();
 
     // ---- phase 7: a full window of queries: s_Loc^cur becomes s_Loc^past (Sec. 3.3) ----
-    if ((step + 1) % W == 0) {
+    if ((step + 1) % W == 0) {                               // block-uniform
+        __syncthreads();
         for (int j = tid; j < Tn; j += kBlock) { tok_past[j] = tok_cur[j]; tok_cur[j] = 0.f; }
     }
     // the counter: in the sliced step every block reads the hand-over copy, and a step whose number
@@ -1199,7 +1169,12 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
 // (The same with four launches, the scores by the table's slices, the cosines' and the commit's chains not yet shortened:
 // 21.1, 23.4, 27.7, 21.4; 24.1, 22.7, 28.0, 25.9.)
 constexpr long long kChooseScores = 3000000;
-// kWhich: the step kernel's parts, 6 = logits, 7 = choice of the centres
+// Threads of the one-launch step: a block of 512 has half the rows and table elements a wave, but pays the rest of the step twice as often.
+// (us a step, 256 / 512 threads, head size 128, 4 q-heads, merge ratio 0.5 unless stated: 32 heads of budget 128 9.4 / 10.0, one of 200 at ratio 2
+// 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Before sweeps ended with the table and the new token had a row
+// of its own, 256 threads: 10.5, 12.0, 14.2, 21.4; 16.5.)
+constexpr int kOneBlockTable = 256;
+// kWhich: the step kernel's parts (8 = part 0 with 512 threads), 6 = logits, 7 = choice of the centres
 template <typename T, int D, int G, int kWhich>
 static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
 {
@@ -1216,10 +1191,11 @@ static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
         }
     }
     else {
+        constexpr int kPart = kWhich == 8 ? 0 : kWhich;
         constexpr bool kRows = kWhich == 1 || kWhich == 5;      // a block per slice of rows
-        constexpr int kBlock = kWhich == 2 ? 1024 : 256;
-        const size_t lds = kWhich == 0 || kWhich == 2 ? sizeof(float) * (size_t)(a.lds_floats + a.lds_centres) : 0;
-        hipLaunchKernelGGL((decode_step_kernel<T, D, G, kBlock, kWhich>), dim3(kRows ? a.n_slices : 1, a.bkv), dim3(kBlock), lds, st, a);
+        constexpr int kBlock = kWhich == 2 ? 1024 : kWhich == 8 ? 512 : 256;
+        const size_t lds = kPart == 0 || kPart == 2 ? sizeof(float) * (size_t)(a.lds_floats + a.lds_centres) : 0;
+        hipLaunchKernelGGL((decode_step_kernel<T, D, G, kBlock, kPart>), dim3(kRows ? a.n_slices : 1, a.bkv), dim3(kBlock), lds, st, a);
     }
 }
 
@@ -1274,7 +1250,8 @@ static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
             return hipErrorInvalidValue;
         }
     }
-    const hipError_t e = launch_decode_part<T, D, 0>(a, st);
+    const bool wide = a.n_imp + a.n_tbm + a.window > kOneBlockTable;
+    const hipError_t e = wide ? launch_decode_part<T, D, 8>(a, st) : launch_decode_part<T, D, 0>(a, st);
     // A step whose number came with the call advances the counter itself: only blocks that read the
     // counter need it to stand still until all have (2.7 us of 13.6 a step, 32 heads with a budget of 128).
     if (e != hipSuccess || a.step >= 0) return e;

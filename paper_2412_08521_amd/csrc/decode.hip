@@ -1171,7 +1171,8 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
 constexpr long long kChooseScores = 3000000;
 // Threads of the one-launch step: a block of 512 has half the rows and table elements a wave, but pays the rest of the step twice as often.
 // (us a step, 256 / 512 threads, head size 128, 4 q-heads, merge ratio 0.5 unless stated: 32 heads of budget 128 9.4 / 10.0, one of 200 at ratio 2
-// 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Before sweeps ended with the table and the new token had a row
+// 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Head size 64 and 8 q-heads, whose
+// dots are most of a wave's work and half as many: 128 heads of 300 at ratio 2 16.1 / 16.5, one of 200 12.4 / 12.7.  Before sweeps ended with the table and the new token had a row
 // of its own, 256 threads: 10.5, 12.0, 14.2, 21.4; 16.5.)
 constexpr int kOneBlockTable = 256;
 // kWhich: the step kernel's parts (8 = part 0 with 512 threads), 6 = logits, 7 = choice of the centres
@@ -1250,7 +1251,7 @@ static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
             return hipErrorInvalidValue;
         }
     }
-    const bool wide = a.n_imp + a.n_tbm + a.window > kOneBlockTable;
+    const bool wide = a.n_imp + a.n_tbm + a.window > kOneBlockTable && !(D == 64 && a.group == 8);
     const hipError_t e = wide ? launch_decode_part<T, D, 8>(a, st) : launch_decode_part<T, D, 0>(a, st);
     // A step whose number came with the call advances the counter itself: only blocks that read the
     // counter need it to stand still until all have (2.7 us of 13.6 a step, 32 heads with a budget of 128).

@@ -13,7 +13,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 OBJ_DIR = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libems_hip.so")
-SOURCES = ["ems_api.hip", "score.hip", "score_f32.hip", "select.hip", "merge.hip", "decode.hip", "stats.hip"]
+SOURCES = ["ems_api.hip", "score.hip", "score_m16.hip", "score_f32.hip", "select.hip", "merge.hip", "decode.hip", "stats.hip"]
 HEADERS = ["ems_common.h", "ems_kernels.h", "ems_red_weights.h", "ems_rows.h", "ems_score.h", "ems_stream.h", os.path.join("..", "..", "include", "ems.h")]
 # the benchmark's ceiling measurements: a library of their own, outside the product's interface
 PROBE_DIR = os.path.join(_HERE, "bench_probe")
@@ -29,11 +29,11 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
 # These kernels read every accumulator element with the vector ALU: matrix results go to
 # ordinary vector registers, never to the accumulation file (which the ALU cannot read).
 _STREAM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-Rpass-analysis=kernel-resource-usage"]
-FILE_FLAGS = {"score.hip": _STREAM, "score_f32.hip": _STREAM, "stats.hip": _STREAM, "merge.hip": _STREAM[:2]}
+FILE_FLAGS = {"score.hip": _STREAM, "score_m16.hip": _STREAM, "score_f32.hip": _STREAM, "stats.hip": _STREAM, "merge.hip": _STREAM[:2]}
 # Kernels that count their own vector-memory operations (s_waitcnt vmcnt(n) by hand around the
 # LDS DMA): a register spill would add scratch loads/stores the count does not know about, so
 # such a build is rejected instead of being allowed to run with a silent race.
-NO_SCRATCH = {"score.hip": ("score_pass1", "score_pass2"), "score_f32.hip": ("score_pass1", "score_pass2"), "stats.hip": ("redundancy_stream",)}
+NO_SCRATCH = {"score.hip": ("score_pass1", "score_pass2"), "score_m16.hip": ("score_pass1", "score_pass2"), "score_f32.hip": ("score_pass1", "score_pass2"), "stats.hip": ("redundancy_stream",)}
 
 
 def _check_no_scratch(src: str, remarks: str) -> None:

@@ -337,7 +337,38 @@ __device__ __forceinline__ void stream_edge_tile(const frag_t (&aq)[Tile<T, D>::
     }
 }
 
-// The float32 passes (score_f32.hip): what score.hip's launchers start in their place.
+// The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
+// the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
+// last stage of all is issued (t_left <= 1); `l` likewise with kLStep / l_jump.  Written out: left
+// to the compiler these few selects become several times as many instructions, part of them on
+// the vector ALU.
+template <int kQStep, int kLStep>
+__device__ __forceinline__ void advance_cursor(int& h_left, int& t_left, const char*& q, const char*& l, int per_head,
+                                               long long q_jump, long long l_jump)
+{
+    long long aq, al;
+    asm volatile(
+        "s_cmp_eq_u32 %[h], 1\n\t"
+        "s_cselect_b64 %[aq], %[qj], %[qs]\n\t"
+        "s_cselect_b64 %[al], %[lj], %[ls]\n\t"
+        "s_cselect_b32 %[h], %[ph], %[h]\n\t"
+        "s_sub_u32 %[h], %[h], 1\n\t"
+        "s_cmp_gt_i32 %[t], 1\n\t"
+        "s_cselect_b64 %[aq], %[aq], 0\n\t"
+        "s_cselect_b64 %[al], %[al], 0\n\t"
+        "s_sub_u32 %[t], %[t], 1"
+        : [h] "+s"(h_left), [t] "+s"(t_left), [aq] "=&s"(aq), [al] "=&s"(al)
+        : [qj] "s"(q_jump), [lj] "s"(l_jump), [ph] "s"(per_head + 1), [qs] "i"(kQStep), [ls] "i"(kLStep)
+        : "scc");
+    q += aq;
+    l += al;
+}
+
+// What score.hip's launchers start in place of its own kernels: the passes by 16x16x32 products (score_m16.hip), the float32
+// passes (score_f32.hip).
+constexpr int kSubBf16 = 8;            // 32-wide subtiles of the stationary operand per wave
+void start_pass1_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
+void start_pass2_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
 constexpr int kSubF32 = 2;             // 32-wide subtiles of the stationary operand per wave
 void start_pass1_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
 void start_pass2_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);

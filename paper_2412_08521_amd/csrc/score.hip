@@ -169,35 +169,8 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(ScoreArgs a)
 //                  row operand and log-sum-exp are fetched from LDS into a second register set.
 // 32-wide subtiles of the stationary operand per wave (8 x 8 fragments = the 256 accumulation
 // registers in the 16-bit types) and LDS stages in the wave's ring
-constexpr int kSub = 8, kRing = 4;
+constexpr int kSub = kSubBf16, kRing = 4;
 using T = bf16_t;
-
-// The interior loops' DMA cursor, one step: source address `q` advances by a stage (kQStep bytes), at
-// the last stage of a head (h_left == 1 of per_head) by q_jump instead, and not at all once the
-// last stage of all is issued (t_left <= 1); `l` likewise with kLStep / l_jump.  Written out: left
-// to the compiler these few selects become several times as many instructions, part of them on
-// the vector ALU.
-template <int kQStep, int kLStep>
-__device__ __forceinline__ void advance_cursor(int& h_left, int& t_left, const char*& q, const char*& l, int per_head,
-                                               long long q_jump, long long l_jump)
-{
-    long long aq, al;
-    asm volatile(
-        "s_cmp_eq_u32 %[h], 1\n\t"
-        "s_cselect_b64 %[aq], %[qj], %[qs]\n\t"
-        "s_cselect_b64 %[al], %[lj], %[ls]\n\t"
-        "s_cselect_b32 %[h], %[ph], %[h]\n\t"
-        "s_sub_u32 %[h], %[h], 1\n\t"
-        "s_cmp_gt_i32 %[t], 1\n\t"
-        "s_cselect_b64 %[aq], %[aq], 0\n\t"
-        "s_cselect_b64 %[al], %[al], 0\n\t"
-        "s_sub_u32 %[t], %[t], 1"
-        : [h] "+s"(h_left), [t] "+s"(t_left), [aq] "=&s"(aq), [al] "=&s"(al)
-        : [qj] "s"(q_jump), [lj] "s"(l_jump), [ph] "s"(per_head + 1), [qs] "i"(kQStep), [ls] "i"(kLStep)
-        : "scc");
-    q += aq;
-    l += al;
-}
 
 template <int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_stream_kernel(ScoreArgs a)
@@ -1074,10 +1047,28 @@ ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*he
     return f32 ? score_deal_t<true>(batch, q_heads, kv_heads, seq_len) : score_deal_t<false>(batch, q_heads, kv_heads, seq_len);
 }
 
+// Which products: by 16x16x32 (score_m16.hip) where the launch is long enough for the chip to lower its clock, counted in stages of 32 x 256
+// per resident wave, and the sequence so long that the masked stages, which cost a tenth more there, are few.  Both passes, us, 32x32x16 / 16x16x32:
+//     32 heads over 8, 2700   14 stages    96.8 /  98.4          8 over 8, 5500   15    90.5 /  92.7
+//                      2900   17          104.4 / 104.2          4 over 2, 8200   17    96.0 /  94.7
+//                      3300   21          119.6 / 118.4         16 over 16, 4096  16    91.7 /  91.1
+//                      8192  128          490.1 / 474.7         32 over 8, 16384 512  1739 / 1695
+//    112 heads over 16, 1921, the whole case 228 / 243
+// With fewer (batch, kv-head) pairs than XCDs a pair's rows are streamed through several of their L2s and there is as much to lose as to win:
+// 32 over 4, 32768 3416 + 3598 / 3341 + 3682, 8 over 2, 98304 8145 + 8347 / 8452 + 8227, 4 over 1, 131072 6762 + 7411 / 6684 + 7328.
+constexpr double kLongStages = 16.;
+constexpr int kLongRows = 3200;
+static bool long_launch(const ScoreArgs& a)
+{
+    const DealPass1<kSub> d(a.seq_len);
+    return a.head_dim == 128 && a.batch * a.kv_heads >= kXcds && a.seq_len >= kLongRows && 0.5 * a.batch * a.q_heads * d.n_stages * d.n_units >= kLongStages * kResident;
+}
+
 template <bool kF32, bool kDeal>
 static void start_pass1(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass1_f32(a, kDeal, grid, st);
+    else if (long_launch(a)) start_pass1_m16(a, kDeal, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass1_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass1_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }
@@ -1086,6 +1077,7 @@ template <bool kF32, bool kDeal>
 static void start_pass2(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass2_f32(a, kDeal, grid, st);
+    else if (long_launch(a)) start_pass2_m16(a, kDeal, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass2_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass2_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }

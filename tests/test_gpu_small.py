@@ -170,6 +170,30 @@ def test_score_whole_items(mode, shape, forms):
         np.testing.assert_allclose(lse[i, h * g:(h + 1) * g].cpu().numpy(), o[2][0], rtol=0, atol=2e-5 if mode == B.EMS_F32 else 2e-2)
 
 
+@pytest.mark.parametrize("far", [False, True])
+@pytest.mark.parametrize("group,n", [(3, 3232), (3, 3264), (3, 3296), (3, 3328), (3, 3233), (1, 3360), (4, 3231), (4, 3200)])
+def test_score_by_the_smaller_products(group, n, far):
+    """Launches of 16 and more stages of 32 x 256 per resident wave, 3200 rows and more, at head size 128, which run by 16x16x32
+    products: every remainder of the trips, ragged ends.  far: later logits exceed the first stage's by more than the float range, so that parts are
+    redone with a running maximum (bounds as in the test below).  First and last kv-head against the oracle."""
+    hkv, d, w = 36 // group, 128, 40
+    _log("smaller products", group, n, far)
+    p = B.EmsParams(1, 36, hkv, d, n, w)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    k = torch.randn((1, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    q = torch.randn((1, 36, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    if far:
+        k[:, :, 700:] *= 64.0                                # exact in bf16
+    s_glo, s_loc, lse = B.ems_global_local_score(p, q, k, want_lse=True)
+    rtol = 4e-4 if far else 1e-5                             # (without far: the float32 mode's bar, the products of bf16 inputs are exact)
+    for h in (0, hkv - 1):
+        ref = ems_ref.RefParams(1, group, 1, d, n, w)
+        o = ems_ref.score(ref, q[:, h * group:(h + 1) * group].float().cpu().numpy(), k[:, h:h + 1].float().cpu().numpy(), want_lse=True)
+        assert_rel(s_glo[0, h].cpu().numpy(), o[0][0, 0], rtol, "s_glo")
+        assert_rel(s_loc[0, h].cpu().numpy(), o[1][0, 0], rtol, "s_loc")
+        np.testing.assert_allclose(lse[0, h * group:(h + 1) * group].cpu().numpy(), o[2][0], rtol=2e-6, atol=1e-4 if far else 2e-5)
+
+
 @pytest.mark.parametrize("mode", MODES)
 def test_score_first_stage_far_below_the_others(mode):
     """The first stage of a part gives the reference exponent; here later logits exceed it by far more than

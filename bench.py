@@ -156,7 +156,7 @@ def main():
         import re
         m = re.search(r"hbm_bytes_per_launch:\s*([0-9.eE+]+)", open(tpath).read())
         traffic = float(m.group(1)) if m else None
-    roofline = {"bound": "mfma", "kernel": "score_pass2_stream_kernel", "achieved": round(achieved, 2),
+    roofline = {"bound": "mfma", "kernel": "score_pass2", "achieved": round(achieved, 2),
                 "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
                 "traffic": traffic,
                 "traffic_source": (f"profiles/score_pass2_{w.name}.md: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE "
@@ -164,14 +164,14 @@ def main():
                                    if traffic is not None else None),
                 "flops_per_launch": flops_pass,
                 "ms_per_launch": round(ms_pass2, 4)}
-    pass1 = {"kernel": "score_pass1_stream_kernel", "achieved": round(flops_pass / (ms_pass1 * 1e-3) / 1e12, 2),
+    pass1 = {"kernel": "score_pass1", "achieved": round(flops_pass / (ms_pass1 * 1e-3) / 1e12, 2),
              "unit": "TFLOP/s", "frac": round(flops_pass / (ms_pass1 * 1e-3) / 1e12 / peak, 4),
              "ms_per_launch": round(ms_pass1, 4)}
 
     # ---- the machine's own ceilings in the same process (bench-only library): a loop of bf16
     # MFMAs (32x32x16, the score passes' form), 16 waves per compute unit, on operands that are all
     # 1.0, on constants that differ from lane to lane, and on random ones (the more bits toggle, the
-    # lower the clock the power limit allows), the same work as 16x16x32 on random ones (it takes
+    # lower the clock the power limit allows), the same work as 16x16x32 (that of middling passes) on random ones (it takes
     # less power; the higher of the two random-operand figures is the ceiling real inputs see),
     # and a plain 16-byte vector copy of Q.  Each loop runs for about 20 ms before it is timed
     # over about 50, so that the clock is its own and not the one before it

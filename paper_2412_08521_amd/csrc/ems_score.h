@@ -368,7 +368,7 @@ __device__ __forceinline__ void advance_cursor(int& h_left, int& t_left, const c
 // passes (score_f32.hip).
 constexpr int kSubBf16 = 8;            // 32-wide subtiles of the stationary operand per wave
 void start_pass1_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
-void start_pass2_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
+void start_pass2_m16(const ScoreArgs& a, unsigned grid, hipStream_t st);      // (an even deal)
 constexpr int kSubF32 = 2;             // 32-wide subtiles of the stationary operand per wave
 void start_pass1_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);
 void start_pass2_f32(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st);

@@ -1054,21 +1054,25 @@ ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*he
 //                      3300   21          119.6 / 118.4         16 over 16, 4096  16    91.7 /  91.1
 //                      8192  128          490.1 / 474.7         32 over 8, 16384 512  1739 / 1695
 //    112 heads over 16, 1921, the whole case 228 / 243
+// Launches of several milliseconds settle at a power limit where it depends on the chip which is faster (ms on three): 4 x 32 over 8, 16384 6.97 / 6.85,
+// 7.16 / 7.23, -; 32768 28.3 / 27.5, 28.0 / 27.7, 28.0 / 29.0.  They stay with the larger products.
 // With fewer (batch, kv-head) pairs than XCDs a pair's rows are streamed through several of their L2s and there is as much to lose as to win:
 // 32 over 4, 32768 3416 + 3598 / 3341 + 3682, 8 over 2, 98304 8145 + 8347 / 8452 + 8227, 4 over 1, 131072 6762 + 7411 / 6684 + 7328.
-constexpr double kLongStages = 16.;
-constexpr int kLongRows = 3200;
-static bool long_launch(const ScoreArgs& a)
+constexpr double kM16Stages = 16., kM16Most = 1024.;
+constexpr int kM16Rows = 3200;
+static_assert(kM16Most * 1.1 < kDealStages, "a second pass by 16x16x32 products is an even deal (its stages are padded by 3 in 100 at most)");
+static bool m16_launch(const ScoreArgs& a)
 {
     const DealPass1<kSub> d(a.seq_len);
-    return a.head_dim == 128 && a.batch * a.kv_heads >= kXcds && a.seq_len >= kLongRows && 0.5 * a.batch * a.q_heads * d.n_stages * d.n_units >= kLongStages * kResident;
+    const double stages = 0.5 * a.batch * a.q_heads * d.n_stages * d.n_units / kResident;
+    return a.head_dim == 128 && a.batch * a.kv_heads >= kXcds && a.seq_len >= kM16Rows && stages >= kM16Stages && stages <= kM16Most;
 }
 
 template <bool kF32, bool kDeal>
 static void start_pass1(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass1_f32(a, kDeal, grid, st);
-    else if (long_launch(a)) start_pass1_m16(a, kDeal, grid, st);
+    else if (m16_launch(a)) start_pass1_m16(a, kDeal, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass1_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass1_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }
@@ -1077,7 +1081,7 @@ template <bool kF32, bool kDeal>
 static void start_pass2(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass2_f32(a, kDeal, grid, st);
-    else if (long_launch(a)) start_pass2_m16(a, kDeal, grid, st);
+    else if (kDeal && m16_launch(a)) start_pass2_m16(a, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass2_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass2_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }

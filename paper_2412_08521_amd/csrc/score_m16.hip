@@ -1,10 +1,10 @@
-// The two bf16 score passes at head size 128 by 16x16x32 products: what long launches run in place of score.hip's kernels,
-// whose work items, partial results, ring, stages, edge and interior loops these share (see there).
+// The two bf16 score passes at head size 128 by 16x16x32 products: what launches of up to two milliseconds run in place of score.hip's
+// kernels (rule there), whose work items, partial results, ring, stages, edge and interior loops these share.
 //
 // A 32x32x16 product and four of 16x16x32 take the same matrix time, but these take less power, which is what limits the
 // clock of a long launch, and twice the issue slots, which is what bounds a short one.  A loop of nothing but a tile's products and weights,
 // without the DMA: 206 ns a tile by 32x32x16, 194 by 16x16x32.  Both passes, us, 32x32x16 / 16x16x32, in turn: 32 heads over 8, 16384
-// 1739 / 1695, 4 x 32 over 8, 16384 6968 / 6851, 32 over 8, 49152 15276 / 14841 (short ones at the rule in score.hip).  Column sums against 64 bits, rms
+// 1739 / 1695, 8192 490 / 475, 3 x 12 over 4, 16384 2098 / 2032.  Column sums against 64 bits, rms
 // of 6 seeds, 3300 to 20001 rows: 1.1-2.3e-7 -> 1.0-1.8e-7 (all rows), 1.2-2.8e-7 -> 1.1-2.4e-7 (window).  At head size 64 the weights' exp2 are the bound
 // and nothing is won at any length (4 x 32 over 8, 16384: 5174 / 5232).
 //
@@ -161,7 +161,6 @@ __device__ __forceinline__ void groups_join(const float (&m)[kGroups], const flo
     M = m0; L = l0;
 }
 
-template <bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_m16_kernel(ScoreArgs a)
 {
     constexpr int kRowBytes = Tile<T, D>::kRowBytes;
@@ -175,13 +174,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 
     __shared__ __attribute__((aligned(1024))) char lds_q[kRing][kStageBytes];
     __shared__ __attribute__((aligned(256))) float lds_lse[kRing][2 * kStreamRows];   // second half: spare
-    __shared__ float lds_sum[kDeal ? kGroups : 1][kWave];   // the column sums that were set aside, a lane's own
+    __shared__ float lds_sum[kGroups][kWave];               // the column sums that were set aside, a lane's own
 
     const float c = a.scale_log2e;
     const int N = a.seq_len, W = a.window;
     const int G = a.q_heads / a.kv_heads;
 
-    Pass2Items<kSub, kDeal> items(a);
+    Pass2Items<kSub, true> items(a);
     while (items.next()) {
     const int bkv = items.bkv, r_begin = items.r_begin, r_end = items.r_end;
     const int key_base = items.J * kKeys;
@@ -232,7 +231,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     float part[kGroups][2];                                 // a key's sums over the lane's rows, by row half
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) {
-        if constexpr (kDeal) lds_sum[g][lane] = 0.f;
+        lds_sum[g][lane] = 0.f;
         part[g][0] = part[g][1] = 0.f;
     }
 
@@ -427,7 +426,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
             stage(ic<2>{});
             stage(ic<3>{});
             until_fold -= kUnroll;
-            if (kDeal && __builtin_expect(until_fold == 0, 0)) {     // the sums so far are set aside, in LDS
+            if (__builtin_expect(until_fold == 0, 0)) {     // the sums so far are set aside, in LDS
                 until_fold = fold;
                 const int ln = lane_here();
 #pragma unroll
@@ -447,7 +446,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     items.outputs(out_glo, out_loc);
     const int out_lane = opaque_lane(lane);                 // (likewise not kept across the loops above)
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) part[g][0] = (kDeal ? lds_sum[g][out_lane] : 0.f) + (part[g][0] + part[g][1]);
+    for (int g = 0; g < kGroups; ++g) part[g][0] = lds_sum[g][out_lane] + (part[g][0] + part[g][1]);
 #pragma unroll
     for (int g = 0; g < kGroups; g += 4) {                  // the quarters hold disjoint rows of the same keys
         const int kj = key_base + g * 16 + out_lane;
@@ -819,10 +818,9 @@ void start_pass1_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t s
     else hipLaunchKernelGGL(score_pass1_m16_kernel<false>, dim3(grid), dim3(kWave), 0, st, a);
 }
 
-void start_pass2_m16(const ScoreArgs& a, bool deal, unsigned grid, hipStream_t st)
+void start_pass2_m16(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
-    if (deal) hipLaunchKernelGGL(score_pass2_m16_kernel<true>, dim3(grid), dim3(kWave), 0, st, a);
-    else hipLaunchKernelGGL(score_pass2_m16_kernel<false>, dim3(grid), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL(score_pass2_m16_kernel, dim3(grid), dim3(kWave), 0, st, a);
 }
 
 }  // namespace ems

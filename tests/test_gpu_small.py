@@ -135,6 +135,8 @@ def test_score_float32_values_that_do_not_split(what, d):
 @pytest.mark.parametrize("mode,shape,forms", [
     (B.EMS_BF16, (1, 256, 8, 64, 2040, 100), ("block", "deal")),     # two row tiles per wave, one pair per XCD
     (B.EMS_BF16, (1, 64, 2, 128, 8177, 90), ("block", "deal")),      # the q-heads of a row tile together
+    (B.EMS_BF16, (1, 64, 8, 128, 8177, 90), ("block", "deal")),      # these two by 16x16x32 products
+    (B.EMS_BF16, (1, 80, 8, 128, 8177, 33), ("queue", "deal")),
     (B.EMS_BF16, (1, 320, 8, 128, 2040, 100), ("queue", "deal")),
     (B.EMS_BF16, (1, 500, 5, 64, 1270, 33), ("queue", "deal")),
     (B.EMS_BF16, (1, 804, 804, 64, 5003, 1500), ("queue", "block")),  # pairs that do not divide over the XCDs
@@ -173,7 +175,7 @@ def test_score_whole_items(mode, shape, forms):
 @pytest.mark.parametrize("far", [False, True])
 @pytest.mark.parametrize("group,n", [(3, 3232), (3, 3264), (3, 3296), (3, 3328), (3, 3233), (1, 3360), (4, 3231), (4, 3200)])
 def test_score_by_the_smaller_products(group, n, far):
-    """Launches of 16 and more stages of 32 x 256 per resident wave, 3200 rows and more, at head size 128, which run by 16x16x32
+    """Launches of 16 to 1024 stages of 32 x 256 per resident wave, 3200 rows and more, at head size 128, which run by 16x16x32
     products: every remainder of the trips, ragged ends.  far: later logits exceed the first stage's by more than the float range, so that parts are
     redone with a running maximum (bounds as in the test below).  First and last kv-head against the oracle."""
     hkv, d, w = 36 // group, 128, 40

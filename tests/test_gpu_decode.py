@@ -133,7 +133,7 @@ def test_decode_init_matches_oracle(shape, mode):
     assert (st.tok_row < 0).any() and (st.tok_row >= 0).any()
 
 
-# large caches: with so few heads the bf16 step runs as four launches, two of them over slices of the table, with the
+# large caches: with so few heads the bf16 step runs as three or four launches, all but the last over slices, with the
 # logits in the workspace; in float32 it is one launch, whose row dots BIG stages in the workspace (they do not fit
 # in LDS) and BIG_LDS in LDS
 BIG = (1, 8, 1, 64, 4000, 8, 1800, 0.5)

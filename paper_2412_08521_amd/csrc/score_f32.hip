@@ -17,14 +17,22 @@
 //
 // Not every float has three such pieces.  Infinities, NaN and values that round to infinity in bf16 give NaN, which no
 // later step loses; rows with elements of 2^60 and more, or below 2^-100 (whose low piece falls below bf16's range
-// while the other factor could be large), are found when they are split.  Either sends the item to a plain loop of
-// float32 instructions, so that infinite logits come out as they do there.
+// while the other factor could be large), are found when they are split.  The latter's items go by float32 products, of any values, from the
+// first stage on; the others' from the set of stages on whose sums left the float range (they are put back to what they were before it), so that
+// infinite logits come out as by float32 products and cost no more than those.  One key of -inf, which every later row of its head streams, us
+// of both passes by float32 products alone / begun anew without a pipeline / now: 8 heads over 2 of 128, 3000 rows 235 / 315 / 212, of 64 113 / 168 / 116;
+// 32 over 8, 6000 rows 3361 / 4197 / 2594; 4 x 32 over 8, 4096 4677 / 7922 / 5121 (a wave alone at that pace, among others that draw
+// the power of 16-bit products), in the middle of the sequence 4941 / - / 3467; a large element in every key 4687 / 6376 / 3581.
 #include "ems_common.h"
 #include "ems_kernels.h"
 #include "ems_score.h"
 #include "ems_stream.h"
 
 namespace ems {
+
+// Stages from one look at the sums to the next: two, and twice as many each time up to this.  (What the first value without pieces
+// throws away is then little against what went well before it.)
+constexpr int kFoldStagesF32 = 8;
 
 typedef __bf16 bf16x2v_t __attribute__((ext_vector_type(2)));
 typedef float f32x2v_t __attribute__((ext_vector_type(2)));
@@ -63,7 +71,6 @@ struct F32 {
     static constexpr int kCpr = Tile<float, D>::kChunksPerRow;
     static constexpr int kStageBytes = kStreamRows * kRowBytes;
     static constexpr int kInstr = kStageBytes / 1024;                  // DMA instructions per stage
-    static constexpr int kPerStep = 16 / kSteps;                       // accumulator elements of a tile weighed per step
     static_assert(kInstr % 4 == 0 && kSteps % 2 == 0 && kSteps >= 4, "");
 
     // where a lane finds its fragments of its row of 32, 32 bytes apart (past the end of the matrix: of the last row, whose
@@ -100,6 +107,21 @@ struct F32 {
             __builtin_amdgcn_sched_barrier(0);                         // one subtile's rows at a time
         }
         return !(most < 0x1p60f) || least < 0x1p-100f;
+    }
+
+    // the same rows as they are
+    static __device__ __forceinline__ void load_exact(const float* X, int row0, int N, int lane, frag_t (&b)[kSubF32][kFrags])
+    {
+#pragma unroll
+        for (int s = 0; s < kSubF32; ++s) {
+            const char* x = row_bytes(X, row0 + s * 32, N, lane);
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) b[s][f] = *reinterpret_cast<const frag_t*>(x + f * 32);
+        }
+#pragma unroll
+        for (int s = 0; s < kSubF32; ++s)
+#pragma unroll
+            for (int f = 0; f < kFrags; ++f) asm volatile("" : "+a"(b[s][f]));
     }
 
     // Source offsets of a stage's DMA, less what the instruction itself adds (1 KiB x its place in a group of four); those of
@@ -182,11 +204,12 @@ struct F32 {
         }
     };
 
-    // The products of one stage, 32 streamed rows x kSubF32 tiles.  `landed` waits for the next stage (which
-    // step kSteps - 2 begins to read); `weigh(f, i)`: vector work of slot i of 12 of step f.
-    template <class Landed, class Weigh>
+    // The products of one stage, 32 streamed rows x kSubF32 tiles.  `landed` waits for the next stage (which step kSteps - 2 begins to
+    // read); `begin(s)`: vector work ahead of tile s's; `weigh(e)`: vector work of element e of 2 * 16, in the last slots of the steps.
+    static constexpr int kEach = 32 / kSteps;
+    template <class Landed, class Begin, class Weigh>
     static __device__ __forceinline__ void stage(const char* here, const char* after, const unsigned (&off)[kKeys], Feed& q,
-                                                 const Pieces (&b)[kSubF32][kSteps], f32x16_t (&acc)[kSubF32], Landed landed, Weigh weigh)
+                                                 const Pieces (&b)[kSubF32][kSteps], f32x16_t (&acc)[kSubF32], Landed landed, Begin begin, Weigh weigh)
     {
 #pragma unroll
         for (int f = 0; f < kSteps; ++f) {
@@ -206,10 +229,36 @@ struct F32 {
                 const frag_t& y = k == 1 ? p.l : k == 2 || k == 4 ? p.m : p.h;
                 mma_piece(acc[s], x, y, f == 0 && k == 0);
                 q.part(i);
-                weigh(f, i);
+                if (f == 0 && i < kSubF32) begin(i);
+                if (i >= 12 - kEach) weigh(f * kEach + i - (12 - kEach));
                 __builtin_amdgcn_sched_barrier(0);
             }
             q.now = q.next;
+        }
+    }
+
+    // The same by float32 products, of any values.  `first`: a lane's first fragment, fetched a stage ahead; `early`: what waits for nothing.
+    template <class Early, class Landed, class Begin, class Weigh>
+    static __device__ __forceinline__ void exact_stage(const char* here, const char* after, const unsigned (&off)[kKeys], frag_t& first,
+                                                       const frag_t (&b)[kSubF32][kFrags], f32x16_t (&acc)[kSubF32], Early early, Landed landed,
+                                                       Begin begin, Weigh weigh)
+    {
+        frag_t x[2];
+        x[0] = first;
+#pragma unroll
+        for (int f = 0; f < kFrags; ++f) {
+            if (f + 1 < kFrags) x[(f + 1) & 1] = fetch(here, off, f + 1);
+            else { landed(); first = fetch(after, off, 0); }
+#pragma unroll
+            for (int s = 0; s < kSubF32; ++s) {
+                if (f == 0) mma_first<float>(acc[s], x[0], b[s][0]);
+                else mma<float>(acc[s], x[f & 1], b[s][f]);
+                if (f == 0 && s == 0) { begin(0); begin(1); }
+                if (f == 0 && s == 1) early();
+#pragma unroll
+                for (int e = (2 * f + s) * 16 / kFrags; e < (2 * f + s + 1) * 16 / kFrags; ++e) weigh(e);
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
     }
 };
@@ -217,13 +266,13 @@ struct F32 {
 // ------------------------------------------------------------------------------------
 // Second pass: 64 keys stationary, the query rows of every q-head of the group streamed with their log-sum-exp.
 // The weights of a stage are formed under the products of the next one; those of a stage with window rows (which go
-// to the local sums too) at its end.  Rows above the diagonal get logits of -inf.
+// to the local sums too), and by float32 products of one on the diagonal, at its end.  By pieces rows above the diagonal get logits of -inf.
 // ------------------------------------------------------------------------------------
 template <int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass2_f32_kernel(ScoreArgs a)
 {
     using E = F32<D>;
-    constexpr int kSub = kSubF32, kKeys = 32 * kSub, kSteps = E::kSteps, kEach = E::kPerStep;
+    constexpr int kSub = kSubF32, kKeys = 32 * kSub;
     __shared__ __attribute__((aligned(1024))) char lds_q[2][E::kStageBytes];
     __shared__ __attribute__((aligned(256))) float lds_lse[2][2 * kStreamRows];       // second half: spare
 
@@ -239,141 +288,162 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int lane = opaque_lane(threadIdx.x);
     const int col = lane & 31, half = lane >> 5;
 
-    Pieces bk[kSub][kSteps];
-    bool plain = E::load_stationary(K, key_base, N, lane, bk);
     unsigned dma_off[E::kOffs], frag_off[E::kKeys];
     E::dma_offsets(lane, dma_off);
     E::frag_offsets(lane, frag_off);
     const unsigned lds_q0 = lds_address(&lds_q[0][0]), lds_l0 = lds_address(&lds_lse[0][0]);
-    wait_vmem_all_visible();
 
     const int per_head = (r_end - r_begin + kStreamRows - 1) / kStreamRows, n_stages = per_head * G;
-    int g_next = 0, row_next = r_begin, row_now = r_begin;              // the stage to fetch next, the present one
-    auto issue_next = [&](int slot) __attribute__((always_inline)) {
-        E::issue(reinterpret_cast<const char*>(Q0) + (size_t)g_next * N * E::kRowBytes, row_next, N, lds_q0 + slot * E::kStageBytes, dma_off);
-        // the rows' log-sum-exp (+inf up to n_pad); the upper half-wave's copy goes to the spare half of the slot
-        dma_to_lds<4>(L0 + (size_t)g_next * a.n_pad, (unsigned)(row_next + col) * 4u, lds_l0 + slot * (2 * kStreamRows * 4));
-        row_next += kStreamRows;
-        if (row_next >= r_end) { row_next = r_begin; ++g_next; }
-    };
-
-    f32x16_t acc[2][kSub], lse_v[2];
-    float part[kSub][2], aside[kSub], loc[kSub];
+    float glo[kSub], loc[kSub];
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) { part[s][0] = part[s][1] = aside[s] = loc[s] = 0.f; acc[1][s] = zero_acc(); }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) lse_v[1][r] = INFINITY;                // before the first stage: weights of zero
-    typename E::Feed feed;
-    issue_next(0);
-    wait_vmem<0>();
-    feed.start(lds_q[0], frag_off);
+    for (int s = 0; s < kSub; ++s) glo[s] = loc[s] = 0.f;
 
-    auto stage = [&](auto set_c, int t) __attribute__((always_inline)) {
-        constexpr int set = decltype(set_c)::value;
-        // the other slot was last read (its log-sum-exp included) before the last steps of the stage before this one
+    // Stages [from, n_stages).  kExact: by float32 products.  By pieces: up to a set of stages that leaves a sum out of the float range; the sums are then
+    // as before it.  Returns the first stage that is not in the sums.
+    auto sweep = [&](auto exact_c, const auto& bk, int from) __attribute__((always_inline)) {
+        constexpr bool kExact = decltype(exact_c)::value;
+        int g_next = scalar(from / per_head), row_next = r_begin + (from - g_next * per_head) * kStreamRows;      // the stage to fetch next
+        int row_now = row_next;
+        auto issue_next = [&](int slot) __attribute__((always_inline)) {
+            E::issue(reinterpret_cast<const char*>(Q0) + (size_t)g_next * N * E::kRowBytes, row_next, N, lds_q0 + slot * E::kStageBytes, dma_off);
+            // the rows' log-sum-exp (+inf up to n_pad); the upper half-wave's copy goes to the spare half of the slot
+            dma_to_lds<4>(L0 + (size_t)g_next * a.n_pad, (unsigned)(row_next + col) * 4u, lds_l0 + slot * (2 * kStreamRows * 4));
+            row_next += kStreamRows;
+            if (row_next >= r_end) { row_next = r_begin; ++g_next; }
+        };
+
+        f32x16_t acc[2][kSub], lse_v[2];
+        float part[kSub][2], glo_in[kSub], loc_in[kSub];
+        bool counted = false;                                           // the last stage's weights are in the sums
+#pragma unroll
+        for (int s = 0; s < kSub; ++s) { part[s][0] = part[s][1] = 0.f; glo_in[s] = glo[s]; loc_in[s] = loc[s]; acc[1][s] = zero_acc(); }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) lse_v[1][r] = INFINITY;            // before the first stage: weights of zero
+        typename E::Feed feed;
+        frag_t first = zero_frag();
         wait_lds_all_visible();
-        if (t + 1 < n_stages) issue_next(1 - set);
+        issue_next(0);
+        wait_vmem<0>();
+        if constexpr (kExact) first = E::fetch(lds_q[0], frag_off, 0);
+        else feed.start(lds_q[0], frag_off);
+
+        auto stage = [&](auto set_c, int t) __attribute__((always_inline)) {
+            constexpr int set = decltype(set_c)::value;
+            // the other slot was last read (its log-sum-exp included) before the last steps of the stage before this one
+            auto issue = [&]() __attribute__((always_inline)) { wait_lds_all_visible(); if (t + 1 < n_stages) issue_next(1 - set); };
+            auto landed = []() __attribute__((always_inline)) { wait_vmem<0>(); };
+            if constexpr (!kExact) issue();
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(lds_lse[set] + 8 * q4 + 4 * half);
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(lds_lse[set] + 8 * q4 + 4 * half);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) lse_v[set][4 * q4 + i] = v[i];
-        }
-        E::stage(lds_q[set], lds_q[1 - set], frag_off, feed, bk, acc[set], []() __attribute__((always_inline)) { wait_vmem<0>(); },
-                 [&](int f, int i) __attribute__((always_inline)) {
-                     // 2 * kEach elements of the stage before, one in each of the last slots
-                     const int e = i - (12 - 2 * kEach);
-                     if (e < 0) return;
-                     const int s = e & 1, r = f * kEach + (e >> 1);
-                     part[s][r & 1] += exp2_fast(__builtin_fmaf(acc[1 - set][s][r], c, -lse_v[1 - set][r]));
-                 });
+                for (int i = 0; i < 4; ++i) lse_v[set][4 * q4 + i] = v[i];
+            }
+            auto weigh = [&](int e) __attribute__((always_inline)) {    // (of the stage before)
+                const int s = e & 1, r = e >> 1;
+                part[s][r & 1] += exp2_fast(__builtin_fmaf(acc[1 - set][s][r], c, -lse_v[1 - set][r]));
+            };
+            if constexpr (kExact) {
+                E::exact_stage(lds_q[set], lds_q[1 - set], frag_off, first, bk, acc[set], issue, landed, [](int) __attribute__((always_inline)) {}, weigh);
+            } else {
+                E::stage(lds_q[set], lds_q[1 - set], frag_off, feed, bk, acc[set], landed, [](int) __attribute__((always_inline)) {}, weigh);
+            }
 #pragma unroll
-        for (int s = 0; s < kSub; ++s) { stays_here(part[s][0]); stays_here(part[s][1]); }
-        const int row0 = row_now;
-        row_now += kStreamRows;
-        if (row_now >= r_end) row_now = r_begin;
-        if (row0 < key_base + kKeys) {                                  // on the diagonal: rows before the key
-            const int lane = lane_here(), col = lane & 31, half = lane >> 5;      // (nothing is kept for this)
+            for (int s = 0; s < kSub; ++s) { stays_here(part[s][0]); stays_here(part[s][1]); }
+            const int row0 = row_now;
+            row_now += kStreamRows;
+            if (row_now >= r_end) row_now = r_begin;
+            const bool diagonal = row0 < key_base + kKeys;              // rows before the key are above it
+            counted = row0 + kStreamRows > win0 || (kExact && diagonal);
+            if (!kExact && diagonal) {
+                const int lane = lane_here(), col = lane & 31, half = lane >> 5;      // (nothing is kept for this)
+#pragma unroll
+                for (int s = 0; s < kSub; ++s)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r)
+                        if (row0 + acc_row(r, half) < key_base + s * 32 + col) acc[set][s][r] = -INFINITY;
+            }
+            if (counted) {                                              // at once, and none left for the next stage
+                const int lane = lane_here(), col = lane & 31, half = lane >> 5;
+#pragma unroll
+                for (int s = 0; s < kSub; ++s) {
+                    float p[16];
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[set][s][r], c, -lse_v[set][r]));
+                    // (above the diagonal no weight, whatever the log-sum-exp: minus infinity would make NaN of a logit of minus infinity)
+                    if (kExact) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) p[r] = row0 + acc_row(r, half) < key_base + s * 32 + col ? 0.f : p[r];
+                    }
+                    part[s][0] += sum16(p);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) p[r] = row0 + acc_row(r, half) < win0 ? 0.f : p[r];
+                    loc[s] += sum16(p);
+                    acc[set][s] = zero_acc();
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) lse_v[set][r] = INFINITY;
+            }
+        };
+        // the sums so far are set aside; by pieces, they are those before the set again where one of them has left the float range
+        auto fold = [&]() __attribute__((always_inline)) {
+            bool left = false;
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                glo[s] += part[s][0] + part[s][1];
+                part[s][0] = part[s][1] = 0.f;
+                left |= (glo_in[s] < INFINITY && !(glo[s] < INFINITY)) || (loc_in[s] < INFINITY && !(loc[s] < INFINITY));
+            }
+            if constexpr (kExact) return false;
+            const bool any = __any(left);                               // wave-uniform
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                if (any) { glo[s] = glo_in[s]; loc[s] = loc_in[s]; }
+                else { glo_in[s] = glo[s]; loc_in[s] = loc[s]; }
+            }
+            return any;
+        };
+        int run = 2, until_fold = run;
+        int t = from;
+        do {                                                            // (an item has rows)
+            stage(ic<0>{}, t);
+            if (t + 1 < n_stages) stage(ic<1>{}, t + 1);
+            until_fold -= 2;
+            if (until_fold <= 0 && t + 2 < n_stages) {
+                until_fold = run = min(2 * run, kFoldStagesF32);
+                if (fold()) return from;
+                from = counted ? t + 2 : t + 1;
+            }
+        } while ((t += 2) < n_stages);
+        wait_vmem<0>();
+        auto last = [&](const f32x16_t (&x)[kSub], const f32x16_t& l) __attribute__((always_inline)) {
 #pragma unroll
             for (int s = 0; s < kSub; ++s)
 #pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (row0 + acc_row(r, half) < key_base + s * 32 + col) acc[set][s][r] = -INFINITY;
-        }
-        if (row0 + kStreamRows > win0) {                                // rows of the window: at once, and none left for the next stage
-            const int half = lane_here() >> 5;
-#pragma unroll
-            for (int s = 0; s < kSub; ++s) {
-                float p[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[r] = exp2_fast(__builtin_fmaf(acc[set][s][r], c, -lse_v[set][r]));
-                part[s][0] += sum16(p);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) p[r] = row0 + acc_row(r, half) < win0 ? 0.f : p[r];
-                loc[s] += sum16(p);
-                acc[set][s] = zero_acc();
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) lse_v[set][r] = INFINITY;
-        }
+                for (int r = 0; r < 16; ++r) part[s][r & 1] += exp2_fast(__builtin_fmaf(x[s][r], c, -l[r]));
+        };
+        if ((t - n_stages) & 1) last(acc[0], lse_v[0]);
+        else last(acc[1], lse_v[1]);
+        return fold() ? from : n_stages;
     };
-    const int fold = kFoldRows / kStreamRows * max(G, 2) / 2 * 2;
-    int until_fold = fold;
-    int t = 0;
-    do {                                                                // (an item has rows)
-        stage(ic<0>{}, t);
-        if (t + 1 < n_stages) stage(ic<1>{}, t + 1);
-        until_fold -= 2;
-        if (until_fold == 0) {
-            until_fold = fold;
-#pragma unroll
-            for (int s = 0; s < kSub; ++s) { aside[s] += part[s][0] + part[s][1]; part[s][0] = part[s][1] = 0.f; }
-        }
-    } while ((t += 2) < n_stages);
-    wait_vmem<0>();
-    auto last = [&](const f32x16_t (&x)[kSub], const f32x16_t& l) __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < kSub; ++s)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) part[s][r & 1] += exp2_fast(__builtin_fmaf(x[s][r], c, -l[r]));
-    };
-    if (n_stages & 1) last(acc[0], lse_v[0]);
-    else last(acc[1], lse_v[1]);
-#pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        aside[s] += part[s][0] + part[s][1];
-        plain |= !(aside[s] < INFINITY) || !(loc[s] < INFINITY);
+    int from = 0;
+    {
+        Pieces bk[kSub][E::kSteps];
+        const bool whole = !__any(E::load_stationary(K, key_base, N, lane, bk));
+        wait_vmem_all_visible();
+        if (whole) from = scalar(sweep(std::false_type{}, bk, 0));
     }
-    if (__any(plain)) {                                                 // wave-uniform
-#pragma unroll 1
-        for (int s = 0; s < kSub; ++s) {
-            constexpr int kFrags = E::kFrags;
-            const int lane = lane_here(), col = lane & 31, half = lane >> 5;      // (nothing is kept for this path)
-            const char* k = E::row_bytes(K, key_base + s * 32, N, lane);
-            frag_t bf[kFrags];
-#pragma unroll
-            for (int f = 0; f < kFrags; ++f) bf[f] = *reinterpret_cast<const frag_t*>(k + f * 32);
-            float glo = 0.f, lo = 0.f;
-            for (int g = 0; g < G; ++g)
-                for (int row0 = r_begin; row0 < r_end; row0 += kStreamRows) {
-                    const char* q = E::row_bytes(Q0 + (size_t)g * N * D, row0, N, lane);
-                    frag_t aq[kFrags];
-                    f32x16_t l;
-#pragma unroll
-                    for (int f = 0; f < kFrags; ++f) aq[f] = *reinterpret_cast<const frag_t*>(q + f * 32);
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) l[r] = L0[(size_t)g * a.n_pad + row0 + acc_row(r, half)];
-                    stream_edge_tile<float, D>(aq, bf, l, c, glo, lo, row0, key_base + s * 32 + col, half, win0);
-                }
-            if (s == 0) { aside[0] = glo; loc[0] = lo; }
-            else { aside[1] = glo; loc[1] = lo; }
-        }
+    if (from < n_stages) {
+        frag_t bk[kSub][E::kFrags];
+        E::load_exact(K, key_base, N, lane, bk);
+        wait_vmem_all_visible();
+        sweep(std::true_type{}, bk, from);
     }
     float *out_glo, *out_loc;
     items.outputs(out_glo, out_loc);
 #pragma unroll
     for (int s = 0; s < kSub; ++s) {
-        const float gsum = halves_sum(aside[s]), lsum = halves_sum(loc[s]);       // the half-waves hold disjoint rows of the same keys
+        const float gsum = halves_sum(glo[s]), lsum = halves_sum(loc[s]);         // the half-waves hold disjoint rows of the same keys
         const int kj = key_base + s * 32 + col;
         if (half == 0 && kj < N) {
             out_glo[kj] = gsum;
@@ -391,8 +461,7 @@ template <int D, bool kDeal>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) void score_pass1_f32_kernel(ScoreArgs a)
 {
     using E = F32<D>;
-    constexpr int kSub = kSubF32, kRows = 32 * kSub, kSteps = E::kSteps, kEach = E::kPerStep;
-    constexpr int kFold = kFoldKeys / kStreamRows;
+    constexpr int kSub = kSubF32, kRows = 32 * kSub;
     __shared__ __attribute__((aligned(1024))) char lds_k[2][E::kStageBytes];
 
     const float c = a.scale_log2e;
@@ -407,53 +476,60 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const int col = lane & 31, half = lane >> 5;
     const int q_base = rt * kRows;
 
-    Pieces bq[kSub][kSteps];
-    bool plain = E::load_stationary(Q, q_base, N, lane, bq);
     unsigned dma_off[E::kOffs], frag_off[E::kKeys];
     E::dma_offsets(lane, dma_off);
     E::frag_offsets(lane, frag_off);
     const unsigned lds_k0 = lds_address(&lds_k[0][0]);
-    wait_vmem_all_visible();
-    auto issue = [&](int t) __attribute__((always_inline)) {
-        E::issue(reinterpret_cast<const char*>(K), t * kStreamRows, N, lds_k0 + ((t - t0) & 1) * E::kStageBytes, dma_off);
-    };
 
-    // running maximum, the reference in use (0 while nothing is seen), the sums since the last fold and before it
-    float m_run[kSub], m_use[kSub], l_run[kSub][2], l_old[kSub];
+    float m_run[kSub], l_sum[kSub];                                     // running maximum, the sum relative to it
 #pragma unroll
-    for (int s = 0; s < kSub; ++s) { m_run[s] = -INFINITY; m_use[s] = 0.f; l_run[s][0] = l_run[s][1] = l_old[s] = 0.f; }
-    auto raise = [&](int s, const f32x16_t& x) __attribute__((always_inline)) {
-        const float m_new = fmaxf(m_run[s], max16(x) * c);
-        m_use[s] = m_new == -INFINITY ? 0.f : m_new;
-        const float down = exp2_fast(m_run[s] - m_use[s]);
-        l_run[s][0] *= down; l_run[s][1] *= down; l_old[s] *= down;
-        m_run[s] = m_new;
-    };
-    auto add = [&](int s, int r, const f32x16_t& x) __attribute__((always_inline)) {
-        l_run[s][r & 1] += exp2_fast(__builtin_fmaf(x[r], c, -m_use[s]));
-    };
+    for (int s = 0; s < kSub; ++s) { m_run[s] = -INFINITY; l_sum[s] = 0.f; }
 
-    const int n_stages = t1 - t0;                                       // (none where a part is padding)
-    if (n_stages > 0) {
+    // Stages [from, t1), as in the second pass.
+    auto sweep = [&](auto exact_c, const auto& bq, int from) __attribute__((always_inline)) {
+        constexpr bool kExact = decltype(exact_c)::value;
+        auto issue = [&](int t, int slot) __attribute__((always_inline)) {
+            E::issue(reinterpret_cast<const char*>(K), t * kStreamRows, N, lds_k0 + slot * E::kStageBytes, dma_off);
+        };
+        // the reference in use (0 while nothing is seen), the sums since the last fold; what a set of stages began with
+        float m_use[kSub], l_run[kSub][2], m_in[kSub], l_in[kSub];
         f32x16_t acc[2][kSub];
 #pragma unroll
-        for (int s = 0; s < kSub; ++s)
+        for (int s = 0; s < kSub; ++s) {
+            m_use[s] = 0.f; l_run[s][0] = l_run[s][1] = 0.f; m_in[s] = m_run[s]; l_in[s] = l_sum[s];
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[1][s][r] = -INFINITY;      // before the first stage: nothing seen
+        }
+        auto raise = [&](int s, const f32x16_t& x) __attribute__((always_inline)) {
+            const float m_new = fmaxf(m_run[s], max16(x) * c);
+            m_use[s] = m_new == -INFINITY ? 0.f : m_new;
+            const float down = exp2_fast(m_run[s] - m_use[s]);
+            l_run[s][0] *= down; l_run[s][1] *= down; l_sum[s] *= down;
+            m_run[s] = m_new;
+        };
+        auto add = [&](int s, int r, const f32x16_t& x) __attribute__((always_inline)) {
+            l_run[s][r & 1] += exp2_fast(__builtin_fmaf(x[r], c, -m_use[s]));
+        };
         typename E::Feed feed;
-        issue(t0);
+        frag_t first = zero_frag();
+        wait_lds_all_visible();
+        issue(from, 0);
         wait_vmem<0>();
-        feed.start(lds_k[0], frag_off);
+        if constexpr (kExact) first = E::fetch(lds_k[0], frag_off, 0);
+        else feed.start(lds_k[0], frag_off);
+
         auto stage = [&](auto set_c, int t) __attribute__((always_inline)) {
             constexpr int set = decltype(set_c)::value;
-            wait_lds_all_visible();                                     // (the other slot's last reads)
-            if (t + 1 < t1) issue(t + 1);
-            E::stage(lds_k[set], lds_k[1 - set], frag_off, feed, bq, acc[set], []() __attribute__((always_inline)) { wait_vmem<0>(); },
-                     [&](int f, int i) __attribute__((always_inline)) {
-                         if (f == 0 && i < 2) raise(i, acc[1 - set][i]);
-                         const int e = i - (12 - 2 * kEach);
-                         if (e >= 0) add(e & 1, f * kEach + (e >> 1), acc[1 - set][e & 1]);
-                     });
+            auto next = [&]() __attribute__((always_inline)) { wait_lds_all_visible(); if (t + 1 < t1) issue(t + 1, 1 - set); };     // (the other slot's last reads)
+            auto landed = []() __attribute__((always_inline)) { wait_vmem<0>(); };
+            if constexpr (!kExact) next();
+            auto begin = [&](int s) __attribute__((always_inline)) { raise(s, acc[1 - set][s]); };
+            auto weigh = [&](int e) __attribute__((always_inline)) { add(e & 1, e >> 1, acc[1 - set][e & 1]); };
+            if constexpr (kExact) {
+                E::exact_stage(lds_k[set], lds_k[1 - set], frag_off, first, bq, acc[set], next, landed, begin, weigh);
+            } else {
+                E::stage(lds_k[set], lds_k[1 - set], frag_off, feed, bq, acc[set], landed, begin, weigh);
+            }
 #pragma unroll
             for (int s = 0; s < kSub; ++s) { stays_here(l_run[s][0]); stays_here(l_run[s][1]); }
             if (t * kStreamRows + kStreamRows > q_base) {               // on the diagonal: keys after the row
@@ -465,16 +541,33 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                         if (t * kStreamRows + acc_row(r, half) > q_base + s * 32 + col) acc[set][s][r] = -INFINITY;
             }
         };
-        int until_fold = kFold;
-        int t = t0;
+        auto fold = [&]() __attribute__((always_inline)) {
+            bool left = false;
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                l_sum[s] += l_run[s][0] + l_run[s][1];
+                l_run[s][0] = l_run[s][1] = 0.f;
+                left |= l_in[s] < INFINITY && !(l_sum[s] < INFINITY);
+            }
+            if constexpr (kExact) return false;
+            const bool any = __any(left);                               // wave-uniform
+#pragma unroll
+            for (int s = 0; s < kSub; ++s) {
+                if (any) { m_run[s] = m_in[s]; l_sum[s] = l_in[s]; }
+                else { m_in[s] = m_run[s]; l_in[s] = l_sum[s]; }
+            }
+            return any;
+        };
+        int run = 2, until_fold = run;
+        int t = from;
         do {
             stage(ic<0>{}, t);
             if (t + 1 < t1) stage(ic<1>{}, t + 1);
             until_fold -= 2;
-            if (until_fold == 0) {                                      // a long sum is set aside, so that small weights are not lost against it
-                until_fold = kFold;
-#pragma unroll
-                for (int s = 0; s < kSub; ++s) { l_old[s] += l_run[s][0] + l_run[s][1]; l_run[s][0] = l_run[s][1] = 0.f; }
+            if (until_fold <= 0 && t + 2 < t1) {
+                until_fold = run = min(2 * run, kFoldStagesF32);
+                if (fold()) return from;
+                from = t + 1;
             }
         } while ((t += 2) < t1);
         wait_vmem<0>();
@@ -486,35 +579,23 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
                 for (int r = 0; r < 16; ++r) add(s, r, x[s]);
             }
         };
-        if (n_stages & 1) last(acc[0]);
+        if ((t - t1) & 1) last(acc[0]);
         else last(acc[1]);
-    }
-    float L[kSub];
-#pragma unroll
-    for (int s = 0; s < kSub; ++s) {
-        L[s] = l_old[s] + (l_run[s][0] + l_run[s][1]);
-        plain |= !(L[s] < INFINITY);
-    }
-    if (__any(plain)) {                                                 // wave-uniform
-#pragma unroll 1
-        for (int s = 0; s < kSub; ++s) {
-            constexpr int kFrags = E::kFrags;
-            const int lane = lane_here(), half = lane >> 5;                       // (nothing is kept for this path)
-            const int qs0 = q_base + s * 32;
-            const char* q = E::row_bytes(Q, qs0, N, lane);
-            frag_t bf[kFrags];
-#pragma unroll
-            for (int f = 0; f < kFrags; ++f) bf[f] = *reinterpret_cast<const frag_t*>(q + f * 32);
-            float m = -INFINITY, l = 0.f;
-            for (int key0 = t0 * kStreamRows; key0 < min(t1 * kStreamRows, qs0 + 32); key0 += kStreamRows) {
-                const char* k = E::row_bytes(K, key0, N, lane);
-                frag_t ak[kFrags];
-#pragma unroll
-                for (int f = 0; f < kFrags; ++f) ak[f] = *reinterpret_cast<const frag_t*>(k + f * 32);
-                pass1_tile<float, D>(ak, bf, m, l, c, key0, qs0 + (lane & 31), half);
-            }
-            if (s == 0) { m_run[0] = m; L[0] = l; }
-            else { m_run[1] = m; L[1] = l; }
+        return fold() ? from : t1;
+    };
+    if (t0 < t1) {                                                      // (else: a part that is padding)
+        int from = t0;
+        {
+            Pieces bq[kSub][E::kSteps];
+            const bool whole = !__any(E::load_stationary(Q, q_base, N, lane, bq));
+            wait_vmem_all_visible();
+            if (whole) from = scalar(sweep(std::false_type{}, bq, t0));
+        }
+        if (from < t1) {
+            frag_t bq[kSub][E::kFrags];
+            E::load_exact(Q, q_base, N, lane, bq);
+            wait_vmem_all_visible();
+            sweep(std::true_type{}, bq, from);
         }
     }
 
@@ -522,9 +603,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     float* lse2 = a.lse2 + bh * a.n_pad;
 #pragma unroll
     for (int s = 0; s < kSub; ++s) {
-        const float m_o = __shfl_xor(m_run[s], 32), l_o = __shfl_xor(L[s], 32);
+        const float m_o = __shfl_xor(m_run[s], 32), l_o = __shfl_xor(l_sum[s], 32);
         const float M = fmaxf(m_run[s], m_o), Mu = M == -INFINITY ? 0.f : M;
-        const float sum = L[s] * exp2_fast(m_run[s] - Mu) + l_o * exp2_fast(m_o - Mu);
+        const float sum = l_sum[s] * exp2_fast(m_run[s] - Mu) + l_o * exp2_fast(m_o - Mu);
         const int qi = q_base + s * 32 + col;
         if constexpr (kDeal) {                                          // a part, for lse_combine_kernel
             const size_t at = (bh * (a.p1_waves + items.deal.n_units) + items.place.wave + rt) * kRows + s * 32 + col;

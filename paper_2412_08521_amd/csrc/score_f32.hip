@@ -3,17 +3,22 @@
 // A float32 product costs sixteen times the matrix time of a 16-bit one.  Every operand is therefore
 // written as the exact sum of three bf16 pieces (a float's 24 digits are three times eight),
 // x = h + m + l with |m| <= 2^-9 |x|, |l| <= 2^-18 |x|, and a product as the six products of pieces down to
-// 2^-18: hh, hm, mh, mm, hl, lh (what is left out, ml and lm, is below 2^-26).  Six
-// 32x32x16 instructions of 32 clocks stand where eight 32x32x2 ones of 64 did, and a sum of 128 products is
-// rounded 48 times instead of 64.  Measured (us of the first / second pass by float32 products, now): 8 heads over 2 of 128, 3000 rows
-// 93.5 / 107.1 -> 54.7 / 62.5; 32 over 8, 6000 rows 1234 / 1282 -> 698 / 697, of 64 594 / 604 -> 394 / 394; the whole case of 8 heads
-// 226 -> 141.  Column sums against 64 bits, rms of 16 seeds each: 700 to 5000 rows of 128 0.9-1.7e-7 -> 0.9-1.3e-7 (all rows),
-// 1.2-3.2e-7 -> 1.1-2.7e-7 (window); of 64 0.7-1.3e-7 -> 0.6-1.2e-7, 1.0-2.2e-7 -> 0.8-2.0e-7.
+// 2^-18: hh, hm, mh, mm, hl, lh (what is left out, ml, lm and ll, is below 2^-26 of it); the method is that of Henry, Tang and Heinecke,
+// "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019.  Six
+// 32x32x16 instructions of 32 clocks stand where eight 32x32x2 ones of 64 did.  Those with a lower piece are summed first, over all
+// columns, those of the high pieces last: a sum of 128 products is rounded 8 times at its full size instead of 64 times.
+// Measured (us of the first / second pass by float32 products, now): 8 heads over 2 of 128, 3000 rows
+// 93.5 / 107.1 -> 54.7 / 62.5; 32 over 8, 6000 rows 1242 / 1279 -> 702 / 718, of 64 594 / 604 -> 394 / 394; the whole case of 8 heads
+// 226 -> 141.  Errors against 64 bits, by float32 products / column by column / now: row log-sum-exp, rms, 3000 rows
+// of 128 7.7e-7 / 6.7e-7 / 4.6e-7, of 64 7.0e-7 / 6.1e-7 / 4.6e-7.  Column sums, 2-norm of the error over that of the sums, means of 12 to 48 seeds of 13 shapes of 600 to 6000
+// rows, each below its own figure by float32 products: of 128 0.9-2.1e-7 -> 0.7-1.3e-7 (all rows), 1.2-2.7e-7 -> 0.8-1.4e-7 (window), of 64 0.7-1.6e-7 -> 0.6-0.8e-7,
+// 1.2-2.1e-7 -> 0.8-1.1e-7.  With every column weighted alike, whatever its sum, 0.9-1.8e-7 -> 0.8-1.0e-7 of 128, but of 64 1.0-1.5e-7 -> 1.2-1.4e-7 (window
+// 1.2-2.0e-7 -> 1.4-1.7e-7): the 16-bit matrix instruction's own sums draw the logits towards zero by 4e-9 of their size, which lifts the smallest weights.
 //
 // A wave keeps 64 rows in registers as their pieces (split once per item) and streams the other operand as
 // float32 through its ring of two stages; a stage is split on the way to the matrix pipe, in the vector slots
 // between the products: per 16 columns 12 products (384 clocks), 44 operations of splitting, 12 to 24 of weighing the
-// stage before.  That is what bounds it: 3072 clocks of products and up to 2900 of issue per stage of 32 x 64 x 128.
+// stage before (beside the products of the high pieces, where there is nothing to split, as much of that as fits).  That is what bounds it: 3072 clocks of products and up to 2900 of issue per stage of 32 x 64 x 128.
 //
 // Not every float has three such pieces.  Infinities, NaN and values that round to infinity in bf16 give NaN, which no
 // later step loses; rows with elements of 2^60 and more, or below 2^-100 (whose low piece falls below bf16's range
@@ -183,11 +188,11 @@ struct F32 {
                 for (int e = 0; e < 4; ++e) x[4 * i + e] = v[e];
             }
         }
-        __device__ __forceinline__ void part(int slot)                 // 1/12 of the splitting
+        __device__ __forceinline__ void part(int slot)                 // 1/10 of the splitting
         {
             if (slot < 4) next.h[slot] = split_pair(x[2 * slot], x[2 * slot + 1]);
             else if (slot < 8) next.m[slot - 4] = split_pair(x[2 * slot - 8], x[2 * slot - 7]);
-            else if (slot < 10) {
+            else {
 #pragma unroll
                 for (int w = 2 * slot - 16; w < 2 * slot - 14; ++w) next.l[w] = last_pair(x[2 * w], x[2 * w + 1]);
             }
@@ -199,18 +204,21 @@ struct F32 {
             raw[1][0] = fetch(stage, off, 2); raw[1][1] = fetch(stage, off, 3);
             take(0);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) part(k);
+            for (int k = 0; k < kLow; ++k) part(k);
             now = next;
         }
     };
 
-    // The products of one stage, 32 streamed rows x kSubF32 tiles.  `landed` waits for the next stage (which step kSteps - 2 begins to
-    // read); `begin(s)`: vector work ahead of tile s's; `weigh(e)`: vector work of element e of 2 * 16, in the last slots of the steps.
-    static constexpr int kEach = 32 / kSteps;
+    // The products of one stage, 32 streamed rows x kSubF32 tiles; the two tiles' chains alternate.  Those with a lower piece come first, step by
+    // step, then those of the high pieces, so that only the latter are rounded at the size of the whole sum.  `landed` waits for the next stage
+    // (which step kSteps - 2 begins to read); `begin(s)`: vector work ahead of tile s's; `weigh(e)`: vector work of element e of 2 * 16, in
+    // the slots that the splitting leaves room in.
+    static constexpr int kLow = 10, kEach = 32 / kSteps - 2;           // slots of a step; elements weighed in its last ones, the rest beside the high pieces
     template <class Landed, class Begin, class Weigh>
     static __device__ __forceinline__ void stage(const char* here, const char* after, const unsigned (&off)[kKeys], Feed& q,
                                                  const Pieces (&b)[kSubF32][kSteps], f32x16_t (&acc)[kSubF32], Landed landed, Begin begin, Weigh weigh)
     {
+        frag_t high[kSteps];
 #pragma unroll
         for (int f = 0; f < kSteps; ++f) {
             if (f == kSteps - 2) landed();
@@ -221,19 +229,28 @@ struct F32 {
                 q.raw[f & 1][0] = fetch(from, off, at);
                 q.raw[f & 1][1] = fetch(from, off, at + 1);
             }
+            high[f] = q.now.h;
+            asm volatile("" : "+a"(high[f]));                          // (only the products read it)
 #pragma unroll
-            for (int i = 0; i < 12; ++i) {
-                const int s = i & 1, k = i >> 1;                       // the two tiles' chains alternate; small products first
+            for (int i = 0; i < kLow; ++i) {
+                const int s = i & 1, k = i >> 1;
                 const Pieces& p = b[s][f];
-                const frag_t& x = k == 0 ? q.now.l : k == 1 || k == 5 || k == 4 ? q.now.h : q.now.m;
-                const frag_t& y = k == 1 ? p.l : k == 2 || k == 4 ? p.m : p.h;
+                const frag_t& x = k == 0 ? q.now.l : k == 1 || k == 3 ? high[f] : q.now.m;
+                const frag_t& y = k == 1 ? p.l : k == 2 || k == 3 ? p.m : p.h;
                 mma_piece(acc[s], x, y, f == 0 && k == 0);
                 q.part(i);
                 if (f == 0 && i < kSubF32) begin(i);
-                if (i >= 12 - kEach) weigh(f * kEach + i - (12 - kEach));
+                if (i >= kLow - kEach) weigh(f * kEach + i - (kLow - kEach));
                 __builtin_amdgcn_sched_barrier(0);
             }
             q.now = q.next;
+        }
+        asm volatile("" : "+v"(q.now.h)); asm volatile("" : "+v"(q.now.m)); asm volatile("" : "+v"(q.now.l));       // (as in stays_here)
+#pragma unroll
+        for (int i = 0; i < 2 * kSteps; ++i) {
+            mma<bf16_t>(acc[i & 1], high[i >> 1], b[i & 1][i >> 1].h);
+            weigh(kSteps * kEach + i);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 

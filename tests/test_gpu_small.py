@@ -133,6 +133,31 @@ def test_score_float32_values_that_do_not_split(what, d):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+def test_score_float32_is_as_close_as_float32_products(d):
+    """Row log-sum-exp of heavy-tailed logits against 64 bits, rms over all rows of four seeds.  Bound: what float32 products
+    left is 6.9e-7 (64) and 7.7e-7 (128), of which the two roundings of the result are 3.9e-7 (base 2, then natural, at 8 to 16:
+    2^-20 / sqrt(12) each, the first times ln 2; half of the rows' lie in 16 to 32 in base 2); the six products of pieces in the
+    order of the columns 6.1e-7 and 6.7e-7, those with a lower piece first 4.6e-7 for both."""
+    n = 3000
+    p = B.EmsParams(1, 8, 2, d, n, 32, dtype=B.EMS_F32)
+    causal = torch.ones(n, n, dtype=torch.bool, device="cuda").tril()
+    square = 0.0
+    for seed in range(4):
+        gen = torch.Generator(device="cuda").manual_seed(seed)
+        randn = lambda *s: torch.randn(s, device="cuda", generator=gen)  # noqa: E731
+        u = randn(2, 1, d)
+        u /= u.norm(dim=-1, keepdim=True)
+        heavy = torch.empty((2, n, 1), device="cuda").exponential_(1.0, generator=gen)
+        k = (randn(2, n, d) + 0.25 * d ** 0.5 * heavy * u)[None]
+        q = (randn(2, 4, n, d) + 4.0 * u[:, None]).reshape(1, 8, n, d)
+        lse = B.ems_attention_lse(p, q, k)
+        for h in range(8):
+            logits = (q[0, h].double() @ k[0, h // 4].double().T * d ** -0.5).masked_fill(~causal, -torch.inf)
+            square += float((lse[0, h].double() - torch.logsumexp(logits, -1)).square().mean()) / 32
+    assert square ** 0.5 < 5.3e-7
+
+
+@pytest.mark.parametrize("d", [64, 128])
 def test_score_float32_values_that_do_not_split_in_queues(d):
     """The same where the passes take whole items from queues.  One (batch, kv-head) pair each: keys of 2^70, keys of -inf, a query
     row of NaN (of which only the rows' own weights are lost), a key of NaN.  Against the oracle, for NaN on finite values in their

@@ -183,6 +183,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kCpr = Tile<T, D>::kChunksPerRow;
     constexpr int kStageBytes = kStreamRows * kRowBytes;
     constexpr int kQInstr = kStageBytes / 1024;             // 16-byte DMA instructions per stage
+    static_assert(kQInstr == 4 || kQInstr == 8, "one or two groups of four");
     constexpr int kLoads = kQInstr + 1;                     // + one 4-byte DMA for the rows' log-sum-exp
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
     constexpr int kKeys = 32 * kSub;
@@ -234,18 +235,13 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 #pragma unroll
         for (int f = 0; f < kFrags; ++f) asm volatile("" : "+a"(bk[s][f]));
 
-    // per-lane constants: DMA source offsets inside a stage (kept in registers when a stage is
-    // few instructions; recomputed per stage otherwise, which only the wide-row validation
-    // type needs) and the LDS offsets of this lane's operand fragments
-    constexpr bool kKeepDmaOff = kQInstr <= 8;
-    auto dma_src_off = [&](int j, int ln) __attribute__((always_inline)) {
-        const int slot = j * kWave + ln, row = slot / kCpr;
-        return (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz_key<T, D>(row)) << 4);
-    };
-    unsigned dma_rel[kKeepDmaOff ? kQInstr : 1];            // the same, less the offset the instruction itself adds (1 KiB x its place in a group of four)
-    if (kKeepDmaOff) {
+    // per-lane constants: DMA source offsets inside a stage, less what the instruction itself adds (1 KiB x its place in a
+    // group of four), and the LDS offsets of this lane's operand fragments
+    unsigned dma_rel[kQInstr];
 #pragma unroll
-        for (int j = 0; j < kQInstr; ++j) dma_rel[j] = dma_src_off(j, lane) - (unsigned)(j % 4) * 1024u;
+    for (int j = 0; j < kQInstr; ++j) {
+        const int slot = j * kWave + lane, row = slot / kCpr;
+        dma_rel[j] = (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz_key<T, D>(row)) << 4) - (unsigned)(j % 4) * 1024u;
     }
     unsigned frag_off[kFrags];
 #pragma unroll
@@ -256,29 +252,20 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const unsigned lds_l0 = lds_address(&lds_lse[0][0]);
 
     // DMA of the 32 rows starting at `row` of q-head g of the group into ring slot `slot`
-    auto issue = [&](int g, int row, int slot, auto in_range_c) __attribute__((always_inline)) {
-        constexpr bool kInRange = decltype(in_range_c)::value;   // caller knows row + 32 <= N
+    auto issue = [&](int g, int row, int slot) __attribute__((always_inline)) {
         const char* qg = reinterpret_cast<const char*>(Q0) + (size_t)g * N * kRowBytes;
         const unsigned dst = lds_q0 + slot * kStageBytes;
-        int ln = lane;
-        if (!kKeepDmaOff) ln = opaque_lane(ln);             // keeps the offsets from being hoisted into registers
-        if (kInRange || row + kStreamRows <= N) {
+        if (row + kStreamRows <= N) {
             const char* base = qg + (size_t)row * kRowBytes;
-            if (kKeepDmaOff && kQInstr % 4 == 0) {
 #pragma unroll
-                for (int j = 0; j < kQInstr; j += 4)
-                    dma_to_lds_x4(base, dma_rel[j], dma_rel[j + 1], dma_rel[j + 2], dma_rel[j + 3], dst + j * 1024);
-            } else {
-#pragma unroll
-                for (int j = 0; j < kQInstr; ++j)
-                    dma_to_lds<16>(base, kKeepDmaOff ? dma_rel[j] + (unsigned)(j % 4) * 1024u : dma_src_off(j, ln), dst + j * 1024);
-            }
+            for (int j = 0; j < kQInstr; j += 4)
+                dma_to_lds_x4(base, dma_rel[j], dma_rel[j + 1], dma_rel[j + 2], dma_rel[j + 3], dst + j * 1024);
         } else {                                            // rows past the end re-read the last row
 #pragma unroll
             for (int j = 0; j < kQInstr; ++j) {
                 const int r = (j * kWave + lane) / kCpr;
                 const int over = max(row + r - (N - 1), 0);
-                const unsigned off = kKeepDmaOff ? dma_rel[j] + (unsigned)(j % 4) * 1024u : dma_src_off(j, ln);
+                const unsigned off = dma_rel[j] + (unsigned)(j % 4) * 1024u;
                 dma_to_lds<16>(qg, (unsigned)row * kRowBytes + off - (unsigned)over * kRowBytes, dst + j * 1024);
             }
         }
@@ -352,7 +339,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         };
         int g_next = 0, u_next = 0, u_now = 0;              // next stage to fetch (q-head, place in the head); place of the present one
         auto issue_edge = [&](int slot) __attribute__((always_inline)) {
-            issue(g_next, row_of(u_next), slot, std::false_type{});
+            issue(g_next, row_of(u_next), slot);
             if (++u_next == per_head) { u_next = 0; ++g_next; }
         };
         for (int t = 0; t < kRing - 1 && t < n_stages; ++t) issue_edge(t);
@@ -435,13 +422,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         f32x16_t lse_v[2];
         f32x16_t acc[4];
         // issue cursor of the next stage to fetch: countdowns of the stages it has left in its q-head
-        // and in all.  Where four DMA instructions go under one M0, the position is kept as running
+        // and in all.  Four DMA instructions go under one M0; the position is kept as running
         // addresses (source rows, their log-sum-exp) that advance by a stage, at the last stage of
         // a q-head by the jump to the next head's first interior row, and not at all once the last
         // stage is issued -- masks instead of selects, a dozen scalar instructions per stage.
-        constexpr bool kRunning = kKeepDmaOff && kQInstr % 4 == 0;
         int h_left = per_head, t_left = n_stages;
-        int g_next = 0, row_next = e_end;
         const char* q_src = reinterpret_cast<const char*>(Q0) + (size_t)e_end * kRowBytes;
         const char* l_src = reinterpret_cast<const char*>(L0 + e_end);
         const long long q_jump = ((long long)N - (i_end - e_end) + kStreamRows) * kRowBytes;   // last stage of a head -> next head
@@ -450,22 +435,12 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         const unsigned lds_q0s = __builtin_amdgcn_readfirstlane(lds_q0), lds_l0s = __builtin_amdgcn_readfirstlane(lds_l0);
         auto issue_next = [&](auto slot_c) __attribute__((always_inline)) {
             constexpr int slot = decltype(slot_c)::value;
-            if constexpr (kRunning) {
-                dma_to_lds_x4_at<slot * kStageBytes>(q_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds_q0s);
-                if constexpr (kQInstr > 4)
-                    dma_to_lds_x4_at<slot * kStageBytes + 4096>(q_src, dma_rel[4 % kQInstr], dma_rel[5 % kQInstr],
-                                                                dma_rel[6 % kQInstr], dma_rel[7 % kQInstr], lds_q0s);
-                static_assert(kQInstr <= 8 || !kRunning, "two groups of four per stage at most");
-                dma_dword_to_lds_at<slot * (2 * kStreamRows * 4)>(l_src, lse_lane_off, lds_l0s);
-                advance_cursor<kStageBytes, kStreamRows * 4>(h_left, t_left, q_src, l_src, per_head, q_jump, l_jump);
-            } else {
-                issue(g_next, row_next, slot, std::true_type{});
-                const bool wrap = h_left == 1, more = t_left > 1;
-                h_left = wrap ? per_head : h_left - 1;
-                --t_left;
-                g_next = more && wrap ? g_next + 1 : g_next;
-                row_next = more ? (wrap ? e_end : row_next + kStreamRows) : row_next;
-            }
+            dma_to_lds_x4_at<slot * kStageBytes>(q_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds_q0s);
+            if constexpr (kQInstr > 4)
+                dma_to_lds_x4_at<slot * kStageBytes + 4096>(q_src, dma_rel[4 % kQInstr], dma_rel[5 % kQInstr],
+                                                            dma_rel[6 % kQInstr], dma_rel[7 % kQInstr], lds_q0s);
+            dma_dword_to_lds_at<slot * (2 * kStreamRows * 4)>(l_src, lse_lane_off, lds_l0s);
+            advance_cursor<kStageBytes, kStreamRows * 4>(h_left, t_left, q_src, l_src, per_head, q_jump, l_jump);
         };
 
         issue_next(ic<0>{});
@@ -603,6 +578,7 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     constexpr int kCpr = Tile<T, D>::kChunksPerRow;
     constexpr int kStageBytes = kStreamRows * kRowBytes;
     constexpr int kLoads = kStageBytes / 1024;              // 16-byte DMA instructions per stage
+    static_assert(kLoads == 4 || kLoads == 8, "one or two groups of four");
     static_assert((kRing - 1) * kLoads < 64, "vmcnt is a 6-bit counter");
     constexpr int kRows = 32 * kSub;                        // query rows per wave
     // stages per trip of the interior loop (operand register sets and ring slots back at their start)
@@ -641,15 +617,11 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
 #pragma unroll
         for (int f = 0; f < kFrags; ++f) asm volatile("" : "+a"(bq[s][f]));
 
-    constexpr bool kKeepDmaOff = kLoads <= 8;
-    auto dma_src_off = [&](int j, int ln) __attribute__((always_inline)) {
-        const int slot = j * kWave + ln, row = slot / kCpr;
-        return (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz_key<T, D>(row)) << 4);
-    };
-    unsigned dma_rel[kKeepDmaOff ? kLoads : 1];             // less the offset the instruction itself adds (1 KiB x its place in a group of four)
-    if (kKeepDmaOff) {
+    unsigned dma_rel[kLoads];                               // source offsets inside a stage, as in the second pass
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) dma_rel[j] = dma_src_off(j, lane) - (unsigned)(j % 4) * 1024u;
+    for (int j = 0; j < kLoads; ++j) {
+        const int slot = j * kWave + lane, row = slot / kCpr;
+        dma_rel[j] = (unsigned)row * kRowBytes + (unsigned)(((slot % kCpr) ^ swz_key<T, D>(row)) << 4) - (unsigned)(j % 4) * 1024u;
     }
     unsigned frag_off[kFrags];
 #pragma unroll
@@ -658,29 +630,20 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     const unsigned lds_k0 = lds_address(&lds_k[0][0]);
 
     // DMA of key stage t (keys 32 t ..) into ring slot `slot`
-    auto issue = [&](int t, int slot, auto in_range_c) __attribute__((always_inline)) {
-        constexpr bool kInRange = decltype(in_range_c)::value;   // caller knows 32 t + 32 <= N
+    auto issue = [&](int t, int slot) __attribute__((always_inline)) {
         const int row = t * kStreamRows;
         const unsigned dst = lds_k0 + slot * kStageBytes;
-        int ln = lane;
-        if (!kKeepDmaOff) ln = opaque_lane(ln);
-        if (kInRange || row + kStreamRows <= N) {
+        if (row + kStreamRows <= N) {
             const char* base = reinterpret_cast<const char*>(K) + (size_t)row * kRowBytes;
-            if (kKeepDmaOff && kLoads % 4 == 0) {
 #pragma unroll
-                for (int j = 0; j < kLoads; j += 4)
-                    dma_to_lds_x4(base, dma_rel[j], dma_rel[j + 1], dma_rel[j + 2], dma_rel[j + 3], dst + j * 1024);
-            } else {
-#pragma unroll
-                for (int j = 0; j < kLoads; ++j)
-                    dma_to_lds<16>(base, kKeepDmaOff ? dma_rel[j] + (unsigned)(j % 4) * 1024u : dma_src_off(j, ln), dst + j * 1024);
-            }
+            for (int j = 0; j < kLoads; j += 4)
+                dma_to_lds_x4(base, dma_rel[j], dma_rel[j + 1], dma_rel[j + 2], dma_rel[j + 3], dst + j * 1024);
         } else {                                            // keys past the end re-read the last key (always masked)
 #pragma unroll
             for (int j = 0; j < kLoads; ++j) {
                 const int r = (j * kWave + lane) / kCpr;
                 const int over = max(row + r - (N - 1), 0);
-                const unsigned off = kKeepDmaOff ? dma_rel[j] + (unsigned)(j % 4) * 1024u : dma_src_off(j, ln);
+                const unsigned off = dma_rel[j] + (unsigned)(j % 4) * 1024u;
                 dma_to_lds<16>(K, (unsigned)row * kRowBytes + off - (unsigned)over * kRowBytes, dst + j * 1024);
             }
         }
@@ -713,9 +676,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     // Textbook online softmax over the stages [first, end), one tile at a time.
     auto online_phase = [&](int first, int end) __attribute__((always_inline)) {
         const int n_stages = end - first;
-        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(first + u, u % kRing, std::false_type{});
+        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(first + u, u % kRing);
         for (int u = 0; u < n_stages; ++u) {
-            if (u + kRing - 1 < n_stages) issue(first + u + kRing - 1, (u + kRing - 1) % kRing, std::false_type{});
+            if (u + kRing - 1 < n_stages) issue(first + u + kRing - 1, (u + kRing - 1) % kRing);
             wait_landed(u, min(n_stages - 1, u + kRing - 1));
             frag_t ak[kFrags];
             fetch_keys(u % kRing, ak);
@@ -767,9 +730,9 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
     {
         const int n_stages = n_lead + n_edge;
         auto stage_of = [&](int u) __attribute__((always_inline)) { return u < n_lead ? t0 + u : t_diag + (u - n_lead); };
-        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(stage_of(u), u % kRing, std::false_type{});
+        for (int u = 0; u < kRing - 1 && u < n_stages; ++u) issue(stage_of(u), u % kRing);
         for (int u = 0; u < n_stages; ++u) {
-            if (u + kRing - 1 < n_stages) issue(stage_of(u + kRing - 1), (u + kRing - 1) % kRing, std::false_type{});
+            if (u + kRing - 1 < n_stages) issue(stage_of(u + kRing - 1), (u + kRing - 1) % kRing);
             wait_landed(u, min(n_stages - 1, u + kRing - 1));
             frag_t ak[kFrags];
             fetch_keys(u % kRing, ak);
@@ -816,25 +779,17 @@ __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 1))) v
         frag_t ak[2][kFrags];
         f32x16_t acc[4];
 
-        // issue cursor: where four DMA instructions go under one M0, a running source address
-        // that advances by a stage until the last stage is issued and then stays
-        constexpr bool kRunning = kKeepDmaOff && kLoads % 4 == 0;
-        int u_next = 0, t_left = n_int;
+        // issue cursor: a running source address that advances by a stage until the last stage is issued and then stays
+        int t_left = n_int;
         const char* k_src = reinterpret_cast<const char*>(K) + (size_t)ti0 * kStageBytes;
         const unsigned lds_k0s = __builtin_amdgcn_readfirstlane(lds_k0);
         auto issue_next = [&](auto slot_c) __attribute__((always_inline)) {   // past the end: the last stage again, unread
             constexpr int slot = decltype(slot_c)::value;
-            if constexpr (kRunning) {
-                dma_to_lds_x4_at<slot * kStageBytes>(k_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds_k0s);
-                if constexpr (kLoads > 4)
-                    dma_to_lds_x4_at<slot * kStageBytes + 4096>(k_src, dma_rel[4 % kLoads], dma_rel[5 % kLoads],
-                                                                dma_rel[6 % kLoads], dma_rel[7 % kLoads], lds_k0s);
-                static_assert(kLoads <= 8 || !kRunning, "two groups of four per stage at most");
-                advance_cursor<kStageBytes>(t_left, k_src);
-            } else {
-                issue(ti0 + min(u_next, n_int - 1), slot, std::true_type{});
-                ++u_next;
-            }
+            dma_to_lds_x4_at<slot * kStageBytes>(k_src, dma_rel[0], dma_rel[1], dma_rel[2], dma_rel[3], lds_k0s);
+            if constexpr (kLoads > 4)
+                dma_to_lds_x4_at<slot * kStageBytes + 4096>(k_src, dma_rel[4 % kLoads], dma_rel[5 % kLoads],
+                                                            dma_rel[6 % kLoads], dma_rel[7 % kLoads], lds_k0s);
+            advance_cursor<kStageBytes>(t_left, k_src);
         };
         issue_next(ic<0>{});
         issue_next(ic<1>{});

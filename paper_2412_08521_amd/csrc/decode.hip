@@ -191,7 +191,7 @@ __global__ __launch_bounds__(256) void decode_init_kernel(DecodeInitArgs a)
 }
 
 // ------------------------------------------------------------------------------------
-// One block per (batch, kv-head) runs the whole step (kPart = 0, 256 threads: the step is a chain of short
+// One block per (batch, kv-head) runs the whole step (kPart = 0, 256 threads, or 512 for longer tables: the step is a chain of short
 // dependent phases, and every instruction a wave spends on a block-wide bookkeeping step is paid once
 // per wave) while the cache is small.
 //
@@ -1169,6 +1169,7 @@ hipError_t launch_decode_init(const DecodeInitArgs& a, bool f32, hipStream_t st)
 // (The same with four launches, the scores by the table's slices, the cosines' and the commit's chains not yet shortened:
 // 21.1, 23.4, 27.7, 21.4; 24.1, 22.7, 28.0, 25.9.)
 constexpr long long kChooseScores = 3000000;
+static bool choose_in_one(int heads, int n_imp, int group, int blocks) { return (long long)blocks * heads * n_imp * (group + 1) <= kChooseScores; }
 // Threads of the one-launch step: a block of 512 has half the rows and table elements a wave, but pays the rest of the step twice as often.
 // (us a step, 256 / 512 threads, head size 128, 4 q-heads, merge ratio 0.5 unless stated: 32 heads of budget 128 9.4 / 10.0, one of 200 at ratio 2
 // 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Head size 64 and 8 q-heads, whose
@@ -1183,7 +1184,7 @@ static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
         hipLaunchKernelGGL((decode_logits_kernel<D, G>), dim3(a.n_tok_slices, a.bkv), dim3(256), 0, st, a);
     else if constexpr (kWhich == 7) {
         const dim3 toks(a.n_tok_slices, a.bkv), rows(a.n_slices, a.bkv), most(max(a.n_tok_slices, a.n_slices), a.bkv);
-        if ((long long)most.x * a.bkv * a.n_imp * (G + 1) <= kChooseScores)
+        if (choose_in_one(a.bkv, a.n_imp, G, most.x))
             hipLaunchKernelGGL((decode_choose_kernel<D, G, 512, kChoose>), most, dim3(512), 0, st, a);
         else {
             hipLaunchKernelGGL((decode_choose_kernel<D, G, 256, kWeights>), toks, dim3(256), 0, st, a);
@@ -1213,7 +1214,7 @@ static hipError_t launch_decode_part(const DecodeStepArgs& a, hipStream_t st)
     return hipGetLastError();
 }
 
-// Whether the step runs as four launches, and how the rows and (up to kTableHeads heads) the token table are cut.
+// Whether the step runs as several launches, and how the rows and (up to kTableHeads heads) the token table are cut.
 // f32 rows need twice the operand registers: the validation mode always takes the one-block kernel.
 constexpr int kTableHeads = 32;        // figures at the step kernel
 bool decode_split(int heads, int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s)
@@ -1233,6 +1234,13 @@ bool decode_split(int heads, int budget, int n_imp, int n_tbm, int window, bool 
         cut(budget + 1, &s->rows, &s->n_rows);               // the new key's row included
     }
     return true;
+}
+
+int decode_launches(int heads, int group, int budget, int n_imp, int n_tbm, int window, bool f32)
+{
+    DecodeSlices s;
+    if (!decode_split(heads, budget, n_imp, n_tbm, window, f32, &s)) return 1;
+    return s.toks > 0 && choose_in_one(heads, n_imp, group, std::max(s.n_toks, s.n_rows)) ? 3 : 4;
 }
 
 template <typename T, int D>

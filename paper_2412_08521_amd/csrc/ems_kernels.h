@@ -166,6 +166,7 @@ int score_keys_per_block(int dtype_is_f32);
 // the pass takes whole items), and the floats of one partial-result array.
 struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len, p1_by_block; size_t p1_floats, p2_floats; };
 ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32);
+bool score_by_16x16x32(int batch, int q_heads, int kv_heads, int seq_len, int head_dim);       // which products a 16-bit launch takes
 int select_chunks(int seq_len);     // blocks per head of the long-sequence select
 int select_coarse_bins();
 hipError_t launch_sparsity(const StatsArgs& a, hipStream_t st);
@@ -176,6 +177,7 @@ constexpr int kDecodeMaxSlices = 32;     // slices per head of the sliced decode
 constexpr int kDecodeHandFloats = 1024;  // floats of its per-head hand-over record
 struct DecodeSlices { int rows, n_rows, toks, n_toks; };   // rows and table elements per slice, slices; toks = 0: the table is not cut
 bool decode_split(int heads, int budget, int n_imp, int n_tbm, int window, bool f32, DecodeSlices* s);
+int decode_launches(int heads, int group, int budget, int n_imp, int n_tbm, int window, bool f32);       // of a step whose number comes with the call
 hipError_t launch_expand(const ExpandArgs& a, bool f32, hipStream_t st);
 hipError_t launch_score_pass1(ScoreArgs& a, bool f32, hipStream_t st);   // rows' log-sum-exp; sets a.queue_clear
 hipError_t launch_score_pass2(const ScoreArgs& a, bool f32, hipStream_t st);   // column sums

@@ -1016,12 +1016,13 @@ ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*he
 constexpr double kM16Stages = 16., kM16Most = 1024.;
 constexpr int kM16Rows = 3200;
 static_assert(kM16Most * 1.1 < kDealStages, "a second pass by 16x16x32 products is an even deal (its stages are padded by 3 in 100 at most)");
-static bool m16_launch(const ScoreArgs& a)
+bool score_by_16x16x32(int batch, int q_heads, int kv_heads, int seq_len, int head_dim)
 {
-    const DealPass1<kSub> d(a.seq_len);
-    const double stages = 0.5 * a.batch * a.q_heads * d.n_stages * d.n_units / kResident;
-    return a.head_dim == 128 && a.batch * a.kv_heads >= kXcds && a.seq_len >= kM16Rows && stages >= kM16Stages && stages <= kM16Most;
+    const DealPass1<kSub> d(seq_len);
+    const double stages = 0.5 * batch * q_heads * d.n_stages * d.n_units / kResident;
+    return head_dim == 128 && batch * kv_heads >= kXcds && seq_len >= kM16Rows && stages >= kM16Stages && stages <= kM16Most;
 }
+static bool m16_launch(const ScoreArgs& a) { return score_by_16x16x32(a.batch, a.q_heads, a.kv_heads, a.seq_len, a.head_dim); }
 
 template <bool kF32, bool kDeal>
 static void start_pass1(const ScoreArgs& a, unsigned grid, hipStream_t st)

@@ -43,6 +43,23 @@ def score_forms(p: B.EmsParams):
     return first, "deal" if d.p2_waves else "queue" if p.batch * p.kv_heads % 8 == 0 else "block"
 
 
+def score_products(p: B.EmsParams):
+    """Which matrix products the score passes of `p` take: "16x16x32", "32x32x16" or "pieces" (float32)."""
+    if p.dtype == B.EMS_F32:
+        return "pieces"
+    f = getattr(B.lib(), "_ZN3ems17score_by_16x16x32Eiiiii")
+    f.restype, f.argtypes = C.c_bool, [C.c_int] * 5
+    return "16x16x32" if f(p.batch, p.q_heads, p.kv_heads, p.seq_len, p.head_dim) else "32x32x16"
+
+
+def decode_launches(p: B.EmsParams):
+    """Launches of a decode step of `p` (one block per head, or several over slices), as the host side decides it."""
+    f = getattr(B.lib(), "_ZN3ems15decode_launchesEiiiiiib")
+    f.restype, f.argtypes = C.c_int, [C.c_int] * 6 + [C.c_bool]
+    n_imp, n_tbm = B.ems_partition_sizes(p)
+    return f(p.batch * p.kv_heads, p.q_heads // p.kv_heads, p.budget, n_imp, n_tbm, p.window, p.dtype == B.EMS_F32)
+
+
 def rel_err(got, ref, floor_frac=1e-3):
     """max |got - ref| / max(|ref|, floor), floor = floor_frac * mean|ref| (per call)."""
     got = np.asarray(got, np.float64)

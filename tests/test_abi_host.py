@@ -266,3 +266,35 @@ def test_score_passes_are_dealt_by_rule(lib, shape, forms):
     from gpu_util import score_forms
     f32, b, hq, hkv, d, n = shape
     assert score_forms(B.EmsParams(b, hq, hkv, d, n, 16, dtype=B.EMS_F32 if f32 else B.EMS_BF16)) == forms
+
+
+# (batch, q_heads, kv_heads, head_dim, seq_len): either side of every line of the rule for the 16-bit products
+@pytest.mark.parametrize("shape,products", [
+    ((1, 32, 8, 128, 3200), "16x16x32"),
+    ((1, 32, 8, 128, 3199), "32x32x16"),                      # too many masked stages
+    ((1, 8, 8, 128, 5500), "32x32x16"),                       # 14.8 stages per resident wave
+    ((1, 8, 8, 128, 5800), "16x16x32"),                       # 16.3
+    ((1, 64, 8, 128, 16384), "16x16x32"),                     # 1024
+    ((1, 65, 13, 128, 16384), "32x32x16"),
+    ((1, 28, 7, 128, 8192), "32x32x16"),                      # fewer pairs than XCDs
+    ((1, 32, 8, 64, 8192), "32x32x16"),
+])
+def test_score_products_are_chosen_by_rule(lib, shape, products):
+    from gpu_util import score_products
+    b, hq, hkv, d, n = shape
+    assert score_products(B.EmsParams(b, hq, hkv, d, n, 16)) == products
+
+
+# (batch, q_heads, kv_heads, head_dim, seq_len, window, budget, merge_ratio): small caches, table slices with the choice in one launch
+# and in two, row slices
+@pytest.mark.parametrize("shape,launches", [
+    ((4, 32, 8, 128, 4096, 64, 128, 0.5), 1),
+    ((1, 32, 8, 128, 16384, 64, 2048, 0.5), 3),
+    ((1, 32, 8, 128, 16384, 64, 2900, 0.5), 3),               # 23 slices of centres, 17 of the table (256): 2.6 million scores
+    ((1, 32, 8, 128, 16384, 64, 4096, 0.5), 4),               # 32 slices of centres: 5.2 million
+    ((5, 32, 8, 128, 16384, 64, 2048, 0.5), 4),               # 40 heads
+])
+def test_decode_steps_are_cut_by_rule(lib, shape, launches):
+    from gpu_util import decode_launches
+    b, hq, hkv, d, n, w, nb, r = shape
+    assert decode_launches(B.EmsParams(b, hq, hkv, d, n, w, nb, merge_ratio=r)) == launches

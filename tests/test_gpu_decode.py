@@ -8,7 +8,7 @@ import pytest
 import torch
 
 import ems_inputs
-from gpu_util import dev_tensor, ref_params
+from gpu_util import decode_launches, dev_tensor, ref_params
 from oracle import ems_decode_ref as dec
 from oracle import ems_ref
 from paper_2412_08521_amd import binding as B
@@ -220,18 +220,21 @@ def test_decode_steps_of_long_tables_match_oracle(shape, tau):
 
 
 # head counts and centre lists on both sides of the sizes where the least important centre is chosen in a launch of its own
-# (blocks x centres x (q-heads + 1) over 3 million), last slices of a few rows; units: a first, a middle and the last head.
+# (four launches: blocks x centres x (q-heads + 1) over 3 million), last slices of a few rows; units: a first, a middle and the last head.
 # Bounds as in the tests above; all steps of a unit count for the flips.
-@pytest.mark.parametrize("shape", [
-    (2, 32, 4, 64, 3000, 8, 1290, 0.5),      # 8 heads of 8, 1282 centres: 16 slices of the table, the last of 15: 1.5 million
-    (4, 64, 8, 64, 3000, 8, 1033, 0.5),      # 32 heads of 8, 1025 centres, one of them in the last slice: 3.8 million
-    (1, 16, 16, 128, 9000, 8, 4200, 1.0),    # 16 heads of 1, 4192 centres in slices of 256: 4.4 million
-    (2, 32, 16, 128, 3000, 8, 1410, 1.0),    # 32 heads of 2, 1402 centres: 3.1 million
+@pytest.mark.parametrize("shape,launches", [
+    ((2, 32, 4, 64, 3000, 8, 1290, 0.5), 3),      # 8 heads of 8, 1282 centres: 16 slices of the table, the last of 15: 1.5 million
+    ((4, 64, 8, 64, 3000, 8, 1033, 0.5), 4),      # 32 heads of 8, 1025 centres, one of them in the last slice: 3.8 million
+    ((1, 16, 16, 128, 9000, 8, 4200, 1.0), 3),    # 16 heads of 1, 17 slices of the table (512) and of 4192 centres (256): 2.3 million
+    ((1, 64, 16, 128, 9000, 8, 4200, 1.0), 4),    # the same of 4: 5.7 million
+    ((1, 32, 32, 64, 9000, 8, 4200, 1.0), 4),     # 32 heads of 1: 4.6 million
+    ((2, 32, 16, 128, 3000, 8, 1410, 1.0), 4),    # 32 heads of 2, 1402 centres: 3.1 million
 ])
-def test_decode_steps_choose_in_one_launch_or_two(shape):
+def test_decode_steps_choose_in_one_launch_or_two(shape, launches):
     _log("decode_step", shape)
     tau = 0.3
     p, merged, tbm, s_glo, s_loc, st = _prefill(shape, B.EMS_BF16, tau, seed=shape[6])
+    assert decode_launches(p) == launches
     n_imp, n_tbm = B.ems_partition_sizes(p)
     rng = np.random.default_rng(29)
     n_merge = n_flip = 0

@@ -8,7 +8,7 @@ import ems_inputs
 from oracle import ems_ref
 from paper_2412_08521_amd import binding as B
 from gpu_util import (RTOL, RTOL_MERGE, assert_dest_valid, assert_rel, check_band, dev_tensor, is_sorted_unique,
-                      ref_params, score_forms)
+                      ref_params, score_forms, score_products)
 
 pytestmark = pytest.mark.gpu
 
@@ -97,7 +97,7 @@ def test_score_even_deal(shape, mode):
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n", [600, 1300, 1400, 1470, 1500, 1660, 1750, 1850])
 def test_score_short_float32_stretches(n, d):
-    """Stretches of four to eight stages (8 heads over 2), the shortest of them without the pipelined loop."""
+    """Stretches of four to eight stages (8 heads over 2): either number of the ring's two slots, the first looks at the sums."""
     test_score_even_deal((1, 8, 2, d, n, 40), B.EMS_F32)
 
 
@@ -157,6 +157,26 @@ def test_score_float32_is_as_close_as_float32_products(d):
     assert square ** 0.5 < 5.3e-7
 
 
+def _check_reached(glo, loc, lse, o_glo, o_loc, o_lse, nan_row, nan_is_key, no_weight):
+    """One kv-head's scores and row log-sum-exp against the oracle's on finite values, apart from what a NaN reaches: of query row
+    `nan_row` (second q-head, which is before the window) its own log-sum-exp and the columns up to it, of key `nan_row` every later
+    row and through them every column.  Columns `no_weight` are keys of -inf."""
+    rows, cols, local = np.ones(lse.shape, bool), np.ones(len(glo), bool), np.ones(len(glo), bool)
+    if nan_row is not None and nan_is_key:
+        rows[:, nan_row:] = cols[:] = local[:] = False
+    elif nan_row is not None:
+        rows[1, nan_row] = cols[:nan_row + 1] = False
+    # (a row of nothing but NaN logits has no maximum: where its parts are combined, its log-sum-exp is that of no parts)
+    assert not np.isfinite(lse[~rows]).any() and np.isnan(glo[~cols]).all() and np.isnan(loc[~local]).all()
+    np.testing.assert_allclose(lse[rows], o_lse[rows], rtol=0, atol=2e-5)
+    if no_weight is not None:
+        assert (glo[no_weight] == 0).all() and (loc[no_weight] == 0).all()
+        cols[no_weight] = local[no_weight] = False
+    for got, ref, at, what in ((glo, o_glo, cols, "s_glo"), (loc, o_loc, local, "s_loc")):
+        if at.any():
+            assert_rel(got[at], ref[at], RTOL[B.EMS_F32], what)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_score_float32_values_that_do_not_split_in_queues(d):
     """The same where the passes take whole items from queues.  One (batch, kv-head) pair each: keys of 2^70, keys of -inf, a query
@@ -177,25 +197,10 @@ def test_score_float32_values_that_do_not_split_in_queues(d):
     q[0, g * nan_q + 1, row, 7] = torch.nan
     k[0, nan_k, row, 7] = torch.nan
     s_glo, s_loc, lse = (x.cpu().numpy() for x in B.ems_global_local_score(p, q, k, want_lse=True))
-    bar = RTOL[B.EMS_F32]
     for h, (qh, kh) in kept.items():
         o_glo, o_loc, o_lse = ems_ref.score(ems_ref.RefParams(1, g, 1, d, n, w), qh, kh, want_lse=True)
-        glo, loc, l = s_glo[0, h], s_loc[0, h], lse[0, g * h:g * h + g]
-        if h == nan_k:                                    # every row from the key on, and through them every column
-            assert np.isnan(l[:, row:]).all() and np.isnan(glo).all() and np.isnan(loc).all()
-            np.testing.assert_allclose(l[:, :row], o_lse[0, :, :row], rtol=0, atol=2e-5)
-            continue
-        rows, cols = np.ones((g, n), bool), np.ones(n, bool)
-        if h == nan_q:
-            rows[1, row] = False
-            cols[:row + 1] = False
-        if h == inf:
-            cols[100:2000:97] = False
-            assert (glo[~cols] == 0).all() and (loc[~cols] == 0).all()
-        assert h != nan_q or (np.isnan(l[~rows]).all() and np.isnan(glo[~cols]).all())
-        np.testing.assert_allclose(l[rows], o_lse[0][rows], rtol=0, atol=2e-5)
-        assert_rel(glo[cols], o_glo[0, 0][cols], bar, "s_glo")
-        assert_rel(loc if h == nan_q else loc[cols], o_loc[0, 0] if h == nan_q else o_loc[0, 0][cols], bar, "s_loc")
+        _check_reached(s_glo[0, h], s_loc[0, h], lse[0, g * h:g * h + g], o_glo[0, 0], o_loc[0, 0], o_lse[0],
+                       row if h in (nan_q, nan_k) else None, h == nan_k, slice(100, 2000, 97) if h == inf else None)
 
 
 def test_score_float32_values_that_do_not_split_cost_float32_products():
@@ -225,9 +230,10 @@ def test_score_float32_values_that_do_not_split_cost_float32_products():
 
 
 @pytest.mark.parametrize("mode,shape,forms", [
+    (B.EMS_BF16, (1, 32, 16, 128, 8177, 90), ("deal", "deal")),      # 132 stages a stretch: every set-aside of both passes
     (B.EMS_BF16, (1, 256, 8, 64, 2040, 100), ("block", "deal")),     # two row tiles per wave, one pair per XCD
     (B.EMS_BF16, (1, 64, 2, 128, 8177, 90), ("block", "deal")),      # the q-heads of a row tile together
-    (B.EMS_BF16, (1, 64, 8, 128, 8177, 90), ("block", "deal")),      # these two by 16x16x32 products
+    (B.EMS_BF16, (1, 64, 8, 128, 8177, 90), ("block", "deal")),
     (B.EMS_BF16, (1, 80, 8, 128, 8177, 33), ("queue", "deal")),
     (B.EMS_BF16, (1, 320, 8, 128, 2040, 100), ("queue", "deal")),
     (B.EMS_BF16, (1, 500, 5, 64, 1270, 33), ("queue", "deal")),
@@ -248,6 +254,8 @@ def test_score_whole_items(mode, shape, forms):
     _log("whole items", mode, shape)
     p = B.EmsParams(b, hq, hkv, d, n, w, dtype=mode)
     assert score_forms(p) == forms
+    by_smaller = mode == B.EMS_BF16 and n == 8177 and hkv >= 8       # (of the listed ones)
+    assert score_products(p) == ("pieces" if mode == B.EMS_F32 else "16x16x32" if by_smaller else "32x32x16")
     gen = torch.Generator(device="cuda").manual_seed(n + hq)
     k = torch.randn((b, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16).to(p.torch_dtype)
     q = torch.empty((b, hq, n, d), dtype=p.torch_dtype, device="cuda")
@@ -273,6 +281,7 @@ def test_score_by_the_smaller_products(group, n, far):
     hkv, d, w = 36 // group, 128, 40
     _log("smaller products", group, n, far)
     p = B.EmsParams(1, 36, hkv, d, n, w)
+    assert score_products(p) == "16x16x32"
     gen = torch.Generator(device="cuda").manual_seed(n)
     k = torch.randn((1, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
     q = torch.randn((1, 36, n, d), device="cuda", generator=gen).to(torch.bfloat16)
@@ -286,6 +295,31 @@ def test_score_by_the_smaller_products(group, n, far):
         assert_rel(s_glo[0, h].cpu().numpy(), o[0][0, 0], rtol, "s_glo")
         assert_rel(s_loc[0, h].cpu().numpy(), o[1][0, 0], rtol, "s_loc")
         np.testing.assert_allclose(lse[0, h * group:(h + 1) * group].cpu().numpy(), o[2][0], rtol=2e-6, atol=1e-4 if far else 2e-5)
+
+
+@pytest.mark.parametrize("d,n,products", [(128, 3233, "16x16x32"), (128, 3100, "32x32x16"), (64, 3233, "32x32x16")])
+def test_score_infinite_and_nan_values(d, n, products):
+    """16-bit calls, one (batch, kv-head) pair each: keys of -inf where every query is positive (logits of -inf: no weight), a query
+    row of NaN (only its own weights are lost), a key of NaN (every later row's).  Against the oracle, for NaN on finite values in
+    their place, what they reach apart.  Tolerance: the float32 mode's bar, the products of bf16 inputs are exact."""
+    hkv, g, w, row = 12, 3, 40, 1777
+    p = B.EmsParams(1, g * hkv, hkv, d, n, w)
+    assert score_products(p) == products
+    _log("infinite and NaN", d, n)
+    gen = torch.Generator(device="cuda").manual_seed(n + d)
+    k = torch.randn((1, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    q = torch.randn((1, g * hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    plain, inf, nan_q, nan_k = 0, 4, 7, 11
+    q[0, g * inf:g * inf + g, :, 3] = q[0, g * inf:g * inf + g, :, 3].abs() + 0.125
+    k[0, inf, 100:2000:97, 3] = -torch.inf
+    kept = {h: (q[:, g * h:g * h + g].float().cpu().numpy(), k[:, h:h + 1].float().cpu().numpy()) for h in (plain, inf, nan_q, nan_k)}
+    q[0, g * nan_q + 1, row, 7] = torch.nan
+    k[0, nan_k, row, 7] = torch.nan
+    s_glo, s_loc, lse = (x.cpu().numpy() for x in B.ems_global_local_score(p, q, k, want_lse=True))
+    for h, (qh, kh) in kept.items():
+        o_glo, o_loc, o_lse = ems_ref.score(ems_ref.RefParams(1, g, 1, d, n, w), qh, kh, want_lse=True)
+        _check_reached(s_glo[0, h], s_loc[0, h], lse[0, g * h:g * h + g], o_glo[0, 0], o_loc[0, 0], o_lse[0],
+                       row if h in (nan_q, nan_k) else None, h == nan_k, slice(100, 2000, 97) if h == inf else None)
 
 
 @pytest.mark.parametrize("mode", MODES)

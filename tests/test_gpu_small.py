@@ -254,8 +254,8 @@ def test_score_whole_items(mode, shape, forms):
     _log("whole items", mode, shape)
     p = B.EmsParams(b, hq, hkv, d, n, w, dtype=mode)
     assert score_forms(p) == forms
-    by_smaller = mode == B.EMS_BF16 and n == 8177 and hkv >= 8       # (of the listed ones)
-    assert score_products(p) == ("pieces" if mode == B.EMS_F32 else "16x16x32" if by_smaller else "32x32x16")
+    if mode == B.EMS_BF16:
+        assert score_products(p) == ((16, 16) if n == 8177 and hkv >= 8 else (32, 32))       # (of the listed ones)
     gen = torch.Generator(device="cuda").manual_seed(n + hq)
     k = torch.randn((b, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16).to(p.torch_dtype)
     q = torch.empty((b, hq, n, d), dtype=p.torch_dtype, device="cuda")
@@ -275,44 +275,44 @@ def test_score_whole_items(mode, shape, forms):
 @pytest.mark.parametrize("far", [False, True])
 @pytest.mark.parametrize("group,n", [(3, 3232), (3, 3264), (3, 3296), (3, 3328), (3, 3233), (1, 3360), (4, 3231), (4, 3200)])
 def test_score_by_the_smaller_products(group, n, far):
-    """Launches of 16 to 1024 stages of 32 x 256 per resident wave, 3200 rows and more, at head size 128, which run by 16x16x32
-    products: every remainder of the trips, ragged ends.  far: later logits exceed the first stage's by more than the float range, so that parts are
+    """Launches of 80 to 1024 stages of 32 x 256 per resident wave, 3200 rows and more, at head size 128, both of whose passes run by
+    16x16x32 products: every remainder of the trips, ragged ends.  far: later logits exceed the first stage's by more than the float range, so that parts are
     redone with a running maximum (bounds as in the test below).  First and last kv-head against the oracle."""
-    hkv, d, w = 36 // group, 128, 40
+    b, hkv, d, w = 4, 36 // group, 128, 40
     _log("smaller products", group, n, far)
-    p = B.EmsParams(1, 36, hkv, d, n, w)
-    assert score_products(p) == "16x16x32"
+    p = B.EmsParams(b, 36, hkv, d, n, w)
+    assert score_products(p) == (16, 16)
     gen = torch.Generator(device="cuda").manual_seed(n)
-    k = torch.randn((1, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
-    q = torch.randn((1, 36, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    k = torch.randn((b, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    q = torch.randn((b, 36, n, d), device="cuda", generator=gen).to(torch.bfloat16)
     if far:
         k[:, :, 700:] *= 64.0                                # exact in bf16
     s_glo, s_loc, lse = B.ems_global_local_score(p, q, k, want_lse=True)
     rtol = 4e-4 if far else 1e-5                             # (without far: the float32 mode's bar, the products of bf16 inputs are exact)
-    for h in (0, hkv - 1):
+    for i, h in ((0, 0), (b - 1, hkv - 1)):
         ref = ems_ref.RefParams(1, group, 1, d, n, w)
-        o = ems_ref.score(ref, q[:, h * group:(h + 1) * group].float().cpu().numpy(), k[:, h:h + 1].float().cpu().numpy(), want_lse=True)
-        assert_rel(s_glo[0, h].cpu().numpy(), o[0][0, 0], rtol, "s_glo")
-        assert_rel(s_loc[0, h].cpu().numpy(), o[1][0, 0], rtol, "s_loc")
-        np.testing.assert_allclose(lse[0, h * group:(h + 1) * group].cpu().numpy(), o[2][0], rtol=2e-6, atol=1e-4 if far else 2e-5)
+        o = ems_ref.score(ref, q[i:i + 1, h * group:(h + 1) * group].float().cpu().numpy(), k[i:i + 1, h:h + 1].float().cpu().numpy(), want_lse=True)
+        assert_rel(s_glo[i, h].cpu().numpy(), o[0][0, 0], rtol, "s_glo")
+        assert_rel(s_loc[i, h].cpu().numpy(), o[1][0, 0], rtol, "s_loc")
+        np.testing.assert_allclose(lse[i, h * group:(h + 1) * group].cpu().numpy(), o[2][0], rtol=2e-6, atol=1e-4 if far else 2e-5)
 
 
-@pytest.mark.parametrize("d,n,products", [(128, 3233, "16x16x32"), (128, 3100, "32x32x16"), (64, 3233, "32x32x16")])
-def test_score_infinite_and_nan_values(d, n, products):
+@pytest.mark.parametrize("b,d,n,products", [(4, 128, 3233, (16, 16)), (1, 128, 3100, (32, 32)), (1, 64, 3233, (32, 32))])
+def test_score_infinite_and_nan_values(b, d, n, products):
     """16-bit calls, one (batch, kv-head) pair each: keys of -inf where every query is positive (logits of -inf: no weight), a query
     row of NaN (only its own weights are lost), a key of NaN (every later row's).  Against the oracle, for NaN on finite values in
     their place, what they reach apart.  Tolerance: the float32 mode's bar, the products of bf16 inputs are exact."""
     hkv, g, w, row = 12, 3, 40, 1777
-    p = B.EmsParams(1, g * hkv, hkv, d, n, w)
+    p = B.EmsParams(b, g * hkv, hkv, d, n, w)
     assert score_products(p) == products
-    _log("infinite and NaN", d, n)
+    _log("infinite and NaN", b, d, n)
     gen = torch.Generator(device="cuda").manual_seed(n + d)
-    k = torch.randn((1, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
-    q = torch.randn((1, g * hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    k = torch.randn((b, hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
+    q = torch.randn((b, g * hkv, n, d), device="cuda", generator=gen).to(torch.bfloat16)
     plain, inf, nan_q, nan_k = 0, 4, 7, 11
     q[0, g * inf:g * inf + g, :, 3] = q[0, g * inf:g * inf + g, :, 3].abs() + 0.125
     k[0, inf, 100:2000:97, 3] = -torch.inf
-    kept = {h: (q[:, g * h:g * h + g].float().cpu().numpy(), k[:, h:h + 1].float().cpu().numpy()) for h in (plain, inf, nan_q, nan_k)}
+    kept = {h: (q[:1, g * h:g * h + g].float().cpu().numpy(), k[:1, h:h + 1].float().cpu().numpy()) for h in (plain, inf, nan_q, nan_k)}
     q[0, g * nan_q + 1, row, 7] = torch.nan
     k[0, nan_k, row, 7] = torch.nan
     s_glo, s_loc, lse = (x.cpu().numpy() for x in B.ems_global_local_score(p, q, k, want_lse=True))

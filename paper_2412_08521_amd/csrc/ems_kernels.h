@@ -166,7 +166,7 @@ int score_keys_per_block(int dtype_is_f32);
 // the pass takes whole items), and the floats of one partial-result array.
 struct ScoreDeal { int p1_waves, p1_len, p2_waves, p2_len, p1_by_block; size_t p1_floats, p2_floats; };
 ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int head_dim, bool f32);
-bool score_by_16x16x32(int pass, int batch, int q_heads, int kv_heads, int seq_len, int head_dim);     // which products a 16-bit pass (1, 2) takes
+bool score_by_16x16x32(int batch, int q_heads, int kv_heads, int seq_len, int head_dim);       // which products 16-bit passes take
 int select_chunks(int seq_len);     // blocks per head of the long-sequence select
 int select_coarse_bins();
 hipError_t launch_sparsity(const StatsArgs& a, hipStream_t st);

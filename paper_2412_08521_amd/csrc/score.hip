@@ -1004,38 +1004,39 @@ ScoreDeal score_deal(int batch, int q_heads, int kv_heads, int seq_len, int /*he
 
 // Which products: by 16x16x32 (score_m16.hip) where the launch is long enough for the chip to lower its clock, counted in stages of 32 x 256
 // per resident wave, and the sequence so long that the masked stages, which cost a tenth more there, are few.  The second pass has more
-// of those (its window's as well) and shorter stretches of interior rows: its line lies higher.  Time by 16x16x32 over that by 32x32x16, in turn on one
-// card, first / second pass:
-//     16 over 16, 4096   16 stages   1.00 / 1.05        16 over 16, 8192    64 stages   0.98 / 0.99
-//      8 over 8, 6000    18          1.02 / 1.00        64 over 8, 4096     64          0.98 / 1.06
-//     32 over 32, 3300   21          1.01 / 1.05        56 over 8, 4500     69          0.99 / 1.02
-//      8 over 8, 8192    32          0.98 / 1.01        32 over 8, 6000     71          0.99 / 0.99
-//     32 over 32, 4096   32          1.00 / 1.06        4 x 32 over 8, 3300 85          0.99 / 0.98
-//     32 over 8, 4096    32          0.99 / 1.06        32 over 8, 7000     96          0.99 / 0.99
-//     2 x 32 over 8, 3300 42         0.99 / 1.02        32 over 8, 8192    128          0.97 / 1.00
-//     32 over 8, 5003    49          0.99 / 1.01        32 over 32, 8192   128          0.98 / 0.98
-//     3 x 12 over 4, 5003 55         1.00 / 1.02        32 over 8, 12000   275          0.97 / 0.98
-// (With the second pass's line at 16 stages, whole score calls of 3300 to 4096 rows were 2 to 3 % slower.)
+// of those (its window's as well) and wins later; both passes take the same products, whose roundings of a logit then cancel (the first alone by
+// 16x16x32: 16 over 16, 8191 rows, column sums weighted alike 0.9e-7 from 64 bits -> 1.1e-7).  Time by 16x16x32 over that by 32x32x16, in turn on one
+// card (on another where there are two), first / second pass:
+//     16 over 16, 4096   16 stages   1.00 / 1.05 (1.05)     64 over 8, 4096     64 stages    0.98 / 1.06 (1.03)
+//      8 over 8, 6000    18          1.02 / 1.00            56 over 8, 4500     69           0.99 / 1.02 (1.01)
+//     32 over 32, 3300   21          1.01 / 1.05 (1.08)     32 over 32, 6000    71           0.99 / 0.98 (0.97)
+//      8 over 8, 8192    32          0.98 / 1.01 (0.99)     32 over 8, 6000     71           0.99 / 0.99 (0.98)
+//     32 over 32, 4096   32          1.00 / 1.06 (1.01)     4 x 32 over 8, 3300 85           0.99 / 0.98
+//     2 x 32 over 8, 3300 42         0.99 / 1.02 (1.01)     32 over 8, 7000     96           0.99 / 0.99
+//     32 over 8, 5003    49          0.99 / 1.01 (0.98)     32 over 8, 8192    128           0.97 / 1.00
+//     3 x 12 over 4, 5003 55         1.00 / 1.02 (1.02)     4 x 32 over 32, 4096 128         0.98 / 1.02
+//     16 over 16, 8192   64          0.98 / 0.99 (1.00)     32 over 8, 12000   275           0.97 / 0.98
+// (With the line at 16 stages, whole score calls of 3300 to 4096 rows were 2 to 3 % slower than by 32x32x16.)
 // Launches of several milliseconds settle at a power limit where it depends on the chip which is faster (ms on three): 4 x 32 over 8, 16384 6.97 / 6.85,
 // 7.16 / 7.23, -; 32768 28.3 / 27.5, 28.0 / 27.7, 28.0 / 29.0.  They stay with the larger products.
 // With fewer (batch, kv-head) pairs than XCDs a pair's rows are streamed through several of their L2s and there is as much to lose as to win:
 // 32 over 4, 32768 3416 + 3598 / 3341 + 3682, 8 over 2, 98304 8145 + 8347 / 8452 + 8227, 4 over 1, 131072 6762 + 7411 / 6684 + 7328.
-constexpr double kM16Stages[2] = {32., 80.}, kM16Most = 1024.;
+constexpr double kM16Stages = 70., kM16Most = 1024.;
 constexpr int kM16Rows = 3200;
 static_assert(kM16Most * 1.1 < kDealStages, "a second pass by 16x16x32 products is an even deal (its stages are padded by 3 in 100 at most)");
-bool score_by_16x16x32(int pass, int batch, int q_heads, int kv_heads, int seq_len, int head_dim)
+bool score_by_16x16x32(int batch, int q_heads, int kv_heads, int seq_len, int head_dim)
 {
     const DealPass1<kSub> d(seq_len);
     const double stages = 0.5 * batch * q_heads * d.n_stages * d.n_units / kResident;
-    return head_dim == 128 && batch * kv_heads >= kXcds && seq_len >= kM16Rows && stages >= kM16Stages[pass - 1] && stages <= kM16Most;
+    return head_dim == 128 && batch * kv_heads >= kXcds && seq_len >= kM16Rows && stages >= kM16Stages && stages <= kM16Most;
 }
-static bool m16_launch(int pass, const ScoreArgs& a) { return score_by_16x16x32(pass, a.batch, a.q_heads, a.kv_heads, a.seq_len, a.head_dim); }
+static bool m16_launch(const ScoreArgs& a) { return score_by_16x16x32(a.batch, a.q_heads, a.kv_heads, a.seq_len, a.head_dim); }
 
 template <bool kF32, bool kDeal>
 static void start_pass1(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass1_f32(a, kDeal, grid, st);
-    else if (m16_launch(1, a)) start_pass1_m16(a, kDeal, grid, st);
+    else if (m16_launch(a)) start_pass1_m16(a, kDeal, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass1_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass1_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }
@@ -1044,7 +1045,7 @@ template <bool kF32, bool kDeal>
 static void start_pass2(const ScoreArgs& a, unsigned grid, hipStream_t st)
 {
     if constexpr (kF32) start_pass2_f32(a, kDeal, grid, st);
-    else if (kDeal && m16_launch(2, a)) start_pass2_m16(a, grid, st);
+    else if (kDeal && m16_launch(a)) start_pass2_m16(a, grid, st);
     else if (a.head_dim == 64) hipLaunchKernelGGL((score_pass2_stream_kernel<64, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
     else hipLaunchKernelGGL((score_pass2_stream_kernel<128, kDeal>), dim3(grid), dim3(kWave), 0, st, a);
 }

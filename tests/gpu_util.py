@@ -44,10 +44,10 @@ def score_forms(p: B.EmsParams):
 
 
 def score_products(p: B.EmsParams):
-    """Rows of the matrix products that the two score passes of `p` take: 16 (16x16x32) or 32 (32x32x16)."""
-    f = getattr(B.lib(), "_ZN3ems17score_by_16x16x32Eiiiiii")
-    f.restype, f.argtypes = C.c_bool, [C.c_int] * 6
-    return tuple(16 if f(i, p.batch, p.q_heads, p.kv_heads, p.seq_len, p.head_dim) else 32 for i in (1, 2))
+    """Rows of the matrix products that the 16-bit score passes of `p` take: 16 (16x16x32) or 32 (32x32x16)."""
+    f = getattr(B.lib(), "_ZN3ems17score_by_16x16x32Eiiiii")
+    f.restype, f.argtypes = C.c_bool, [C.c_int] * 5
+    return 16 if f(p.batch, p.q_heads, p.kv_heads, p.seq_len, p.head_dim) else 32
 
 
 def decode_launches(p: B.EmsParams):

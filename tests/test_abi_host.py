@@ -268,19 +268,17 @@ def test_score_passes_are_dealt_by_rule(lib, shape, forms):
     assert score_forms(B.EmsParams(b, hq, hkv, d, n, 16, dtype=B.EMS_F32 if f32 else B.EMS_BF16)) == forms
 
 
-# (batch, q_heads, kv_heads, head_dim, seq_len): either side of every line of the rule for the 16-bit products, first and second pass
+# (batch, q_heads, kv_heads, head_dim, seq_len): either side of every line of the rule for the 16-bit products
 @pytest.mark.parametrize("shape,products", [
-    ((1, 32, 32, 128, 3300), (32, 32)),                       # 21 stages per resident wave
-    ((1, 32, 32, 128, 4096), (16, 32)),                       # 32
-    ((1, 64, 8, 128, 4096), (16, 32)),                        # 64
-    ((1, 32, 8, 128, 6400), (16, 32)),                        # 78.1
-    ((1, 32, 8, 128, 6600), (16, 16)),                        # 84.1
-    ((4, 32, 8, 128, 3200), (16, 16)),                        # 81.3
-    ((4, 32, 8, 128, 3199), (32, 32)),                        # too many masked stages
-    ((1, 64, 8, 128, 16384), (16, 16)),                       # 1024
-    ((1, 65, 13, 128, 16384), (32, 32)),
-    ((1, 28, 7, 128, 16384), (32, 32)),                       # fewer pairs than XCDs
-    ((1, 32, 8, 64, 8192), (32, 32)),
+    ((1, 32, 32, 128, 4096), 32),                             # 32 stages per resident wave
+    ((1, 56, 8, 128, 4500), 32),                              # 69.4
+    ((1, 32, 8, 128, 6000), 16),                              # 70.5
+    ((4, 32, 8, 128, 3200), 16),                              # 81.3
+    ((4, 32, 8, 128, 3199), 32),                              # too many masked stages
+    ((1, 64, 8, 128, 16384), 16),                             # 1024
+    ((1, 65, 13, 128, 16384), 32),
+    ((1, 28, 7, 128, 16384), 32),                             # fewer pairs than XCDs
+    ((1, 32, 8, 64, 8192), 32),
 ])
 def test_score_products_are_chosen_by_rule(lib, shape, products):
     from gpu_util import score_products

@@ -1172,10 +1172,13 @@ constexpr long long kChooseScores = 3000000;
 static bool choose_in_one(int heads, int n_imp, int group, int blocks) { return (long long)blocks * heads * n_imp * (group + 1) <= kChooseScores; }
 // Threads of the one-launch step: a block of 512 has half the rows and table elements a wave, but pays the rest of the step twice as often.
 // (us a step, 256 / 512 threads, head size 128, 4 q-heads, merge ratio 0.5 unless stated: 32 heads of budget 128 9.4 / 10.0, one of 200 at ratio 2
-// 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Head size 64 and 8 q-heads, whose
-// dots are most of a wave's work and half as many: 128 heads of 300 at ratio 2 16.1 / 16.5, one of 200 12.4 / 12.7.  Before sweeps ended with the table and the new token had a row
+// 12.0 / 11.2, 8 of 256 13.2 / 12.0, of 512 20.1 / 16.6; 128 of 300 15.7 / 13.8.  Before sweeps ended with the table and the new token had a row
 // of its own, 256 threads: 10.5, 12.0, 14.2, 21.4; 16.5.)
-constexpr int kOneBlockTable = 256;
+// In 16 bits at head size 64 with 8 q-heads the dots are most of a wave's work and half as many, and the line lies higher, in rows and in table
+// elements: 8 heads, budget / table 300 / 450 14.2 / 14.8, 300 / 900 15.2 / 15.4, 380 / 570 16.0 / 16.0, 420 / 630 16.8 / 16.5, 512 / 768 17.6 / 17.0,
+// 256 / 1280 15.2 / 14.8, 400 / 1200 17.6 / 16.3, 512 / 1536 20.6 / 17.8; 32 heads of 200 / 600 13.0 / 14.1, of 380 / 1140 18.3 / 16.9; 256 heads of
+// 256 / 512 13.0 / 14.3.  (In float32 200 / 400 15.3 / 15.1, 300 / 900 19.5 / 17.7.)
+constexpr int kOneBlockTable = 256, kNarrowRows = 400, kNarrowTable = 1024;
 // kWhich: the step kernel's parts (8 = part 0 with 512 threads), 6 = logits, 7 = choice of the centres
 template <typename T, int D, int G, int kWhich>
 static void launch_decode_group(const DecodeStepArgs& a, hipStream_t st)
@@ -1259,7 +1262,9 @@ static hipError_t launch_decode_step_t(const DecodeStepArgs& a, hipStream_t st)
             return hipErrorInvalidValue;
         }
     }
-    const bool wide = a.n_imp + a.n_tbm + a.window > kOneBlockTable && !(D == 64 && a.group == 8);
+    const int table = a.n_imp + a.n_tbm + a.window;
+    const bool narrow = sizeof(T) == 2 && D == 64 && a.group == 8 && a.budget <= kNarrowRows && table <= kNarrowTable;
+    const bool wide = table > kOneBlockTable && !narrow;
     const hipError_t e = wide ? launch_decode_part<T, D, 8>(a, st) : launch_decode_part<T, D, 0>(a, st);
     // A step whose number came with the call advances the counter itself: only blocks that read the
     // counter need it to stand still until all have (2.7 us of 13.6 a step, 32 heads with a budget of 128).

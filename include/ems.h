@@ -50,7 +50,12 @@ typedef enum {
 
 typedef enum {
     EMS_BF16 = 0,  /* bf16 I/O, bf16 MFMA with f32 accumulation */
-    EMS_F32 = 1    /* f32 I/O, f32 MFMA: the validation mode */
+    /* f32 I/O, the validation mode.  Matrix products are f32 MFMA, except that the score passes write every
+     * operand as the exact sum of three bf16 pieces (h, m, l) and form six of the nine products of pieces on
+     * the bf16 pipe, added in f32: hh, hm, mh, mm, hl, lh.  What is left out (ml, lm, ll) is below 2^-26 of a
+     * product.  Values without such pieces (infinities, NaN, elements of 2^60 and more or below 2^-100 in
+     * the operand that stays in registers) go by f32 MFMA. */
+    EMS_F32 = 1
 } ems_dtype;
 
 typedef enum {

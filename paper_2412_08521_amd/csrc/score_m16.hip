@@ -1,12 +1,15 @@
-// The two bf16 score passes at head size 128 by 16x16x32 products: what launches of up to two milliseconds run in place of score.hip's
+// The two bf16 score passes at head size 128 by 16x16x32 products: what launches of about a quarter to two milliseconds run in place of score.hip's
 // kernels (rule there), whose work items, partial results, ring, stages, edge and interior loops these share.
 //
 // A 32x32x16 product and four of 16x16x32 take the same matrix time, but these take less power, which is what limits the
 // clock of a long launch, and twice the issue slots, which is what bounds a short one.  A loop of nothing but a tile's products and weights,
-// without the DMA: 206 ns a tile by 32x32x16, 194 by 16x16x32.  Both passes, us, 32x32x16 / 16x16x32, in turn: 32 heads over 8, 16384
-// 1739 / 1695, 8192 490 / 475, 3 x 12 over 4, 16384 2098 / 2032.  Column sums against 64 bits, rms
-// of 6 seeds, 3300 to 20001 rows: 1.1-2.3e-7 -> 1.0-1.8e-7 (all rows), 1.2-2.8e-7 -> 1.1-2.4e-7 (window).  At head size 64 the weights' exp2 are the bound
-// and nothing is won at any length (4 x 32 over 8, 16384: 5174 / 5232).
+// without the DMA: 206 ns a tile by 32x32x16, 194 by 16x16x32.  First / second pass, us, 32x32x16 -> 16x16x32, traced in turn on one card: 32 heads over
+// 8, 8000 rows 242 / 235 -> 238 / 228 (1.95 -> 2.21-2.24 GHz, matrix pipe busy 0.55 -> 0.49 of the clocks), 16384 886 / 915 -> 860 / 886 (1.80 -> 2.10 GHz,
+// 0.65 -> 0.57).  (4096, which keeps the others: 77 / 80 -> 79 / 85.)  Column sums against 64 bits, 2-norm of the error over that of the sums, means of 24
+// seeds, all rows (window): 4 x 32 over 8, 3300 rows 1.48e-7 -> 1.25e-7 (1.28e-7 -> 1.09e-7), 32 over 8, 8000 1.42 -> 1.37 (1.57 -> 1.42), 64 over 8, 6000 1.73 -> 1.32
+// (1.64 -> 1.55), 3 x 12 over 4, 8192 1.72 -> 1.41 (2.15 -> 1.65), 8 over 8, 16384 2.22 -> 1.64 (3.10 -> 2.49), 32 over 8, 16384 8.7 -> 6.0 (16.6 -> 9.8).  With every column
+// weighted alike all rows' are smaller too (0.85-2.45e-7 -> 0.67-2.39e-7), the window's between 6 % smaller and 8 % larger (64 over 8, 6000: 0.77e-7 -> 0.83e-7).
+// At head size 64 the weights' exp2 are the bound and nothing is won at any length (4 x 32 over 8, 16384: 5174 / 5232).
 //
 // A tile is 32 rows x 32 keys, as four chains of products (two groups of 16 of the stationary rows, two halves of
 // the streamed ones) that alternate, so that consecutive matrix instructions never depend on each other; the vector ALU has the weights of the tile

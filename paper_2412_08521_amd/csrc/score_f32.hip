@@ -24,7 +24,7 @@
 // later step loses; rows with elements of 2^60 and more, or below 2^-100 (whose low piece falls below bf16's range
 // while the other factor could be large), are found when they are split.  The latter's items go by float32 products, of any values, from the
 // first stage on; the others' from the set of stages on whose sums left the float range (they are put back to what they were before it), so that
-// infinite logits come out as by float32 products and cost no more than those.  One key of -inf, which every later row of its head streams, us
+// infinite logits come out as by float32 products, at about their cost.  One key of -inf, which every later row of its head streams, us
 // of both passes by float32 products alone / begun anew without a pipeline / now: 8 heads over 2 of 128, 3000 rows 235 / 315 / 212, of 64 113 / 168 / 116;
 // 32 over 8, 6000 rows 3361 / 4197 / 2576; 4 x 32 over 8, 4096 4690 / 7922 / 5034 (a wave alone at that pace, among others that draw
 // the power of 16-bit products), in the middle of the sequence 4929 / - / 3394; a large element in every key 4701 / 6376 / 3556.
